@@ -17,6 +17,9 @@ struct Launch {
     size_t ws_off = 0;      // floats into the tenant's split-K workspace: chunks of one operator own disjoint parts
 };
 
+// the cut of one operator's K range (see GemmArgs)
+struct KSplit { int ksplit = 1, kb_per_slice = 1 << 28, kwaves = 0, kb_per_wave = 0; };
+
 struct Tenant {
     std::vector<gacer_op> ops;
     std::vector<gacer_tensor> tensors;
@@ -24,9 +27,9 @@ struct Tenant {
     gacer_dtype dtype = GACER_F32;
     hipStream_t stream = nullptr;
     hipStream_t sibling = nullptr;                  // optional second stream for decompositions marked `sibling`
-    // split-K bookkeeping (conv / GEMM operators only): slices and 64-byte K blocks per slice, fixed per
-    // operator from its unsplit shape; one library-owned workspace per tenant (its operators never overlap)
-    std::vector<int> ksplit, kb_per_slice;
+    // split-K bookkeeping (conv / GEMM operators only), fixed per operator from its unsplit shape; one library-owned
+    // workspace per tenant (its operators never overlap)
+    std::vector<KSplit> ksplit;
     float *ws = nullptr;
     size_t ws_floats = 0;
 };

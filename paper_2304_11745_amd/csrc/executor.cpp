@@ -147,7 +147,8 @@ Launch make_launch(const Tenant &t, int oi, int b_lo, int b_hi, int c_lo, int c_
         g.y_row = out.pitch ? out.pitch : out.c;
         g.m_lo = b_lo * q_out * g.Ho * g.Wo; g.m_hi = b_hi * q_out * g.Ho * g.Wo;
         g.n_lo = c_lo; g.n_hi = c_hi;
-        g.ksplit = t.ksplit[oi]; g.kb_per_slice = t.kb_per_slice[oi];
+        g.ksplit = t.ksplit[oi].ksplit; g.kb_per_slice = t.ksplit[oi].kb_per_slice;
+        g.kwaves = t.ksplit[oi].kwaves; g.kb_per_wave = t.ksplit[oi].kb_per_wave;
         g.ws = nullptr;                       // the workspace is chosen per call (see enqueue)
         break;
     }
@@ -407,13 +408,40 @@ static gacer_status check_op(Ctx *c, int ti, const gacer_tenant &t, int oi, cons
     return GACER_OK;
 }
 
-// Split-K decision, from the operator's UNSPLIT shape only (so every chunk of it adds in the same order):
-// when 64x64 tiles alone would leave most compute units idle, cut K into up to 16 slices of at least four
-// 64-byte blocks, aiming at about two workgroups per compute unit.
-static void decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, int *S, int *kbps)
+// How the K range of a convolution / GEMM is cut (see GemmArgs), from the operator's UNSPLIT shape only, so that every chunk
+// of it adds in the same order.
+static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool slices_ok)
 {
-    const int bk = dtype == GACER_BF16 ? 32 : 16;
+    KSplit r;
+    const bool bf16 = dtype == GACER_BF16;
+    const int bk = bf16 ? 32 : 16;
     const int nkb = (K + bk - 1) / bk;
+    // K slices inside a workgroup (slices_kernel, one 32x32 tile per workgroup) while there are at most about two such tiles per
+    // compute unit.  Measured in isolation, microseconds, this kernel against the tiled kernels with their finishing pass:
+    // bf16 49x160x960 4.5 / 8.8, 392x512x4608 9.6 / 13.8, 1568x256x2304 (392 tiles) 10.2 / 14.2, 144x3072x768 (480) 6.1 / 6.8,
+    // 6272x128x512 (784) 9.0 / 6.5; fp32 125x32x1152 9.9 / 31.3, 392x160x960 8.5 / 11.5, 392x512x2048 13.8 / 18.4, 392x1280x320
+    // (520) 10.9 / 10.3.  One column of tiles (N <= 32) wastes half of a 64-wide tile's work, so it goes on longer: fp32
+    // 19200x32x1152 (600) 26.4 / 33.4, 25088x32x1152 (784) 31.8 / 34.0; bf16 11.8 / 11.8 and 13.7 / 12.1.
+    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t32_max = N > 32 ? 512 : bf16 ? 600 : 800;
+    const int nb = (nkb + 1) / 2;                // 128-byte batches of K per row
+    // short bf16 rows belong to rowgemm_kernel; in fp32 a batch is 1024 clocks of MFMA, and with tiles for most units a long K
+    // is as fast or faster with each operand shared by four waves (392x512x4608: 28.4 here, 29.8 there; 512x768x3072: 34.2 / 30.8)
+    if (slices_ok && nb >= 2 && (!bf16 || K > 96) && t32 <= t32_max && (bf16 || t32 <= 128 || nb <= 80)) {
+        // more workgroups along K, and a finishing pass, only where units would stay empty and a wave's chain is long: bf16
+        // 8x4096x25088 and fp32 144x768x3072 (17.9 -> 15.8), 8x4096x4096 (24.4 -> 22.2); at 9 batches per wave the pass costs
+        // more than it gives (bf16 49x512x4608: 9.0 -> 11.1)
+        const int64_t longest = bf16 ? 12 : 5;
+        int64_t so = 1;
+        while (so < 8 && t32 * so * 2 <= 256 && nb > longest * 8 * so) so *= 2;
+        // four waves leave room for a second workgroup on the unit; eight hide more latency when there is only one
+        const int64_t w = t32 > 256 || nb <= (bf16 ? 24 : 18) ? 4 : 8;
+        const int64_t per = (nb + w * so - 1) / (w * so);
+        r.kwaves = (int)w;
+        r.kb_per_wave = (int)(2 * per);
+        r.kb_per_slice = r.kwaves * r.kb_per_wave;
+        r.ksplit = (int)((nb + per * w - 1) / (per * w));
+        return r;
+    }
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
     int64_t s = 1;
     // Measured on whole concurrent rounds: splitting pays only when the unsplit launch would leave more than half of
@@ -433,8 +461,10 @@ static void decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, int *S,
     }
     int per = (int)((nkb + s - 1) / s);
     per += per & 1;
-    *kbps = s == 1 ? (1 << 28) : per;
-    *S = s == 1 ? 1 : (nkb + per - 1) / per;
+    if (s == 1) return r;
+    r.kb_per_slice = per;
+    r.ksplit = (nkb + per - 1) / per;
+    return r;
 }
 
 static void release_workspaces(std::vector<Tenant> &ts)
@@ -445,13 +475,24 @@ static void release_workspaces(std::vector<Tenant> &ts)
     }
 }
 
+// Whether the operands of a convolution / GEMM can be read in whole 16-byte vectors along K (what slices_kernel needs)
+static bool slices_operands(const Tenant &t, const gacer_op &op)
+{
+    const gacer_tensor &in = t.tensors[op.in0];
+    const int vec = t.dtype == GACER_BF16 ? 8 : 4;
+    const bool flat = op.kind == GACER_GEMM && op.cin != in.c;
+    const int64_t pitch = flat ? op.cin : in.pitch ? in.pitch : in.c;
+    if (op.kind == GACER_CONV2D && op.kh * op.kw > 31) return false;
+    return (op.kind == GACER_GEMM ? op.cin : in.c) % vec == 0 && pitch % vec == 0 && (((uintptr_t)in.dptr) & 15) == 0 &&
+           (((uintptr_t)op.w) & 15) == 0;
+}
+
 // Sizes the per-tenant split-K workspace and tries to allocate it.  Without a usable device the pointers
 // stay null and gacer_run reports the failure; descriptor-only use (validation, search) still works.
 static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
 {
     for (Tenant &t : ts) {
-        t.ksplit.assign(t.ops.size(), 1);
-        t.kb_per_slice.assign(t.ops.size(), 1 << 28);
+        t.ksplit.assign(t.ops.size(), KSplit());
         t.ws_floats = 0;
         for (size_t i = 0; i < t.ops.size(); ++i) {
             const gacer_op &op = t.ops[i];
@@ -459,8 +500,8 @@ static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
             const gacer_tensor &in = t.tensors[op.in0], &out = t.tensors[op.out];
             const int64_t M = out.n * out.h * out.w, N = out.c;
             const int K = op.kind == GACER_GEMM ? op.cin : (int)in.c * op.kh * op.kw;
-            decide_split(M, N, K, t.dtype, &t.ksplit[i], &t.kb_per_slice[i]);
-            if (t.ksplit[i] > 1) t.ws_floats = std::max<size_t>(t.ws_floats, (size_t)t.ksplit[i] * M * N);
+            t.ksplit[i] = decide_split(M, N, K, t.dtype, slices_operands(t, op));
+            if (t.ksplit[i].ksplit > 1) t.ws_floats = std::max<size_t>(t.ws_floats, (size_t)t.ksplit[i].ksplit * M * N);
         }
         if (t.ws_floats) {
             if (hipMalloc((void **)&t.ws, t.ws_floats * sizeof(float)) != hipSuccess) {
@@ -492,7 +533,7 @@ static bool fusable_pair(const Tenant &T, int i)
     if (pw.kh != 1 || pw.kw != 1 || pw.stride != 1 || pw.pad != 0 || pw.groups != 1 || pw.in0 != af.out || pw.res == af.out) return false;
     const gacer_tensor &in = T.tensors[af.in0], &mid = T.tensors[af.out];
     const int vec = T.dtype == GACER_BF16 ? 8 : 4;
-    if (in.c % vec) return false;
+    if (in.c % vec || (T.ksplit[i + 1].kwaves && in.c > SLICES_PRE_MAX)) return false;
     return aligned16p(in.dptr) && aligned16p(mid.dptr) && aligned16p(af.scale) && aligned16p(af.shift) && aligned16p(pw.w);
 }
 

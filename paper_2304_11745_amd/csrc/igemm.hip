@@ -25,7 +25,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 static constexpr int THREADS = 256;
-enum { LOAD_VEC = 0, LOAD_GATHER = 1, LOAD_BT = 2, LOAD_TAPS = 3, LOAD_AFFINE = 4 };
+enum { LOAD_VEC = 0, LOAD_GATHER = 1, LOAD_BT = 2, LOAD_TAPS = 3, LOAD_AFFINE = 4, LOAD_TAPS_ANY = 5 };
 
 __device__ __forceinline__ float bf16_to_f32(unsigned short v) { return __uint_as_float(((unsigned)v) << 16); }
 __device__ __forceinline__ unsigned short f32_to_bf16(float f)     // round to nearest even (hardware conversion)
@@ -132,6 +132,43 @@ template <int EV> __device__ __forceinline__ void load_bias_vec(const float *bia
             bv[q] = b4.x; bv[q + 1] = b4.y; bv[q + 2] = b4.z; bv[q + 3] = b4.w;
         }
     }
+}
+
+// four consecutive elements as floats, and back (8-byte vectors for bf16, 16-byte for fp32)
+__device__ __forceinline__ void load_vec4(const float *p, float *v)
+{
+    const float4 t = *(const float4 *)p;
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+}
+__device__ __forceinline__ void load_vec4(const unsigned short *p, float *v)
+{
+    const uint2 t = *(const uint2 *)p;
+    v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xFFFF0000u);
+    v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xFFFF0000u);
+}
+__device__ __forceinline__ void store_vec4(float *p, const float *v) { *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void store_vec4(unsigned short *p, const float *v) { *(uint2 *)p = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])); }
+
+// The arithmetic of a stand-alone per-channel affine operator on one 16-byte vector: one FMA, the clamp (none, ReLU or
+// ReLU6), one rounding to the element type.
+template <int DT> __device__ __forceinline__ uint4 affine_vec(uint4 x, const float *sc, const float *sh, int act)
+{
+    constexpr int VEC = El<DT>::VEC;
+    float v[VEC];
+    if constexpr (DT == DT_BF16) {
+        const unsigned x4[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { v[2 * q] = __uint_as_float(x4[q] << 16); v[2 * q + 1] = __uint_as_float(x4[q] & 0xFFFF0000u); }
+    } else {
+        v[0] = __uint_as_float(x.x); v[1] = __uint_as_float(x.y); v[2] = __uint_as_float(x.z); v[3] = __uint_as_float(x.w);
+    }
+#pragma unroll
+    for (int q = 0; q < VEC; ++q) {
+        const float t = __fmaf_rn(v[q], sc[q], sh[q]);
+        v[q] = act == ACT_RELU ? __builtin_fmaxf(t, 0.f) : act == ACT_RELU6 ? __builtin_amdgcn_fmed3f(t, 0.f, 6.f) : t;
+    }
+    if constexpr (DT == DT_BF16) return make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
+    else return make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
 }
 
 // Ragged or unaligned tail: element by element (rare: odd channel counts, unaligned channel chunks).
@@ -473,26 +510,8 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
         for (int i = 0; i < AV; ++i) {
             const int row = vrow + i * RPP;
             uint4 va = pa[i];
-            if constexpr (PRE) {                // the stand-alone operator's arithmetic: one FMA, the activation, one rounding
-                float v[VEC];
-                if constexpr (DT == DT_BF16) {
-                    const unsigned x4[4] = {va.x, va.y, va.z, va.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) { v[2 * q] = __uint_as_float(x4[q] << 16); v[2 * q + 1] = __uint_as_float(x4[q] & 0xFFFF0000u); }
-                } else {
-                    v[0] = __uint_as_float(va.x); v[1] = __uint_as_float(va.y); v[2] = __uint_as_float(va.z); v[3] = __uint_as_float(va.w);
-                }
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) {
-                    const float t = __fmaf_rn(v[q], sc[q], sh[q]);
-                    v[q] = a.pre_act == ACT_RELU ? __builtin_fmaxf(t, 0.f) : a.pre_act == ACT_RELU6 ? __builtin_amdgcn_fmed3f(t, 0.f, 6.f) : t;
-                }
-                if constexpr (DT == DT_BF16) {
-                    va.x = (unsigned)to_bf16(v[0]) | ((unsigned)to_bf16(v[1]) << 16); va.y = (unsigned)to_bf16(v[2]) | ((unsigned)to_bf16(v[3]) << 16);
-                    va.z = (unsigned)to_bf16(v[4]) | ((unsigned)to_bf16(v[5]) << 16); va.w = (unsigned)to_bf16(v[6]) | ((unsigned)to_bf16(v[7]) << 16);
-                } else {
-                    va = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
-                }
+            if constexpr (PRE) {
+                va = affine_vec<DT>(va, sc, sh, a.pre_act);
                 if (pre_store && a_hm[i] && pkv < k_end && (BM % RPP == 0 || row < BM))
                     *(uint4 *)((T *)a.pre_y + (int64_t)(m0 + row) * a.Cin + pkv) = va;
             }
@@ -1025,6 +1044,246 @@ __global__ __launch_bounds__(THREADS) void rowgemm_kernel(GemmArgs a)
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// K slices side by side in one workgroup: for products with few output tiles and a long K (late convolution layers, short
+// token batches, classifiers).  Wave w of the workgroup owns slice w of the K range and a whole 32x32 output tile; the slice
+// accumulators meet in LDS, are added in ascending order and go through the epilogue, so one launch does what a slice kernel
+// plus a finishing pass over fp32 partial tiles in memory did.  Very long K (the first classifier layer of a VGG) is cut once
+// more over the grid: workgroup row y owns slices y * S .. y * S + S - 1 and writes its sum to the workspace, splitk_finish
+// adds those.  An output element is the sum of its slice chains in that fixed order, whatever part of the operator is launched.
+//
+// Waves share no operand (their K ranges are disjoint), so each has two LDS stages of its own and there is no barrier in the
+// loop: a stage is one batch of 128 bytes of K for 32 + 32 rows, filled by eight direct-to-LDS loads of eight rows each,
+// swizzled as in igemm_dma_kernel, read into fragments at once and refilled while the MFMAs of the batch run.
+//
+// What bounds it: the path from L2 into LDS, about 45 bytes per clock and unit (each wave computes the tile for its own K, so
+// 64 rows are moved per 32x32 of output, twice what four waves sharing a 64x64 tile move), hence few tiles only; in fp32 the
+// matrix cores from about 4 KB of K on.  Fragments loaded straight into registers in operand layout (32 rows x 32 bytes per
+// load) reach 19 bytes per clock: 49x512x4608 bf16 took 17.3 us that way, 9.0 us like this, 9.9 us as slices plus finishing
+// pass.  144x768x768 bf16 9.0 -> 4.6 us, 125x32x1152 fp32 31.3 -> 9.9 us, where an empty kernel reads 3.9 us.
+template <int DT, int LOAD, int S>
+__global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
+{
+    typedef typename El<DT>::T T;
+    constexpr int VEC = El<DT>::VEC;
+    constexpr int ESZ = (int)sizeof(T);
+    constexpr int BE = 128 / ESZ;               // elements per batch and row
+    constexpr int STAGE = 64 * 128;             // bytes of one wave's stage: 32 A rows, then 32 B rows
+    constexpr bool PRE = LOAD == LOAD_AFFINE;
+    __shared__ __align__(1024) unsigned char st0[S * STAGE];
+    __shared__ __align__(1024) unsigned char st1[S * STAGE];
+    __shared__ __align__(16) float pre[PRE ? 2 * SLICES_PRE_MAX : 4];           // scale, shift
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+    const int by_m = div_by(tile, a.div_tiles_m), by_n = div_by(tile, a.div_tiles_n);
+    const int tile_m = __builtin_amdgcn_readfirstlane(a.n_major ? tile - by_m * a.tiles_m : by_n);
+    const int tile_n = __builtin_amdgcn_readfirstlane(a.n_major ? by_m : tile - by_n * a.tiles_n);
+    const int m0 = a.m_lo + tile_m * 32, n0 = a.n_lo + tile_n * 32;
+    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes), wr = make_rsrc(a.w, a.w_bytes);
+
+    // Load p of a stage fills rows 8 p .. 8 p + 7: lane l row 8 p + l / 8, slot l % 8, which holds logical chunk
+    // (l % 8) ^ ((row / 2) % 8) -- two values per lane, by the parity of p
+    const int c0 = (lane & 7) ^ (lane >> 4);
+    const int kl[2] = {c0 * VEC, (c0 ^ 4) * VEC};
+    unsigned a_off[4], a_hm[4], b_off[4];
+    bool b_ok[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int row = 8 * p + (lane >> 3);
+        const int m = m0 + row;
+        const bool ok = m < a.m_hi;
+        const int mm = ok ? m : a.m_lo;
+        const int HoWo = a.Ho * a.Wo;
+        const int img = div_by(mm, a.div_howo), rem = mm - img * HoWo;
+        const int oh = div_by(rem, a.div_wo), ow = rem - oh * a.Wo;
+        const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
+        const int64_t e0 = (int64_t)img * a.x_img + ((int64_t)ih0 * a.W + iw0) * a.x_pix + (LOAD == LOAD_TAPS_ANY ? 0 : kl[p & 1]);
+        a_off[p] = (unsigned)(int)(e0 * ESZ);
+        a_hm[p] = ok ? (LOAD == LOAD_TAPS || LOAD == LOAD_TAPS_ANY ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 1u) : 0u;
+        b_ok[p] = n0 + row < a.n_hi;
+        b_off[p] = (unsigned)(((int64_t)(n0 + row) * a.w_row + kl[p & 1]) * ESZ);
+    }
+
+    // K range of this wave, in elements; loads at or beyond k_end return zeros
+    const int per = a.kb_per_wave * (64 / ESZ);
+    const int slice = (int)blockIdx.y * S + wave;
+    const int k_lo = min(a.K, slice * per), k_end = min(a.K, k_lo + per);
+    const int batches = (k_end - k_lo + BE - 1) / BE;
+
+    // position of the next batch; LOAD_TAPS: a batch never crosses a tap (128 bytes divide a tap's channels), so the tap is
+    // a scalar
+    int kb = k_lo, kr = 0, ksx = 0, kci = k_lo;
+    if constexpr (LOAD == LOAD_TAPS) {
+        const int tap = div_by(k_lo, a.div_cin);
+        kci = k_lo - tap * a.Cin;
+        kr = div_by(tap, a.div_kw);
+        ksx = tap - kr * a.kw;
+    }
+    auto request = [&](unsigned char *stage) {
+        unsigned da[2], tap[2];
+        bool k_ok[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int kv = kb + kl[h];
+            k_ok[h] = kv < k_end;
+            tap[h] = 0u;
+            if constexpr (LOAD == LOAD_TAPS) {
+                da[h] = (unsigned)((((int64_t)kr * a.W + ksx) * a.x_pix + kci) * ESZ);
+                tap[h] = (unsigned)(kr * a.kw + ksx);
+            } else if constexpr (LOAD == LOAD_TAPS_ANY) {
+                const int t = div_by(kv, a.div_cin), ci = kv - t * a.Cin;
+                const int r = div_by(t, a.div_kw), q = t - r * a.kw;
+                da[h] = (unsigned)((((int64_t)r * a.W + q) * a.x_pix + ci) * ESZ);
+                tap[h] = (unsigned)t & 31u;
+            } else {
+                da[h] = (unsigned)(kb * ESZ);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GACER_LDS(stage + p * 1024), 16,
+                                                     (int)((k_ok[p & 1] && ((a_hm[p] >> tap[p & 1]) & 1u)) ? a_off[p] + da[p & 1] : OOB), 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + 4096 + p * 1024), 16,
+                                                     (int)((k_ok[p & 1] && b_ok[p]) ? b_off[p] + (unsigned)(kb * ESZ) : OOB), 0, 0, 0);
+        kb += BE;
+        if constexpr (LOAD == LOAD_TAPS) {
+            kci += BE;
+            const bool w1 = kci >= a.Cin;
+            kci -= w1 ? a.Cin : 0;
+            ksx += w1 ? 1 : 0;
+            const bool w2 = ksx == a.kw;
+            ksx = w2 ? 0 : ksx;
+            kr += w2 ? 1 : 0;
+        }
+    };
+
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    const int frag = lrow * 128, frag_lo = (lhalf ^ ((lrow >> 1) & 7)) * 16;
+    constexpr int WAIT_BATCH = (8 & 15) | (7 << 4) | (15 << 8);                 // vmcnt(8): the older of the two batches in flight has landed
+    constexpr int WAIT_LDS = 15 | (7 << 4) | (3 << 14);                         // lgkmcnt(0)
+    auto step = [&](unsigned char *stage, int k0) {
+        __builtin_amdgcn_s_waitcnt(WAIT_BATCH);
+        asm volatile("" ::: "memory");
+        uint4 fa[4], fb[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            fa[g] = *(const uint4 *)(stage + frag + (frag_lo ^ (g * 32)));
+            fb[g] = *(const uint4 *)(stage + 4096 + frag + (frag_lo ^ (g * 32)));
+        }
+        __builtin_amdgcn_s_waitcnt(WAIT_LDS);                                   // the stage may be refilled
+        asm volatile("" ::: "memory");
+        request(stage);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if constexpr (PRE) {                // the stand-alone operator's arithmetic, and its output tensor on the side
+                const int kv = k0 + g * 2 * VEC + lhalf * VEC;
+                float sc[VEC], sh[VEC];
+#pragma unroll
+                for (int q = 0; q < VEC; q += 4) {
+                    const float4 s4 = *(const float4 *)(pre + kv + q), h4 = *(const float4 *)(pre + SLICES_PRE_MAX + kv + q);
+                    sc[q] = s4.x; sc[q + 1] = s4.y; sc[q + 2] = s4.z; sc[q + 3] = s4.w;
+                    sh[q] = h4.x; sh[q + 1] = h4.y; sh[q + 2] = h4.z; sh[q + 3] = h4.w;
+                }
+                fa[g] = affine_vec<DT>(fa[g], sc, sh, a.pre_act);
+                if (n0 == 0 && m0 + lrow < a.m_hi && kv < k_end) *(uint4 *)((T *)a.pre_y + (int64_t)(m0 + lrow) * a.Cin + kv) = fa[g];
+            }
+            if constexpr (DT == DT_BF16) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[g]), __builtin_bit_cast(bf16x8, fb[g]), acc, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float av = __uint_as_float(e == 0 ? fa[g].x : e == 1 ? fa[g].y : e == 2 ? fa[g].z : fa[g].w);
+                    const float bv = __uint_as_float(e == 0 ? fb[g].x : e == 1 ? fb[g].y : e == 2 ? fb[g].z : fb[g].w);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
+                }
+            }
+        }
+    };
+
+    unsigned char *w0 = st0 + wave * STAGE, *w1 = st1 + wave * STAGE;
+    request(w0);
+    if constexpr (PRE) {                        // zeros beyond K: a zero element of B meets something finite
+        const int pre_n = (a.K + BE - 1) / BE * BE;
+        for (int k = tid; k < pre_n; k += 64 * S) {
+            pre[k] = k < a.K ? a.pre_scale[k] : 0.f;
+            pre[SLICES_PRE_MAX + k] = k < a.K ? a.pre_shift[k] : 0.f;
+        }
+    }
+    request(w1);
+    if constexpr (PRE) __syncthreads();
+    int b = 0;
+    for (; b + 2 <= batches; b += 2) {
+        step(w0, k_lo + b * BE);
+        step(w1, k_lo + (b + 1) * BE);
+    }
+    if (b < batches) step(w0, k_lo + b * BE);
+    __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));                           // vmcnt(0): the requests beyond the slice have landed
+    asm volatile("" ::: "memory");
+    __syncthreads();                            // `part` overlays the stages of several waves
+
+    // ---- sum over the slices and epilogue ----
+    // accumulator element e of lane l is row (e/4)*8 + (l/32)*4 + e%4, column l%32: thread t of the first 256 owns element
+    // t / 16 of lanes 4 (t % 16) .. + 3, i.e. four consecutive channels of one row, and reads LDS contiguously
+    float *part = (float *)st0;                 // [slice][16][64]
+#pragma unroll
+    for (int e = 0; e < 16; ++e) part[(wave * 16 + e) * 64 + lane] = acc[e];
+    const bool split = a.ksplit > 1;
+    const int Nl = a.n_hi - a.n_lo;
+    float *ws = split ? a.ws + (int64_t)blockIdx.y * (a.m_hi - a.m_lo) * Nl : nullptr;
+    T *yg = (T *)a.y;
+    const T *rg = (const T *)a.res;
+    constexpr int AL = 4 * ESZ - 1;
+    const bool vec_out = split ? (Nl % 4 == 0 && (((uintptr_t)a.ws) & 15) == 0)
+                               : (a.y_row % 4 == 0 && a.n_lo % 4 == 0 && (((uintptr_t)a.y) & AL) == 0 && (((uintptr_t)a.res) & AL) == 0 &&
+                                  (((uintptr_t)a.bias) & 15) == 0);
+    if (tid >= 256) { __syncthreads(); return; }
+    const int e = tid >> 4, l0 = (tid & 15) * 4;
+    const int m = m0 + (e >> 2) * 8 + (l0 >> 5) * 4 + (e & 3), n = n0 + (l0 & 31);
+    const bool inside = m < a.m_hi && n < a.n_hi, n_vec = inside && vec_out && n + 4 <= a.n_hi;
+    const int64_t o = (int64_t)m * a.y_row + n;
+    float bv[4];
+    load_bias_vec<4>(a.bias, n, !split && n_vec, bv);
+    float rv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (rg && !split && n_vec) load_vec4(rg + o, rv);
+    __syncthreads();
+    if (!inside) return;
+    const float *p = part + e * 64 + l0;
+    float4 s4 = *(const float4 *)p;
+    float v[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+    for (int s = 1; s < S; ++s) {
+        s4 = *(const float4 *)(p + s * 1024);
+        v[0] = __fadd_rn(v[0], s4.x); v[1] = __fadd_rn(v[1], s4.y); v[2] = __fadd_rn(v[2], s4.z); v[3] = __fadd_rn(v[3], s4.w);
+    }
+    if (split) {
+        float *q = ws + (int64_t)(m - a.m_lo) * Nl + (n - a.n_lo);
+        if (n_vec) {
+            *(float4 *)q = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+            for (int c = 0; c < 4; ++c)
+                if (n + c < a.n_hi) q[c] = v[c];
+        }
+    } else if (n_vec) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = __fmaf_rn(v[c], a.alpha, bv[c]);
+        if (rg) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = __fadd_rn(v[c], rv[c]);
+        }
+        act_vec<4>(v, a.act);
+        store_vec4(yg + o, v);
+    } else {
+        for (int c = 0; c < 4; ++c) finish_one<DT>(v[c], a.alpha, a.bias, a.act, rg, yg, o + c, n + c, a.n_hi);
+    }
+}
+
 // Second pass of a split-K operator: out = act(alpha * (s0 + s1 + ... ) + bias + res), slices added in
 // ascending order.  One thread per FV consecutive output channels of the launched sub-range (FV = 4 when
 // the range and the pointers allow 16-byte accesses), coalesced along n.
@@ -1274,10 +1533,44 @@ static LaunchInfo pick_rows(const GemmArgs &a, hipStream_t s, bool dry)
     }
 }
 
+// Launcher of slices_kernel: S waves per workgroup (one K slice each), ksplit workgroups along K.
+template <int DT, int S>
+static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase)
+{
+    typedef typename El<DT>::T T;
+    const int tiles_m = (a.m_hi - a.m_lo + 31) / 32, tiles_n = (a.n_hi - a.n_lo + 31) / 32;
+    LaunchInfo li;
+    li.workgroups = tiles_m * tiles_n * a.ksplit;
+    li.threads = 64 * S;
+    li.lds_bytes = S * 16384 + (a.pre_scale ? 8 * SLICES_PRE_MAX : 0);
+    li.wg_per_cu = (160 * 1024) / li.lds_bytes;
+    static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S);
+    static const std::string n_one = "igemm_slices_" + shape, n_pre = "igemm_affine_slices_" + shape;
+    li.kernel = phase == 2 ? "splitk_finish" : a.pre_scale ? n_pre.c_str() : n_one.c_str();
+    li.phases = a.ksplit > 1 ? 2 : 1;
+    if (dry || li.workgroups == 0) return li;
+    if (phase != 2) {
+        GemmArgs b = a;
+        b.n_major = tile_order(a, tiles_m, tiles_n, (int)sizeof(T));
+        set_divisors(b);
+        set_tiling(b, tiles_m, tiles_n);
+        const dim3 grid(tiles_m * tiles_n, a.ksplit), block(64 * S);
+        const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
+        if (a.pre_scale) GACER_LAUNCH((slices_kernel<DT, LOAD_AFFINE, S>), grid, block, 0, s, b);
+        else if (!taps) GACER_LAUNCH((slices_kernel<DT, LOAD_VEC, S>), grid, block, 0, s, b);
+        else if (a.Cin * (int)sizeof(T) % 128 == 0) GACER_LAUNCH((slices_kernel<DT, LOAD_TAPS, S>), grid, block, 0, s, b);
+        else GACER_LAUNCH((slices_kernel<DT, LOAD_TAPS_ANY, S>), grid, block, 0, s, b);
+    }
+    if (a.ksplit > 1 && phase != 1) launch_finish<T>(a, s);
+    return li;
+}
+
 template <int DT>
 static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     constexpr int VEC = El<DT>::VEC;
+    if (a.kwaves == 8) return go_slices<DT, 8>(a, s, dry, phase);
+    if (a.kwaves == 4) return go_slices<DT, 4>(a, s, dry, phase);
     const bool vec_ok = (a.Cin % VEC == 0) && (a.x_pix % VEC == 0) && (a.x_img % VEC == 0) && (a.w_row % VEC == 0) &&
                         (a.x_zb % VEC == 0) && (a.x_zh % VEC == 0) && (a.w_zb % VEC == 0) && (a.w_zh % VEC == 0) &&
                         (((uintptr_t)a.x) % 16 == 0) && (((uintptr_t)a.w) % 16 == 0);

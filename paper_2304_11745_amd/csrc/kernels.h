@@ -8,6 +8,8 @@
 
 namespace gacer {
 
+// most channels of a fused affine operator whose parameters slices_kernel keeps in LDS
+enum { SLICES_PRE_MAX = 4096 };
 enum { DT_F32 = 0, DT_BF16 = 1 };
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3, ACT_HSWISH = 4, ACT_HSIGMOID = 5 };
 
@@ -45,6 +47,9 @@ struct GemmArgs {
     // second kernel adds the slices in order 0,1,2,... and applies the epilogue.  Both numbers are fixed per
     // operator from its unsplit shape, so every decomposition adds in the same order.
     int ksplit, kb_per_slice;
+    // kwaves > 0 (4 or 8): the product runs on slices_kernel, each workgroup (one of `ksplit` along K) holding `kwaves` slices
+    // of `kb_per_wave` (an even number of) 64-byte blocks whose accumulators it adds in order; fixed per operator like ksplit.
+    int kwaves, kb_per_wave;
     float *ws;
     int n_major;               // set by the launcher: tiles are numbered n-major (1) or m-major (0), see tile_order()
     // set by the launcher: n / d for 0 <= n < 2^31 as (n * mul) >> (32 + shift), mul = 0 meaning d = 1; d = Ho*Wo, Wo, Cin, kw

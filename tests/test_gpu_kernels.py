@@ -1,0 +1,74 @@
+"""Single kernels at the sizes where they can go wrong (tile edges, remainders, both ends of the range a dispatch rule gives
+them): every operator against the oracle evaluated on the operator's own inputs, every decomposition bit-exact."""
+import numpy as np
+import pytest
+
+from parity import TOL_ONE_OP, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def check(tenants, expect, splits=()):
+    """Runs the tenants unsplit, compares every operator with the oracle, checks that the kernels named in `expect` (prefixes)
+    ran, and that the decompositions in `splits` ((axis, factor) applied wherever legal) reproduce every output bit."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import forward as F
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    data = [G.materialise(t, 411, i << 20) for i, t in enumerate(tenants)]
+    sess = harness.Session(tenants, data)
+    sess.poison_outputs()
+    sess.run(B.GACER_MODE_SEQUENTIAL, 1)
+    for i, (t, (_, params)) in enumerate(zip(tenants, data)):
+        got = [sess.tensor(i, k) for k in range(len(t.tensors))]
+        for k, op in enumerate(t.ops):
+            e = rel_err(got[op.out], F.run_op(t, k, got, params))
+            assert e <= TOL_ONE_OP[t.dtype], f"{t.name} op {k} ({op.kind}): rel err {e}"
+    base = [[sess.tensor_bytes(i, op.out) for op in t.ops] for i, t in enumerate(tenants)]
+    ran = {r["kernel"] for r in sess.trace(B.GACER_MODE_SEQUENTIAL, 1)}
+    for prefix in expect:
+        assert any(k.startswith(prefix) for k in ran), f"{prefix} did not run: {sorted(ran)}"
+    for axis, factor in splits:
+        sess.set_plan(sess.uniform_splits(axis, factor), [])
+        sess.poison_outputs()
+        sess.run(B.GACER_MODE_PLAN, 1)
+        for i, t in enumerate(tenants):
+            for k, op in enumerate(t.ops):
+                assert sess.tensor_bytes(i, op.out) == base[i][k], f"{axis} x{factor}: {t.name} op {k} differs"
+    sess.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_k_slices_inside_a_workgroup(dtype):
+    """slices_kernel: one row and one channel, one past a 32-wide tile, K that ends inside a 128-byte batch, taps that a batch
+    crosses and taps it does not, four and eight waves, 512 tiles, K cut over the grid as well, a fused affine."""
+    from synth import graphs as G
+    specs = [  # batch, hw, cin, [(cout, k, stride, pad, act, residual)]
+        (1, 1, 512, [(1, 1, 1, 0, "none", False)]),
+        (3, 11, 72, [(33, 1, 1, 0, "relu", False), (40, 1, 1, 0, "none", False), (40, 3, 1, 1, "relu6", True), (65, 3, 2, 1, "gelu", False)]),
+        (2, 9, 128, [(31, 3, 1, 1, "hswish", False)]),
+        (2, 14, 64, [(64, 3, 1, 1, "relu", False), (64, 3, 1, 1, "none", True)]),
+        (1, 64, 128, [(128, 1, 1, 0, "relu", False)]),          # 512 tiles of 32x32
+        (5, 13, 256, [(288, 1, 1, 0, "relu", False)]),          # 243 tiles, then 297
+        (5, 13, 256, [(352, 1, 1, 0, "relu", False)]),
+    ]
+    tenants = []
+    for i, (batch, hw, cin, layers) in enumerate(specs):
+        b = G._B(f"slices{i}", dtype, batch)
+        x = y = b.tensor(batch, cin, hw, hw)
+        for cout, k, stride, pad, act, res in layers:
+            y = b.conv(y, cout, k, stride, pad, act, res=y if res else -1)
+        tenants.append(b.done(x, y))
+    b = G._B("long_rows", dtype, 7)
+    x = b.tensor(7, 128, 7, 7)
+    tenants.append(b.done(x, b.gemm(x, 26, "relu", flatten=True)))
+    b = G._B("affine", dtype, 3)
+    x = b.tensor(3, 136, 5, 5)
+    y = b.conv(b.affine(x, "relu"), 40, 1, 1, 0, "relu")
+    tenants.append(b.done(x, y))
+    names = {"f32": ["igemm_slices_f32_x4", "igemm_slices_f32_x8", "igemm_affine_slices_f32", "splitk_finish"],
+             "bf16": ["igemm_slices_bf16_x4", "igemm_slices_bf16_x8", "igemm_affine_slices_bf16", "splitk_finish"]}
+    check(tenants, names[dtype], [("batch", 2), ("cout", 2), ("cout", 8)])
