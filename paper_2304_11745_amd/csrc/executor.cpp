@@ -20,6 +20,7 @@
 #include <set>
 #include <tuple>
 #include "ctx.h"
+#include "stem_geom.h"
 
 using namespace gacer;
 
@@ -149,6 +150,7 @@ Launch make_launch(const Tenant &t, int oi, int b_lo, int b_hi, int c_lo, int c_
         g.n_lo = c_lo; g.n_hi = c_hi;
         g.ksplit = t.ksplit[oi].ksplit; g.kb_per_slice = t.ksplit[oi].kb_per_slice;
         g.kwaves = t.ksplit[oi].kwaves; g.kb_per_wave = t.ksplit[oi].kb_per_wave;
+        g.stem = t.ksplit[oi].stem ? 1 : 0;
         g.ws = nullptr;                       // the workspace is chosen per call (see enqueue)
         break;
     }
@@ -500,7 +502,13 @@ static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
             const gacer_tensor &in = t.tensors[op.in0], &out = t.tensors[op.out];
             const int64_t M = out.n * out.h * out.w, N = out.c;
             const int K = op.kind == GACER_GEMM ? op.cin : (int)in.c * op.kh * op.kw;
-            t.ksplit[i] = decide_split(M, N, K, t.dtype, slices_operands(t, op));
+            const bool vectors = slices_operands(t, op);
+            StemGeom geom;
+            if (op.kind == GACER_CONV2D && !vectors && K <= 512 && stem_geometry(make_launch(t, (int)i, 0, t.batch, 0, (int)N).g, 1, &geom)) {
+                t.ksplit[i].stem = true;
+                continue;
+            }
+            t.ksplit[i] = decide_split(M, N, K, t.dtype, vectors);
             if (t.ksplit[i].ksplit > 1) t.ws_floats = std::max<size_t>(t.ws_floats, (size_t)t.ksplit[i].ksplit * M * N);
         }
         if (t.ws_floats) {

@@ -72,3 +72,28 @@ def test_k_slices_inside_a_workgroup(dtype):
     names = {"f32": ["igemm_slices_f32_x4", "igemm_slices_f32_x8", "igemm_affine_slices_f32", "splitk_finish"],
              "bf16": ["igemm_slices_bf16_x4", "igemm_slices_bf16_x8", "igemm_affine_slices_bf16", "splitk_finish"]}
     check(tenants, names[dtype], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_stems_and_odd_channel_counts(dtype):
+    """stem_kernel: runs of one chunk and of many, odd and even chunk counts, odd strides (runs that start on an odd element in
+    bf16), image rows of odd length, output rows shorter and longer than a 128-position tile, windows wider than the padding,
+    1 / 33 / 65 channels, a residual."""
+    from synth import graphs as G
+    specs = [  # batch, h, cin, [(cout, k, stride, pad, act, residual)]
+        (2, 33, 3, [(64, 7, 2, 3, "relu", False)]),
+        (1, 150, 3, [(65, 3, 1, 1, "relu", False)]),
+        (3, 35, 3, [(16, 3, 2, 1, "hswish", False)]),
+        (1, 67, 3, [(33, 11, 4, 2, "none", False)]),
+        (2, 9, 5, [(5, 5, 1, 2, "relu6", True), (7, 1, 1, 0, "none", False), (1, 2, 1, 0, "gelu", False)]),
+        (2, 8, 1, [(3, 3, 1, 1, "none", False), (13, 3, 1, 0, "relu", False), (40, 4, 3, 2, "none", False)]),
+        (1, 4, 3, [(8, 3, 1, 1, "none", False)]),
+    ]
+    tenants = []
+    for i, (batch, hw, cin, layers) in enumerate(specs):
+        b = G._B(f"stem{i}", dtype, batch)
+        x = y = b.tensor(batch, cin, hw, hw)
+        for cout, k, stride, pad, act, res in layers:
+            y = b.conv(y, cout, k, stride, pad, act, res=y if res else -1)
+        tenants.append(b.done(x, y))
+    check(tenants, [f"stem_{dtype}"], [("batch", 2), ("cout", 2), ("cout", 8)])
