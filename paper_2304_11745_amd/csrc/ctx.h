@@ -18,7 +18,7 @@ struct Launch {
 };
 
 // the cut of one operator's K range (see GemmArgs)
-struct KSplit { int ksplit = 1, kb_per_slice = 1 << 28, kwaves = 0, kb_per_wave = 0; bool stem = false; };
+struct KSplit { int ksplit = 1, kb_per_slice = 1 << 28, kwaves = 0, kb_per_wave = 0; bool stem = false, halo = false; };
 
 struct Tenant {
     std::vector<gacer_op> ops;

@@ -20,6 +20,7 @@
 #include <set>
 #include <tuple>
 #include "ctx.h"
+#include "conv3_geom.h"
 #include "stem_geom.h"
 
 using namespace gacer;
@@ -151,6 +152,7 @@ Launch make_launch(const Tenant &t, int oi, int b_lo, int b_hi, int c_lo, int c_
         g.ksplit = t.ksplit[oi].ksplit; g.kb_per_slice = t.ksplit[oi].kb_per_slice;
         g.kwaves = t.ksplit[oi].kwaves; g.kb_per_wave = t.ksplit[oi].kb_per_wave;
         g.stem = t.ksplit[oi].stem ? 1 : 0;
+        g.halo = t.ksplit[oi].halo ? 1 : 0;
         g.ws = nullptr;                       // the workspace is chosen per call (see enqueue)
         break;
     }
@@ -509,6 +511,8 @@ static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
                 continue;
             }
             t.ksplit[i] = decide_split(M, N, K, t.dtype, vectors);
+            if (op.kind == GACER_CONV2D && t.ksplit[i].ksplit == 1 && !t.ksplit[i].kwaves)
+                t.ksplit[i].halo = conv3_takes(make_launch(t, (int)i, 0, t.batch, 0, (int)N).g);
             if (t.ksplit[i].ksplit > 1) t.ws_floats = std::max<size_t>(t.ws_floats, (size_t)t.ksplit[i].ksplit * M * N);
         }
         if (t.ws_floats) {

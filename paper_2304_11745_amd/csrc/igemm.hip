@@ -1465,6 +1465,7 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     if (a.stem) return launch_stem(a, s, dry);
+    if (a.halo) return launch_conv3(a, s, dry);
     return a.dtype == DT_BF16 ? pick<DT_BF16>(a, s, dry, phase) : pick<DT_F32>(a, s, dry, phase);
 }
 

@@ -51,6 +51,7 @@ struct GemmArgs {
     // of `kb_per_wave` (an even number of) 64-byte blocks whose accumulators it adds in order; fixed per operator like ksplit.
     int kwaves, kb_per_wave;
     int stem;                  // the convolution runs on stem_kernel (channels that do not fill a 16-byte vector); fixed per operator
+    int halo;                  // the convolution runs on conv3_kernel (3x3, input staged once for all taps); fixed per operator
     float *ws;
     int n_major;               // set by the launcher: tiles are numbered n-major (1) or m-major (0), see tile_order()
     // set by the launcher: n / d for 0 <= n < 2^31 as (n * mul) >> (32 + shift), mul = 0 meaning d = 1; d = Ho*Wo, Wo, Cin, kw
@@ -103,6 +104,7 @@ struct LaunchInfo { int workgroups; int threads; int lds_bytes; int wg_per_cu; c
 // phase 0 enqueues everything the operator needs; 1 only the slice / main kernel; 2 only the finishing pass
 LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase = 0);
 LaunchInfo launch_stem(const GemmArgs &a, hipStream_t s, bool dry);        // launch_igemm hands over operators marked `stem`
+LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry);       // and operators marked `halo`
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry);
 LaunchInfo launch_maxpool(const StreamArgs &a, hipStream_t s, bool dry);
 LaunchInfo launch_gavgpool(const StreamArgs &a, hipStream_t s, bool dry);
