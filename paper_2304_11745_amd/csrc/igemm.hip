@@ -503,8 +503,8 @@ void igemm_dma_kernel(GemmArgs a)
     const int vrow = tid / KV;                                  // tile row of this thread's slot in pass 0
     const int lcol = (tid % KV) ^ ((vrow / R256) % KV);         // logical chunk that belongs into the slot
 
-    // per-thread A rows: byte offset of the window origin (or OOB) and one validity bit per tap
-    unsigned a_off[AV], a_hm[AV];
+    // per-thread A rows: byte offset of the window origin (or OOB) and one bit per tap, set where the tap reads nothing
+    unsigned a_off[AV], a_bad[AV];
 #pragma unroll
     for (int i = 0; i < AV; ++i) {
         const int m = m0 + vrow + i * RPP;
@@ -515,7 +515,7 @@ void igemm_dma_kernel(GemmArgs a)
         const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
         const int64_t e0 = (int64_t)img * a.x_img + ((int64_t)ih0 * a.W + iw0) * a.x_pix;   // may be negative at the border
         a_off[i] = ok ? (unsigned)(int)(e0 * ESZ) : OOB;
-        a_hm[i] = ok ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 0u;
+        a_bad[i] = TAPS ? ~(ok ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 0u) : 0u;
     }
     unsigned b_off[BV];
 #pragma unroll
@@ -546,14 +546,15 @@ void igemm_dma_kernel(GemmArgs a)
     // data into LDS takes the loads of all four waves in turn, and a wave that queues several at once is held there
     // while its matrix core runs dry.
     const int wave_slot = wave * 1024;
-    bool rq_ok = false;
-    unsigned rq_da = 0, rq_db = 0, rq_tap = 31u;
+    // What is masked gets an offset with the top bit set (OOB), by arithmetic: of selects the compiler makes branches with
+    // loads in both arms, and since it cannot count loads across them it then waits for requests of the newest blocks.
+    unsigned rq_bad = 0, rq_da = 0, rq_db = 0, rq_tap = 31u;
     auto request_begin = [&]() {
-        rq_ok = kv < k_end;
+        rq_bad = ~(unsigned)((kv - k_end) >> 31) & OOB;
         rq_db = (unsigned)(kv * ESZ);
         if constexpr (TAPS) {
             rq_da = (unsigned)((((int64_t)kr * a.W + ksx) * a.x_pix + kci) * ESZ);
-            rq_tap = rq_ok ? (unsigned)(kr * a.kw + ksx) : 31u;                 // bit 31 is never set
+            rq_tap = (unsigned)(kr * a.kw + ksx) & 31u;                         // beyond K rq_bad masks whatever tap this is
         } else {
             rq_da = rq_db;
         }
@@ -561,13 +562,13 @@ void igemm_dma_kernel(GemmArgs a)
     auto request_part = [&](unsigned char *stage, int p) {                      // p in [0, AV + BV), a compile-time constant
         if (p < AV) {
             const int i = p;
-            const bool ok = TAPS ? (((a_hm[i] >> rq_tap) & 1u) != 0) : (rq_ok && a_hm[i]);
+            const unsigned bad = rq_bad | (TAPS ? (a_bad[i] >> rq_tap) << 31 : 0u);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GACER_LDS(stage + i * RPP * ROWB + wave_slot), 16,
-                                                     (int)(ok ? a_off[i] + rq_da : OOB), 0, 0, 0);
+                                                     (int)((a_off[i] + rq_da) | bad), 0, 0, 0);
         } else {
             const int i = p - AV;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + (BM + i * RPP) * ROWB + wave_slot), 16,
-                                                     (int)((rq_ok && b_off[i] != OOB) ? b_off[i] + rq_db : OOB), 0, 0, 0);
+                                                     (int)((b_off[i] + rq_db) | rq_bad), 0, 0, 0);
         }
     };
     auto request_end = [&]() {
@@ -908,8 +909,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
     // (l % 8) ^ ((row / 2) % 8) -- two values per lane, by the parity of p
     const int c0 = (lane & 7) ^ (lane >> 4);
     const int kl[2] = {c0 * VEC, (c0 ^ 4) * VEC};
-    unsigned a_off[4], a_hm[4], b_off[4];
-    bool b_ok[4];
+    unsigned a_off[4], a_bad[4], b_off[4];      // a_bad: one bit per tap, set where the tap reads nothing
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int row = 8 * p + (lane >> 3);
@@ -922,9 +922,8 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
         const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
         const int64_t e0 = (int64_t)img * a.x_img + ((int64_t)ih0 * a.W + iw0) * a.x_pix + (LOAD == LOAD_TAPS_ANY ? 0 : kl[p & 1]);
         a_off[p] = (unsigned)(int)(e0 * ESZ);
-        a_hm[p] = ok ? (LOAD == LOAD_TAPS || LOAD == LOAD_TAPS_ANY ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 1u) : 0u;
-        b_ok[p] = n0 + row < a.n_hi;
-        b_off[p] = (unsigned)(((int64_t)(n0 + row) * a.w_row + kl[p & 1]) * ESZ);
+        a_bad[p] = ~(ok ? (LOAD == LOAD_TAPS || LOAD == LOAD_TAPS_ANY ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 1u) : 0u);
+        b_off[p] = n0 + row < a.n_hi ? (unsigned)(((int64_t)(n0 + row) * a.w_row + kl[p & 1]) * ESZ) : OOB;
     }
 
     // K range of this wave, in elements; loads at or beyond k_end return zeros
@@ -943,16 +942,18 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
         ksx = tap - kr * a.kw;
     }
     auto request = [&](unsigned char *stage) {
-        unsigned da[2], tap[2];
-        bool k_ok[2];
+        // LOAD_AFFINE masks by arithmetic (the top bit puts an offset out of range): of selects the compiler makes branches with
+        // loads in both arms, cannot count across them and waits for loads of the newest batch too, which costs the variant
+        // with stores in flight a memory latency per batch.  Without stores the branches are 1-6 % faster.
+        unsigned da[2], tap[2], k_bad[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int kv = kb + kl[h];
-            k_ok[h] = kv < k_end;
+            k_bad[h] = PRE ? ~(unsigned)((kv - k_end) >> 31) & OOB : kv < k_end ? 0u : OOB;
             tap[h] = 0u;
             if constexpr (LOAD == LOAD_TAPS) {
                 da[h] = (unsigned)((((int64_t)kr * a.W + ksx) * a.x_pix + kci) * ESZ);
-                tap[h] = (unsigned)(kr * a.kw + ksx);
+                tap[h] = (unsigned)(kr * a.kw + ksx) & 31u;
             } else if constexpr (LOAD == LOAD_TAPS_ANY) {
                 const int t = div_by(kv, a.div_cin), ci = kv - t * a.Cin;
                 const int r = div_by(t, a.div_kw), q = t - r * a.kw;
@@ -963,13 +964,17 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
             }
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GACER_LDS(stage + p * 1024), 16,
-                                                     (int)((k_ok[p & 1] && ((a_hm[p] >> tap[p & 1]) & 1u)) ? a_off[p] + da[p & 1] : OOB), 0, 0, 0);
+        for (int p = 0; p < 4; ++p) {
+            const unsigned off = PRE ? (a_off[p] + da[p & 1]) | k_bad[p & 1] | (a_bad[p] << 31)
+                                     : k_bad[p & 1] == 0u && !((a_bad[p] >> tap[p & 1]) & 1u) ? a_off[p] + da[p & 1] : OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GACER_LDS(stage + p * 1024), 16, (int)off, 0, 0, 0);
+        }
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + 4096 + p * 1024), 16,
-                                                     (int)((k_ok[p & 1] && b_ok[p]) ? b_off[p] + (unsigned)(kb * ESZ) : OOB), 0, 0, 0);
+        for (int p = 0; p < 4; ++p) {
+            const unsigned off = PRE ? (b_off[p] + (unsigned)(kb * ESZ)) | k_bad[p & 1]
+                                     : k_bad[p & 1] == 0u && b_off[p] != OOB ? b_off[p] + (unsigned)(kb * ESZ) : OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + 4096 + p * 1024), 16, (int)off, 0, 0, 0);
+        }
         kb += BE;
         if constexpr (LOAD == LOAD_TAPS) {
             kci += BE;
@@ -989,8 +994,15 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
     const int frag = lrow * 128, frag_lo = (lhalf ^ ((lrow >> 1) & 7)) * 16;
     constexpr int WAIT_BATCH = (8 & 15) | (7 << 4) | (15 << 8);                 // vmcnt(8): the older of the two batches in flight has landed
     constexpr int WAIT_LDS = 15 | (7 << 4) | (3 << 14);                         // lgkmcnt(0)
-    auto step = [&](unsigned char *stage, int k0) {
-        __builtin_amdgcn_s_waitcnt(WAIT_BATCH);
+    // LOAD_AFFINE: the waves of channel 0 also store the transformed A, four stores per batch behind the batch's requests (the
+    // other waves, and masked lanes, store out of range).  vmcnt counts them: four more may be outstanding
+    // at every second batch, where a wait for eight would cost one memory latency (at the loop's entry there are no stores yet).
+    // With that and the parameters requested together with the operands, DenseNet's 40 such products of 8 images take 299 us in
+    // bf16, 378 before.
+    constexpr int WAIT_STORED = 12 | (7 << 4) | (15 << 8);
+    const __amdgpu_buffer_rsrc_t yr = make_rsrc(PRE ? a.pre_y : nullptr, PRE && n0 == 0 ? (int64_t)a.m_hi * a.Cin * ESZ : 0);
+    auto step = [&](unsigned char *stage, int k0, bool entry) {
+        if (PRE && !entry) __builtin_amdgcn_s_waitcnt(WAIT_STORED); else __builtin_amdgcn_s_waitcnt(WAIT_BATCH);
         asm volatile("" ::: "memory");
         uint4 fa[4], fb[4];
 #pragma unroll
@@ -1013,7 +1025,9 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
                     sh[q] = h4.x; sh[q + 1] = h4.y; sh[q + 2] = h4.z; sh[q + 3] = h4.w;
                 }
                 fa[g] = affine_vec<DT>(fa[g], sc, sh, a.pre_act);
-                if (n0 == 0 && m0 + lrow < a.m_hi && kv < k_end) *(uint4 *)((T *)a.pre_y + (int64_t)(m0 + lrow) * a.Cin + kv) = fa[g];
+                const i32x4 v = {(int)fa[g].x, (int)fa[g].y, (int)fa[g].z, (int)fa[g].w};
+                const unsigned bad = ~(unsigned)(((m0 + lrow - a.m_hi) & (kv - k_end)) >> 31) & OOB;
+                __builtin_amdgcn_raw_buffer_store_b128(v, yr, (int)((unsigned)(((int64_t)(m0 + lrow) * a.Cin + kv) * ESZ) | bad), 0, 0);
             }
             if constexpr (DT == DT_BF16) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[g]), __builtin_bit_cast(bf16x8, fb[g]), acc, 0, 0, 0);
@@ -1029,22 +1043,36 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
     };
 
     unsigned char *w0 = st0 + wave * STAGE, *w1 = st1 + wave * STAGE;
-    request(w0);
     if constexpr (PRE) {                        // zeros beyond K: a zero element of B meets something finite
         const int pre_n = (a.K + BE - 1) / BE * BE;
-        for (int k = tid; k < pre_n; k += 64 * S) {
-            pre[k] = k < a.K ? a.pre_scale[k] : 0.f;
-            pre[SLICES_PRE_MAX + k] = k < a.K ? a.pre_shift[k] : 0.f;
+        const __amdgpu_buffer_rsrc_t psr = make_rsrc(a.pre_scale, (int64_t)a.K * 4), phr = make_rsrc(a.pre_shift, (int64_t)a.K * 4);
+        const int k0 = tid * 4;                 // the first 256 S channels are requested ahead of the operands: one memory latency
+        const uint4 sc = buf_load16(psr, (unsigned)(k0 * 4)), sh = buf_load16(phr, (unsigned)(k0 * 4));
+        asm volatile("" ::: "memory");
+        request(w0);
+        request(w1);
+        if (k0 < pre_n) {
+            *(uint4 *)(pre + k0) = sc;
+            *(uint4 *)(pre + SLICES_PRE_MAX + k0) = sh;
         }
+        for (int k = k0 + 256 * S; k < pre_n; k += 256 * S) {
+            *(uint4 *)(pre + k) = buf_load16(psr, (unsigned)(k * 4));
+            *(uint4 *)(pre + SLICES_PRE_MAX + k) = buf_load16(phr, (unsigned)(k * 4));
+        }
+        __builtin_amdgcn_s_waitcnt(WAIT_LDS);   // parameters written; the requests stay in flight across the barrier
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    } else {
+        request(w0);
+        request(w1);
     }
-    request(w1);
-    if constexpr (PRE) __syncthreads();
     int b = 0;
     for (; b + 2 <= batches; b += 2) {
-        step(w0, k_lo + b * BE);
-        step(w1, k_lo + (b + 1) * BE);
+        step(w0, k_lo + b * BE, true);
+        step(w1, k_lo + (b + 1) * BE, false);
     }
-    if (b < batches) step(w0, k_lo + b * BE);
+    if (b < batches) step(w0, k_lo + b * BE, true);
     __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));                           // vmcnt(0): the requests beyond the slice have landed
     asm volatile("" ::: "memory");
     __syncthreads();                            // `part` overlays the stages of several waves
