@@ -60,10 +60,12 @@ __global__ __launch_bounds__(TPB) void dwconv_kernel(StreamArgs a)
     st_vec<T, V>((T *)a.y, o, yv);
 }
 
-// ---- depthwise 3x3, register tiled: one thread = TW consecutive output pixels of one row x one channel vector ----
-// The 3 x ((TW-1)*S + 3) input window and the 9 weight vectors are loaded once and reused by the TW outputs, which
-// cuts load instructions about three-fold.  Every output is still the same chain of nine fused multiply-adds over
+// ---- depthwise 3x3 and 5x5, register tiled: one thread = TW consecutive output pixels of one row x one channel vector ----
+// The K x ((TW-1)*S + K) input window and the K*K weight vectors are loaded once and reused by the TW outputs, which
+// cuts what goes through L1 about three-fold.  Every output is still the same chain of fused multiply-adds over
 // taps (r, s) ascending (zero fill outside the image adds exact zeros), so results equal the generic kernel's.
+// 5x5: MobileNetV3's six such layers at 32 images bf16 take 71 us, 130 with one output vector per thread (bound by L1: 25
+// window loads per output); at batch 7, 147x147, fp32 31 / 51 us.
 template <typename T, int V> struct Unpack;
 template <> struct Unpack<float, 4> {
     static __device__ __forceinline__ void run(const uint4 &r, float *f)
@@ -93,8 +95,9 @@ template <> struct Unpack<unsigned short, 8> {
     }
 };
 
-// outputs per thread along W: as many as fit 128 registers (four waves per SIMD keep enough loads in flight)
-template <int V, int S> struct DW_TW { static constexpr int value = S == 2 ? 2 : 4; };
+// outputs per thread along W.  3x3: as many as fit 128 registers (four waves per SIMD keep enough loads in flight); 5x5: 256, with
+// window and weights of fp32 twice as large
+template <typename T, int S, int K> struct DW_TW { static constexpr int value = (S == 2 ? 2 : 4) / (K == 5 && sizeof(T) == 4 ? 2 : 1); };
 
 template <> struct Unpack<unsigned short, 4> {
     static __device__ __forceinline__ void run(const uint2 &r, float *f)
@@ -110,10 +113,10 @@ template <> struct Unpack<unsigned short, 4> {
 template <typename T, int V> struct Raw { typedef uint4 type; static __device__ __forceinline__ uint4 load(__amdgpu_buffer_rsrc_t r, unsigned o) { return buf_load16(r, o); } };
 template <> struct Raw<unsigned short, 4> { typedef uint2 type; static __device__ __forceinline__ uint2 load(__amdgpu_buffer_rsrc_t r, unsigned o) { return buf_load8(r, o); } };
 
-template <typename T, int V, int S>
-__global__ __launch_bounds__(TPB, 4) void dwconv3_kernel(StreamArgs a)
+template <typename T, int V, int S, int K>
+__global__ __launch_bounds__(TPB, K == 3 ? 4 : 2) void dwconv_tile_kernel(StreamArgs a)
 {
-    constexpr int TW = DW_TW<V, S>::value, NC = (TW - 1) * S + 3, ESZ = (int)sizeof(T);
+    constexpr int TW = DW_TW<T, S, K>::value, NC = (TW - 1) * S + K, ESZ = (int)sizeof(T);
     const int CV = (a.c_hi - a.c_lo) / V;
     const int WT = (a.Wo + TW - 1) / TW;
     const int64_t total = (int64_t)(a.n_hi - a.n_lo) * a.Ho * WT * CV;
@@ -128,10 +131,10 @@ __global__ __launch_bounds__(TPB, 4) void dwconv3_kernel(StreamArgs a)
     const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, (int64_t)a.N * a.H * a.W * a.C * ESZ);
     // all loads are issued up front, without branches: positions outside the image read as zero
     typedef typename Raw<T, V>::type R;
-    R raw[3][NC], wraw[9];
+    R raw[K][NC], wraw[K * K];
     const int iw0 = ow0 * S - a.pad;
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
+    for (int r = 0; r < K; ++r) {
         const int ih = oh * S - a.pad + r;
         const bool row_ok = ih >= 0 && ih < a.H;
         const unsigned row_off = (unsigned)((((int64_t)n * a.H + ih) * a.W * a.C + c) * ESZ);
@@ -144,22 +147,22 @@ __global__ __launch_bounds__(TPB, 4) void dwconv3_kernel(StreamArgs a)
     }
     const T *w = (const T *)a.w;
 #pragma unroll
-    for (int t = 0; t < 9; ++t) wraw[t] = *(const R *)(w + (int64_t)t * a.C + c);
+    for (int t = 0; t < K * K; ++t) wraw[t] = *(const R *)(w + (int64_t)t * a.C + c);
     float acc[TW][V];
 #pragma unroll
     for (int t = 0; t < TW; ++t)
 #pragma unroll
         for (int q = 0; q < V; ++q) acc[t][q] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        float wf[3][V];
+    for (int r = 0; r < K; ++r) {
+        float wf[K][V];
 #pragma unroll
-        for (int q3 = 0; q3 < 3; ++q3) Unpack<T, V>::run(wraw[r * 3 + q3], wf[q3]);
+        for (int q3 = 0; q3 < K; ++q3) Unpack<T, V>::run(wraw[r * K + q3], wf[q3]);
         float in[NC][V];
 #pragma unroll
         for (int j = 0; j < NC; ++j) Unpack<T, V>::run(raw[r][j], in[j]);
 #pragma unroll
-        for (int q3 = 0; q3 < 3; ++q3)
+        for (int q3 = 0; q3 < K; ++q3)
 #pragma unroll
             for (int t = 0; t < TW; ++t)
 #pragma unroll
@@ -188,7 +191,8 @@ __global__ __launch_bounds__(TPB, 4) void dwconv3_kernel(StreamArgs a)
     }
 }
 
-// ---- depthwise K x K with K known at compile time (5 x 5): the loops are unrolled and branch-free, so the taps and their
+// ---- depthwise K x K with K known at compile time, one output vector per thread (5 x 5 where the tiled kernel does not apply:
+// ragged channel ranges, strides above 2): the loops are unrolled and branch-free, so the taps and their
 // weights are requested together instead of one load per trip of a loop; a tap outside the image reads as zero and is
 // multiplied like the others, which leaves the FMA chain of dwconv_kernel (row-major from zero) bit for bit.
 template <typename T, int V, int K>
@@ -592,28 +596,27 @@ static LaunchInfo info(int64_t wgs, const char *kernel)
         return info(g, NAME);                                                                                   \
     }
 
+template <typename T, int V, int S, int K>
+static LaunchInfo go_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
+{
+    constexpr int TW = DW_TW<T, S, K>::value;
+    const int64_t tiles = (int64_t)(a.n_hi - a.n_lo) * a.Ho * ((a.Wo + TW - 1) / TW);
+    const int64_t g = (tiles * ((a.c_hi - a.c_lo) / V) + TPB - 1) / TPB;
+    if (!dry && g) GACER_LAUNCH((dwconv_tile_kernel<T, V, S, K>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, V, TW));
+    return info(g, K == 3 ? "dwconv3x3" : "dwconv5x5");
+}
+
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry)
 {
-    if (a.k == 3 && (a.stride == 1 || a.stride == 2)) {
-        auto tiles_for = [&](int tw) { return (int64_t)(a.n_hi - a.n_lo) * a.Ho * ((a.Wo + tw - 1) / tw); };
+    if ((a.k == 3 || a.k == 5) && (a.stride == 1 || a.stride == 2)) {
+        // bfloat16: 8-byte vectors (4 channels per lane) keep the window in registers without spilling
         if (a.dtype == DT_BF16 && a.C % 4 == 0 && a.c_lo % 4 == 0 && (a.c_hi - a.c_lo) % 4 == 0 && vec_ok<unsigned short, 1>(a)) {
-            // bfloat16: 8-byte vectors (4 channels per lane) keep the window in registers without spilling
-            const int64_t tiles = tiles_for(a.stride == 1 ? DW_TW<4, 1>::value : DW_TW<4, 2>::value);
-            const int64_t g = (tiles * ((a.c_hi - a.c_lo) / 4) + TPB - 1) / TPB;
-            if (!dry && g) {
-                if (a.stride == 1) GACER_LAUNCH((dwconv3_kernel<unsigned short, 4, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 4, DW_TW<4, 1>::value));
-                else GACER_LAUNCH((dwconv3_kernel<unsigned short, 4, 2>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 4, DW_TW<4, 2>::value));
-            }
-            return info(g, "dwconv3x3");
+            if (a.k == 3) return a.stride == 1 ? go_dwconv_tile<unsigned short, 4, 1, 3>(a, s, dry) : go_dwconv_tile<unsigned short, 4, 2, 3>(a, s, dry);
+            return a.stride == 1 ? go_dwconv_tile<unsigned short, 4, 1, 5>(a, s, dry) : go_dwconv_tile<unsigned short, 4, 2, 5>(a, s, dry);
         }
         if (a.dtype == DT_F32 && vec_ok<float, 4>(a)) {
-            const int64_t tiles = tiles_for(a.stride == 1 ? DW_TW<4, 1>::value : DW_TW<4, 2>::value);
-            const int64_t g = (tiles * ((a.c_hi - a.c_lo) / 4) + TPB - 1) / TPB;
-            if (!dry && g) {
-                if (a.stride == 1) GACER_LAUNCH((dwconv3_kernel<float, 4, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 4, DW_TW<4, 1>::value));
-                else GACER_LAUNCH((dwconv3_kernel<float, 4, 2>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 4, DW_TW<4, 2>::value));
-            }
-            return info(g, "dwconv3x3");
+            if (a.k == 3) return a.stride == 1 ? go_dwconv_tile<float, 4, 1, 3>(a, s, dry) : go_dwconv_tile<float, 4, 2, 3>(a, s, dry);
+            return a.stride == 1 ? go_dwconv_tile<float, 4, 1, 5>(a, s, dry) : go_dwconv_tile<float, 4, 2, 5>(a, s, dry);
         }
     }
     const int64_t outs = (int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * (a.c_hi - a.c_lo);

@@ -123,3 +123,20 @@ def test_input_staged_once_for_nine_taps():
     y = b.conv(x, 64, 3, 1, 1, "relu", out=b.view(wide, 64, 64))
     tenants.append(b.done(x, b.conv(y, 64, 3, 1, 1, "none")))
     check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128"], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_depthwise_5x5(dtype):
+    """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; ragged
+    channel ranges and stride 3 on the one-vector kernel."""
+    from synth import graphs as G
+    specs = [  # batch, hw, c, stride, pad, act, residual
+        (3, 7, 24, 1, 2, "hswish", True), (2, 14, 40, 2, 2, "relu", False), (1, 5, 8, 1, 0, "none", False), (2, 9, 12, 2, 1, "relu6", False),
+        (2, 13, 9, 1, 2, "none", False), (1, 11, 16, 3, 2, "relu", False),
+    ]
+    tenants = []
+    for i, (batch, hw, c, stride, pad, act, res) in enumerate(specs):
+        b = G._B(f"dw{i}", dtype, batch)
+        x = b.tensor(batch, c, hw, hw)
+        tenants.append(b.done(x, b.conv(x, c, 5, stride, pad, act, groups=c, res=x if res else -1)))
+    check(tenants, ["dwconv5x5"], [("batch", 2), ("cout", 2), ("cout", 8)])
