@@ -140,3 +140,19 @@ def test_depthwise_5x5(dtype):
         x = b.tensor(batch, c, hw, hw)
         tenants.append(b.done(x, b.conv(x, c, 5, stride, pad, act, groups=c, res=x if res else -1)))
     check(tenants, ["dwconv5x5"], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_affine_in_front_of_a_product_around_channel_windows(dtype):
+    """Affine + ReLU that writes a channel window of a wider tensor, read by a 1x1 convolution: the neighbouring channels,
+    written by another operator, keep their contents."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, hw, cout) in enumerate([(2, 5, 40), (3, 40, 64), (1, 64, 136)]):          # K slices, one and several tiles per unit
+        b = G._B(f"pair{i}", dtype, batch)
+        x, wide = b.tensor(batch, 24, hw, hw), b.tensor(batch, 64, hw, hw)
+        b.conv(x, 16, 1, 1, 0, "none", out=b.view(wide, 24, 16))
+        y, mid = b.conv(x, 16, 3, 1, 1, "relu"), b.view(wide, 8, 16)
+        b.t.ops.append(G.Op("affine", y, mid, scale=b.param((16,), "uniform"), shift=b.param((16,), "uniform"), cin=16, cout=16, act="relu"))
+        tenants.append(b.done(x, b.conv(mid, cout, 1, 1, 0, "relu")))
+    check(tenants, ["eltwise"], [("batch", 2), ("cout", 2)])

@@ -190,6 +190,29 @@ def test_channel_window_validation(ctx):
         assert st == status, (bad.__name__, st, B.gacer_last_error(ctx))
 
 
+def _affine_then_product(dtype, pitch_in, pitch_mid, c_off_mid=8):
+    """conv -> affine + ReLU -> 1x1 convolution over 16 channels; a pitch makes the affine's input / output a channel window."""
+    from synth import graphs as G
+    b = G._B("pair", dtype, 2)
+    x = b.tensor(2, 24, 5, 5)
+    src = b.view(b.tensor(2, pitch_in, 5, 5), 0, 16) if pitch_in else None
+    y = b.conv(x, 16, 3, 1, 1, "relu", out=src)
+    mid = b.view(b.tensor(2, pitch_mid, 5, 5), c_off_mid, 16) if pitch_mid else b.tensor(2, 16, 5, 5)
+    b.t.ops.append(G.Op("affine", y, mid, scale=b.param((16,), "uniform"), shift=b.param((16,), "uniform"), cin=16, cout=16, act="relu"))
+    return b.done(x, b.conv(mid, 40, 1, 1, 0, "relu"))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_affine_that_writes_a_channel_window_keeps_its_own_launch(ctx, dtype):
+    """The fused launch stores the affine's output gap-free: a window of a wider tensor must not be fused over."""
+    for pitch_mid, launches in ((0, 2), (32, 3)):
+        st, _ = load(ctx, [_affine_then_product(dtype, 0, pitch_mid)])
+        assert st == B.GACER_OK, B.gacer_last_error(ctx)
+        n = C.c_int()
+        assert B.gacer_launch_count(ctx, B.GACER_MODE_SEQUENTIAL, C.byref(n)) == B.GACER_OK
+        assert n.value == launches, pitch_mid
+
+
 def _plan(splits=(), syncs=()):
     sp = (B.gacer_split * max(1, len(splits)))(*[B.gacer_split(*s) for s in splits])
     sy = (B.gacer_sync * max(1, len(syncs)))(*[B.gacer_sync(*s) for s in syncs])
