@@ -533,7 +533,7 @@ static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
 // arithmetic on the way in and also writes operator i's output tensor; operator i then has no launch of its own.  Both give
 // the bits of the two stand-alone kernels.  Not fused: pairs of which either operator is decomposed by the plan, pairs whose
 // first operator's completion is a sync pointer's source, pairs whose tensor in between is a channel window, operands that are
-// not 16-byte aligned or whose channel count is not a multiple of a 16-byte vector.
+// not 16-byte aligned or whose channel count or position pitch is not a multiple of a 16-byte vector.
 static bool aligned16p(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 static bool fusable_pair(const Tenant &T, int i)
@@ -546,7 +546,7 @@ static bool fusable_pair(const Tenant &T, int i)
     const gacer_tensor &in = T.tensors[af.in0], &mid = T.tensors[af.out];
     const int vec = T.dtype == GACER_BF16 ? 8 : 4;
     if (mid.pitch) return false;                 // the fused launch stores the tensor between the two gap-free
-    if (in.c % vec || (T.ksplit[i + 1].kwaves && in.c > SLICES_PRE_MAX)) return false;
+    if (in.c % vec || (in.pitch && in.pitch % vec) || (T.ksplit[i + 1].kwaves && in.c > SLICES_PRE_MAX)) return false;
     return aligned16p(in.dptr) && aligned16p(mid.dptr) && aligned16p(af.scale) && aligned16p(af.shift) && aligned16p(pw.w);
 }
 

@@ -145,9 +145,14 @@ def test_depthwise_5x5(dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_affine_in_front_of_a_product_around_channel_windows(dtype):
     """Affine + ReLU that writes a channel window of a wider tensor, read by a 1x1 convolution: the neighbouring channels,
-    written by another operator, keep their contents."""
+    written by another operator, keep their contents.  One that reads a window whose rows do not start at whole vectors."""
     from synth import graphs as G
     tenants = []
+    for i, (batch, hw, cout) in enumerate([(2, 5, 40), (3, 40, 64)]):           # a window read at a pitch that is no whole vector
+        b = G._B(f"rows{i}", dtype, batch)
+        x, wide = b.tensor(batch, 24, hw, hw), b.tensor(batch, 21, hw, hw)
+        y = b.affine(b.conv(x, 16, 3, 1, 1, "none", out=b.view(wide, 0, 16)), "relu")
+        tenants.append(b.done(x, b.conv(y, cout, 1, 1, 0, "relu")))
     for i, (batch, hw, cout) in enumerate([(2, 5, 40), (3, 40, 64), (1, 64, 136)]):          # K slices, one and several tiles per unit
         b = G._B(f"pair{i}", dtype, batch)
         x, wide = b.tensor(batch, 24, hw, hw), b.tensor(batch, 64, hw, hw)

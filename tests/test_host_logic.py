@@ -213,6 +213,19 @@ def test_affine_that_writes_a_channel_window_keeps_its_own_launch(ctx, dtype):
         assert n.value == launches, pitch_mid
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_affine_that_reads_unaligned_rows_keeps_its_own_launch(ctx, dtype):
+    """The fused launch reads the affine's input in 16-byte vectors: a window whose pitch is no multiple of one, or that starts
+    inside one, must not be fused over; the stand-alone operator reads it element by element."""
+    vec = 8 if dtype == "bf16" else 4
+    for pitch_in, launches in ((0, 2), (16 + vec, 2), (16 + vec // 2, 3), (17, 3)):
+        st, _ = load(ctx, [_affine_then_product(dtype, pitch_in, 0)])
+        assert st == B.GACER_OK, B.gacer_last_error(ctx)
+        n = C.c_int()
+        assert B.gacer_launch_count(ctx, B.GACER_MODE_SEQUENTIAL, C.byref(n)) == B.GACER_OK
+        assert n.value == launches, pitch_in
+
+
 def _plan(splits=(), syncs=()):
     sp = (B.gacer_split * max(1, len(splits)))(*[B.gacer_split(*s) for s in splits])
     sy = (B.gacer_sync * max(1, len(syncs)))(*[B.gacer_sync(*s) for s in syncs])
