@@ -106,8 +106,8 @@ __global__ __launch_bounds__(STEM_THREADS) void stem_kernel(StemArgs a)
         for (int q = tid & 7; q < 2 * pairs * a.kh; q += 8) {
             const int kr = div_by(q, a.div_pairs2), c = q - kr * 2 * pairs, n = n0 + r, valid = run - c * VEC;
             const int e = n * (a.kh * run) + kr * run + c * VEC;
-            uint4 v = chunk<DT>(wr, e, n < a.n_hi && valid > 0 && e * ESZ + 20 <= w_bytes);
-            if (e * ESZ + 20 > w_bytes) v = chunk_edge<DT>(wr, w_bytes, e, n < a.n_hi && valid > 0);
+            uint4 v = chunk<DT>(wr, e, n < a.n_hi && valid > 0 && e * ESZ <= w_bytes - 20);
+            if (e * ESZ > w_bytes - 20) v = chunk_edge<DT>(wr, w_bytes, e, n < a.n_hi && valid > 0);
             *(uint4 *)(Bs + r * a.rowb + q * 16) = make_uint4(v.x & valid_mask<DT>(0, valid), v.y & valid_mask<DT>(1, valid),
                                                               v.z & valid_mask<DT>(2, valid), v.w & valid_mask<DT>(3, valid));
         }
@@ -144,8 +144,7 @@ __global__ __launch_bounds__(STEM_THREADS) void stem_kernel(StemArgs a)
         const int oh_b = __builtin_amdgcn_readfirstlane(div_by(min(s.p0 + STEM_BM, HoWo) - 1, a.div_wo));
         s.ih0 = s.oh_a * a.stride - a.pad;
         s.rows = (oh_b - s.oh_a) * a.stride + a.kh;
-        // rows that hold the tensor's first element or reach its last bytes
-        s.edge = (s.img == 0 && s.ih0 <= 0) || ((s.img * a.H + min(s.ih0 + s.rows, a.H)) * WC + 3 * VEC) * ESZ > x_bytes;
+        s.edge = stem_edge(s.img == 0 && s.ih0 <= 0, s.img * a.H + min(s.ih0 + s.rows, a.H), WC, x_bytes / ESZ, VEC);
         return s;
     };
     auto load = [&](const Strip &s, int r, int k) {

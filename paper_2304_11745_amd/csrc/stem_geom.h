@@ -1,5 +1,6 @@
-// Geometry of stem_kernel's operators (host code): which convolutions it takes and how their data lies in LDS.
+// Geometry of stem_kernel's operators (host code): which convolutions it takes and how their data lies in LDS and at the ends of its tensor.
 #pragma once
+#include <hip/hip_runtime.h>
 #include "kernels.h"
 
 namespace gacer {
@@ -17,8 +18,8 @@ struct StemGeom {
 };
 
 // Fills *out for workgroups of 32 * tn channels; false when the kernel does not take the operator: input positions with gaps, or
-// weights and input strip too large for half the LDS of a
-// compute unit (with one workgroup per unit the generic gather loader is as fast: 64x11x11x3 fp32, 8 images, 41.8 us here, 39.4 there).
+// weights and input strip too large for half the LDS of a compute unit (with one workgroup per unit the generic gather loader
+// is as fast: 64x11x11x3 fp32, 8 images, 41.8 us here, 39.4 there).
 inline bool stem_geometry(const GemmArgs &a, int tn, StemGeom *out)
 {
     const int VEC = a.dtype == DT_BF16 ? 8 : 4, ESZ = 16 / VEC;
@@ -45,6 +46,14 @@ inline bool stem_geometry(const GemmArgs &a, int tn, StemGeom *out)
     g.tiles = ((a.m_hi - a.m_lo) / (a.Ho * a.Wo)) * g.tiles_img;
     *out = g;
     return true;
+}
+
+// Whether a strip, read in chunks of 20 bytes, may reach over an end of the tensor: it holds the tensor's first row, or its last
+// rows (`rows` image rows from the tensor's start) end within three chunks of the tensor's end.  Counted in elements: in bytes
+// the sum does not fit an int for tensors just below the 2 GiB that a tensor may have.
+__host__ __device__ inline bool stem_edge(bool first_row, int rows, int WC, int elements, int VEC)
+{
+    return first_row || rows * WC > elements - 3 * VEC;
 }
 
 }  // namespace gacer

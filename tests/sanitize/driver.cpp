@@ -1,6 +1,7 @@
 // Host-side exerciser of the library's C ABI for sanitizer builds (AddressSanitizer + UndefinedBehaviorSanitizer on the
 // host code of executor.cpp / search.cpp).  No GPU is needed: kernels are never launched, HIP calls that need a device
 // fail and are reported as statuses.  Exit code 0 = every check held; the sanitizers abort on their own findings.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -8,6 +9,7 @@
 #include <string>
 #include <vector>
 #include "../../include/gacer.h"
+#include "../../paper_2304_11745_amd/csrc/stem_geom.h"
 
 #define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #cond); std::exit(1); } } while (0)
 
@@ -43,9 +45,24 @@ struct Chain {
     }
 };
 
+// stem_edge in 64 bits and bytes, for inputs of every size a tensor may have, those a few bytes below 2 GiB among them
+static void check_stem_edge(std::mt19937 &rng)
+{
+    for (int trial = 0; trial < 20000; ++trial) {
+        const int VEC = trial % 2 ? 8 : 4, ESZ = 16 / VEC;
+        const int64_t most = ((int64_t)1 << 31) / ESZ - 1;                      // elements of the largest tensor
+        const int64_t WC = trial % 5 ? 1 + rng() % 2000 : most >> rng() % 12;
+        const int64_t all = trial % 3 ? most / WC : 1 + rng() % (most / WC);    // image rows of the tensor
+        const int64_t rows = std::max<int64_t>(1, all - (int64_t)(rng() % 8));
+        CHECK(gacer::stem_edge(false, (int)rows, (int)WC, (int)(all * WC), VEC) == ((rows * WC + 3 * VEC) * ESZ > all * WC * ESZ));
+        CHECK(gacer::stem_edge(true, (int)rows, (int)WC, (int)(all * WC), VEC));
+    }
+}
+
 int main()
 {
     std::mt19937 rng(7);
+    check_stem_edge(rng);
     for (int trial = 0; trial < 30; ++trial) {
         gacer_ctx *ctx = nullptr;
         CHECK(gacer_create(&ctx) == GACER_OK);
