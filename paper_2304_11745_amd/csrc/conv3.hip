@@ -1,9 +1,9 @@
 // 3x3 convolutions (stride 1, padding 1, bf16) with many output positions: the input is staged once per channel block instead
 // of once per tap.
 //
-// A workgroup owns 256 output positions (consecutive in a column strip of at most 56 columns, row by row through all images)
-// x BN channels.  Per block of 32 channels the positions and their one-pixel halo, at most 384 pixels of 64 bytes, go into LDS
-// by direct loads (zeros left and right of the image); all nine taps read their A fragments from there, a tap being a fixed
+// A workgroup owns BM output positions (consecutive in a column strip of at most 56 columns, row by row through all images)
+// x BN channels.  Per block of 32 channels the positions and their one-pixel halo (for 256 positions at most 384 pixels of 64
+// bytes) go into LDS by direct loads (zeros left and right of the image); all nine taps read their A fragments from there, a tap being a fixed
 // displacement of the LDS row.  Taps above or below an image read a row of zeros instead.  The weights stream past in stages of
 // one tap (BN = 128, three stages) or three taps (BN = 64, two stages).  Two input blocks alternate, the next one being
 // requested while this one is used.  The step structure is that of igemm_dma_kernel: counted waits, one bare barrier per
@@ -15,9 +15,10 @@
 // 224x224 64->64 284.6 / 179.0, 112x112 64->128 110.7 / 80.2, 112x112 128->128 156.4 / 122.2, 56x56 256->256 153.8 / 119.3,
 // 28x28 512->512 144.2 / 112.4 (1053 TFLOP/s), 56x56 64->64 22.0 / 16.8.
 //
-// An output element is one MFMA chain over channel blocks of 32, in a block over the taps in ascending order; which kernel an
-// operator takes depends on its unsplit shape only, so every chunk of it adds alike.
+// An output element is one MFMA chain over channel blocks of 32, in a block over the taps in ascending order, whatever the tile;
+// which kernel an operator takes depends on its unsplit shape only, so every chunk of it adds alike.
 #include <hip/hip_runtime.h>
+#include <string>
 #include "device_util.h"
 #include "gemm_util.h"
 #include "kernels.h"
@@ -27,6 +28,11 @@ namespace gacer {
 
 static constexpr int THREADS = 256;
 static constexpr int ROWB = 64;                // bytes of a channel block: one LDS row
+static constexpr int SROW = 36;                // floats per row of the epilogue's patches, which overlay an input block
+constexpr int conv3_input_bytes(int bm)        // LDS of an input block: pixels and rows of zeros, at least the patches of four waves
+{
+    return (conv3_rows(bm) + 16) * ROWB > 4 * 32 * SROW * 4 ? (conv3_rows(bm) + 16) * ROWB : 4 * 32 * SROW * 4;
+}
 #define GACER_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 
 template <int N> __device__ __forceinline__ void wait_loads()       // at most N loads outstanding, own LDS reads done
@@ -35,20 +41,23 @@ template <int N> __device__ __forceinline__ void wait_loads()       // at most N
     asm volatile("" ::: "memory");
 }
 
-template <int BN>
+template <int BM, int BN>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 void conv3_kernel(GemmArgs a, Conv3Geom geo)
 {
     typedef unsigned short T;
-    constexpr int WM = BN == 128 ? 2 : 4, WN = 4 / WM;
-    constexpr int TM = CONV3_BM / WM / 32, TN = BN / WN / 32;
+    constexpr int WM = BM == 256 && BN == 64 ? 4 : 2, WN = 4 / WM;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int ROWS = conv3_rows(BM);       // input pixels (LDS rows) per tile and channel block
     constexpr int TPS = BN == 128 ? 1 : 3;     // taps per step
     constexpr int NSB = BN == 128 ? 3 : 2;     // weight stages
     constexpr int SPB = 9 / TPS;               // steps per channel block (a multiple of NSB over two blocks)
     constexpr int NB = BN * TPS / 64;          // weight loads per thread and step
-    constexpr int NA = CONV3_ROWS / 64;        // input loads per thread and channel block
+    constexpr int NA = ROWS / 64;              // input loads per thread and channel block
+    constexpr int A_STEPS = TPS == 1 ? NA : 2, PA = NA / A_STEPS;               // the steps of a block that request inputs, and how many each
     constexpr int G = 2 * TPS;                 // k groups (32 bytes of k) per step
-    constexpr int ABYTES = (CONV3_ROWS + 16) * ROWB, BBYTES = BN * TPS * ROWB;
+    constexpr int ABYTES = conv3_input_bytes(BM), BBYTES = BN * TPS * ROWB;
+    static_assert(NA % A_STEPS == 0 && A_STEPS <= SPB * 2 / 3, "inputs are requested in the first two thirds of a block");
 
     // separate arrays named by compile-time indices: the compiler can tell what is being filled from what is being read
     __shared__ __align__(1024) unsigned char a0[ABYTES];
@@ -67,7 +76,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     const int tile_m = __builtin_amdgcn_readfirstlane(geo.n_major ? tile - by_m * geo.tiles_m : by_n);
     const int tile_n = __builtin_amdgcn_readfirstlane(geo.n_major ? by_m : tile - by_n * geo.tiles_n);
     const int strip = __builtin_amdgcn_readfirstlane(div_by(tile_m, geo.div_strip));
-    const int p0 = (tile_m - strip * geo.tiles_strip) * CONV3_BM, c0 = strip * geo.tw, n0 = a.n_lo + tile_n * BN;
+    const int p0 = (tile_m - strip * geo.tiles_strip) * BM, c0 = strip * geo.tw, n0 = a.n_lo + tile_n * BN;
     const int tw = geo.tw, tw2 = tw + 2;
     const int row0 = __builtin_amdgcn_readfirstlane(div_by(p0, geo.div_tw)), col0 = p0 - row0 * tw;
 
@@ -110,7 +119,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     bool up[TM], down[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        const int p = p0 + wm * (CONV3_BM / WM) + i * 32 + lrow;
+        const int p = p0 + wm * (BM / WM) + i * 32 + lrow;
         const int r = div_by(p, geo.div_tw), h = r - div_by(r, geo.div_h) * a.H;
         f_row[i] = (r - row0) * tw2 + (p - r * tw) - col0;
         up[i] = h > 0;
@@ -141,9 +150,9 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     };
     constexpr int SCHED_ALU_MAY_CROSS = 0x2 | 0x4;
 
-    // zero rows of both input blocks (rows CONV3_ROWS .. + 15, never loaded)
-    if (tid < 64) *(uint4 *)(a0 + CONV3_ROWS * ROWB + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
-    else if (tid < 128) *(uint4 *)(a1 + CONV3_ROWS * ROWB + (tid - 64) * 16) = make_uint4(0u, 0u, 0u, 0u);
+    // zero rows of both input blocks (rows ROWS .. + 15, never loaded)
+    if (tid < 64) *(uint4 *)(a0 + ROWS * ROWB + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
+    else if (tid < 128) *(uint4 *)(a1 + ROWS * ROWB + (tid - 64) * 16) = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
     for (int p = 0; p < NA; ++p) request_a(a0, 0, p);
 #pragma unroll
@@ -159,9 +168,8 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     for (int cb = 0; cb < ncb; cb += 2) {
 #pragma unroll
         for (int u = 0; u < 2 * SPB; ++u) {
-            constexpr int PA = NA / (SPB * 2 / 3);
             const int blk = u / SPB, t = u % SPB;
-            const int na = t < SPB * 2 / 3 ? PA : 0;
+            const int na = t < A_STEPS ? PA : 0;
             const int v = u + NSB - 1;                                           // the step whose weights are requested
             const unsigned char *cur_a = a_at(blk), *cur_b = b_at(u % NSB);
             // opaque: the fragment addresses of all nine taps would otherwise be kept in registers around the loop and spill
@@ -174,8 +182,8 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     int L = f_row[i] + r * tw2 + q;
-                    if (r == 0) L = up[i] ? L : CONV3_ROWS;
-                    if (r == 2) L = down[i] ? L : CONV3_ROWS;
+                    if (r == 0) L = up[i] ? L : ROWS;
+                    if (r == 2) L = down[i] ? L : ROWS;
                     fa[set][i] = *(const uint4 *)(cur_a + L * ROWB + (((2 * g + lhalf) ^ ((L >> 2) & 3)) * 16));
                 }
 #pragma unroll
@@ -192,7 +200,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
             // The weights of the next step have landed.  Younger than them: with three stages the inputs of the step before
             // and this step's requests, with two stages this step's inputs.  Before a new block no input is outstanding.
             constexpr int NA_MAX = 2 * PA + NB;
-            const int before = t > 0 && t - 1 < SPB * 2 / 3 ? PA : 0;
+            const int before = t > 0 && t - 1 < A_STEPS ? PA : 0;
             const int pending = NSB == 3 ? before + NB + na : na;
             static_assert(NA_MAX < 16, "the wait count is encoded in four bits");
             if (pending == 0) wait_loads<0>();
@@ -210,7 +218,6 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     asm volatile("" ::: "memory");
 
     // ---- epilogue: as in igemm_epilogue, with the output position of a tile row computed from the strip ----
-    constexpr int SROW = 36;
     float *stage = (float *)a0 + wave * (32 * SROW);
     T *yg = (T *)a.y;
     const T *rg = (const T *)a.res;
@@ -223,7 +230,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
         bool ok[2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            const int p = p0 + wm * (CONV3_BM / WM) + i * 32 + erow + g * 16;
+            const int p = p0 + wm * (BM / WM) + i * 32 + erow + g * 16;
             const int r = div_by(p, geo.div_tw), c = c0 + p - r * tw;
             ok[g] = r < geo.rows && c < a.W;
             pos[g] = (int64_t)(geo.row_lo + r) * a.W + c;
@@ -262,7 +269,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     }
 }
 
-template <int BN>
+template <int BM, int BN>
 static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
 {
     Conv3Geom g;
@@ -270,15 +277,16 @@ static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
     g.strips = (a.W + g.tw - 1) / g.tw;
     g.rows = (a.m_hi - a.m_lo) / a.W;
     g.row_lo = a.m_lo / a.W;
-    g.tiles_strip = (int)(((int64_t)g.rows * g.tw + CONV3_BM - 1) / CONV3_BM);
+    g.tiles_strip = (int)(((int64_t)g.rows * g.tw + BM - 1) / BM);
     g.tiles_m = g.strips * g.tiles_strip;
     g.tiles_n = (a.n_hi - a.n_lo + BN - 1) / BN;
     LaunchInfo li;
     li.workgroups = g.tiles_m * g.tiles_n;
     li.threads = THREADS;
-    li.lds_bytes = 2 * (CONV3_ROWS + 16) * ROWB + (BN == 128 ? 3 : 6) * BN * ROWB;
+    li.lds_bytes = 2 * conv3_input_bytes(BM) + (BN == 128 ? 3 : 6) * BN * ROWB;
     li.wg_per_cu = 2;
-    li.kernel = BN == 128 ? "conv3_bf16_256x128" : "conv3_bf16_256x64";
+    static const std::string name = "conv3_bf16_" + std::to_string(BM) + "x" + std::to_string(BN);
+    li.kernel = name.c_str();
     li.phases = 1;
     if (dry || li.workgroups == 0) return li;
     // An XCD's band of tiles shares weights along m and inputs along n: number along the side that moves fewer bytes
@@ -290,13 +298,15 @@ static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
     divisor(g.tiles_strip, g.div_strip);
     divisor(g.tiles_m, g.div_tiles_m);
     divisor(g.tiles_n, g.div_tiles_n);
-    GACER_LAUNCH((conv3_kernel<BN>), dim3(li.workgroups), dim3(THREADS), 0, s, a, g);
+    GACER_LAUNCH((conv3_kernel<BM, BN>), dim3(li.workgroups), dim3(THREADS), 0, s, a, g);
     return li;
 }
 
 LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry)
 {
-    return conv3_bn(a.n_hi - a.n_lo) == 128 ? go_conv3<128>(a, s, dry) : go_conv3<64>(a, s, dry);
+    const Conv3Tile t = conv3_tile(a);
+    if (t.bn == 128) return go_conv3<256, 128>(a, s, dry);
+    return t.bm == 256 ? go_conv3<256, 64>(a, s, dry) : go_conv3<128, 64>(a, s, dry);
 }
 
 }  // namespace gacer

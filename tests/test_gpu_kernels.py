@@ -101,8 +101,8 @@ def test_stems_and_odd_channel_counts(dtype):
 
 def test_input_staged_once_for_nine_taps():
     """conv3_kernel: images narrower and wider than a column strip, a last strip that is narrower, rows shorter than a tile by
-    far, a tile that ends inside an image row, 64 and 128 channels per workgroup with remainders, a residual, one and several
-    pairs of channel blocks, an input that is a channel window of a wider tensor."""
+    far, a tile that ends inside an image row, the three tile shapes with remainders (chunks take smaller tiles than the whole
+    operator), a residual, one and several pairs of channel blocks, an input that is a channel window of a wider tensor."""
     from synth import graphs as G
     specs = [  # batch, h, w, cin, [(cout, act, residual)]
         (16, 56, 56, 64, [(64, "relu", False), (64, "relu", True)]),
@@ -110,6 +110,7 @@ def test_input_staged_once_for_nine_taps():
         (1, 191, 251, 128, [(65, "relu6", False)]),
         (67, 29, 13, 128, [(250, "gelu", False)]),
         (61, 53, 5, 64, [(130, "none", False)]),
+        (15, 101, 37, 64, [(250, "hswish", False)]),
     ]
     tenants = []
     for i, (batch, h, w, cin, layers) in enumerate(specs):
@@ -122,7 +123,7 @@ def test_input_staged_once_for_nine_taps():
     x, wide = b.tensor(15, 64, 55, 57), b.tensor(15, 192, 55, 57)
     y = b.conv(x, 64, 3, 1, 1, "relu", out=b.view(wide, 64, 64))
     tenants.append(b.done(x, b.conv(y, 64, 3, 1, 1, "none")))
-    check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128", "conv3_bf16_128x64"], [("batch", 2), ("cout", 2), ("cout", 8)])
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
