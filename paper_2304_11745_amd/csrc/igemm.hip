@@ -883,7 +883,7 @@ __global__ __launch_bounds__(THREADS) void rowgemm_kernel(GemmArgs a)
 // matrix cores from about 4 KB of K on.  Fragments loaded straight into registers in operand layout (32 rows x 32 bytes per
 // load) reach 19 bytes per clock: 49x512x4608 bf16 took 17.3 us that way, 9.0 us like this, 9.9 us as slices plus finishing
 // pass.  144x768x768 bf16 9.0 -> 4.6 us, 125x32x1152 fp32 31.3 -> 9.9 us, where an empty kernel reads 3.9 us.
-template <int DT, int LOAD, int S>
+template <int DT, int LOAD, int S, int PRE_MAX = 0>
 __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
 {
     typedef typename El<DT>::T T;
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
     constexpr bool PRE = LOAD == LOAD_AFFINE;
     __shared__ __align__(1024) unsigned char st0[S * STAGE];
     __shared__ __align__(1024) unsigned char st1[S * STAGE];
-    __shared__ __align__(16) float pre[PRE ? 2 * SLICES_PRE_MAX : 4];           // scale, shift
+    __shared__ __align__(16) float pre[PRE ? 2 * PRE_MAX : 4];                  // scale, shift
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
                 float sc[VEC], sh[VEC];
 #pragma unroll
                 for (int q = 0; q < VEC; q += 4) {
-                    const float4 s4 = *(const float4 *)(pre + kv + q), h4 = *(const float4 *)(pre + SLICES_PRE_MAX + kv + q);
+                    const float4 s4 = *(const float4 *)(pre + kv + q), h4 = *(const float4 *)(pre + PRE_MAX + kv + q);
                     sc[q] = s4.x; sc[q + 1] = s4.y; sc[q + 2] = s4.z; sc[q + 3] = s4.w;
                     sh[q] = h4.x; sh[q + 1] = h4.y; sh[q + 2] = h4.z; sh[q + 3] = h4.w;
                 }
@@ -1053,11 +1053,11 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
         request(w1);
         if (k0 < pre_n) {
             *(uint4 *)(pre + k0) = sc;
-            *(uint4 *)(pre + SLICES_PRE_MAX + k0) = sh;
+            *(uint4 *)(pre + PRE_MAX + k0) = sh;
         }
         for (int k = k0 + 256 * S; k < pre_n; k += 256 * S) {
             *(uint4 *)(pre + k) = buf_load16(psr, (unsigned)(k * 4));
-            *(uint4 *)(pre + SLICES_PRE_MAX + k) = buf_load16(phr, (unsigned)(k * 4));
+            *(uint4 *)(pre + PRE_MAX + k) = buf_load16(phr, (unsigned)(k * 4));
         }
         __builtin_amdgcn_s_waitcnt(WAIT_LDS);   // parameters written; the requests stay in flight across the barrier
         asm volatile("" ::: "memory");
@@ -1391,7 +1391,13 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
     LaunchInfo li;
     li.workgroups = tiles_m * tiles_n * a.ksplit;
     li.threads = 64 * S;
-    li.lds_bytes = S * 16384 + (a.pre_scale ? 8 * SLICES_PRE_MAX : 0);
+    // 16 KB of affine parameters beside the stages of four waves leave room for a second workgroup on the unit, which the rule for
+    // four waves counts on; 32 KB do not.  Affine + product, us, with 32 / 16 KB: fp32 3136x128x128 9.6 / 6.8, 3136x128x1000 28.5 /
+    // 21.5, bf16 8.6 / 6.2 and 15.7 / 12.4.  (Sized at launch instead, the array costs bf16 up to 11 %: the compiler then no longer
+    // knows that the loads into the stages do not fill it, and waits for them.)
+    constexpr int PRE_SMALL = S == 4 ? SLICES_PRE_MAX / 2 : SLICES_PRE_MAX;
+    const bool small = a.K <= PRE_SMALL;
+    li.lds_bytes = S * 16384 + (a.pre_scale ? 8 * (small ? PRE_SMALL : SLICES_PRE_MAX) : 0);
     li.wg_per_cu = (160 * 1024) / li.lds_bytes;
     static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S);
     static const std::string n_one = "igemm_slices_" + shape, n_pre = "igemm_affine_slices_" + shape;
@@ -1405,7 +1411,8 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
         set_tiling(b, tiles_m, tiles_n);
         const dim3 grid(tiles_m * tiles_n, a.ksplit), block(64 * S);
         const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
-        if (a.pre_scale) GACER_LAUNCH((slices_kernel<DT, LOAD_AFFINE, S>), grid, block, 0, s, b);
+        if (a.pre_scale && small) GACER_LAUNCH((slices_kernel<DT, LOAD_AFFINE, S, PRE_SMALL>), grid, block, 0, s, b);
+        else if (a.pre_scale) GACER_LAUNCH((slices_kernel<DT, LOAD_AFFINE, S, SLICES_PRE_MAX>), grid, block, 0, s, b);
         else if (!taps) GACER_LAUNCH((slices_kernel<DT, LOAD_VEC, S>), grid, block, 0, s, b);
         else if (a.Cin * (int)sizeof(T) % 128 == 0) GACER_LAUNCH((slices_kernel<DT, LOAD_TAPS, S>), grid, block, 0, s, b);
         else GACER_LAUNCH((slices_kernel<DT, LOAD_TAPS_ANY, S>), grid, block, 0, s, b);

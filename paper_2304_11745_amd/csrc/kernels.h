@@ -8,7 +8,7 @@
 
 namespace gacer {
 
-// most channels of a fused affine operator whose parameters slices_kernel keeps in LDS
+// most channels of a fused affine operator whose parameters slices_kernel keeps in LDS (with eight waves they fill it)
 enum { SLICES_PRE_MAX = 4096 };
 enum { DT_F32 = 0, DT_BF16 = 1 };
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3, ACT_HSWISH = 4, ACT_HSIGMOID = 5 };

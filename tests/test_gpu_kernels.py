@@ -75,6 +75,20 @@ def test_k_slices_inside_a_workgroup(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_affine_with_many_channels_in_front_of_k_slices(dtype):
+    """The fused affine form of slices_kernel with several batches of K per wave (its stores counted by the waits), K that ends
+    inside a batch, four and eight waves, more channels than one pass over the parameters copies, K cut over the grid, the most
+    channels it takes.  Batch and channel chunks un-fuse the pairs: their outputs, the affine tensor among them, keep every bit."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, hw, cin, cout) in enumerate([(3, 5, 1000, 40), (2, 7, 1160, 33), (2, 6, 2056, 65), (2, 5, 4096, 40), (5, 40, 600, 64), (2, 34, 2056, 136)]):
+        b = G._B(f"pre{i}", dtype, batch)
+        x = b.tensor(batch, cin, hw, hw)
+        tenants.append(b.done(x, b.conv(b.affine(x, ["relu", "relu6", "none"][i % 3]), cout, 1, 1, 0, "relu")))
+    check(tenants, [f"igemm_affine_slices_{dtype}_x4", f"igemm_affine_slices_{dtype}_x8"], [("batch", 2), ("cout", 2)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_stems_and_odd_channel_counts(dtype):
     """stem_kernel: runs of one chunk and of many, odd and even chunk counts, odd strides (runs that start on an odd element in
     bf16), image rows of odd length, output rows shorter and longer than a 128-position tile, windows wider than the padding,
