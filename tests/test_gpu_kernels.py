@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 def check(tenants, expect, splits=()):
     """Runs the tenants unsplit, compares every operator with the oracle, checks that the kernels named in `expect` (prefixes)
-    ran, and that the decompositions in `splits` ((axis, factor) applied wherever legal) reproduce every output bit."""
+    ran, and that the decompositions in `splits` ((axis, factor) applied wherever legal) reproduce every output bit.  Returns the
+    names of the kernels that ran unsplit."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -39,6 +40,7 @@ def check(tenants, expect, splits=()):
             for k, op in enumerate(t.ops):
                 assert sess.tensor_bytes(i, op.out) == base[i][k], f"{axis} x{factor}: {t.name} op {k} differs"
     sess.close()
+    return ran
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -72,6 +74,18 @@ def test_k_slices_inside_a_workgroup(dtype):
     names = {"f32": ["igemm_slices_f32_x4", "igemm_slices_f32_x8", "igemm_affine_slices_f32", "splitk_finish"],
              "bf16": ["igemm_slices_bf16_x4", "igemm_slices_bf16_x8", "igemm_affine_slices_bf16", "splitk_finish"]}
     check(tenants, names[dtype], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_limits_of_k_slices_in_one_column_of_tiles(dtype):
+    """At most 32 channels: 512 tiles of 32 rows and one more at a short K, which the tiled kernels take, and more tiles at a long K."""
+    from synth import graphs as G
+    ran = {}
+    for i, (rows, cin, cout, k) in enumerate([(16384, 144, 24, 1), (16385, 144, 24, 1), (16400, 384, 32, 1), (19000, 128, 32, 3)]):
+        b = G._B(f"column{i}", dtype, 1)
+        x = b.tensor(1, cin, rows // 20 if k == 3 else rows, 20 if k == 3 else 1)
+        ran[rows] = check([b.done(x, b.conv(x, cout, k, 1, k // 2, "relu"))], [], [("cout", 2)])
+    assert [all(n.startswith("igemm_slices") for n in ran[r]) for r in (16384, 16385, 16400, 19000)] == [True, False, False, True], ran
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
