@@ -430,15 +430,25 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
     // 6.0; bf16 17408x32x256 6.8 / 5.7; up to 512 tiles it does at any K: fp32 16384x32x64 5.5 / 6.1, bf16 16384x32x128 4.9 / 5.1.
     const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t32_max = N > 32 || K < 1024 ? 512 : bf16 ? 600 : 800;
     const int nb = (nkb + 1) / 2;                // 128-byte batches of K per row
-    // short bf16 rows belong to rowgemm_kernel; in fp32 a batch is 1024 clocks of MFMA, and with tiles for most units a long K
-    // is as fast or faster with each operand shared by four waves (392x512x4608: 28.4 here, 29.8 there; 512x768x3072: 34.2 / 30.8)
-    if (slices_ok && nb >= 2 && (!bf16 || K > 96) && t32 <= t32_max && (bf16 || t32 <= 128 || nb <= 80)) {
-        // more workgroups along K, and a finishing pass, only where units would stay empty and a wave's chain is long: bf16
-        // 8x4096x25088 and fp32 144x768x3072 (17.9 -> 15.8), 8x4096x4096 (24.4 -> 22.2); at 9 batches per wave the pass costs
-        // more than it gives (bf16 49x512x4608: 9.0 -> 11.1)
-        const int64_t longest = bf16 ? 12 : 5;
+    // short bf16 rows belong to rowgemm_kernel.  In fp32 a batch is 1024 clocks of MFMA, and a long K is as fast or faster with each
+    // operand shared by four waves once tiles fill most units (512x768x3072: 34.2 here, 30.8 there), or where the slices would
+    // be cut over the grid at most three ways and 64x64 tiles compute little that is not needed (416x256x2304 14.4 / 13.6,
+    // 245x512x4608 20.6 / 19.3, 320x256x4608 16.8 / 15.6; 147x512x4608, with a row of tiles three quarters empty, 15.6 / 17.0)
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+    const bool shared = !bf16 && (t32 > 128 ? nb > 80 : t32 > 64 && nb > 64 && 32 * tiles <= 9 * t32);
+    if (slices_ok && nb >= 2 && (!bf16 || K > 96) && t32 <= t32_max && !shared) {
+        // more workgroups along K, and a finishing pass, only where units would stay empty and a wave's chain is long.  bf16: doubled
+        // while a wave has more than twelve batches: 8x4096x25088; at 9 batches the pass costs more than it gives (49x512x4608: 9.0 ->
+        // 11.1).  fp32: as many as the chip holds at once: 8x1000x2048 in one workgroup row 14.0, two 12.0, eight 8.8 (tiled kernel
+        // 9.9), 49x512x4608 26.3, 18.3 and 11.5 (13.0), 169x256x2304 15.1, 13.3 and five 9.9 (11.6), 147x512x4608 26.2, 18.9 and
+        // three 15.6 (17.0), 8x4096x4096 28.2 and two 22.5 (26.9), 32x1000x1280 10.7 and five 8.6 (10.1); below 40 batches the pass
+        // costs more than it gives (392x256x1024: 9.4 and two 10.1).
+        // The cut follows the unsplit shape: chunks of a long product can be slower than on the tiled kernels, which cut the unsplit
+        // shape finer (quarters of 784x512x2048, of 400 tiles, 18.1 / 13.7 each, halves of 392x512x2048 14.3 / 12.9; unsplit 24.9 /
+        // 26.8 and 14.8 / 18.5).
         int64_t so = 1;
-        while (so < 8 && t32 * so * 2 <= 256 && nb > longest * 8 * so) so *= 2;
+        if (bf16) while (so < 8 && t32 * so * 2 <= 256 && nb > 96 * so) so *= 2;
+        else if (nb >= 40) so = std::max<int64_t>(1, std::min<int64_t>(8, 256 / t32));
         // four waves leave room for a second workgroup on the unit; eight hide more latency when there is only one
         const int64_t w = t32 > 256 || nb <= (bf16 ? 24 : 18) ? 4 : 8;
         const int64_t per = (nb + w * so - 1) / (w * so);
@@ -448,7 +458,6 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
         r.ksplit = (int)((nb + per * w - 1) / (per * w));
         return r;
     }
-    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
     int64_t s = 1;
     // Measured on whole concurrent rounds: splitting pays only when the unsplit launch would leave more than half of
     // the compute units empty, and only with slices of at least 8 blocks (the finishing pass costs a kernel boundary).

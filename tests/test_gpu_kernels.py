@@ -88,6 +88,21 @@ def test_limits_of_k_slices_in_one_column_of_tiles(dtype):
     assert [all(n.startswith("igemm_slices") for n in ran[r]) for r in (16384, 16385, 16400, 19000)] == [True, False, False, True], ran
 
 
+def test_long_k_with_few_tiles_in_fp32():
+    """K cut over the grid beside the slices of a workgroup (one, three, five and eight workgroup rows along K, the last row with
+    fewer batches than the others), and the shapes with 65 to 128 tiles that the tiled kernels with their own cut of K take."""
+    from synth import graphs as G
+    ran = {}
+    for rows, cout, cin, k in [(8, 1000, 2048, 1), (7, 999, 1284, 1), (169, 256, 256, 3), (147, 500, 520, 3), (300, 72, 1244, 1), (416, 256, 256, 3), (405, 250, 2308, 1)]:
+        b = G._B(f"few{rows}", "f32", 1)
+        x = b.tensor(1, cin, rows if k == 1 else {169: 13, 147: 21, 416: 26}[rows], 1 if k == 1 else {169: 13, 147: 7, 416: 16}[rows])
+        ran[rows] = check([b.done(x, b.conv(x, cout, k, 1, k // 2, "relu"))], [], [("cout", 2), ("cout", 8)])
+    sliced = {r: any(n.startswith("igemm_slices_f32_x8") for n in names) for r, names in ran.items()}
+    assert sliced == {8: True, 7: True, 169: True, 147: True, 300: True, 416: False, 405: False}, ran
+    assert {r for r, names in ran.items() if "splitk_finish" in names} == {8, 7, 169, 147, 416, 405}, ran
+    assert any(n.startswith("igemm_dma_taps_f32_64x64") for n in ran[416]) and any(n.startswith("igemm_dma_f32_64x64") for n in ran[405]), ran
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_affine_with_many_channels_in_front_of_k_slices(dtype):
     """The fused affine form of slices_kernel with several batches of K per wave (its stores counted by the waits), K that ends
