@@ -192,7 +192,7 @@ __global__ __launch_bounds__(TPB, K == 3 ? 4 : 2) void dwconv_tile_kernel(Stream
 }
 
 // ---- depthwise K x K with K known at compile time, one output vector per thread (5 x 5 where the tiled kernel does not apply:
-// ragged channel ranges, strides above 2): the loops are unrolled and branch-free, so the taps and their
+// few outputs, ragged channel ranges, strides above 2): the loops are unrolled and branch-free, so the taps and their
 // weights are requested together instead of one load per trip of a loop; a tap outside the image reads as zero and is
 // multiplied like the others, which leaves the FMA chain of dwconv_kernel (row-major from zero) bit for bit.
 template <typename T, int V, int K>
@@ -603,11 +603,21 @@ static LaunchInfo go_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
     const int64_t tiles = (int64_t)(a.n_hi - a.n_lo) * a.Ho * ((a.Wo + TW - 1) / TW);
     const int64_t g = (tiles * ((a.c_hi - a.c_lo) / V) + TPB - 1) / TPB;
     if (!dry && g) GACER_LAUNCH((dwconv_tile_kernel<T, V, S, K>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, V, TW));
-    return info(g, K == 3 ? "dwconv3x3" : "dwconv5x5");
+    return info(g, K == 3 ? "dwconv3x3" : "dwconv5x5_tiled");
 }
 
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry)
 {
+    const int64_t outs = (int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * (a.c_hi - a.c_lo);
+    // bf16 5x5 of few outputs: one output per thread, so that the launch fills the chip; the tiled kernel has a sixteenth of the threads
+    // and each goes through 25 to 40 window loads and 25 weights.  Us tiled / here: 1 image 28x28 60 channels 6.0 / 4.1, 1 image
+    // 14x14 -> 7x7 672 channels 5.8 / 4.2, 16 images 16x16 60 channels (960 workgroups here) 6.1 / 5.1, 8 images 56x56 -> 28x28 36
+    // channels (882) 5.2 / 5.1, 8 images 28x28 60 channels (1470) 6.1 / 6.7.
+    if (a.k == 5 && a.dtype == DT_BF16 && outs <= 1024 * TPB) {
+        const int64_t g = (outs + TPB - 1) / TPB;
+        if (!dry && g) GACER_LAUNCH((dwconv5_kernel<unsigned short, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1, 1));
+        return info(g, "dwconv5x5");
+    }
     if ((a.k == 3 || a.k == 5) && (a.stride == 1 || a.stride == 2)) {
         // bfloat16: 8-byte vectors (4 channels per lane) keep the window in registers without spilling
         if (a.dtype == DT_BF16 && a.C % 4 == 0 && a.c_lo % 4 == 0 && (a.c_hi - a.c_lo) % 4 == 0 && vec_ok<unsigned short, 1>(a)) {
@@ -619,7 +629,6 @@ LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry)
             return a.stride == 1 ? go_dwconv_tile<float, 4, 1, 5>(a, s, dry) : go_dwconv_tile<float, 4, 2, 5>(a, s, dry);
         }
     }
-    const int64_t outs = (int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * (a.c_hi - a.c_lo);
     if (a.k == 5) { GACER_DISPATCH_VEC(dwconv5_kernel, "dwconv5x5") }
     GACER_DISPATCH_VEC(dwconv_kernel, "dwconv")
 }

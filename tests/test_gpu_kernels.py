@@ -171,19 +171,22 @@ def test_input_staged_once_for_nine_taps():
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_5x5(dtype):
-    """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; ragged
-    channel ranges and stride 3 on the one-vector kernel."""
+    """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; few outputs
+    (bf16), ragged channel ranges and stride 3 on the one-vector kernel.  Chunks of what is tiled as a whole run on either."""
     from synth import graphs as G
     specs = [  # batch, hw, c, stride, pad, act, residual
         (3, 7, 24, 1, 2, "hswish", True), (2, 14, 40, 2, 2, "relu", False), (1, 5, 8, 1, 0, "none", False), (2, 9, 12, 2, 1, "relu6", False),
         (2, 13, 9, 1, 2, "none", False), (1, 11, 16, 3, 2, "relu", False),
+        (70, 9, 48, 1, 2, "hswish", True), (23, 25, 72, 2, 2, "relu", False), (31, 19, 40, 1, 0, "none", False), (45, 30, 36, 2, 1, "relu6", False),
+        (190, 3, 160, 1, 2, "none", False),
     ]
     tenants = []
     for i, (batch, hw, c, stride, pad, act, res) in enumerate(specs):
         b = G._B(f"dw{i}", dtype, batch)
         x = b.tensor(batch, c, hw, hw)
         tenants.append(b.done(x, b.conv(x, c, 5, stride, pad, act, groups=c, res=x if res else -1)))
-    check(tenants, ["dwconv5x5"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    ran = check(tenants, ["dwconv5x5_tiled"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    assert "dwconv5x5" in ran, sorted(ran)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
