@@ -46,7 +46,8 @@ def check(tenants, expect, splits=()):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_k_slices_inside_a_workgroup(dtype):
     """slices_kernel: one row and one channel, one past a 32-wide tile, K that ends inside a 128-byte batch, taps that a batch
-    crosses and taps it does not, four and eight waves, 512 tiles, K cut over the grid as well, a fused affine."""
+    crosses and taps it does not, four and eight waves, 512 tiles (once with taps on a channel window), K cut over the grid as
+    well, a fused affine."""
     from synth import graphs as G
     specs = [  # batch, hw, cin, [(cout, k, stride, pad, act, residual)]
         (1, 1, 512, [(1, 1, 1, 0, "none", False)]),
@@ -64,6 +65,10 @@ def test_k_slices_inside_a_workgroup(dtype):
         for cout, k, stride, pad, act, res in layers:
             y = b.conv(y, cout, k, stride, pad, act, res=y if res else -1)
         tenants.append(b.done(x, y))
+    b = G._B("window", dtype, 1)                    # 512 tiles, taps, an input that is a channel window
+    x, wide = b.tensor(1, 64, 64, 64), b.tensor(1, 192, 64, 64)
+    y = b.conv(x, 64, 1, 1, 0, "relu", out=b.view(wide, 64, 64))
+    tenants.append(b.done(x, b.conv(y, 128, 3, 1, 1, "none")))
     b = G._B("long_rows", dtype, 7)
     x = b.tensor(7, 128, 7, 7)
     tenants.append(b.done(x, b.gemm(x, 26, "relu", flatten=True)))
@@ -140,6 +145,88 @@ def test_stems_and_odd_channel_counts(dtype):
             y = b.conv(y, cout, k, stride, pad, act, res=y if res else -1)
         tenants.append(b.done(x, y))
     check(tenants, [f"stem_{dtype}"], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_stems_whose_workgroups_walk_several_tiles(dtype):
+    """stem_kernel with about 1200 tiles for at most 1024 workgroups, an image that is no whole number of tiles and of odd row
+    length (strips at the ends of the tensor alternate with others, chunks start at other images than the first): 64 and 32
+    channels per workgroup, whole groups and remainders, even and odd strides; weights and strip of more than 64 KB."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, h, w, cout, k, stride, pad, act) in enumerate([
+            (12, 113, 113, 64, 3, 1, 1, "relu"), (12, 113, 113, 65, 3, 1, 1, "relu6"), (12, 113, 113, 24, 3, 1, 1, "gelu"),
+            (12, 227, 227, 33, 7, 2, 3, "none"), (2, 37, 500, 32, 7, 2, 3, "hswish")]):
+        b = G._B(f"walk{i}", dtype, batch)
+        x = b.tensor(batch, 3, h, w)
+        tenants.append(b.done(x, b.conv(x, cout, k, stride, pad, act)))
+    ran = check(tenants, [], [("batch", 2), ("cout", 2)])
+    assert ran == {f"stem_{dtype}"}, ran
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_direct_to_lds_pipeline(dtype):
+    """igemm_dma_kernel: ragged M, N and K, channels that are no multiple of a K block (a block crosses taps) and that are, strides,
+    5x5 taps, a residual, one tap, every tile shape."""
+    from synth import graphs as G
+    specs = [  # batch, h, w, cin, cout, k, stride, pad, act, residual
+        (3, 45, 37, 40, 100, 5, 1, 2, "relu", False), (2, 61, 59, 120, 120, 3, 1, 1, "relu6", True), (3, 91, 83, 96, 124, 3, 2, 1, "none", False),
+        (1, 80, 53, 1000, 250, 1, 1, 0, "gelu", False), (1, 63, 1, 2056, 8248, 1, 1, 0, "none", False), (1, 112, 112, 776, 1000, 1, 1, 0, "hswish", False),
+        (2, 95, 79, 160, 250, 3, 1, 1, "relu", False), (4, 95, 79, 88, 250, 3, 1, 1, "none", False), (3, 40, 37, 240, 120, 3, 1, 1, "relu", False),
+    ]
+    tenants = []
+    for i, (batch, h, w, cin, cout, k, stride, pad, act, res) in enumerate(specs):
+        b = G._B(f"dma{i}", dtype, batch)
+        x = b.tensor(batch, cin, h, w)
+        tenants.append(b.done(x, b.conv(x, cout, k, stride, pad, act, res=x if res else -1)))
+    ran = check(tenants, [], [("batch", 2), ("cout", 2)])
+    names = {"f32": ["f32_64x64x32s3", "taps_f32_64x64x32s3"],
+             "bf16": ["bf16_64x64x64s3", "bf16_64x64x64s4", "bf16_256x128x32s3", "taps_bf16_64x64x64s3", "taps_bf16_64x64x64s4", "taps_bf16_128x128x64s3", "taps_bf16_128x128x32s4"]}
+    assert ran == {"igemm_dma_" + n for n in names[dtype]}, sorted(ran)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_non_finite_inputs_reach_their_windows_only(dtype):
+    """Infinities and NaN in the input make exactly the outputs non-finite whose window holds one (padding, tails of K and of tiles
+    and the neighbours in memory are zeros times something finite); all other outputs are as without them."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import forward as F
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    specs = [  # batch, cin, h, w, cout, k, stride, pad, groups
+        (2, 3, 37, 41, 64, 7, 2, 3, 1), (2, 3, 33, 35, 40, 3, 1, 1, 1), (2, 72, 9, 11, 40, 3, 1, 1, 1), (2, 64, 9, 9, 33, 3, 1, 1, 1),
+        (3, 200, 5, 5, 70, 1, 1, 0, 1), (16, 64, 56, 56, 64, 3, 1, 1, 1), (2, 88, 61, 59, 70, 3, 1, 1, 1), (3, 40, 40, 40, 96, 1, 1, 0, 1),
+        (2, 24, 9, 9, 24, 5, 1, 2, 24), (70, 48, 9, 9, 48, 5, 1, 2, 48),
+    ]
+    tenants, data, clean, bad = [], [], [], []
+    for i, (batch, cin, h, w, cout, k, stride, pad, groups) in enumerate(specs):
+        b = G._B(f"nonfinite{i}", dtype, batch)
+        x = b.tensor(batch, cin, h, w)
+        tenants.append(b.done(x, b.conv(x, cout, k, stride, pad, "none", groups=groups)))
+        xv, params = G.materialise(tenants[-1], 77, i << 20)
+        mark = np.zeros(xv.shape, bool)
+        for (n, c, r, q), v in {(0, 0, 0, 0): np.nan, (0, cin - 1, h - 1, w - 1): np.inf, (batch - 1, cin - 1, h - 1, w - 1): -np.inf,
+                                (batch // 2, cin // 2, h // 2, w // 2): np.nan}.items():
+            mark[n, c, r, q] = True
+        clean.append(np.where(mark, np.float32(0), xv))
+        xv = np.where(mark, np.float32(np.nan), xv)
+        xv[0, cin - 1, h - 1, w - 1], xv[batch - 1, cin - 1, h - 1, w - 1] = np.inf, -np.inf
+        data.append((xv, params))
+        ones = torch.ones((cout, cin // groups, k, k))
+        bad.append(torch.nn.functional.conv2d(torch.from_numpy(mark.astype(np.float32)), ones, stride=stride, padding=pad, groups=groups).numpy() > 0)
+    sess = harness.Session(tenants, data)
+    sess.poison_outputs()
+    sess.run(B.GACER_MODE_SEQUENTIAL, 1)
+    for i, t in enumerate(tenants):
+        got = sess.output(i)
+        assert np.array_equal(~np.isfinite(got), bad[i]), f"{t.name}: non-finite outputs elsewhere"
+        ref = F.run_op(t, 0, [clean[i], None], data[i][1])
+        e = rel_err(np.where(bad[i], 0, got), np.where(bad[i], 0, ref))
+        assert e <= TOL_ONE_OP[dtype], f"{t.name}: rel err {e}"
+    sess.close()
 
 
 def test_input_staged_once_for_nine_taps():

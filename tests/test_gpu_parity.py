@@ -190,9 +190,9 @@ def test_random_conv_shapes(gpu, dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_long_k_conv_shapes(gpu, dtype):
-    """Convolutions and GEMMs whose K rows are long enough for the direct-to-LDS pipeline (several stages of K blocks in
-    flight): ragged M / N / K tails, taps narrower and wider than a K block, strides, K ranges cut into slices, wide
-    outputs that take the larger tiles.  Parity on every tensor, bit-exactness under decomposition."""
+    """Convolutions and GEMMs with long K rows and few output tiles (K slices inside a workgroup, some cut over the grid as
+    well): ragged M / N / K tails, taps narrower and wider than a K batch, strides.  Parity on every tensor in every mode and
+    plan, bit-exactness under decomposition.  The direct-to-LDS pipeline at odd sizes: test_direct_to_lds_pipeline."""
     from synth import graphs as G
     specs = [  # (batch, hw, cin, [(cout, k, stride, pad, act, residual)])
         (3, 9, 64, [(100, 5, 1, 2, "relu", False), (136, 3, 2, 1, "none", False), (136, 3, 1, 1, "relu6", True)]),
