@@ -16,6 +16,7 @@
 // of the output channels) therefore produces exactly the bits the unsplit launch produces.
 #include <hip/hip_runtime.h>
 #include <string>
+#include <type_traits>
 #include "device_util.h"
 #include "gemm_util.h"
 #include "kernels.h"
@@ -1264,10 +1265,10 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
     b.n_major = tile_order(a, tiles_m, tiles_n, (int)sizeof(T));
     set_divisors(b);
     set_tiling(b, tiles_m, tiles_n);
-    if (a.pre_scale)
-        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_AFFINE>), grid, block, 0, s, b);
-    else if (a.b_trans)
-        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_BT>), grid, block, 0, s, b);
+    // the picker pairs a fused affine with 128-byte and a B stored [k][n] with 64-byte blocks only
+    constexpr int LOAD_OTHER = KV == 8 ? LOAD_AFFINE : LOAD_BT;
+    if (KV == 8 ? a.pre_scale != nullptr : a.b_trans != 0)
+        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_OTHER>), grid, block, 0, s, b);
     else if (!vec_ok)
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_GATHER>), grid, block, 0, s, b);
     else if (taps)
@@ -1442,59 +1443,48 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     if (waste(32) < waste(bn) - 1e-9) bn = 32;
     auto wgs = [&](int bm, int bnn) { return (int64_t)((M + bm - 1) / bm) * ((N + bnn - 1) / bnn) * z; };
     // Cost of a tile shape: workgroups landing on the busiest compute unit x outputs per workgroup / relative
-    // efficiency of the shape.  Measured: bf16 gains from the 128x128 tile (fewer LDS reads per MFMA), the two
-    // smaller shapes are equal; fp32 MFMAs are slow enough that all shapes are equal and only the fill counts.
+    // efficiency of the shape.  Measured: bf16 gains from the 128x128 tile (fewer LDS reads per MFMA); fp32 MFMAs are slow
+    // enough that all shapes are equal and only the fill counts, which is never worse with the 64x64 tile.
     // Fewer workgroups than compute units leaves units idle and hides no latency: penalised.
-    constexpr double e_small = DT == DT_BF16 ? 0.8 : 1.0, e_mid = e_small;
     auto cost = [&](int bm, int bnn, double eff) {
         const int64_t w = wgs(bm, bnn);
         return (double)((w + 255) / 256) * bm * bnn / eff * (w < 256 ? 1.1 : 1.0);
     };
-    int shape = 0;                               // 0: 64x64, 1: 128x64, 2: 128x128, 3: 128x32
-    if (bn < 64) shape = 3;
-    else {
-        double best = cost(64, 64, e_small);
-        if (cost(128, 64, e_mid) < best * 0.999) { best = cost(128, 64, e_mid); shape = 1; }
-        if (bn == 128 && cost(128, 128, 1.0) < best * 0.999) shape = 2;
-    }
-    if (a.pre_scale) {                           // fused per-channel affine: the A tile passes through registers, so the register-staged kernel
-        switch (shape) {                         // (the executor fuses only 16-byte aligned, vector-multiple operands)
-        case 2: return go<DT, 128, 128, 2, 2, 8>(a, s, dry, true, phase);
-        case 1: return go<DT, 128, 64, 2, 2, 8>(a, s, dry, true, phase);
-        case 0: return go<DT, 64, 64, 2, 2, 8>(a, s, dry, true, phase);
-        default: return go<DT, 128, 32, 4, 1, 8>(a, s, dry, true, phase);
-        }
-    }
+    enum { T64x64, T128x128, T128x32 } shape = T64x64;
+    if (bn < 64) shape = T128x32;
+    else if (DT == DT_BF16 && bn == 128 && cost(128, 128, 1.0) < cost(64, 64, 0.8) * 0.999) shape = T128x128;
+    // kernels staged through registers, with blocks of 128 (KV = 8) or 64 bytes of K
+    auto staged = [&](auto kv, bool vec) {
+        constexpr int KV = decltype(kv)::value;
+        if constexpr (DT == DT_BF16)
+            if (shape == T128x128) return go<DT, 128, 128, 2, 2, KV>(a, s, dry, vec, phase);
+        if (shape == T64x64) return go<DT, 64, 64, 2, 2, KV>(a, s, dry, vec, phase);
+        return go<DT, 128, 32, 4, 1, KV>(a, s, dry, vec, phase);
+    };
+    const std::integral_constant<int, 8> blocks128;
+    const std::integral_constant<int, 4> blocks64;
+    // fused per-channel affine: the A tile passes through registers (the executor fuses only 16-byte aligned, vector-multiple operands)
+    if (a.pre_scale) return staged(blocks128, true);
     // Long K rows: the direct-to-LDS pipeline (igemm_dma_kernel) keeps several K blocks in flight and wins once the K
     // loop is long enough to amortise filling its stages (measured layer by layer: from about 1.5 KB of K per row).
     const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
-    if (vec_ok && !a.b_trans && shape != 3 && (!taps || a.kh * a.kw <= 31) && (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 1536) {
-        const bool long_k = (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 4096;
-        if (shape == 2) {
-            // 256x128 halves the L2 traffic of the A operand per flop again; it needs enough rows to still fill the chip
-            if (DT == DT_BF16 && wgs(256, 128) >= 384) return go_dma<DT, 256, 128, 2, 2, 4, 3>(a, s, dry, vec_ok, phase);
-            // one workgroup per compute unit anyway: whole 128-byte row segments (fewer, larger L2 requests)
-            if (wgs(128, 128) <= 256) return go_dma<DT, 128, 128, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
-            return go_dma<DT, 128, 128, 2, 2, 4, 4>(a, s, dry, vec_ok, phase);
+    if (vec_ok && !a.b_trans && shape != T128x32 && (!taps || a.kh * a.kw <= 31) && (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 1536) {
+        if constexpr (DT == DT_BF16) {
+            const bool long_k = (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 4096;
+            if (shape == T128x128) {
+                // 256x128 halves the L2 traffic of the A operand per flop again; it needs enough rows to still fill the chip
+                if (wgs(256, 128) >= 384) return go_dma<DT, 256, 128, 2, 2, 4, 3>(a, s, dry, vec_ok, phase);
+                // one workgroup per compute unit anyway: whole 128-byte row segments (fewer, larger L2 requests)
+                if (wgs(128, 128) <= 256) return go_dma<DT, 128, 128, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
+                return go_dma<DT, 128, 128, 2, 2, 4, 4>(a, s, dry, vec_ok, phase);
+            }
+            if (long_k) return go_dma<DT, 64, 64, 2, 2, 8, 4>(a, s, dry, vec_ok, phase);   // measured: a fourth stage pays for bf16 only
         }
-        if (shape == 1) return go_dma<DT, 128, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
-        if (long_k && DT == DT_BF16) return go_dma<DT, 64, 64, 2, 2, 8, 4>(a, s, dry, vec_ok, phase);   // measured: a fourth stage pays for bf16 only
         return go_dma<DT, 64, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
     }
-    if (a.b_trans || a.K <= 16 * VEC || !vec_ok) {   // short K, or the latency-bound gather loader (more waves per unit): 64-byte blocks
-        switch (shape) {
-        case 2: return go<DT, 128, 128, 2, 2, 4>(a, s, dry, vec_ok, phase);
-        case 1: return go<DT, 128, 64, 2, 2, 4>(a, s, dry, vec_ok, phase);
-        case 0: return go<DT, 64, 64, 2, 2, 4>(a, s, dry, vec_ok, phase);
-        default: return go<DT, 128, 32, 4, 1, 4>(a, s, dry, vec_ok, phase);
-        }
-    }
-    switch (shape) {
-    case 2: return go<DT, 128, 128, 2, 2, 8>(a, s, dry, vec_ok, phase);
-    case 1: return go<DT, 128, 64, 2, 2, 8>(a, s, dry, vec_ok, phase);
-    case 0: return go<DT, 64, 64, 2, 2, 8>(a, s, dry, vec_ok, phase);
-    default: return go<DT, 128, 32, 4, 1, 8>(a, s, dry, vec_ok, phase);
-    }
+    // short K, or the latency-bound gather loader (more waves per unit): 64-byte blocks
+    if (a.b_trans || a.K <= 16 * VEC || !vec_ok) return staged(blocks64, vec_ok);
+    return staged(blocks128, vec_ok);
 }
 
 LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase)
