@@ -50,7 +50,7 @@ inline int64_t conv3_wgs(const GemmArgs &a, int bm, int bn)
 // Whether the operator (its UNSPLIT shape, so that every chunk of it adds in the same order) runs on conv3_kernel: from about
 // three tiles of 256 positions on four compute units; below, smaller tiles fill the chip better.  At 196, microseconds on the
 // tiled kernels / here: 16 images 28x28 512->512 77.6 / 57.0, 8 images 56x56 128->256 28.1 / 21.1, 4 images 112x112 64->128
-// 20.2 / 15.6, 16 images 56x56 64->64 12.5 / 9.8.  Its chunks: half of the images or of the channels 42.2 / 36.2 (8 images 28x28
+// 20.2 / 15.6, 16 images 56x56 64->64 12.5 / 12.2.  Its chunks: half of the images or of the channels 42.2 / 36.2 (8 images 28x28
 // 512->512), a quarter 28.1 / 27.0 (4 images) and 28.4 / 32.4 (128 channels), an eighth 20.4 / 22.8 (2 images); 2 images 56x56
 // 256->256 16.4 / 15.1.
 inline bool conv3_takes(const GemmArgs &a)
@@ -65,16 +65,20 @@ inline bool conv3_takes(const GemmArgs &a)
 
 // Tile of one launch, chunks of a decomposed operator included (the tile never changes an element's order of additions).
 // 256 x 128 moves the fewest bytes per MFMA once there are well over one such tile per compute unit; 256 x 64 while those reach
-// every unit; 128 x 64 below.  Microseconds of 256x128 / 256x64 / 128x64, by the number of 256x128 tiles: 50 (2 images 56x56
-// 256->256) 33.4 / 19.1 / 15.1, 100 (8 images 28x28 512->512) 59.7 / 36.2 / 37.1, 196 (16 of those) 66.3 / 57.0 / 71.6, 358 (16
-// images 75x75 128->128) 35.9 / 32.5 / 38.3, 392 (16 images 56x56 256->256) 59.7 / 62.7 / 74.4, 784 (32 of those) 114.6 / 109.8 /
-// 134.4, 1568 (32 images 112x112 64->128) 77.2 / 78.3 / 93.7.  By the number of 256x64 tiles at 64 channels: 98 (8 images 56x56)
-// 10.4 / 7.9, 254 (32 images 45x45) 13.2 / 10.6, 264 (3 images 150x150) 14.1 / 15.3, 392 (32 images 56x56) 16.0 / 18.1.
+// half of the units; 128 x 64 below.  One launch alone, microseconds of 256x128 / 256x64 / 128x64, by the number of 256x128 tiles:
+// 50 (2 images 56x56 256->256) 33.4 / 19.1 / 15.1, 100 (8 images 28x28 512->512) 59.7 / 36.2 / 37.1, 196 (16 of those) 66.3 / 57.0 /
+// 71.6, 358 (16 images 75x75 128->128) 35.9 / 32.5 / 38.3, 392 (16 images 56x56 256->256) 59.7 / 62.7 / 74.4, 784 (32 of those)
+// 114.6 / 109.8 / 134.4, 1568 (32 images 112x112 64->128) 77.2 / 78.3 / 93.7.  By the number of 256x64 tiles at 64 channels: 98 (8
+// images 56x56) 10.4 / 7.9, 196 (16) 12.2 / 9.8, 264 (3 images 150x150) 14.1 / 15.3, 392 (32 images 56x56) 16.0 / 18.1.
+// Alone, 128 x 64 gains up to 256 tiles, but other tenants use the units that a launch leaves: the round of VGG-16, 8 images, halved
+// along the batch, ResNet-50, 16 images, halved along the channels, and MobileNetV3, 32 images, takes 1760 us with 128 x 64 below 256
+// tiles, 1730 below 128 and 1717 with 256 x 128 throughout (which alone costs that VGG 864 instead of 775, in quarters 1436
+// instead of 1183).
 struct Conv3Tile { int bm, bn; };
 inline Conv3Tile conv3_tile(const GemmArgs &a)
 {
     if (conv3_bn(a.n_hi - a.n_lo) == 128 && conv3_wgs(a, 256, 128) > 360) return {256, 128};
-    return {conv3_wgs(a, 256, 64) >= 256 ? 256 : 128, 64};
+    return {conv3_wgs(a, 256, 64) >= 128 ? 256 : 128, 64};
 }
 
 }  // namespace gacer

@@ -8,10 +8,10 @@ from parity import TOL_ONE_OP, rel_err
 pytestmark = pytest.mark.gpu
 
 
-def check(tenants, expect, splits=()):
+def check(tenants, expect, splits=(), expect_split=()):
     """Runs the tenants unsplit, compares every operator with the oracle, checks that the kernels named in `expect` (prefixes)
-    ran, and that the decompositions in `splits` ((axis, factor) applied wherever legal) reproduce every output bit.  Returns the
-    names of the kernels that ran unsplit."""
+    ran, and that the decompositions in `splits` ((axis, factor) applied wherever legal) reproduce every output bit, with the
+    kernels in `expect_split` among those that ran.  Returns the names of the kernels that ran unsplit."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -32,6 +32,7 @@ def check(tenants, expect, splits=()):
     ran = {r["kernel"] for r in sess.trace(B.GACER_MODE_SEQUENTIAL, 1)}
     for prefix in expect:
         assert any(k.startswith(prefix) for k in ran), f"{prefix} did not run: {sorted(ran)}"
+    ran_split = set()
     for axis, factor in splits:
         sess.set_plan(sess.uniform_splits(axis, factor), [])
         sess.poison_outputs()
@@ -39,6 +40,9 @@ def check(tenants, expect, splits=()):
         for i, t in enumerate(tenants):
             for k, op in enumerate(t.ops):
                 assert sess.tensor_bytes(i, op.out) == base[i][k], f"{axis} x{factor}: {t.name} op {k} differs"
+        if expect_split:
+            ran_split |= {r["kernel"] for r in sess.trace(B.GACER_MODE_PLAN, 1)}
+    assert ran_split >= set(expect_split), sorted(ran_split)
     sess.close()
     return ran
 
@@ -253,7 +257,7 @@ def test_input_staged_once_for_nine_taps():
     x, wide = b.tensor(15, 64, 55, 57), b.tensor(15, 192, 55, 57)
     y = b.conv(x, 64, 3, 1, 1, "relu", out=b.view(wide, 64, 64))
     tenants.append(b.done(x, b.conv(y, 64, 3, 1, 1, "none")))
-    check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128", "conv3_bf16_128x64"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128"], [("batch", 2), ("cout", 2), ("cout", 8)], ["conv3_bf16_128x64", "conv3_bf16_256x64"])
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
