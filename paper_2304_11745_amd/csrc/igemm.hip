@@ -1393,11 +1393,13 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
     li.workgroups = tiles_m * tiles_n * a.ksplit;
     li.threads = 64 * S;
     // 16 KB of affine parameters beside the stages of four waves leave room for a second workgroup on the unit, which the rule for
-    // four waves counts on; 32 KB do not.  Affine + product, us, with 32 / 16 KB: fp32 3136x128x128 9.6 / 6.8, 3136x128x1000 28.5 /
+    // four waves counts on where there are more tiles than units; 32 KB do not, and keep the workgroups of a smaller launch on units of
+    // their own when other tenants fill some (ResNet-101, DenseNet-121 and MobileNetV3 of 8 images, bf16: round 1472 us, with 16
+    // KB throughout 1523).  Affine + product, us, with 32 / 16 KB: fp32 3136x128x128 9.6 / 6.8, 3136x128x1000 28.5 /
     // 21.5, bf16 8.6 / 6.2 and 15.7 / 12.4.  (Sized at launch instead, the array costs bf16 up to 11 %: the compiler then no longer
     // knows that the loads into the stages do not fill it, and waits for them.)
     constexpr int PRE_SMALL = S == 4 ? SLICES_PRE_MAX / 2 : SLICES_PRE_MAX;
-    const bool small = a.K <= PRE_SMALL;
+    const bool small = a.K <= PRE_SMALL && tiles_m * tiles_n * a.ksplit > 256;
     li.lds_bytes = S * 16384 + (a.pre_scale ? 8 * (small ? PRE_SMALL : SLICES_PRE_MAX) : 0);
     li.wg_per_cu = (160 * 1024) / li.lds_bytes;
     static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S);
