@@ -424,11 +424,11 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
     // compute unit.  Measured in isolation, microseconds, this kernel against the tiled kernels with their finishing pass:
     // bf16 49x160x960 4.5 / 8.8, 392x512x4608 9.6 / 13.8, 1568x256x2304 (392 tiles) 10.2 / 14.2, 144x3072x768 (480) 6.1 / 6.8,
     // 6272x128x512 (784) 9.0 / 6.5; fp32 125x32x1152 9.9 / 31.3, 392x160x960 8.5 / 11.5, 392x512x2048 13.8 / 18.4, 392x1280x320
-    // (520) 10.9 / 10.3.  One column of tiles (N <= 32) has only a quarter of the workgroups on the tiled kernels (128x32 tiles) and
-    // goes on longer where K is long: 3x3 fp32 19200x32x1152 (600) 26.4 / 33.4, 25088x32x1152 (784) 31.8 / 34.0; bf16 11.8 / 11.8
-    // and 13.7 / 12.1.  At a short K it does not: fp32 25088x24x144 10.9 / 8.3, 25088x32x384 16.0 / 13.9, 17408x32x64 (544) 7.6 /
-    // 6.0; bf16 17408x32x256 6.8 / 5.7; up to 512 tiles it does at any K: fp32 16384x32x64 5.5 / 6.1, bf16 16384x32x128 4.9 / 5.1.
-    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t32_max = N > 32 || K < 1024 ? 512 : bf16 ? 600 : 800;
+    // (520) 10.9 / 10.3.  One column of tiles (N <= 32) wastes half of a 64-wide tile's work, so it goes on longer: fp32
+    // 19200x32x1152 (600) 26.4 / 33.4, 25088x32x1152 (784) 31.8 / 34.0; bf16 11.8 / 11.8 and 13.7 / 12.1.  At a short K a launch
+    // beyond 512 tiles is slower alone (fp32 25088x24x144 10.9 / 8.3, 25088x24x96 8.8 / 6.9), but whole rounds are not: ResNet-18 and
+    // MobileNetV2 of 8 images 737 us here, 749 there, MobileNetV2 alone 417 / 414, two of them 607 / 602, three mobile networks 910 / 893.
+    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t32_max = N > 32 ? 512 : bf16 ? 600 : 800;
     const int nb = (nkb + 1) / 2;                // 128-byte batches of K per row
     // short bf16 rows belong to rowgemm_kernel.  In fp32 a batch is 1024 clocks of MFMA, and a long K is as fast or faster with each
     // operand shared by four waves once tiles fill most units (512x768x3072: 34.2 here, 30.8 there), or where the slices would

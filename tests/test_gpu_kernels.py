@@ -85,18 +85,6 @@ def test_k_slices_inside_a_workgroup(dtype):
     check(tenants, names[dtype], [("batch", 2), ("cout", 2), ("cout", 8)])
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_limits_of_k_slices_in_one_column_of_tiles(dtype):
-    """At most 32 channels: 512 tiles of 32 rows and one more at a short K, which the tiled kernels take, and more tiles at a long K."""
-    from synth import graphs as G
-    ran = {}
-    for i, (rows, cin, cout, k) in enumerate([(16384, 144, 24, 1), (16385, 144, 24, 1), (16400, 384, 32, 1), (19000, 128, 32, 3)]):
-        b = G._B(f"column{i}", dtype, 1)
-        x = b.tensor(1, cin, rows // 20 if k == 3 else rows, 20 if k == 3 else 1)
-        ran[rows] = check([b.done(x, b.conv(x, cout, k, 1, k // 2, "relu"))], [], [("cout", 2)])
-    assert [all(n.startswith("igemm_slices") for n in ran[r]) for r in (16384, 16385, 16400, 19000)] == [True, False, False, True], ran
-
-
 def test_long_k_with_few_tiles_in_fp32():
     """K cut over the grid beside the slices of a workgroup (one, three, five and eight workgroup rows along K, the last row with
     fewer batches than the others), and the shapes with 65 to 128 tiles that the tiled kernels with their own cut of K take."""
