@@ -8,7 +8,8 @@ operator chunks + pointer edges).  ``value`` is the regulated aggregate items/s 
 workload (configs[1]); ``per_config`` carries the same measurements for configs[2..4], ``paper_mixes`` for three tenant
 mixes of the paper's own evaluation (its Table 2) that need no dataset.
 
-Prints ONE JSON line.  Plan selection (profile, search, short trials) happens before the timed
+Prints ONE JSON line, short enough for readers that keep only the end of a program's output; the full record of every
+workload (kernel tables, percentiles, plan selection) goes to stderr.  Plan selection (profile, search, short trials) happens before the timed
 region, as in offline deployment (Section 4.4, "Search Cost Analysis").
 """
 import argparse
@@ -61,6 +62,28 @@ def measured_traffic(config, kernel, launches_per_round):
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+def rounded(v):
+    """Floats to six significant digits, all the way down."""
+    if isinstance(v, dict):
+        return {k: rounded(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [rounded(x) for x in v]
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
+def summary(r):
+    """What the line says about a workload other than the headline one."""
+    s = {k: r[k] for k in ("workload", "dtype", "plan", "plan_kind", "launches_per_round", "ms_per_step", "regulated_images_per_s",
+                           "sequential_images_per_s", "stream_parallel_images_per_s", "speedup_vs_sequential",
+                           "speedup_vs_stream_parallel", "issue_threads")}
+    s["mfma_frac_of_peak"] = r["mfma_frac_of_peak"]["regulated"]
+    if r.get("roofline"):
+        s["roofline"] = {k: r["roofline"].get(k) for k in ("kernel", "bound", "achieved", "peak", "frac", "share_of_kernel_time")}
+    if r.get("cpu_baseline"):
+        s["cpu_images_per_s"] = r["cpu_baseline"].get("value")
+    return s
 
 
 def pct(v):
@@ -406,6 +429,35 @@ def pointer_sweep(config, rounds):
                                        "Table 4: 0.9 s at 100 rounds to 2 min 52 s at 10000 (Python, other hardware)"}), flush=True)
 
 
+def line(head, steps, warmup, per_config, mixes):
+    """The one JSON line: the headline workload's record, summaries of the others."""
+    out = {
+        "metric": "aggregate tenant images/s (regulated concurrent run)",
+        "value": head["regulated_images_per_s"],
+        "unit": "images/s",
+        "n_gpus": 1, "steps": steps, "warmup": warmup,
+        "ms_per_step": head["ms_per_step"],
+        "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
+        "dtype": head["dtype"], "data": "synthetic",
+        "config": {"workload": head["workload"], "items_per_round": head["items_per_round"], "tenants": head["tenants"],
+                   "plan": head["plan"], "plan_kind": head["plan_kind"], "issue_threads": head["issue_threads"],
+                   "launches_per_round": head["launches_per_round"]},
+    }
+    for k in ("sequential_images_per_s", "stream_parallel_images_per_s", "speedup_vs_sequential", "speedup_vs_stream_parallel",
+              "makespan_ms_median", "makespan_ms_p10_p90", "mfma_frac_of_peak", "kernels", "roofline"):
+        out[k] = head[k]
+    out["plan_selection"] = {k: v for k, v in head["plan_selection"].items()
+                             if k in ("profile_s", "search_s", "refine_s", "searched_pointers", "searched_splits", "trial_ms", "issue_trial_ms")}
+    if "cpu_baseline" in head:
+        out["cpu_baseline"] = head["cpu_baseline"]
+    out["paper_context"] = "GACER reports 1.37x-1.66x over sequential cuDNN on Titan V (Section 5.2); other hardware, context only"
+    if per_config:
+        out["per_config"] = {str(c): summary(r) for c, r in per_config.items()}
+    if mixes:
+        out["paper_mixes"] = {str(c): summary(r) for c, r in mixes.items()}
+    return json.dumps(rounded(out))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -456,41 +508,19 @@ def main():
         log("copy probe: eltwise kernel, 3 dispatches, 268435456 bytes read + 268435456 bytes written each")
 
     head = run_config(args.config, args, 25.0)
-    out = {
-        "metric": "aggregate tenant images/s (regulated concurrent run)",
-        "value": head["regulated_images_per_s"],
-        "unit": "images/s",
-        "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
-        "ms_per_step": head["ms_per_step"],
-        "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": head["dtype"], "data": "synthetic",
-        "config": {"workload": head["workload"], "items_per_round": head["items_per_round"], "tenants": head["tenants"],
-                   "plan": head["plan"], "plan_kind": head["plan_kind"], "issue_threads": head["issue_threads"],
-                   "launches_per_round": head["launches_per_round"]},
-    }
-    for k in ("sequential_images_per_s", "stream_parallel_images_per_s", "speedup_vs_sequential", "speedup_vs_stream_parallel",
-              "makespan_ms_median", "makespan_ms_p10_p90", "mfma_frac_of_peak", "plan_selection", "kernels", "roofline"):
-        out[k] = head[k]
-    if "cpu_baseline" in head:
-        out["cpu_baseline"] = head["cpu_baseline"]
-    out["paper_context"] = "GACER reports 1.37x-1.66x over sequential cuDNN on Titan V (Section 5.2); other hardware, context only"
+    log(f"config {args.config}:", json.dumps(head))
     also = [int(c) for c in args.also.split(",") if c.strip() and int(c) != args.config]
-    if also:
-        out["per_config"] = {}
-        for c in also:
-            r = run_config(c, args, 12.0)
-            r.pop("plan_selection", None)                  # kept on stderr; the line stays readable
-            out["per_config"][str(c)] = r
+    per_config, mix_records = {}, {}
+    for c in also:
+        per_config[c] = run_config(c, args, 12.0)
+        log(f"config {c}:", json.dumps(per_config[c]))
     if args.mixes is None:                                 # any narrowing flag means: exactly what was asked for
         args.mixes = "6,7,8" if (args.config == 2 and args.also == "3,4,5" and not args.only_regulated and args.scale == "full") else ""
     mixes = [int(c) for c in args.mixes.split(",") if c.strip() and int(c) != args.config and int(c) not in also]
-    if mixes:
-        out["paper_mixes"] = {}
-        for c in mixes:
-            r = run_config(c, args, 0.0)
-            r.pop("plan_selection", None)
-            out["paper_mixes"][str(c)] = r
-    print(json.dumps(out), flush=True)
+    for c in mixes:
+        mix_records[c] = run_config(c, args, 0.0)
+        log(f"mix {c}:", json.dumps(mix_records[c]))
+    print(line(head, args.steps, args.warmup, per_config, mix_records), flush=True)
 
 
 if __name__ == "__main__":
