@@ -17,21 +17,22 @@
 namespace gacer {
 
 // Division of an index by a run-time extent d that the launcher knows: the launcher prepares (mul, shift) with
-// n / d == (n * mul) >> (32 + shift) for every 0 <= n < 2^31 -- mul = ceil(2^(31 + c) / d), c = ceil(log2 d), shift = c - 1;
-// the error term n * (mul * d - 2^(31+c)) stays below 2^(31+c) because n < 2^31 <= 2^(31+c) / d -- and the kernel spends
-// one multiply-high and a shift instead of the dozens of instructions of a division.  d = 1 is marked by mul = 0.
+// n / d == (2 n * mul) >> (32 + shift) for every 0 <= n < 2^31 -- shift = ceil(log2 d), mul = ceil(2^(31 + shift) / d) < 2^32; the
+// error term n * (mul * d - 2^(31 + shift)) stays below 2^(31 + shift) because mul * d - 2^(31 + shift) < d <= 2^shift and n < 2^31 --
+// and the kernel spends two shifts and one multiply-high instead of the dozens of instructions of a division.  d = 1 is no
+// special case (mul = 2^31, shift = 0): as a branch it cut the index arithmetic of every kernel into pieces whose scalar loads
+// of the arguments waited for each other.
 inline void divisor(int d, unsigned (&out)[2])
 {
-    if (d <= 1) { out[0] = 0u; out[1] = 0u; return; }
     int c = 0;
     while ((1ll << c) < d) ++c;
-    const unsigned long long two_k = 1ull << (31 + c);
-    out[0] = (unsigned)((two_k + (unsigned long long)d - 1) / (unsigned long long)d);
-    out[1] = (unsigned)(c - 1);
+    const unsigned long long two_k = 1ull << (31 + c), dd = d < 1 ? 1 : (unsigned long long)d;
+    out[0] = (unsigned)((two_k + dd - 1) / dd);
+    out[1] = (unsigned)c;
 }
 __device__ __forceinline__ int div_by(int n, const unsigned (&d)[2])
 {
-    return d[0] ? (int)(__umulhi((unsigned)n, d[0]) >> d[1]) : n;
+    return (int)(__umulhi((unsigned)n << 1, d[0]) >> d[1]);
 }
 
 __device__ __forceinline__ float ld_f32(const float *p, int64_t i) { return p[i]; }

@@ -3,6 +3,9 @@
 #include "device_util.h"
 #include "kernels.h"
 
+// the address of a __shared__ object as the direct-to-LDS load builtins take it
+#define GACER_LDS(p) ((__attribute__((address_space(3))) void *)(p))
+
 namespace gacer {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));

@@ -24,7 +24,7 @@
 namespace gacer {
 
 static constexpr int THREADS = 256;
-enum { LOAD_VEC = 0, LOAD_GATHER = 1, LOAD_BT = 2, LOAD_TAPS = 3, LOAD_AFFINE = 4, LOAD_TAPS_ANY = 5 };
+enum { LOAD_VEC = 0, LOAD_GATHER = 1, LOAD_BT = 2, LOAD_TAPS = 3, LOAD_AFFINE = 4 };
 
 // ---- epilogue shared by the tiled kernels ----
 // MFMA leaves element e of a 32x32 tile at row (e/4)*8 + (lane/32)*4 + e%4, column lane%32.  Each wave
@@ -446,8 +446,6 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
 // NS - 2 youngest blocks are outstanding (block kb + 1 has landed), and for its own fragment reads, then meets the
 // others at a bare s_barrier.  The stages are separate __shared__ arrays so that the compiler can see that a load
 // into one stage does not alias the reads of another (with one array it waits for vmcnt(0) before every read).
-#define GACER_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-
 template <int DT, int BM, int BN, int WM, int WN, int KV, int NS, bool TAPS>
 __global__ __launch_bounds__(THREADS)
 __attribute__((amdgpu_waves_per_eu(2 * NS * (BM + BN) * KV * 16 <= 160 * 1024 ? 2 : 1)))      // two workgroups per unit where LDS allows
@@ -868,272 +866,6 @@ __global__ __launch_bounds__(THREADS) void rowgemm_kernel(GemmArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
-// K slices side by side in one workgroup: for products with few output tiles and a long K (late convolution layers, short
-// token batches, classifiers).  Wave w of the workgroup owns slice w of the K range and a whole 32x32 output tile; the slice
-// accumulators meet in LDS, are added in ascending order and go through the epilogue, so one launch does what a slice kernel
-// plus a finishing pass over fp32 partial tiles in memory did.  Very long K (the first classifier layer of a VGG) is cut once
-// more over the grid: workgroup row y owns slices y * S .. y * S + S - 1 and writes its sum to the workspace, splitk_finish
-// adds those.  An output element is the sum of its slice chains in that fixed order, whatever part of the operator is launched.
-//
-// Waves share no operand (their K ranges are disjoint), so each has two LDS stages of its own and there is no barrier in the
-// loop: a stage is one batch of 128 bytes of K for 32 + 32 rows, filled by eight direct-to-LDS loads of eight rows each,
-// swizzled as in igemm_dma_kernel, read into fragments at once and refilled while the MFMAs of the batch run.
-//
-// What bounds it: the path from L2 into LDS, about 45 bytes per clock and unit (each wave computes the tile for its own K, so
-// 64 rows are moved per 32x32 of output, twice what four waves sharing a 64x64 tile move), hence few tiles only; in fp32 the
-// matrix cores from about 4 KB of K on.  Fragments loaded straight into registers in operand layout (32 rows x 32 bytes per
-// load) reach 19 bytes per clock: 49x512x4608 bf16 took 17.3 us that way, 9.0 us like this, 9.9 us as slices plus finishing
-// pass.  144x768x768 bf16 9.0 -> 4.6 us, 125x32x1152 fp32 31.3 -> 9.9 us, where an empty kernel reads 3.9 us.
-template <int DT, int LOAD, int S, int PRE_MAX = 0>
-__global__ __launch_bounds__(64 * S) void slices_kernel(GemmArgs a)
-{
-    typedef typename El<DT>::T T;
-    constexpr int VEC = El<DT>::VEC;
-    constexpr int ESZ = (int)sizeof(T);
-    constexpr int BE = 128 / ESZ;               // elements per batch and row
-    constexpr int STAGE = 64 * 128;             // bytes of one wave's stage: 32 A rows, then 32 B rows
-    constexpr bool PRE = LOAD == LOAD_AFFINE;
-    __shared__ __align__(1024) unsigned char st0[S * STAGE];
-    __shared__ __align__(1024) unsigned char st1[S * STAGE];
-    __shared__ __align__(16) float pre[PRE ? 2 * PRE_MAX : 4];                  // scale, shift
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tile = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
-    const int by_m = div_by(tile, a.div_tiles_m), by_n = div_by(tile, a.div_tiles_n);
-    const int tile_m = __builtin_amdgcn_readfirstlane(a.n_major ? tile - by_m * a.tiles_m : by_n);
-    const int tile_n = __builtin_amdgcn_readfirstlane(a.n_major ? by_m : tile - by_n * a.tiles_n);
-    const int m0 = a.m_lo + tile_m * 32, n0 = a.n_lo + tile_n * 32;
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes), wr = make_rsrc(a.w, a.w_bytes);
-
-    // Load p of a stage fills rows 8 p .. 8 p + 7: lane l row 8 p + l / 8, slot l % 8, which holds logical chunk
-    // (l % 8) ^ ((row / 2) % 8) -- two values per lane, by the parity of p
-    const int c0 = (lane & 7) ^ (lane >> 4);
-    const int kl[2] = {c0 * VEC, (c0 ^ 4) * VEC};
-    unsigned a_off[4], a_bad[4], b_off[4];      // a_bad: one bit per tap, set where the tap reads nothing
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int row = 8 * p + (lane >> 3);
-        const int m = m0 + row;
-        const bool ok = m < a.m_hi;
-        const int mm = ok ? m : a.m_lo;
-        const int HoWo = a.Ho * a.Wo;
-        const int img = div_by(mm, a.div_howo), rem = mm - img * HoWo;
-        const int oh = div_by(rem, a.div_wo), ow = rem - oh * a.Wo;
-        const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
-        const int64_t e0 = (int64_t)img * a.x_img + ((int64_t)ih0 * a.W + iw0) * a.x_pix + (LOAD == LOAD_TAPS_ANY ? 0 : kl[p & 1]);
-        a_off[p] = (unsigned)(int)(e0 * ESZ);
-        a_bad[p] = ~(ok ? (LOAD == LOAD_TAPS || LOAD == LOAD_TAPS_ANY ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 1u) : 0u);
-        b_off[p] = n0 + row < a.n_hi ? (unsigned)(((int64_t)(n0 + row) * a.w_row + kl[p & 1]) * ESZ) : OOB;
-    }
-
-    // K range of this wave, in elements; loads at or beyond k_end return zeros
-    const int per = a.kb_per_wave * (64 / ESZ);
-    const int slice = (int)blockIdx.y * S + wave;
-    const int k_lo = min(a.K, slice * per), k_end = min(a.K, k_lo + per);
-    const int batches = (k_end - k_lo + BE - 1) / BE;
-
-    // position of the next batch; LOAD_TAPS: a batch never crosses a tap (128 bytes divide a tap's channels), so the tap is
-    // a scalar
-    int kb = k_lo, kr = 0, ksx = 0, kci = k_lo;
-    if constexpr (LOAD == LOAD_TAPS) {
-        const int tap = div_by(k_lo, a.div_cin);
-        kci = k_lo - tap * a.Cin;
-        kr = div_by(tap, a.div_kw);
-        ksx = tap - kr * a.kw;
-    }
-    auto request = [&](unsigned char *stage) {
-        // LOAD_AFFINE masks by arithmetic (the top bit puts an offset out of range): of selects the compiler makes branches with
-        // loads in both arms, cannot count across them and waits for loads of the newest batch too, which costs the variant
-        // with stores in flight a memory latency per batch.  Without stores the branches are 1-6 % faster.
-        unsigned da[2], tap[2], k_bad[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int kv = kb + kl[h];
-            k_bad[h] = PRE ? ~(unsigned)((kv - k_end) >> 31) & OOB : kv < k_end ? 0u : OOB;
-            tap[h] = 0u;
-            if constexpr (LOAD == LOAD_TAPS) {
-                da[h] = (unsigned)((((int64_t)kr * a.W + ksx) * a.x_pix + kci) * ESZ);
-                tap[h] = (unsigned)(kr * a.kw + ksx) & 31u;
-            } else if constexpr (LOAD == LOAD_TAPS_ANY) {
-                const int t = div_by(kv, a.div_cin), ci = kv - t * a.Cin;
-                const int r = div_by(t, a.div_kw), q = t - r * a.kw;
-                da[h] = (unsigned)((((int64_t)r * a.W + q) * a.x_pix + ci) * ESZ);
-                tap[h] = (unsigned)t & 31u;
-            } else {
-                da[h] = (unsigned)(kb * ESZ);
-            }
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const unsigned off = PRE ? (a_off[p] + da[p & 1]) | k_bad[p & 1] | (a_bad[p] << 31)
-                                     : k_bad[p & 1] == 0u && !((a_bad[p] >> tap[p & 1]) & 1u) ? a_off[p] + da[p & 1] : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GACER_LDS(stage + p * 1024), 16, (int)off, 0, 0, 0);
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const unsigned off = PRE ? (b_off[p] + (unsigned)(kb * ESZ)) | k_bad[p & 1]
-                                     : k_bad[p & 1] == 0u && b_off[p] != OOB ? b_off[p] + (unsigned)(kb * ESZ) : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + 4096 + p * 1024), 16, (int)off, 0, 0, 0);
-        }
-        kb += BE;
-        if constexpr (LOAD == LOAD_TAPS) {
-            kci += BE;
-            const bool w1 = kci >= a.Cin;
-            kci -= w1 ? a.Cin : 0;
-            ksx += w1 ? 1 : 0;
-            const bool w2 = ksx == a.kw;
-            ksx = w2 ? 0 : ksx;
-            kr += w2 ? 1 : 0;
-        }
-    };
-
-    f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    const int frag = lrow * 128, frag_lo = (lhalf ^ ((lrow >> 1) & 7)) * 16;
-    constexpr int WAIT_BATCH = (8 & 15) | (7 << 4) | (15 << 8);                 // vmcnt(8): the older of the two batches in flight has landed
-    constexpr int WAIT_LDS = 15 | (7 << 4) | (3 << 14);                         // lgkmcnt(0)
-    // LOAD_AFFINE: the waves of channel 0 also store the transformed A, four stores per batch behind the batch's requests (the
-    // other waves, and masked lanes, store out of range).  vmcnt counts them: four more may be outstanding
-    // at every second batch, where a wait for eight would cost one memory latency (at the loop's entry there are no stores yet).
-    // With that and the parameters requested together with the operands, DenseNet's 40 such products of 8 images take 299 us in
-    // bf16, 378 before.
-    constexpr int WAIT_STORED = 12 | (7 << 4) | (15 << 8);
-    const __amdgpu_buffer_rsrc_t yr = make_rsrc(PRE ? a.pre_y : nullptr, PRE && n0 == 0 ? (int64_t)a.m_hi * a.Cin * ESZ : 0);
-    auto step = [&](unsigned char *stage, int k0, bool entry) {
-        if (PRE && !entry) __builtin_amdgcn_s_waitcnt(WAIT_STORED); else __builtin_amdgcn_s_waitcnt(WAIT_BATCH);
-        asm volatile("" ::: "memory");
-        uint4 fa[4], fb[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            fa[g] = *(const uint4 *)(stage + frag + (frag_lo ^ (g * 32)));
-            fb[g] = *(const uint4 *)(stage + 4096 + frag + (frag_lo ^ (g * 32)));
-        }
-        __builtin_amdgcn_s_waitcnt(WAIT_LDS);                                   // the stage may be refilled
-        asm volatile("" ::: "memory");
-        request(stage);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            if constexpr (PRE) {                // the stand-alone operator's arithmetic, and its output tensor on the side
-                const int kv = k0 + g * 2 * VEC + lhalf * VEC;
-                float sc[VEC], sh[VEC];
-#pragma unroll
-                for (int q = 0; q < VEC; q += 4) {
-                    const float4 s4 = *(const float4 *)(pre + kv + q), h4 = *(const float4 *)(pre + PRE_MAX + kv + q);
-                    sc[q] = s4.x; sc[q + 1] = s4.y; sc[q + 2] = s4.z; sc[q + 3] = s4.w;
-                    sh[q] = h4.x; sh[q + 1] = h4.y; sh[q + 2] = h4.z; sh[q + 3] = h4.w;
-                }
-                fa[g] = affine_vec<DT>(fa[g], sc, sh, a.pre_act);
-                const i32x4 v = {(int)fa[g].x, (int)fa[g].y, (int)fa[g].z, (int)fa[g].w};
-                const unsigned bad = ~(unsigned)(((m0 + lrow - a.m_hi) & (kv - k_end)) >> 31) & OOB;
-                __builtin_amdgcn_raw_buffer_store_b128(v, yr, (int)((unsigned)(((int64_t)(m0 + lrow) * a.Cin + kv) * ESZ) | bad), 0, 0);
-            }
-            if constexpr (DT == DT_BF16) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[g]), __builtin_bit_cast(bf16x8, fb[g]), acc, 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float av = __uint_as_float(e == 0 ? fa[g].x : e == 1 ? fa[g].y : e == 2 ? fa[g].z : fa[g].w);
-                    const float bv = __uint_as_float(e == 0 ? fb[g].x : e == 1 ? fb[g].y : e == 2 ? fb[g].z : fb[g].w);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
-                }
-            }
-        }
-    };
-
-    unsigned char *w0 = st0 + wave * STAGE, *w1 = st1 + wave * STAGE;
-    if constexpr (PRE) {                        // zeros beyond K: a zero element of B meets something finite
-        const int pre_n = (a.K + BE - 1) / BE * BE;
-        const __amdgpu_buffer_rsrc_t psr = make_rsrc(a.pre_scale, (int64_t)a.K * 4), phr = make_rsrc(a.pre_shift, (int64_t)a.K * 4);
-        const int k0 = tid * 4;                 // the first 256 S channels are requested ahead of the operands: one memory latency
-        const uint4 sc = buf_load16(psr, (unsigned)(k0 * 4)), sh = buf_load16(phr, (unsigned)(k0 * 4));
-        asm volatile("" ::: "memory");
-        request(w0);
-        request(w1);
-        if (k0 < pre_n) {
-            *(uint4 *)(pre + k0) = sc;
-            *(uint4 *)(pre + PRE_MAX + k0) = sh;
-        }
-        for (int k = k0 + 256 * S; k < pre_n; k += 256 * S) {
-            *(uint4 *)(pre + k) = buf_load16(psr, (unsigned)(k * 4));
-            *(uint4 *)(pre + PRE_MAX + k) = buf_load16(phr, (unsigned)(k * 4));
-        }
-        __builtin_amdgcn_s_waitcnt(WAIT_LDS);   // parameters written; the requests stay in flight across the barrier
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    } else {
-        request(w0);
-        request(w1);
-    }
-    int b = 0;
-    for (; b + 2 <= batches; b += 2) {
-        step(w0, k_lo + b * BE, true);
-        step(w1, k_lo + (b + 1) * BE, false);
-    }
-    if (b < batches) step(w0, k_lo + b * BE, true);
-    __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));                           // vmcnt(0): the requests beyond the slice have landed
-    asm volatile("" ::: "memory");
-    __syncthreads();                            // `part` overlays the stages of several waves
-
-    // ---- sum over the slices and epilogue ----
-    // accumulator element e of lane l is row (e/4)*8 + (l/32)*4 + e%4, column l%32: thread t of the first 256 owns element
-    // t / 16 of lanes 4 (t % 16) .. + 3, i.e. four consecutive channels of one row, and reads LDS contiguously
-    float *part = (float *)st0;                 // [slice][16][64]
-#pragma unroll
-    for (int e = 0; e < 16; ++e) part[(wave * 16 + e) * 64 + lane] = acc[e];
-    const bool split = a.ksplit > 1;
-    const int Nl = a.n_hi - a.n_lo;
-    float *ws = split ? a.ws + (int64_t)blockIdx.y * (a.m_hi - a.m_lo) * Nl : nullptr;
-    T *yg = (T *)a.y;
-    const T *rg = (const T *)a.res;
-    constexpr int AL = 4 * ESZ - 1;
-    const bool vec_out = split ? (Nl % 4 == 0 && (((uintptr_t)a.ws) & 15) == 0)
-                               : (a.y_row % 4 == 0 && a.n_lo % 4 == 0 && (((uintptr_t)a.y) & AL) == 0 && (((uintptr_t)a.res) & AL) == 0 &&
-                                  (((uintptr_t)a.bias) & 15) == 0);
-    if (tid >= 256) { __syncthreads(); return; }
-    const int e = tid >> 4, l0 = (tid & 15) * 4;
-    const int m = m0 + (e >> 2) * 8 + (l0 >> 5) * 4 + (e & 3), n = n0 + (l0 & 31);
-    const bool inside = m < a.m_hi && n < a.n_hi, n_vec = inside && vec_out && n + 4 <= a.n_hi;
-    const int64_t o = (int64_t)m * a.y_row + n;
-    float bv[4];
-    load_bias_vec<4>(a.bias, n, !split && n_vec, bv);
-    float rv[4] = {0.f, 0.f, 0.f, 0.f};
-    if (rg && !split && n_vec) load_vec4(rg + o, rv);
-    __syncthreads();
-    if (!inside) return;
-    const float *p = part + e * 64 + l0;
-    float4 s4 = *(const float4 *)p;
-    float v[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-    for (int s = 1; s < S; ++s) {
-        s4 = *(const float4 *)(p + s * 1024);
-        v[0] = __fadd_rn(v[0], s4.x); v[1] = __fadd_rn(v[1], s4.y); v[2] = __fadd_rn(v[2], s4.z); v[3] = __fadd_rn(v[3], s4.w);
-    }
-    if (split) {
-        float *q = ws + (int64_t)(m - a.m_lo) * Nl + (n - a.n_lo);
-        if (n_vec) {
-            *(float4 *)q = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-            for (int c = 0; c < 4; ++c)
-                if (n + c < a.n_hi) q[c] = v[c];
-        }
-    } else if (n_vec) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = __fmaf_rn(v[c], a.alpha, bv[c]);
-        if (rg) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = __fadd_rn(v[c], rv[c]);
-        }
-        act_vec<4>(v, a.act);
-        store_vec4(yg + o, v);
-    } else {
-        for (int c = 0; c < 4; ++c) finish_one<DT>(v[c], a.alpha, a.bias, a.act, rg, yg, o + c, n + c, a.n_hi);
-    }
-}
-
 // Second pass of a split-K operator: out = act(alpha * (s0 + s1 + ... ) + bias + res), slices added in
 // ascending order.  One thread per FV consecutive output channels of the launched sub-range (FV = 4 when
 // the range and the pointers allow 16-byte accesses), coalesced along n.
@@ -1190,7 +922,7 @@ __global__ __launch_bounds__(THREADS) void splitk_finish(GemmArgs a)
 }
 
 template <typename T>
-static void launch_finish(const GemmArgs &a, hipStream_t s)
+static void finish(const GemmArgs &a, hipStream_t s)
 {
     const int Nl = a.n_hi - a.n_lo;
     const int64_t total = (int64_t)(a.m_hi - a.m_lo) * Nl;
@@ -1202,6 +934,8 @@ static void launch_finish(const GemmArgs &a, hipStream_t s)
     else
         GACER_LAUNCH((splitk_finish<T, 1>), dim3((unsigned)((total + THREADS - 1) / THREADS)), dim3(THREADS), 0, s, b);
 }
+
+void launch_finish(const GemmArgs &a, hipStream_t s) { a.dtype == DT_BF16 ? finish<unsigned short>(a, s) : finish<float>(a, s); }
 
 static void set_tiling(GemmArgs &b, int tiles_m, int tiles_n)
 {
@@ -1222,7 +956,7 @@ static void set_divisors(GemmArgs &b)
 // Tile numbering of a launch.  m-major numbering gives every XCD a band of output rows: A is fetched into one L2 only,
 // B into every L2 that holds a band; n-major numbering is the mirror image.  Takes the order that moves fewer bytes
 // into the L2s (late convolution layers have far more weights than activations, early ones the opposite).
-static int tile_order(const GemmArgs &a, int tiles_m, int tiles_n, int esz)
+int tile_order(const GemmArgs &a, int tiles_m, int tiles_n, int esz)
 {
     const double Ml = a.m_hi - a.m_lo, Nl = a.n_hi - a.n_lo;
     const double A = Ml * a.stride * a.stride * (double)(a.K / (a.kh * a.kw)) * esz;     // input pixels behind the output rows
@@ -1258,7 +992,7 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
     if (dry || li.workgroups == 0) return li;
     dim3 grid(tiles_m * tiles_n, ks, z), block(THREADS);
     if (phase == 2) {
-        if (ks > 1) launch_finish<T>(a, s);
+        if (ks > 1) finish<T>(a, s);
         return li;
     }
     GemmArgs b = a;
@@ -1275,7 +1009,7 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_TAPS>), grid, block, 0, s, b);
     else
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_VEC>), grid, block, 0, s, b);
-    if (ks > 1 && phase == 0) launch_finish<T>(a, s);
+    if (ks > 1 && phase == 0) finish<T>(a, s);
     return li;
 }
 
@@ -1305,7 +1039,7 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
     if (dry || li.workgroups == 0) return li;
     dim3 grid(tiles_m * tiles_n, ks, z), block(THREADS);
     if (phase == 2) {
-        if (ks > 1) launch_finish<T>(a, s);
+        if (ks > 1) finish<T>(a, s);
         return li;
     }
     GemmArgs b = a;
@@ -1314,7 +1048,7 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
     set_tiling(b, tiles_m, tiles_n);
     if (taps) GACER_LAUNCH((igemm_dma_kernel<DT, BM, BN, WM, WN, KV, NS, true>), grid, block, 0, s, b);
     else GACER_LAUNCH((igemm_dma_kernel<DT, BM, BN, WM, WN, KV, NS, false>), grid, block, 0, s, b);
-    if (ks > 1 && phase == 0) launch_finish<T>(a, s);
+    if (ks > 1 && phase == 0) finish<T>(a, s);
     return li;
 }
 
@@ -1383,53 +1117,10 @@ static LaunchInfo pick_rows(const GemmArgs &a, hipStream_t s, bool dry)
     }
 }
 
-// Launcher of slices_kernel: S waves per workgroup (one K slice each), ksplit workgroups along K.
-template <int DT, int S>
-static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase)
-{
-    typedef typename El<DT>::T T;
-    const int tiles_m = (a.m_hi - a.m_lo + 31) / 32, tiles_n = (a.n_hi - a.n_lo + 31) / 32;
-    LaunchInfo li;
-    li.workgroups = tiles_m * tiles_n * a.ksplit;
-    li.threads = 64 * S;
-    // 16 KB of affine parameters beside the stages of four waves leave room for a second workgroup on the unit, which the rule for
-    // four waves counts on where there are more tiles than units; 32 KB do not, and keep the workgroups of a smaller launch on units of
-    // their own when other tenants fill some (ResNet-101, DenseNet-121 and MobileNetV3 of 8 images, bf16: round 1472 us, with 16
-    // KB throughout 1523).  Affine + product, us, with 32 / 16 KB: fp32 3136x128x128 9.6 / 6.8, 3136x128x1000 28.5 /
-    // 21.5, bf16 8.6 / 6.2 and 15.7 / 12.4.  (Sized at launch instead, the array costs bf16 up to 11 %: the compiler then no longer
-    // knows that the loads into the stages do not fill it, and waits for them.)
-    constexpr int PRE_SMALL = S == 4 ? SLICES_PRE_MAX / 2 : SLICES_PRE_MAX;
-    const bool small = a.K <= PRE_SMALL && tiles_m * tiles_n * a.ksplit > 256;
-    li.lds_bytes = S * 16384 + (a.pre_scale ? 8 * (small ? PRE_SMALL : SLICES_PRE_MAX) : 0);
-    li.wg_per_cu = (160 * 1024) / li.lds_bytes;
-    static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S);
-    static const std::string n_one = "igemm_slices_" + shape, n_pre = "igemm_affine_slices_" + shape;
-    li.kernel = phase == 2 ? "splitk_finish" : a.pre_scale ? n_pre.c_str() : n_one.c_str();
-    li.phases = a.ksplit > 1 ? 2 : 1;
-    if (dry || li.workgroups == 0) return li;
-    if (phase != 2) {
-        GemmArgs b = a;
-        b.n_major = tile_order(a, tiles_m, tiles_n, (int)sizeof(T));
-        set_divisors(b);
-        set_tiling(b, tiles_m, tiles_n);
-        const dim3 grid(tiles_m * tiles_n, a.ksplit), block(64 * S);
-        const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
-        if (a.pre_scale && small) GACER_LAUNCH((slices_kernel<DT, LOAD_AFFINE, S, PRE_SMALL>), grid, block, 0, s, b);
-        else if (a.pre_scale) GACER_LAUNCH((slices_kernel<DT, LOAD_AFFINE, S, SLICES_PRE_MAX>), grid, block, 0, s, b);
-        else if (!taps) GACER_LAUNCH((slices_kernel<DT, LOAD_VEC, S>), grid, block, 0, s, b);
-        else if (a.Cin * (int)sizeof(T) % 128 == 0) GACER_LAUNCH((slices_kernel<DT, LOAD_TAPS, S>), grid, block, 0, s, b);
-        else GACER_LAUNCH((slices_kernel<DT, LOAD_TAPS_ANY, S>), grid, block, 0, s, b);
-    }
-    if (a.ksplit > 1 && phase != 1) launch_finish<T>(a, s);
-    return li;
-}
-
 template <int DT>
 static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     constexpr int VEC = El<DT>::VEC;
-    if (a.kwaves == 8) return go_slices<DT, 8>(a, s, dry, phase);
-    if (a.kwaves == 4) return go_slices<DT, 4>(a, s, dry, phase);
     const bool vec_ok = (a.Cin % VEC == 0) && (a.x_pix % VEC == 0) && (a.x_img % VEC == 0) && (a.w_row % VEC == 0) &&
                         (a.x_zb % VEC == 0) && (a.x_zh % VEC == 0) && (a.w_zb % VEC == 0) && (a.w_zh % VEC == 0) &&
                         (((uintptr_t)a.x) % 16 == 0) && (((uintptr_t)a.w) % 16 == 0);
@@ -1493,6 +1184,7 @@ LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     if (a.stem) return launch_stem(a, s, dry);
     if (a.halo) return launch_conv3(a, s, dry);
+    if (a.kwaves) return launch_slices(a, s, dry, phase);
     return a.dtype == DT_BF16 ? pick<DT_BF16>(a, s, dry, phase) : pick<DT_F32>(a, s, dry, phase);
 }
 

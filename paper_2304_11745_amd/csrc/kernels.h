@@ -54,7 +54,7 @@ struct GemmArgs {
     int halo;                  // the convolution runs on conv3_kernel (3x3, input staged once for all taps); fixed per operator
     float *ws;
     int n_major;               // set by the launcher: tiles are numbered n-major (1) or m-major (0), see tile_order()
-    // set by the launcher: n / d for 0 <= n < 2^31 as (n * mul) >> (32 + shift), mul = 0 meaning d = 1; d = Ho*Wo, Wo, Cin, kw
+    // set by the launcher: multiplier and shift of the division by d (see divisor()); d = Ho*Wo, Wo, Cin, kw
     unsigned div_howo[2], div_wo[2], div_cin[2], div_kw[2];
     // set by the launcher of the tiled kernels: tiles along m and n of this launch, divisors for them and for zh
     int tiles_m, tiles_n;
@@ -105,6 +105,9 @@ struct LaunchInfo { int workgroups; int threads; int lds_bytes; int wg_per_cu; c
 LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase = 0);
 LaunchInfo launch_stem(const GemmArgs &a, hipStream_t s, bool dry);        // launch_igemm hands over operators marked `stem`
 LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry);       // and operators marked `halo`
+LaunchInfo launch_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase);   // and operators with `kwaves`
+void launch_finish(const GemmArgs &a, hipStream_t s);                      // the finishing pass of a split-K operator
+int tile_order(const GemmArgs &a, int tiles_m, int tiles_n, int esz);      // GemmArgs::n_major of a launch
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry);
 LaunchInfo launch_maxpool(const StreamArgs &a, hipStream_t s, bool dry);
 LaunchInfo launch_gavgpool(const StreamArgs &a, hipStream_t s, bool dry);

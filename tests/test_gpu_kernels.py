@@ -85,6 +85,25 @@ def test_k_slices_inside_a_workgroup(dtype):
     check(tenants, names[dtype], [("batch", 2), ("cout", 2), ("cout", 8)])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_k_slices_addressing(dtype):
+    """The ways slices_kernel addresses its rows: one pitch, strided 1x1 (rows that end inside an image), a padded 1x1 (its border
+    rows read nothing), windows with more padding than kernel, one input pixel per window row; slices of no, one, two, three, four
+    and five batches, the last one ending inside a batch; a residual with a channel count that is no multiple of four."""
+    from synth import graphs as G
+    e = 64 if dtype == "bf16" else 32                # elements of a batch
+    tenants = []
+    for i, (batch, hw, cin, cout, k, stride, pad, res) in enumerate([
+            (3, 9, 2 * e, 40, 1, 2, 0, False), (2, 7, 4 * e - 8, 33, 1, 3, 0, False), (2, 6, 3 * e, 36, 1, 1, 1, False), (2, 5, e, 40, 3, 1, 4, False),
+            (3, 7, 72, 32, 3, 2, 3, False), (2, 1, 4 * e, 33, 3, 1, 1, False), (3, 5, 3 * e + 8, 3 * e + 8, 1, 1, 0, True),
+            (3, 5, 7 * e + 8, 70, 1, 1, 0, False), (3, 5, 11 * e + 8, 33, 1, 1, 0, False), (1, 9, 16 * e, 36, 1, 1, 0, False), (1, 9, 20 * e - 8, 36, 1, 1, 0, False)]):
+        b = G._B(f"rows{i}", dtype, batch)
+        x = b.tensor(batch, cin, hw, hw)
+        tenants.append(b.done(x, b.conv(x, cout, k, stride, pad, "relu", res=x if res else -1)))
+    ran = check(tenants, [f"igemm_slices_{dtype}_x4"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    assert all(n.startswith("igemm_slices") or n == "splitk_finish" for n in ran), ran
+
+
 def test_long_k_with_few_tiles_in_fp32():
     """K cut over the grid beside the slices of a workgroup (one, three, five and eight workgroup rows along K, the last row with
     fewer batches than the others), and the shapes with 65 to 128 tiles that the tiled kernels with their own cut of K take."""
