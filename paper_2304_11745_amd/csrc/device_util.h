@@ -42,6 +42,15 @@ __device__ __forceinline__ unsigned short to_bf16(float f)      // round to near
 {
     return __builtin_bit_cast(unsigned short, (__bf16)f);
 }
+// two floats -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi)
+{
+    const f32x2 f = {lo, hi};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
+}
+
 __device__ __forceinline__ void st_f32(float *p, int64_t i, float v) { p[i] = v; }
 __device__ __forceinline__ void st_f32(unsigned short *p, int64_t i, float v) { p[i] = to_bf16(v); }
 

@@ -47,15 +47,6 @@ template <> __device__ __forceinline__ void store_out<unsigned short>(unsigned s
 __device__ __forceinline__ float load_in(const float *p, int64_t o) { return p[o]; }
 __device__ __forceinline__ float load_in(const unsigned short *p, int64_t o) { return bf16_to_f32(p[o]); }
 
-// two floats -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32)
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi)
-{
-    const f32x2 f = {lo, hi};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
-}
-
 // Activation of EV values; `act` is uniform over the launch, so the branch is taken once per vector.
 template <int EV> __device__ __forceinline__ void act_vec(float *v, int act)
 {

@@ -60,12 +60,15 @@ __global__ __launch_bounds__(TPB) void dwconv_kernel(StreamArgs a)
     st_vec<T, V>((T *)a.y, o, yv);
 }
 
-// ---- depthwise 3x3 and 5x5, register tiled: one thread = TW consecutive output pixels of one row x one channel vector ----
-// The K x ((TW-1)*S + K) input window and the K*K weight vectors are loaded once and reused by the TW outputs, which
-// cuts what goes through L1 about three-fold.  Every output is still the same chain of fused multiply-adds over
-// taps (r, s) ascending (zero fill outside the image adds exact zeros), so results equal the generic kernel's.
-// 5x5: MobileNetV3's six such layers at 32 images bf16 take 71 us, 130 with one output vector per thread (bound by L1: 25
-// window loads per output); at batch 7, 147x147, fp32 31 / 51 us.
+// ---- depthwise 3x3 and 5x5, register tiled: one thread = TH x TW outputs x one channel vector ----
+// The ((TH-1)*S + K) x ((TW-1)*S + K) input window and the K*K weight vectors are loaded once, all up front, and reused by the
+// outputs.  Every output is the same chain of fused multiply-adds over taps (r, s) ascending (zero fill outside the image adds exact
+// zeros) whatever the tile, so results equal the generic kernel's.
+// What bounds it: few outputs, one thread's chain of instructions around one round trip to memory; many outputs, in fp32 memory
+// (56x56x144, 32 images: 115.6 MB in 21.3 us), in bf16 the instructions per output (conversion of window and weights, the
+// multiply-adds, loads).  Us per launch, before with one row of outputs per thread and 64-bit addresses / here: bf16 14x14x384 1 image
+// 4.26 / 2.62, 56x56x144 32 images 22.9 / 14.1, stride 2 11.9 / 7.9, 5x5 28x28x120 32 images 12.9 / 9.3; fp32 35.8 / 21.3, stride 2
+// 17.0 / 12.3, 5x5 19.9 / 11.4.
 template <typename T, int V> struct Unpack;
 template <> struct Unpack<float, 4> {
     static __device__ __forceinline__ void run(const uint4 &r, float *f)
@@ -77,28 +80,6 @@ template <> struct Unpack<float, 4> {
         return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
     }
 };
-template <> struct Unpack<unsigned short, 8> {
-    static __device__ __forceinline__ void run(const uint4 &r, float *f)
-    {
-        const unsigned w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { f[2 * q] = __uint_as_float(w[q] << 16); f[2 * q + 1] = __uint_as_float(w[q] & 0xFFFF0000u); }
-    }
-    static __device__ __forceinline__ uint4 pack(const float *f)
-    {
-        uint4 o;
-        o.x = (unsigned)to_bf16(f[0]) | ((unsigned)to_bf16(f[1]) << 16);
-        o.y = (unsigned)to_bf16(f[2]) | ((unsigned)to_bf16(f[3]) << 16);
-        o.z = (unsigned)to_bf16(f[4]) | ((unsigned)to_bf16(f[5]) << 16);
-        o.w = (unsigned)to_bf16(f[6]) | ((unsigned)to_bf16(f[7]) << 16);
-        return o;
-    }
-};
-
-// outputs per thread along W.  3x3: as many as fit 128 registers (four waves per SIMD keep enough loads in flight); 5x5: 256, with
-// window and weights of fp32 twice as large
-template <typename T, int S, int K> struct DW_TW { static constexpr int value = (S == 2 ? 2 : 4) / (K == 5 && sizeof(T) == 4 ? 2 : 1); };
-
 template <> struct Unpack<unsigned short, 4> {
     static __device__ __forceinline__ void run(const uint2 &r, float *f)
     {
@@ -107,92 +88,142 @@ template <> struct Unpack<unsigned short, 4> {
     }
     static __device__ __forceinline__ uint2 pack(const float *f)
     {
-        return make_uint2((unsigned)to_bf16(f[0]) | ((unsigned)to_bf16(f[1]) << 16), (unsigned)to_bf16(f[2]) | ((unsigned)to_bf16(f[3]) << 16));
+        return make_uint2(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]));
     }
 };
-template <typename T, int V> struct Raw { typedef uint4 type; static __device__ __forceinline__ uint4 load(__amdgpu_buffer_rsrc_t r, unsigned o) { return buf_load16(r, o); } };
-template <> struct Raw<unsigned short, 4> { typedef uint2 type; static __device__ __forceinline__ uint2 load(__amdgpu_buffer_rsrc_t r, unsigned o) { return buf_load8(r, o); } };
-
-template <typename T, int V, int S, int K>
-__global__ __launch_bounds__(TPB, K == 3 ? 4 : 2) void dwconv_tile_kernel(StreamArgs a)
+template <> struct Unpack<unsigned short, 2> {
+    static __device__ __forceinline__ void run(unsigned r, float *f) { f[0] = __uint_as_float(r << 16); f[1] = __uint_as_float(r & 0xFFFF0000u); }
+    static __device__ __forceinline__ unsigned pack(const float *f) { return pack_bf16(f[0], f[1]); }
+};
+template <int BYTES> struct Raw;
+template <> struct Raw<4> { typedef unsigned type; };
+template <> struct Raw<8> { typedef uint2 type; };
+template <> struct Raw<16> { typedef uint4 type; };
+template <int BYTES> __device__ __forceinline__ typename Raw<BYTES>::type load_raw(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff)
 {
-    constexpr int TW = DW_TW<T, S, K>::value, NC = (TW - 1) * S + K, ESZ = (int)sizeof(T);
-    const int CV = (a.c_hi - a.c_lo) / V;
-    const int WT = (a.Wo + TW - 1) / TW;
-    const int64_t total = (int64_t)(a.n_hi - a.n_lo) * a.Ho * WT * CV;
-    const int64_t idx = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (idx >= total) return;
-    const int p0 = div_by((int)idx, a.div_cv), cv = (int)idx - p0 * CV;       // idx < 2^31: a tensor holds fewer elements
-    const int p1 = div_by(p0, a.div_w), wt = p0 - p1 * WT;
-    const int p2 = div_by(p1, a.div_h), oh = p1 - p2 * a.Ho;
-    const int n = a.n_lo + p2;
-    const int c = a.c_lo + cv * V;
-    const int ow0 = wt * TW;
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, (int64_t)a.N * a.H * a.W * a.C * ESZ);
-    // all loads are issued up front, without branches: positions outside the image read as zero
-    typedef typename Raw<T, V>::type R;
-    R raw[K][NC], wraw[K * K];
-    const int iw0 = ow0 * S - a.pad;
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    if constexpr (BYTES == 4) return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)soff, 0);
+    else if constexpr (BYTES == 8) return __builtin_bit_cast(uint2, (i32x2)__builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)soff, 0));
+    else return __builtin_bit_cast(uint4, (i32x4)__builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, 0));
+}
+
+// What dwconv_tile_kernel is launched with: V channels per vector, TH x TW outputs per thread.
+struct DwArgs {
+    const void *x;             // the input tensor less the pixels by which a window of its first output begins before it
+    const void *w, *res;
+    const float *bias;
+    void *y;
+    unsigned x_bytes, w_bytes; // to the end of the input tensor, of the weights
+    unsigned pixel, row;       // bytes of a pixel's channels, of an input row
+    int run, extra;            // workgroups per XCD: the first `extra` XCDs have one more
+    int total;                 // threads that have outputs
+    int CV, WT, HT;            // channel vectors per position, tiles per output row, rows of tiles per image
+    unsigned div_cv[2], div_w[2], div_h[2];
+    int c_lo, n_lo;            // first channel, first image
+    int H, W, Ho, Wo, pad, act;
+};
+
+// The loads of a thread need no arithmetic of their own: a window position is the scalar offset of the load, a row or column outside
+// the image puts the vector offset out of range (the hardware then returns zero).
+template <typename T, int V, int S, int K, int TH, int TW>
+__global__ __launch_bounds__(TPB, K == 3 ? 4 : 2) void dwconv_tile_kernel(DwArgs a)
+{
+    constexpr int NR = (TH - 1) * S + K, NC = (TW - 1) * S + K, ESZ = (int)sizeof(T);
+    constexpr unsigned FAR = 0xC0000000u;       // the input's descriptor may reach a little beyond 2 GiB
+    typedef typename Raw<V * ESZ>::type R;
+    const int xcd = (int)blockIdx.x & 7;        // see xcd_contiguous: neighbouring rows share most of their windows
+    const int own = (xcd * a.run + min(xcd, a.extra) + ((int)blockIdx.x >> 3)) * TPB + (int)threadIdx.x;
+    const int idx = min(own, a.total - 1);      // threads beyond the outputs store nothing; leaving here would cost a second wait for arguments
+    const int p0 = div_by(idx, a.div_cv), cv = idx - p0 * a.CV;
+    const int p1 = div_by(p0, a.div_w), ow0 = (p0 - p1 * a.WT) * TW;
+    const int p2 = div_by(p1, a.div_h), oh0 = (p1 - p2 * a.HT) * TH;
+    const unsigned n = (unsigned)(a.n_lo + p2), c = (unsigned)(a.c_lo + cv * V);
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, (int)a.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc((void *)a.w, 0, (int)a.w_bytes, 0x00020000);
+    const unsigned at = (n * (unsigned)a.H + (unsigned)(oh0 * S)) * a.row + (unsigned)(ow0 * S) * a.pixel + c * ESZ;
+    const int ih0 = oh0 * S - a.pad, iw0 = ow0 * S - a.pad;
+    unsigned off[NR], col[NC];
 #pragma unroll
-    for (int r = 0; r < K; ++r) {
-        const int ih = oh * S - a.pad + r;
-        const bool row_ok = ih >= 0 && ih < a.H;
-        const unsigned row_off = (unsigned)((((int64_t)n * a.H + ih) * a.W * a.C + c) * ESZ);
+    for (int r = 0; r < NR; ++r) off[r] = (unsigned)(ih0 + r) < (unsigned)a.H ? at : FAR;
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            const int iw = iw0 + j;
-            const bool ok = row_ok && iw >= 0 && iw < a.W;
-            raw[r][j] = Raw<T, V>::load(xr, ok ? row_off + (unsigned)(iw * a.C * ESZ) : OOB);
+    for (int j = 0; j < NC; ++j) col[j] = (unsigned)(iw0 + j) < (unsigned)a.W ? 0u : FAR;
+    R raw[NR][NC], wraw[K][K];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+#pragma unroll
+        for (int j = 0; j < NC; ++j) raw[r][j] = load_raw<V * ESZ>(xr, off[r] | col[j], (unsigned)r * a.row + (unsigned)j * a.pixel);
+        if (r < K) {
+#pragma unroll
+            for (int q = 0; q < K; ++q) wraw[r][q] = load_raw<V * ESZ>(wr, c * ESZ, (unsigned)(r * K + q) * a.pixel);
         }
     }
-    const T *w = (const T *)a.w;
+    float bias[V];
 #pragma unroll
-    for (int t = 0; t < K * K; ++t) wraw[t] = *(const R *)(w + (int64_t)t * a.C + c);
-    float acc[TW][V];
+    for (int e = 0; e < V; ++e) bias[e] = 0.f;
+    if (a.bias) {
+        typedef typename Raw<V * 4>::type B;
+        const B b = *(const B *)(a.bias + c);
+        __builtin_memcpy(bias, &b, sizeof b);
+    }
+    float acc[TH][TW][V];
 #pragma unroll
-    for (int t = 0; t < TW; ++t)
+    for (int h = 0; h < TH; ++h)
 #pragma unroll
-        for (int q = 0; q < V; ++q) acc[t][q] = 0.f;
+        for (int t = 0; t < TW; ++t)
 #pragma unroll
-    for (int r = 0; r < K; ++r) {
-        float wf[K][V];
+            for (int e = 0; e < V; ++e) acc[h][t][e] = 0.f;
 #pragma unroll
-        for (int q3 = 0; q3 < K; ++q3) Unpack<T, V>::run(wraw[r * K + q3], wf[q3]);
+    for (int r = 0; r < NR; ++r) {              // an input row is the window row r - h * S of output row h
         float in[NC][V];
 #pragma unroll
         for (int j = 0; j < NC; ++j) Unpack<T, V>::run(raw[r][j], in[j]);
 #pragma unroll
-        for (int q3 = 0; q3 < K; ++q3)
+        for (int h = 0; h < TH; ++h) {
+            const int wrow = r - h * S;
+            if (wrow < 0 || wrow >= K) continue;
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                float wf[V];
+                Unpack<T, V>::run(wraw[wrow][q], wf);
+#pragma unroll
+                for (int t = 0; t < TW; ++t)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) acc[h][t][e] = __fmaf_rn(in[t * S + q][e], wf[e], acc[h][t][e]);
+            }
+        }
+    }
+    if (a.bias) {
+#pragma unroll
+        for (int h = 0; h < TH; ++h)
 #pragma unroll
             for (int t = 0; t < TW; ++t)
 #pragma unroll
-                for (int q = 0; q < V; ++q) acc[t][q] = __fmaf_rn(in[t * S + q3][q], wf[q3][q], acc[t][q]);
+                for (int e = 0; e < V; ++e) acc[h][t][e] = __fadd_rn(acc[h][t][e], bias[e]);
     }
-    float bias[V];
+    const unsigned orow = a.pixel * (unsigned)a.Wo, o = (n * (unsigned)a.Ho + (unsigned)oh0) * orow + (unsigned)ow0 * a.pixel + c * ESZ;
+    if (a.res) {
 #pragma unroll
-    for (int q = 0; q < V; ++q) bias[q] = a.bias ? a.bias[c + q] : 0.f;
+        for (int h = 0; h < TH; ++h)
 #pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        const int ow = ow0 + t;
-        if (ow >= a.Wo) break;
-        const int64_t o = (((int64_t)n * a.Ho + oh) * a.Wo + ow) * a.C + c;
-        float rf[V];
-        if (a.res) Unpack<T, V>::run(*(const R *)((const T *)a.res + o), rf);
-        float out[V];
+            for (int t = 0; t < TW; ++t) {
+                if (oh0 + h >= a.Ho || ow0 + t >= a.Wo) continue;
+                float rf[V];
+                Unpack<T, V>::run(*(const R *)((const char *)a.res + (o + (unsigned)h * orow + (unsigned)t * a.pixel)), rf);
 #pragma unroll
-        for (int q = 0; q < V; ++q) {
-            float v = acc[t][q];
-            if (a.bias) v = __fadd_rn(v, bias[q]);
-            if (a.res) v = __fadd_rn(v, rf[q]);
-            out[q] = v;
-        }
-        activate_n<V>(out, a.act);
-        *(R *)((T *)a.y + o) = Unpack<T, V>::pack(out);
+                for (int e = 0; e < V; ++e) acc[h][t][e] = __fadd_rn(acc[h][t][e], rf[e]);
+            }
     }
+    activate_n<TH * TW * V>(&acc[0][0][0], a.act);
+#pragma unroll
+    for (int h = 0; h < TH; ++h)
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+            if (own < a.total && oh0 + h < a.Ho && ow0 + t < a.Wo)
+                *(R *)((char *)a.y + (o + (unsigned)h * orow + (unsigned)t * a.pixel)) = Unpack<T, V>::pack(acc[h][t]);
 }
 
 // ---- depthwise K x K with K known at compile time, one output vector per thread (5 x 5 where the tiled kernel does not apply:
-// few outputs, ragged channel ranges, strides above 2): the loops are unrolled and branch-free, so the taps and their
+// ragged channel ranges, strides above 2): the loops are unrolled and branch-free, so the taps and their
 // weights are requested together instead of one load per trip of a loop; a tap outside the image reads as zero and is
 // multiplied like the others, which leaves the FMA chain of dwconv_kernel (row-major from zero) bit for bit.
 template <typename T, int V, int K>
@@ -596,38 +627,73 @@ static LaunchInfo info(int64_t wgs, const char *kernel)
         return info(g, NAME);                                                                                   \
     }
 
-template <typename T, int V, int S, int K>
+template <typename T, int V, int S, int K, int TH, int TW>
 static LaunchInfo go_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
 {
-    constexpr int TW = DW_TW<T, S, K>::value;
-    const int64_t tiles = (int64_t)(a.n_hi - a.n_lo) * a.Ho * ((a.Wo + TW - 1) / TW);
-    const int64_t g = (tiles * ((a.c_hi - a.c_lo) / V) + TPB - 1) / TPB;
-    if (!dry && g) GACER_LAUNCH((dwconv_tile_kernel<T, V, S, K>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, V, TW));
-    return info(g, K == 3 ? "dwconv3x3" : "dwconv5x5_tiled");
+    constexpr int ESZ = (int)sizeof(T);
+    DwArgs b;
+    b.CV = (a.c_hi - a.c_lo) / V;
+    b.WT = (a.Wo + TW - 1) / TW;
+    b.HT = (a.Ho + TH - 1) / TH;
+    const int64_t threads = (int64_t)(a.n_hi - a.n_lo) * b.HT * b.WT * b.CV, g = (threads + TPB - 1) / TPB;
+    const char *name = K == 3 ? "dwconv3x3" : "dwconv5x5_tiled";
+    if (dry || !g) return info(g, name);
+    const int64_t before = (int64_t)a.pad * (a.W + 1) * a.C * ESZ;
+    b.x = (const char *)a.x - before;
+    b.x_bytes = (unsigned)((int64_t)a.N * a.H * a.W * a.C * ESZ + before);
+    b.w = a.w; b.res = a.res; b.bias = a.bias; b.y = a.y;
+    b.w_bytes = (unsigned)(K * K * a.C * ESZ);
+    b.pixel = (unsigned)(a.C * ESZ);
+    b.row = (unsigned)(a.W * a.C * ESZ);
+    b.run = (int)(g / 8);
+    b.extra = (int)(g % 8);
+    b.total = (int)threads;
+    divisor(b.CV, b.div_cv);
+    divisor(b.WT, b.div_w);
+    divisor(b.HT, b.div_h);
+    b.c_lo = a.c_lo; b.n_lo = a.n_lo;
+    b.H = a.H; b.W = a.W; b.Ho = a.Ho; b.Wo = a.Wo; b.pad = a.pad; b.act = a.act;
+    GACER_LAUNCH((dwconv_tile_kernel<T, V, S, K, TH, TW>), dim3((unsigned)g), dim3(TPB), 0, s, b);
+    return info(g, name);
+}
+
+// Outputs per thread, by the workgroups that single vectors of four channels would make (`wgs`).  Few: one output per thread (bf16:
+// of two channels), because one thread's chain of instructions is what the launch takes; many: a tile, which shares window loads
+// and conversions.  fp32 tiles stop where they no longer fit the registers.  One launch, us, of 1x1 / 2x1 / 2x2 / 2x4 outputs (bf16
+// 1x1: two channels): bf16 3x3 14x14x384 1 image (74) 2.62 / 3.05 / 3.36 / 3.95, 56x56x144 1 image (441) 3.40 / 3.16 / 3.48 / 4.06,
+// 8 images (3528) 10.6 / 7.86 / 6.67 / 5.86; stride 2 56x56x144 8 images (882) 4.20 / 4.02 / 3.94 / 6.49, 28x28x192 32 images
+// (1176) 5.00 / 4.77 / 4.92 / 6.71; 5x5 28x28x120 1 image (92) 3.21 / 4.31 / 5.01 / 6.23, 8 images (735) 6.76 / 6.10 / 5.26 /
+// 6.41, 7x7x960 32 images (1470) 11.2 / 9.61 / 7.34 / 6.73; fp32 3x3 56x56x144 8 images 11.4 / 8.34 / 7.36 / 10.1, stride 2 4.80 /
+// 4.15 / 5.54 / 14.8, 5x5 28x28x120 32 images 20.6 / 13.4 / 11.4 / 17.2.
+template <typename T, int S, int K>
+static LaunchInfo pick_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
+{
+    constexpr bool BF16 = sizeof(T) == 2;
+    const int64_t wgs = ((int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * ((a.c_hi - a.c_lo) / 4) + TPB - 1) / TPB;
+    constexpr int one = BF16 ? (K == 3 && S == 2 ? 512 : 320) : K == 3 ? 256 : 128, two = S == 1 || K == 5 ? 512 : 1500, four = K == 3 ? 2500 : 1024;
+    if (wgs <= one) return go_dwconv_tile<T, BF16 ? 2 : 4, S, K, 1, 1>(a, s, dry);
+    if (wgs <= two || (!BF16 && S == 2)) return go_dwconv_tile<T, 4, S, K, 2, 1>(a, s, dry);
+    if constexpr (BF16 || S == 1) {
+        if constexpr (BF16 && (S == 1 || K == 5))
+            if (wgs > four) return go_dwconv_tile<T, 4, S, K, 2, 4>(a, s, dry);
+        return go_dwconv_tile<T, 4, S, K, 2, 2>(a, s, dry);
+    }
 }
 
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry)
 {
     const int64_t outs = (int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * (a.c_hi - a.c_lo);
-    // bf16 5x5 of few outputs: one output per thread, so that the launch fills the chip; the tiled kernel has a sixteenth of the threads
-    // and each goes through 25 to 40 window loads and 25 weights.  Us tiled / here: 1 image 28x28 60 channels 6.0 / 4.1, 1 image
-    // 14x14 -> 7x7 672 channels 5.8 / 4.2, 16 images 16x16 60 channels (960 workgroups here) 6.1 / 5.1, 8 images 56x56 -> 28x28 36
-    // channels (882) 5.2 / 5.1, 8 images 28x28 60 channels (1470) 6.1 / 6.7.
-    if (a.k == 5 && a.dtype == DT_BF16 && outs <= 1024 * TPB) {
-        const int64_t g = (outs + TPB - 1) / TPB;
-        if (!dry && g) GACER_LAUNCH((dwconv5_kernel<unsigned short, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1, 1));
-        return info(g, "dwconv5x5");
-    }
-    if ((a.k == 3 || a.k == 5) && (a.stride == 1 || a.stride == 2)) {
-        // bfloat16: 8-byte vectors (4 channels per lane) keep the window in registers without spilling
-        if (a.dtype == DT_BF16 && a.C % 4 == 0 && a.c_lo % 4 == 0 && (a.c_hi - a.c_lo) % 4 == 0 && vec_ok<unsigned short, 1>(a)) {
-            if (a.k == 3) return a.stride == 1 ? go_dwconv_tile<unsigned short, 4, 1, 3>(a, s, dry) : go_dwconv_tile<unsigned short, 4, 2, 3>(a, s, dry);
-            return a.stride == 1 ? go_dwconv_tile<unsigned short, 4, 1, 5>(a, s, dry) : go_dwconv_tile<unsigned short, 4, 2, 5>(a, s, dry);
+    // vectors of four channels; the pixels before the tensor that the kernel's offsets start from must not take them beyond 32 bits
+    const bool vec = a.C % 4 == 0 && a.c_lo % 4 == 0 && (a.c_hi - a.c_lo) % 4 == 0 && aligned16(a.x) && aligned16(a.y) && aligned16(a.res) && aligned16(a.w) &&
+                     aligned16(a.bias) && (int64_t)a.pad * (a.W + 1) * a.C < (1 << 28);
+    if (vec && (a.k == 3 || a.k == 5) && (a.stride == 1 || a.stride == 2)) {
+        const bool one = a.stride == 1;
+        if (a.dtype == DT_BF16) {
+            if (a.k == 3) return one ? pick_dwconv_tile<unsigned short, 1, 3>(a, s, dry) : pick_dwconv_tile<unsigned short, 2, 3>(a, s, dry);
+            return one ? pick_dwconv_tile<unsigned short, 1, 5>(a, s, dry) : pick_dwconv_tile<unsigned short, 2, 5>(a, s, dry);
         }
-        if (a.dtype == DT_F32 && vec_ok<float, 4>(a)) {
-            if (a.k == 3) return a.stride == 1 ? go_dwconv_tile<float, 4, 1, 3>(a, s, dry) : go_dwconv_tile<float, 4, 2, 3>(a, s, dry);
-            return a.stride == 1 ? go_dwconv_tile<float, 4, 1, 5>(a, s, dry) : go_dwconv_tile<float, 4, 2, 5>(a, s, dry);
-        }
+        if (a.k == 3) return one ? pick_dwconv_tile<float, 1, 3>(a, s, dry) : pick_dwconv_tile<float, 2, 3>(a, s, dry);
+        return one ? pick_dwconv_tile<float, 1, 5>(a, s, dry) : pick_dwconv_tile<float, 2, 5>(a, s, dry);
     }
     if (a.k == 5) { GACER_DISPATCH_VEC(dwconv5_kernel, "dwconv5x5") }
     GACER_DISPATCH_VEC(dwconv_kernel, "dwconv")

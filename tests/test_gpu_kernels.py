@@ -268,6 +268,28 @@ def test_input_staged_once_for_nine_taps():
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_depthwise_output_tiles(dtype):
+    """Every output tile of the depthwise kernel (from one output per thread to 2 x 4, chosen by the number of outputs), 3x3 and 5x5,
+    strides 1 and 2: rows and columns that end inside a tile, images one pixel wide, padding wider than the kernel reaches, a
+    residual.  Chunks run on other tiles than the whole, chunks of channels that are no multiple of four on the generic kernels."""
+    from synth import graphs as G
+    specs = [  # batch, h, w, c, k, stride, pad, act, residual
+        (2, 13, 11, 36, 3, 1, 1, "relu6", True), (1, 9, 1, 8, 3, 2, 1, "none", False), (2, 7, 5, 12, 3, 1, 4, "relu", False), (2, 8, 9, 20, 5, 2, 5, "gelu", False),
+        (3, 47, 47, 64, 3, 1, 1, "none", True), (7, 45, 47, 64, 3, 1, 1, "hswish", True), (5, 95, 99, 64, 3, 1, 0, "relu6", False), (9, 45, 47, 68, 3, 1, 1, "relu", True),
+        (6, 47, 45, 64, 3, 2, 1, "relu", False), (15, 47, 47, 64, 3, 2, 1, "none", False), (45, 47, 45, 64, 3, 2, 1, "relu6", False),
+        (3, 47, 47, 64, 5, 1, 2, "relu", True), (7, 45, 47, 64, 5, 1, 2, "none", True), (11, 45, 47, 64, 5, 1, 2, "relu6", True),
+        (9, 47, 45, 64, 5, 2, 2, "none", False), (15, 47, 47, 64, 5, 2, 2, "relu", False), (31, 47, 45, 64, 5, 2, 2, "hswish", False),
+    ]
+    tenants = []
+    for i, (batch, h, w, c, k, stride, pad, act, res) in enumerate(specs):
+        b = G._B(f"dwt{i}", dtype, batch)
+        x = b.tensor(batch, c, h, w)
+        tenants.append(b.done(x, b.conv(x, c, k, stride, pad, act, groups=c, res=x if res else -1)))
+    ran = check(tenants, [], [("batch", 2), ("cout", 2)])
+    assert ran == {"dwconv3x3", "dwconv5x5_tiled"}, sorted(ran)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_5x5(dtype):
     """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; few outputs
     (bf16), ragged channel ranges and stride 3 on the one-vector kernel.  Chunks of what is tiled as a whole run on either."""
