@@ -36,7 +36,7 @@ TRAFFIC = {
         "launches_per_round": 16, "algorithmic_bytes": 10.62e6,
         "sources_sha256": "725166bda9138105229d7d1f25ee13b3b905c12dde4e4a3f2d15a37ff79c3ad3"},
 }
-TRAFFIC_SOURCES = ["igemm.hip", "slices.hip", "stream_ops.hip", "device_util.h", "kernels.h"]
+TRAFFIC_SOURCES = ["igemm.hip", "slices.hip", "rows.hip", "stream_ops.hip", "device_util.h", "kernels.h"]
 
 
 def sources_digest():

@@ -705,167 +705,6 @@ void igemm_dma_kernel(GemmArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Row-streaming variant for pointwise (1x1, unpadded) convolutions and plain GEMMs with a short K: these
-// are bound by HBM traffic, not by the matrix cores.  A wavefront owns 32 complete output rows: it reads
-// its A fragments straight from global memory in MFMA operand layout (no LDS round trip, no workgroup
-// barrier in the loop), takes the B fragments of all 32*TN output channels from an LDS copy made once per
-// workgroup, and turns the accumulators through a private LDS patch so that residual loads and output
-// stores are contiguous 16-byte vectors along the channel axis, written back to back by the same wave.
-// Every accumulator is the same MFMA chain over ascending 32-byte k groups as in igemm_kernel, so both
-// kernels produce the same bits.
-template <int DT, int TN, int G>
-__global__ __launch_bounds__(THREADS) void rowgemm_kernel(GemmArgs a)
-{
-    typedef typename El<DT>::T T;
-    constexpr int VEC = El<DT>::VEC;
-    constexpr int ESZ = (int)sizeof(T);
-    constexpr int EV = DT == DT_BF16 ? 8 : 4;
-    constexpr int HALF = 64;                          // staged columns per pass
-    constexpr int SROW = HALF + 4;                    // floats per staged row
-    extern __shared__ __align__(16) unsigned char dyn_smem[];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    const int kg = (a.K * ESZ + 31) / 32;             // 32-byte k groups
-    const int kg4 = (kg + 3) & ~3;                // LDS rows hold whole groups of four
-    const int kgr = (kg + G - 1) / G * G;          // groups walked: G at a time (G = 1 for very short K)
-    const int rowb = kg4 * 32 + 16;                   // LDS bytes per B row
-    unsigned char *Bs = dyn_smem;
-    float *stage = (float *)(dyn_smem + 32 * TN * rowb) + wave * (32 * SROW);
-
-    const int n0 = a.n_lo + (int)blockIdx.y * (32 * TN);
-    const int m0 = a.m_lo + (int)blockIdx.x * 128 + wave * 32;
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
-    const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.w_bytes);
-
-    // B rows of this channel group -> LDS (zero beyond K and beyond the launched channel range)
-    for (int r = tid >> 3; r < 32 * TN; r += THREADS / 8)
-        for (int v = tid & 7; v < kg4 * 2; v += 8) {
-            const int n = n0 + r, k = v * VEC;
-            const bool ok = n < a.n_hi && k < a.K;
-            *(uint4 *)(Bs + r * rowb + v * 16) = buf_load16(wr, ok ? (unsigned)(((int64_t)n * a.w_row + k) * ESZ) : OOB);
-        }
-    // this lane's A row
-    unsigned a_off;
-    {
-        const int m = m0 + lrow;
-        const bool ok = m < a.m_hi;
-        const int mm = ok ? m : a.m_lo;
-        int64_t e0;
-        if (a.stride == 1 && a.x_img == (int64_t)a.Ho * a.Wo * a.x_pix) {      // dense rows: no index arithmetic
-            e0 = (int64_t)mm * a.x_pix;
-        } else {
-            const int HoWo = a.Ho * a.Wo;
-            const int img = div_by(mm, a.div_howo), rem = mm - img * HoWo;
-            const int oh = div_by(rem, a.div_wo), ow = rem - oh * a.Wo;
-            e0 = (int64_t)img * a.x_img + ((int64_t)oh * a.stride * a.W + ow * a.stride) * a.x_pix;
-        }
-        a_off = ok ? (unsigned)(e0 * ESZ) : OOB;
-    }
-    const unsigned k_bytes = (unsigned)(a.K * ESZ);
-    auto load4 = [&](uint4 *f, int g0) {
-#pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const unsigned kb = (unsigned)((g0 + q) * 32 + lhalf * 16);
-            f[q] = buf_load16(xr, (a_off != OOB && kb < k_bytes) ? a_off + kb : OOB);
-        }
-    };
-
-    f32x16 acc[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
-
-    auto compute4 = [&](const uint4 *f, int g0) {
-#pragma unroll
-        for (int q = 0; q < G; ++q) {
-            uint4 fb[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[j] = *(const uint4 *)(Bs + (j * 32 + lrow) * rowb + (g0 + q) * 32 + lhalf * 16);
-            if constexpr (DT == DT_BF16) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[q]), __builtin_bit_cast(bf16x8, fb[j]),
-                                                                     acc[j], 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const float av = __uint_as_float(e == 0 ? f[q].x : e == 1 ? f[q].y : e == 2 ? f[q].z : f[q].w);
-                        const float bv = __uint_as_float(e == 0 ? fb[j].x : e == 1 ? fb[j].y : e == 2 ? fb[j].z : fb[j].w);
-                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[j], 0, 0, 0);
-                    }
-            }
-        }
-    };
-
-    uint4 fa[2][G];
-    load4(fa[0], 0);
-    __syncthreads();
-    int g0 = 0;
-    for (; g0 + G < kgr; g0 += 2 * G) {
-        load4(fa[1], g0 + G);
-        compute4(fa[0], g0);
-        load4(fa[0], g0 + 2 * G);
-        compute4(fa[1], g0 + G);
-    }
-    if (g0 < kgr) compute4(fa[0], g0);
-
-    // ---- epilogue: 64 channels at a time through the wave's LDS patch ----
-    constexpr int CPR = HALF / EV;                    // 16-byte chunks per staged row
-    constexpr int RPI = 64 / CPR;                     // rows per pass of the wave
-    T *yg = (T *)a.y;
-    const T *rg = (const T *)a.res;
-    const bool vec_out = a.y_row % EV == 0 && a.n_lo % EV == 0 && (((uintptr_t)a.y) & 15) == 0 && (((uintptr_t)a.res) & 15) == 0 &&
-                         (((uintptr_t)a.bias) & 15) == 0;
-#pragma unroll
-    for (int hf = 0; hf < (TN + 1) / 2; ++hf) {
-        constexpr int ITER = 32 / RPI;
-        const int width = (hf * 2 + 1 < TN) ? HALF : 32;
-        const int col = (lane % CPR) * EV, n = n0 + hf * HALF + col;
-        const bool n_ok = col < width && n < a.n_hi;
-        const bool n_vec = n_ok && vec_out && n + EV <= a.n_hi;
-        // bias and residual loads before the LDS turn (see igemm_kernel)
-        float bv[EV];
-        load_bias_vec<EV>(a.bias, n, n_vec, bv);
-        uint4 rv[ITER];
-#pragma unroll
-        for (int it = 0; it < ITER; ++it) {
-            const int m = m0 + it * RPI + lane / CPR;
-            rv[it] = make_uint4(0u, 0u, 0u, 0u);
-            if (rg && n_vec && m < a.m_hi) rv[it] = *(const uint4 *)(rg + (int64_t)m * a.y_row + n);
-        }
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int j = hf * 2 + jj;
-            if (j < TN) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) stage[((e >> 2) * 8 + lhalf * 4 + (e & 3)) * SROW + jj * 32 + lrow] = acc[j < TN ? j : 0][e];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int it = 0; it < ITER; ++it) {
-            const int row = it * RPI + lane / CPR;
-            const int m = m0 + row;
-            float v[EV];
-#pragma unroll
-            for (int q = 0; q < EV; q += 4) {
-                const float4 t4 = *(const float4 *)(stage + row * SROW + col + q);
-                v[q] = t4.x; v[q + 1] = t4.y; v[q + 2] = t4.z; v[q + 3] = t4.w;
-            }
-            if (!n_ok || m >= a.m_hi) continue;
-            const int64_t o = (int64_t)m * a.y_row + n;
-            if (n_vec) finish_vec<DT>(a, v, bv, rg != nullptr, rv[it], yg, o);
-            else finish_scalar<DT>(a, v, rg, yg, o, n);
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
 // Second pass of a split-K operator: out = act(alpha * (s0 + s1 + ... ) + bias + res), slices added in
 // ascending order.  One thread per FV consecutive output channels of the launched sub-range (FV = 4 when
 // the range and the pointers allow 16-byte accesses), coalesced along n.
@@ -1052,71 +891,6 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
     return li;
 }
 
-// rowgemm_kernel is taken when the operator is a single-tap, unpadded, unsplit bf16 product whose rows are at most
-// 192 bytes of K (measured: beyond that, and for fp32 at any K, the tiled kernel is as fast or faster): properties
-// of the operator, not of the launched sub-range, so every chunk of an operator takes the same path as its
-// unsplit launch.
-static bool rows_eligible(const GemmArgs &a, int esz, bool vec_ok)
-{
-    return vec_ok && !a.b_trans && a.ksplit == 1 && a.kh == 1 && a.kw == 1 && a.pad == 0 && a.zb * a.zh == 1 && a.z_lo == 0 &&
-           esz == 2 && (int64_t)a.K * esz <= 192;
-}
-static int rows_lds(int tn, int K, int esz)
-{
-    const int kg4 = (((K * esz + 31) / 32) + 3) & ~3;
-    return 32 * tn * (kg4 * 32 + 16) + 4 * 32 * 68 * 4;
-}
-
-template <int DT, int TN, int G>
-static LaunchInfo go_rows_g(const GemmArgs &a, hipStream_t s, const LaunchInfo &li, int groups)
-{
-    GemmArgs b = a;
-    set_divisors(b);
-    GACER_LAUNCH((rowgemm_kernel<DT, TN, G>), dim3((a.m_hi - a.m_lo + 127) / 128, groups), dim3(THREADS), li.lds_bytes, s, b);
-    return li;
-}
-
-template <int DT, int TN>
-static LaunchInfo go_rows(const GemmArgs &a, hipStream_t s, bool dry, int groups)
-{
-    LaunchInfo li;
-    const int M = a.m_hi - a.m_lo;
-    li.workgroups = ((M + 127) / 128) * groups;
-    li.threads = THREADS;
-    li.lds_bytes = rows_lds(TN, a.K, (int)sizeof(typename El<DT>::T));
-    const int by_lds = (160 * 1024) / li.lds_bytes;
-    li.wg_per_cu = by_lds < 8 ? by_lds : 8;
-    static const std::string name = std::string("rowgemm_") + (DT == DT_BF16 ? "bf16" : "f32") + "_x" + std::to_string(32 * TN);
-    li.kernel = name.c_str();
-    li.phases = 1;
-    if (dry || li.workgroups == 0) return li;
-    const int kg = (a.K * (int)sizeof(typename El<DT>::T) + 31) / 32;
-    return kg < 4 ? go_rows_g<DT, TN, 1>(a, s, li, groups) : go_rows_g<DT, TN, 4>(a, s, li, groups);
-}
-
-template <int DT>
-static LaunchInfo pick_rows(const GemmArgs &a, hipStream_t s, bool dry)
-{
-    const int esz = (int)sizeof(typename El<DT>::T);
-    const int N = a.n_hi - a.n_lo, t32 = (N + 31) / 32;
-    int tn_max = 6;
-    while (tn_max > 1 && rows_lds(tn_max, a.K, esz) > 64 * 1024) --tn_max;
-    int groups = (t32 + tn_max - 1) / tn_max;
-    // few rows: spread the channels over more workgroups until every compute unit has one (A is then re-read from L2)
-    const int wgs_m = (a.m_hi - a.m_lo + 127) / 128;
-    while (groups < t32 && wgs_m * groups < 256) ++groups;
-    const int tn = (t32 + groups - 1) / groups;
-    groups = (t32 + tn - 1) / tn;
-    switch (tn) {
-    case 1: return go_rows<DT, 1>(a, s, dry, groups);
-    case 2: return go_rows<DT, 2>(a, s, dry, groups);
-    case 3: return go_rows<DT, 3>(a, s, dry, groups);
-    case 4: return go_rows<DT, 4>(a, s, dry, groups);
-    case 5: return go_rows<DT, 5>(a, s, dry, groups);
-    default: return go_rows<DT, 6>(a, s, dry, groups);
-    }
-}
-
 template <int DT>
 static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
@@ -1124,9 +898,6 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     const bool vec_ok = (a.Cin % VEC == 0) && (a.x_pix % VEC == 0) && (a.x_img % VEC == 0) && (a.w_row % VEC == 0) &&
                         (a.x_zb % VEC == 0) && (a.x_zh % VEC == 0) && (a.w_zb % VEC == 0) && (a.w_zh % VEC == 0) &&
                         (((uintptr_t)a.x) % 16 == 0) && (((uintptr_t)a.w) % 16 == 0);
-    if constexpr (DT == DT_BF16) {
-        if (!a.pre_scale && rows_eligible(a, (int)sizeof(typename El<DT>::T), vec_ok)) return pick_rows<DT>(a, s, dry || phase == 2);
-    }
     const int M = a.m_hi - a.m_lo, N = a.n_hi - a.n_lo;
     const int64_t z = (int64_t)a.zb * a.zh * (a.b_trans ? 1 : a.ksplit);
     // Tile choice is free (it never changes the bits): narrowest N padding first, then the cheapest shape.
@@ -1185,6 +956,7 @@ LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     if (a.stem) return launch_stem(a, s, dry);
     if (a.halo) return launch_conv3(a, s, dry);
     if (a.kwaves) return launch_slices(a, s, dry, phase);
+    if (rows_takes(a)) return launch_rows(a, s, dry || phase == 2);
     return a.dtype == DT_BF16 ? pick<DT_BF16>(a, s, dry, phase) : pick<DT_F32>(a, s, dry, phase);
 }
 

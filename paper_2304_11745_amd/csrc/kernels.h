@@ -106,6 +106,8 @@ LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase = 
 LaunchInfo launch_stem(const GemmArgs &a, hipStream_t s, bool dry);        // launch_igemm hands over operators marked `stem`
 LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry);       // and operators marked `halo`
 LaunchInfo launch_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase);   // and operators with `kwaves`
+bool rows_takes(const GemmArgs &a);                                         // short K: launch_rows instead of the tiled kernels
+LaunchInfo launch_rows(const GemmArgs &a, hipStream_t s, bool dry);
 void launch_finish(const GemmArgs &a, hipStream_t s);                      // the finishing pass of a split-K operator
 int tile_order(const GemmArgs &a, int tiles_m, int tiles_n, int esz);      // GemmArgs::n_major of a launch
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry);

@@ -268,6 +268,37 @@ def test_input_staged_once_for_nine_taps():
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_with_short_k(dtype):
+    """rowgemm_kernel: every number of 32-byte k groups, K that fills half a group, one column of tiles, two and more, four side by
+    side (bf16, more than 6000 tiles), rows and channels that end inside a tile, strided rows, a residual, an output that is a channel
+    window; chunks of channels that start inside a vector."""
+    from synth import graphs as G
+    v = 8 if dtype == "bf16" else 4                  # elements of a vector
+    specs = [  # batch, h, w, cin, cout, stride, act, residual
+        (1, 401, 97, v, 33, 1, "relu", False), (3, 113, 131, 2 * v, 2 * v, 1, "none", True), (1, 211, 193, 3 * v, 70, 1, "gelu", False), (2, 159, 131, 4 * v, 30, 1, "relu6", False),
+        (1, 223, 191, 6 * v, 101, 1, "none", False), (1, 203, 211, 7 * v, 64, 1, "hswish", False), (3, 207, 215, 9 * v, 40, 2, "relu", False), (2, 131, 127, 12 * v, 12 * v, 1, "relu", True),
+        (2, 181, 183, 5 * v, 42, 1, "none", False), (1, 9, 7, 5 * v, 20, 1, "relu", False), (1, 1, 1, 2 * v, 7, 1, "none", False),
+    ]
+    if dtype == "bf16":
+        specs += [(1, 241, 203, 16, 97, 1, "relu6", False), (2, 157, 131, 64, 160, 1, "none", False), (1, 227, 225, 88, 100, 1, "relu", False), (1, 143, 199, 256, 264, 1, "none", False)]
+    tenants = []
+    for i, (batch, h, w, cin, cout, stride, act, res) in enumerate(specs):
+        b = G._B(f"rows{i}", dtype, batch)
+        x = b.tensor(batch, cin, h, w)
+        if cin == 256:                               # a residual behind four columns side by side
+            x = b.conv(x, 64, 1, 1, 0, "relu")
+            y = b.conv(x, cout, 1, 1, 0, "none")
+            tenants.append(b.done(0, b.conv(x, cout, 1, 1, 0, "relu", res=y)))
+            continue
+        tenants.append(b.done(x, b.conv(x, cout, 1, stride, 0, act, res=x if res else -1)))
+    b = G._B("window", dtype, 2)
+    x, wide = b.tensor(2, 3 * v, 151, 149), b.tensor(2, 96, 151, 149)
+    y = b.conv(x, 32, 1, 1, 0, "relu", out=b.view(wide, 40, 32))
+    tenants.append(b.done(x, y))
+    check(tenants, [f"rowgemm_{dtype}_x32", f"rowgemm_{dtype}_x64"] + (["rowgemm_bf16_x128"] if dtype == "bf16" else []), [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_output_tiles(dtype):
     """Every output tile of the depthwise kernel (from one output per thread to 2 x 4, chosen by the number of outputs), 3x3 and 5x5,
     strides 1 and 2: rows and columns that end inside a tile, images one pixel wide, padding wider than the kernel reaches, a
