@@ -26,87 +26,48 @@ namespace gacer {
 static constexpr int THREADS = 256;
 enum { LOAD_VEC = 0, LOAD_GATHER = 1, LOAD_BT = 2, LOAD_TAPS = 3, LOAD_AFFINE = 4 };
 
-// ---- epilogue shared by the tiled kernels ----
-// MFMA leaves element e of a 32x32 tile at row (e/4)*8 + (lane/32)*4 + e%4, column lane%32.  Each wave
-// turns its tiles through a private LDS patch (`stage`, 32 rows of 36 floats) so that a lane owns EV consecutive
-// output channels of one row: residual loads and output stores are then 16-byte vectors along the contiguous axis.
-template <int DT, int BM, int BN, int WM, int WN>
-__device__ __forceinline__ void igemm_epilogue(const GemmArgs &a, f32x16 (&acc)[BM / WM / 32][BN / WN / 32], float *stage, int m0, int n0,
-                                               int wm, int wn, int lane, int slice, int64_t y_off)
+// Epilogue of the tiles of one wave (first row m_wave, first channel n_wave): store_tiles, or the partial tiles of a K slice into the
+// workspace, turned through the wave's patch of LDS so that they leave as whole rows of 32 floats.
+template <int DT, int TM, int TN>
+__device__ __forceinline__ void igemm_epilogue(const GemmArgs &a, f32x16 (&acc)[TM][TN], unsigned char *patch, int m_wave, int n_wave, int lane,
+                                               int slice, int64_t y_off)
 {
-    typedef typename El<DT>::T T;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    if (a.ksplit == 1) {
+        store_tiles<DT, TM, TN>(a, acc, patch, n_wave, lane, (unsigned)y_off, m_wave + TM * 32 <= a.m_hi, [&](int i, int r, unsigned &pos) {
+            pos = (unsigned)(m_wave + i * 32 + r);
+            return (int)pos < a.m_hi;
+        });
+        return;
+    }
+    constexpr int PROW = 144;
     const int lrow = lane & 31, lhalf = lane >> 5;
-    constexpr int EV = DT == DT_BF16 ? 8 : 4;          // outputs per lane and group
-    constexpr int LPR = 32 / EV;                        // lanes per tile row
-    constexpr int GROUPS = 16 / EV;                     // row groups per lane
-    constexpr int SROW = 36;                            // floats per staged row (16-byte aligned, padded)
-    const bool split = a.ksplit > 1;
     const int Nl = a.n_hi - a.n_lo;
-    float *ws = split ? a.ws + (int64_t)slice * (a.m_hi - a.m_lo) * Nl : nullptr;
-    T *yg = (T *)a.y + y_off;
-    const T *rg = a.res ? (const T *)a.res + y_off : nullptr;
-    const bool vec_out = split ? (Nl % 4 == 0 && (((uintptr_t)a.ws) & 15) == 0)
-                               : (a.y_row % EV == 0 && a.n_lo % EV == 0 && (y_off % EV) == 0 && (((uintptr_t)a.y) & 15) == 0 &&
-                                  (((uintptr_t)a.res) & 15) == 0 && (((uintptr_t)a.bias) & 15) == 0);
-    const int erow = lane / LPR, ecol = (lane % LPR) * EV;
+    float *ws = a.ws + (int64_t)slice * (a.m_hi - a.m_lo) * Nl;
+    const bool vec = Nl % 4 == 0 && ((uintptr_t)a.ws & 15) == 0;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn * (BN / WN) + j * 32 + ecol;
-            const bool n_vec = vec_out && n + EV <= a.n_hi;
-            // bias and residual loads first, then the LDS turn: one global round trip per tile, overlapped with the turn
-            float bv[EV];
-            load_bias_vec<EV>(a.bias, n, !split && n_vec, bv);
-            uint4 rv[GROUPS];
 #pragma unroll
-            for (int g = 0; g < GROUPS; ++g) {
-                const int m = m0 + wm * (BM / WM) + i * 32 + erow + g * (64 / LPR);
-                rv[g] = make_uint4(0u, 0u, 0u, 0u);
-                if (!split && rg && n_vec && m < a.m_hi) rv[g] = *(const uint4 *)(rg + (int64_t)m * a.y_row + n);
-            }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) stage[((e >> 2) * 8 + lhalf * 4 + (e & 3)) * SROW + lrow] = acc[i][j][e];
+            for (int q = 0; q < 4; ++q)
+                *(float4 *)(patch + lrow * PROW + (q * 8 + lhalf * 4) * 4) = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int g = 0; g < GROUPS; ++g) {
-                const int row = erow + g * (64 / LPR);
-                const int m = m0 + wm * (BM / WM) + i * 32 + row;
-                float v[EV];
-#pragma unroll
-                for (int q = 0; q < EV; q += 4) {
-                    const float4 t4 = *(const float4 *)(stage + row * SROW + ecol + q);
-                    v[q] = t4.x; v[q + 1] = t4.y; v[q + 2] = t4.z; v[q + 3] = t4.w;
-                }
+            for (int it = 0; it < 4; ++it) {
+                const int row = it * 8 + (lane >> 3), m = m_wave + i * 32 + row, n = n_wave + j * 32 + (lane & 7) * 4;
+                const float4 v = *(const float4 *)(patch + row * PROW + (lane & 7) * 16);
                 if (m >= a.m_hi || n >= a.n_hi) continue;
-                if (split) {
-                    float *p = ws + (int64_t)(m - a.m_lo) * Nl + (n - a.n_lo);
-                    if (vec_out && n + EV <= a.n_hi) {
-#pragma unroll
-                        for (int q = 0; q < EV; q += 4) *(float4 *)(p + q) = make_float4(v[q], v[q + 1], v[q + 2], v[q + 3]);
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < EV; ++q)
-                            if (n + q < a.n_hi) p[q] = v[q];
-                    }
-                    continue;
+                float *p = ws + (int64_t)(m - a.m_lo) * Nl + (n - a.n_lo);
+                if (vec && n + 4 <= a.n_hi) {
+                    *(float4 *)p = v;
+                } else {
+                    const float e[4] = {v.x, v.y, v.z, v.w};
+                    for (int q = 0; q < 4; ++q)
+                        if (n + q < a.n_hi) p[q] = e[q];
                 }
-                const int64_t o = (int64_t)m * a.y_row + n;
-                if (n_vec) finish_vec<DT>(a, v, bv, rg != nullptr, rv[g], yg, o);
-                else finish_scalar<DT>(a, v, rg, yg, o, n);
             }
             __builtin_amdgcn_wave_barrier();
         }
-}
-
-// One validity bit per tap (bit r * kw + q) of a window whose origin is (ih0, iw0): rows and columns are tested once each.
-__device__ __forceinline__ unsigned tap_mask(int ih0, int iw0, int H, int W, int kh, int kw)
-{
-    unsigned cols = 0, tm = 0;
-    for (int q = 0; q < kw; ++q) cols |= (unsigned)(iw0 + q >= 0 && iw0 + q < W) << q;
-    for (int r = 0; r < kh; ++r) tm |= (ih0 + r >= 0 && ih0 + r < H) ? cols << (r * kw) : 0u;
-    return tm;
 }
 
 template <int DT, int BM, int BN, int WM, int WN, int KV, int LOAD>
@@ -147,6 +108,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
     const int64_t y_off = zb * a.y_zb + zh * a.y_zh;
 
     const int HoWo = a.Ho * a.Wo;
+    const unsigned x_img = (unsigned)a.x_img * ESZ, x_pix = (unsigned)a.x_pix * ESZ;         // bytes; offsets fit 32 bits
     const int vcol = tid % KV;                  // which 16-byte vector of the row this thread moves
     const int vrow = tid / KV;
 
@@ -161,15 +123,16 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
         const int img = div_by(mm, a.div_howo), rem = mm - img * HoWo;
         const int oh = div_by(rem, a.div_wo), ow = rem - oh * a.Wo;
         const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
-        const int64_t e0 = (int64_t)img * a.x_img + ((int64_t)ih0 * a.W + iw0) * a.x_pix;   // may be negative at the border
-        a_off[i] = ok ? (unsigned)(int)(e0 * ESZ) : OOB;
-        unsigned hm = 0, wmk = 0;
-        for (int r = 0; r < a.kh; ++r) hm |= (unsigned)(ih0 + r >= 0 && ih0 + r < a.H) << r;
-        for (int q = 0; q < a.kw; ++q) wmk |= (unsigned)(iw0 + q >= 0 && iw0 + q < a.W) << q;
-        a_hm[i] = ok ? hm : 0u;
-        a_wm[i] = wmk;
-        if constexpr (TAPS)                     // one validity bit per tap (kh*kw <= 31 on this path): bit r*kw + q
-            a_hm[i] = ok ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 0u;
+        const unsigned at = (unsigned)img * x_img + (unsigned)(ih0 * a.W + iw0) * x_pix;      // wraps below zero at the border
+        a_off[i] = ok ? at : OOB;
+        a_hm[i] = ok ? 1u : 0u;
+        a_wm[i] = 0u;
+        if constexpr (TAPS) {                   // one validity bit per tap (kh*kw <= 31 on this path): bit r*kw + q
+            a_hm[i] = ok ? taps_inside(ih0, iw0, a.H, a.W, a.kh, a.kw, a.tap_bits) : 0u;
+        } else if constexpr (LOAD == LOAD_GATHER) {     // one bit per tap row and per tap column
+            a_hm[i] = ok ? bit_run(min(a.H - ih0, a.kh) - max(-ih0, 0), max(-ih0, 0)) : 0u;
+            a_wm[i] = bit_run(min(a.W - iw0, a.kw) - max(-iw0, 0), max(-iw0, 0));
+        }
     }
     // ---- per-thread B rows: byte offset of the weight row, and whether the row exists ----
     unsigned b_off[BV];
@@ -179,7 +142,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
         const int row = vrow + i * RPP;
         const int n = n0 + row;
         b_ok[i] = row < BN && n < a.n_hi;
-        b_off[i] = b_ok[i] ? (unsigned)((int64_t)n * a.w_row * ESZ) : 0u;
+        b_off[i] = b_ok[i] ? (unsigned)n * ((unsigned)a.w_row * ESZ) : 0u;
     }
 
     // K range of this slice, in blocks of BK (kb_per_slice counts 64-byte blocks)
@@ -209,7 +172,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
             for (int k = tid; k < a.K; k += THREADS) {
                 const int tap = k / a.Cin, ci = k - tap * a.Cin;
                 const int r = tap / a.kw, q = tap - r * a.kw;
-                ktab_delta[k] = (int)((((int64_t)r * a.W + q) * a.x_pix + ci) * ESZ);
+                ktab_delta[k] = (int)((unsigned)(r * a.W + q) * x_pix + (unsigned)(ci * ESZ));
                 ktab_rq[k] = (r << 8) | q;
             }
             __syncthreads();
@@ -244,7 +207,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
                     const int tap = k / a.Cin, ci = k - tap * a.Cin;
                     r = (tap / a.kw) & 31;
                     q = (tap - (tap / a.kw) * a.kw) & 31;
-                    delta = (unsigned)((((int64_t)r * a.W + q) * a.x_pix + ci) * ESZ);
+                    delta = (unsigned)(r * a.W + q) * x_pix + (unsigned)(ci * ESZ);
                 }
 #pragma unroll
                 for (int i = 0; i < AV; ++i) {
@@ -261,7 +224,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
         } else {
             const bool k_ok = kv < k_end;
             if constexpr (TAPS) {
-                const unsigned delta = (unsigned)((((int64_t)kr * a.W + ksx) * a.x_pix + kci) * ESZ);
+                const unsigned delta = (unsigned)(kr * a.W + ksx) * x_pix + (unsigned)(kci * ESZ);
                 const unsigned tp = k_ok ? (unsigned)(kr * a.kw + ksx) : 31u;      // bit 31 is never set
 #pragma unroll
                 for (int i = 0; i < AV; ++i) pa[i] = buf_load16(xr, ((a_hm[i] >> tp) & 1u) ? a_off[i] + delta : OOB);
@@ -283,7 +246,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
                     const int kk = idx / NV, nv = idx - kk * NV;
                     const int k = kb0 + kk, n = n0 + nv * VEC;
                     const bool ok = idx < BK * NV && k < k_end && n < a.n_hi;
-                    pb[i] = buf_load16(wr, ok ? (unsigned)(((int64_t)k * a.w_row + n) * ESZ) : OOB);
+                    pb[i] = buf_load16(wr, ok ? ((unsigned)k * (unsigned)a.w_row + (unsigned)n) * ESZ : OOB);
                 }
             }
         }
@@ -384,8 +347,8 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]),
-                                                                            __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[j]),
+                                                                            __builtin_bit_cast(bf16x8, fa[i]), acc[i][j], 0, 0, 0);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -395,7 +358,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
                         for (int j = 0; j < TN; ++j) {
                             const float av = __uint_as_float(e == 0 ? fa[i].x : e == 1 ? fa[i].y : e == 2 ? fa[i].z : fa[i].w);
                             const float bv = __uint_as_float(e == 0 ? fb[j].x : e == 1 ? fb[j].y : e == 2 ? fb[j].z : fb[j].w);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av, acc[i][j], 0, 0, 0);
                         }
             }
         }
@@ -423,7 +386,7 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
     if (kb < nkb) compute(0);                   // odd block count: the last block already sits in LDS buffer 0
     __syncthreads();                            // the epilogue reuses the tile buffers
 
-    igemm_epilogue<DT, BM, BN, WM, WN>(a, acc, (float *)smem + wave * (32 * 36), m0, n0, wm, wn, lane, slice, y_off);
+    igemm_epilogue<DT, TM, TN>(a, acc, smem + wave * 4608, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, slice, y_off);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -499,6 +462,7 @@ void igemm_dma_kernel(GemmArgs a)
     const int64_t y_off = zb * a.y_zb + zh * a.y_zh;
 
     const int HoWo = a.Ho * a.Wo;
+    const unsigned x_img = (unsigned)a.x_img * ESZ, x_pix = (unsigned)a.x_pix * ESZ;         // bytes; offsets fit 32 bits
     const int vrow = tid / KV;                                  // tile row of this thread's slot in pass 0
     const int lcol = (tid % KV) ^ ((vrow / R256) % KV);         // logical chunk that belongs into the slot
 
@@ -512,15 +476,15 @@ void igemm_dma_kernel(GemmArgs a)
         const int img = div_by(mm, a.div_howo), rem = mm - img * HoWo;
         const int oh = div_by(rem, a.div_wo), ow = rem - oh * a.Wo;
         const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
-        const int64_t e0 = (int64_t)img * a.x_img + ((int64_t)ih0 * a.W + iw0) * a.x_pix;   // may be negative at the border
-        a_off[i] = ok ? (unsigned)(int)(e0 * ESZ) : OOB;
-        a_bad[i] = TAPS ? ~(ok ? tap_mask(ih0, iw0, a.H, a.W, a.kh, a.kw) : 0u) : 0u;
+        const unsigned at = (unsigned)img * x_img + (unsigned)(ih0 * a.W + iw0) * x_pix;      // wraps below zero at the border
+        a_off[i] = ok ? at : OOB;
+        a_bad[i] = TAPS ? ~(ok ? taps_inside(ih0, iw0, a.H, a.W, a.kh, a.kw, a.tap_bits) : 0u) : 0u;
     }
     unsigned b_off[BV];
 #pragma unroll
     for (int i = 0; i < BV; ++i) {
         const int n = n0 + vrow + i * RPP;
-        b_off[i] = n < a.n_hi ? (unsigned)((int64_t)n * a.w_row * ESZ) : OOB;
+        b_off[i] = n < a.n_hi ? (unsigned)n * ((unsigned)a.w_row * ESZ) : OOB;
     }
 
     // K range of this slice, in blocks of BK (kb_per_slice counts 64-byte blocks)
@@ -552,7 +516,7 @@ void igemm_dma_kernel(GemmArgs a)
         rq_bad = ~(unsigned)((kv - k_end) >> 31) & OOB;
         rq_db = (unsigned)(kv * ESZ);
         if constexpr (TAPS) {
-            rq_da = (unsigned)((((int64_t)kr * a.W + ksx) * a.x_pix + kci) * ESZ);
+            rq_da = (unsigned)(kr * a.W + ksx) * x_pix + (unsigned)(kci * ESZ);
             rq_tap = (unsigned)(kr * a.kw + ksx) & 31u;                         // beyond K rq_bad masks whatever tap this is
         } else {
             rq_da = rq_db;
@@ -627,8 +591,8 @@ void igemm_dma_kernel(GemmArgs a)
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[set][i]),
-                                                                        __builtin_bit_cast(bf16x8, fb[set][j]), acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[set][j]),
+                                                                        __builtin_bit_cast(bf16x8, fa[set][i]), acc[i][j], 0, 0, 0);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -639,7 +603,7 @@ void igemm_dma_kernel(GemmArgs a)
                         const uint4 &va = fa[set][i], &vb = fb[set][j];
                         const float av = __uint_as_float(e == 0 ? va.x : e == 1 ? va.y : e == 2 ? va.z : va.w);
                         const float bv = __uint_as_float(e == 0 ? vb.x : e == 1 ? vb.y : e == 2 ? vb.z : vb.w);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av, acc[i][j], 0, 0, 0);
                     }
         }
     };
@@ -693,15 +657,8 @@ void igemm_dma_kernel(GemmArgs a)
     mfmas(1);                                   // last group of the last block
     meet(1);                                    // trailing requests (all beyond K: zeros) have landed; the epilogue reuses the stages
 
-    float *patch;
-    if constexpr (OWN_PATCH) {
-        patch = (float *)(own_patch + wave * PATCH);
-    } else {
-        const int which = wave % NS;
-        unsigned char *base = stage_at(which);
-        patch = (float *)(base + (wave / NS) * PATCH);
-    }
-    igemm_epilogue<DT, BM, BN, WM, WN>(a, acc, patch, m0, n0, wm, wn, lane, slice, y_off);
+    unsigned char *patch = OWN_PATCH ? own_patch + wave * PATCH : stage_at(wave % NS) + (wave / NS) * PATCH;
+    igemm_epilogue<DT, TM, TN>(a, acc, patch, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, slice, y_off);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -790,6 +747,7 @@ static void set_divisors(GemmArgs &b)
     divisor(b.Wo, b.div_wo);
     divisor(b.Cin, b.div_cin);
     divisor(b.kw, b.div_kw);
+    b.tap_bits = tap_rows(b.kh, b.kw);
 }
 
 // Tile numbering of a launch.  m-major numbering gives every XCD a band of output rows: A is fetched into one L2 only,

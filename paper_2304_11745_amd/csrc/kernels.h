@@ -56,6 +56,7 @@ struct GemmArgs {
     int n_major;               // set by the launcher: tiles are numbered n-major (1) or m-major (0), see tile_order()
     // set by the launcher: multiplier and shift of the division by d (see divisor()); d = Ho*Wo, Wo, Cin, kw
     unsigned div_howo[2], div_wo[2], div_cin[2], div_kw[2];
+    unsigned tap_bits;         // set by the launcher: see tap_rows()
     // set by the launcher of the tiled kernels: tiles along m and n of this launch, divisors for them and for zh
     int tiles_m, tiles_n;
     unsigned div_tiles_m[2], div_tiles_n[2], div_zh[2];

@@ -60,21 +60,6 @@ struct SlicesArgs {
     int pre_act;
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00020000);
-}
-
-// `width` bits from bit `at` on (none for width <= 0, whatever `at`)
-__device__ __forceinline__ unsigned bit_run(int width, int at) { return width > 0 ? ((1u << width) - 1u) << at : 0u; }
-
-// One bit per tap (bit r * kw + q, kh * kw <= 31) of a window whose origin is (ih0, iw0), set where the tap lies in the image
-__device__ __forceinline__ unsigned taps_inside(const SlicesArgs &a, int ih0, int iw0)
-{
-    const int r0 = max(-ih0, 0), r1 = min(a.H - ih0, a.kh), q0 = max(-iw0, 0), q1 = min(a.W - iw0, a.kw);
-    return bit_run(q1 - q0, q0) * (a.tap_rows & bit_run((r1 - r0) * a.kw, r0 * a.kw));
-}
-
 template <int DT, int LOAD, int S, int PRE_MAX = 0>
 __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
 {
@@ -115,7 +100,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
             const int ih0 = oh * a.stride - a.pad, iw0 = ow * a.stride - a.pad;
             a_off[p] = (unsigned)img * a.x_img + (unsigned)(ih0 * a.W + iw0) * a.x_pitch;        // wraps below zero at the border
             if (LOAD != SL_TAPS_ANY) a_off[p] += kb;
-            if constexpr (TAPS) a_bad[p] = ~taps_inside(a, ih0, iw0);
+            if constexpr (TAPS) a_bad[p] = ~taps_inside(ih0, iw0, a.H, a.W, a.kh, a.kw, a.tap_rows);
         }
     }
 
@@ -420,8 +405,7 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
         divisor(b.Wo, b.div_wo);
         divisor(b.Cin, b.div_cin);
         divisor(b.kw, b.div_kw);
-        b.tap_rows = 0;
-        for (int r = 0; r < a.kh && r * a.kw < 31; ++r) b.tap_rows |= 1u << (r * a.kw);
+        b.tap_rows = tap_rows(a.kh, a.kw);
         b.pre_scale = a.pre_scale; b.pre_shift = a.pre_shift; b.pre_y = a.pre_y; b.pre_act = a.pre_act;
         const dim3 grid(tiles_m * tiles_n, a.ksplit), block(64 * S);
         const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);

@@ -299,6 +299,26 @@ def test_rows_with_short_k(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tiles_finished_in_registers(dtype):
+    """The epilogue of the tiled kernels at channel counts that are no multiple of a vector or of four, with and without a residual,
+    one and several tiles per wave; chunks whose channels start inside a vector; attention products of several images."""
+    from synth import graphs as G
+    specs = [  # batch, h, w, cin, cout, k, act, residual
+        (2, 61, 59, 48, 48, 3, "relu", True), (2, 67, 59, 40, 42, 3, "hswish", True), (1, 131, 127, 200, 200, 1, "relu6", True), (3, 75, 71, 136, 133, 1, "none", True),
+        (2, 95, 79, 160, 250, 3, "relu", True), (1, 112, 112, 776, 999, 1, "gelu", False), (2, 113, 111, 136, 27, 1, "relu", True), (1, 150, 149, 104, 130, 1, "relu", False),
+        (1, 130, 129, 104, 122, 1, "relu", True), (2, 113, 111, 24, 58, 3, "relu6", True),
+    ]
+    tenants = []
+    for i, (batch, h, w, cin, cout, k, act, res) in enumerate(specs):
+        b = G._B(f"tiles{i}", dtype, batch)
+        x = b.tensor(batch, cin, h, w)
+        y = b.conv(x, cout, k, 1, k // 2, "none") if res else -1
+        tenants.append(b.done(x, b.conv(x, cout, k, 1, k // 2, act, res=y)))
+    tenants.append(G.small_bert(dtype, 3))
+    check(tenants, [f"igemm_dma_{dtype}", f"igemm_{dtype}_64x64", f"igemm_taps_{dtype}", f"igemm_bt_{dtype}"], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_output_tiles(dtype):
     """Every output tile of the depthwise kernel (from one output per thread to 2 x 4, chosen by the number of outputs), 3x3 and 5x5,
     strides 1 and 2: rows and columns that end inside a tile, images one pixel wide, padding wider than the kernel reaches, a
