@@ -13,7 +13,8 @@
 // 256x128 tile, which is that path's rate; here it is 11 KB.  What is left is the fill of the pipeline and the epilogue of a
 // short K (two workgroups per unit cover for each other) and, at 64 channels, the output.  Microseconds there / here, 32 images:
 // 224x224 64->64 284.6 / 179.0, 112x112 64->128 110.7 / 80.2, 112x112 128->128 156.4 / 122.2, 56x56 256->256 153.8 / 119.3,
-// 28x28 512->512 144.2 / 112.4 (1053 TFLOP/s), 56x56 64->64 22.0 / 16.8.
+// 28x28 512->512 144.2 / 112.4 (1053 TFLOP/s), 56x56 64->64 22.0 / 16.8.  Outputs finished in registers (store_tiles) took, before / after:
+// 16 images 112x112 64->128 49.0 / 44.5, 56x56 64->64 11.1 / 10.4, 224x224 64->64 85.3 / 81.3, 8 images 112x112 128->128 39.2 / 36.9.
 //
 // An output element is one MFMA chain over channel blocks of 32, in a block over the taps in ascending order, whatever the tile;
 // which kernel an operator takes depends on its unsplit shape only, so every chunk of it adds alike.
@@ -28,12 +29,11 @@ namespace gacer {
 
 static constexpr int THREADS = 256;
 static constexpr int ROWB = 64;                // bytes of a channel block: one LDS row
-static constexpr int SROW = 36;                // floats per row of the epilogue's patches, which overlay an input block
+static constexpr int PATCH = 4608;             // bytes of a wave's epilogue patch; the patches overlay an input block
 constexpr int conv3_input_bytes(int bm)        // LDS of an input block: pixels and rows of zeros, at least the patches of four waves
 {
-    return (conv3_rows(bm) + 16) * ROWB > 4 * 32 * SROW * 4 ? (conv3_rows(bm) + 16) * ROWB : 4 * 32 * SROW * 4;
+    return (conv3_rows(bm) + 16) * ROWB > 4 * PATCH ? (conv3_rows(bm) + 16) * ROWB : 4 * PATCH;
 }
-#define GACER_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 
 template <int N> __device__ __forceinline__ void wait_loads()       // at most N loads outstanding, own LDS reads done
 {
@@ -45,7 +45,6 @@ template <int BM, int BN>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 void conv3_kernel(GemmArgs a, Conv3Geom geo)
 {
-    typedef unsigned short T;
     constexpr int WM = BM == 256 && BN == 64 ? 4 : 2, WN = 4 / WM;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int ROWS = conv3_rows(BM);       // input pixels (LDS rows) per tile and channel block
@@ -85,6 +84,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     // Direct loads fill LDS linearly: load p of a thread fills row 64 p + tid / 4, slot tid % 4, which holds logical chunk
     // slot ^ (row / 4) % 4 (fragment reads of 32 rows then meet no bank conflict).
     const int chunk = (tid & 3) ^ ((tid >> 4) & 3);
+    const unsigned x_pix = (unsigned)a.x_pix * 2u;
     // LDS row L is pixel (row0 - 1) * tw2 + col0 + L of the strip, its rows padded by one pixel on either side
     unsigned a_off[NA];
 #pragma unroll
@@ -92,13 +92,13 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
         const int q = row0 * tw2 + col0 + p * 64 + (tid >> 2);                   // counted from row -1
         const int r1 = div_by(q, geo.div_tw2), c = c0 + (q - r1 * tw2) - 1, r = r1 - 1;
         const bool ok = r >= 0 && r < geo.rows && c >= 0 && c < a.W;
-        a_off[p] = ok ? (unsigned)((((int64_t)(geo.row_lo + r) * a.W + c) * a.x_pix + chunk * 8) * 2) : OOB;
+        a_off[p] = ok ? (unsigned)((geo.row_lo + r) * a.W + c) * x_pix + (unsigned)(chunk * 16) : OOB;
     }
     unsigned b_off[BN / 64];
 #pragma unroll
     for (int i = 0; i < BN / 64; ++i) {
         const int n = n0 + i * 64 + (tid >> 2);
-        b_off[i] = n < a.n_hi ? (unsigned)(((int64_t)n * a.w_row + chunk * 8) * 2) : OOB;
+        b_off[i] = n < a.n_hi ? (unsigned)n * ((unsigned)a.w_row * 2u) + (unsigned)(chunk * 16) : OOB;
     }
     const int ncb = a.Cin / 32;                // channel blocks, an even number
     const int wave_slot = wave * 1024;
@@ -145,8 +145,8 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[set][i]),
-                                                                    __builtin_bit_cast(bf16x8, fb[set][j]), acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[set][j]),
+                                                                    __builtin_bit_cast(bf16x8, fa[set][i]), acc[i][j], 0, 0, 0);
     };
     constexpr int SCHED_ALU_MAY_CROSS = 0x2 | 0x4;
 
@@ -217,56 +217,12 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     __builtin_amdgcn_s_barrier();              // the epilogue reuses a0
     asm volatile("" ::: "memory");
 
-    // ---- epilogue: as in igemm_epilogue, with the output position of a tile row computed from the strip ----
-    float *stage = (float *)a0 + wave * (32 * SROW);
-    T *yg = (T *)a.y;
-    const T *rg = (const T *)a.res;
-    const bool vec_out = a.y_row % 8 == 0 && a.n_lo % 8 == 0 && (((uintptr_t)a.y) & 15) == 0 && (((uintptr_t)a.res) & 15) == 0 &&
-                         (((uintptr_t)a.bias) & 15) == 0;
-    const int erow = lane / 4, ecol = (lane % 4) * 8;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        int64_t pos[2];
-        bool ok[2];
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const int p = p0 + wm * (BM / WM) + i * 32 + erow + g * 16;
-            const int r = div_by(p, geo.div_tw), c = c0 + p - r * tw;
-            ok[g] = r < geo.rows && c < a.W;
-            pos[g] = (int64_t)(geo.row_lo + r) * a.W + c;
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn * (BN / WN) + j * 32 + ecol;
-            const bool n_vec = vec_out && n + 8 <= a.n_hi;
-            float bv[8];
-            load_bias_vec<8>(a.bias, n, n_vec, bv);
-            uint4 rv[2];
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                rv[g] = make_uint4(0u, 0u, 0u, 0u);
-                if (rg && n_vec && ok[g]) rv[g] = *(const uint4 *)(rg + pos[g] * a.y_row + n);
-            }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) stage[((e >> 2) * 8 + lhalf * 4 + (e & 3)) * SROW + lrow] = acc[i][j][e];
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const int row = erow + g * 16;
-                float vv[8];
-#pragma unroll
-                for (int q = 0; q < 8; q += 4) {
-                    const float4 t4 = *(const float4 *)(stage + row * SROW + ecol + q);
-                    vv[q] = t4.x; vv[q + 1] = t4.y; vv[q + 2] = t4.z; vv[q + 3] = t4.w;
-                }
-                if (!ok[g] || n >= a.n_hi) continue;
-                const int64_t o = pos[g] * a.y_row + n;
-                if (n_vec) finish_vec<DT_BF16>(a, vv, bv, rg != nullptr, rv[g], yg, o);
-                else finish_scalar<DT_BF16>(a, vv, rg, yg, o, n);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
+    // position of a tile row: counted along the strip, then in the tensor
+    store_tiles<DT_BF16, TM, TN>(a, acc, a0 + wave * PATCH, n0 + wn * (BN / WN), lane, 0u, p0 + BM <= geo.rows * tw && c0 + tw <= a.W, [&](int i, int r, unsigned &pos) {
+        const int p = p0 + wm * (BM / WM) + i * 32 + r, row = div_by(p, geo.div_tw), c = c0 + p - row * tw;
+        pos = (unsigned)((geo.row_lo + row) * a.W + c);
+        return row < geo.rows && c < a.W;
+    });
 }
 
 template <int BM, int BN>
