@@ -239,6 +239,7 @@ LaunchInfo enqueue(const Launch &l, hipStream_t s, bool dry, int phase, float *w
     case LK_GAVGPOOL: return launch_gavgpool(l.s, s, dry);
     case LK_LAYERNORM: return launch_layernorm(l.s, s, dry);
     case LK_SOFTMAX: return launch_softmax(l.s, s, dry);
+    case LK_ABSORBED: return {0, 0, 0, 1, "absorbed", 0};
     default: return launch_eltwise(l.s, s, dry);
     }
 }
@@ -589,6 +590,42 @@ static void fuse_affine_pairs(Ctx *c, std::vector<std::vector<OpExec>> &ex, Deco
     }
 }
 
+// ---- scores, softmax and context of an attention, as one launch --------------------------------------------------------------------
+// Operators i (scores), i + 1 (softmax) and i + 2 (context) of one attention are issued as one launch in the scores' place, which writes
+// all three tensors with the bits of the three kernels; the other two keep an entry in their launch lists that issues nothing.
+// Taken for bf16, 64 features per head and at most 128 keys (12 layers of BERT, two images of 72 tokens: round 477 us with three launches
+// each, 402 with one; four of 200 tokens 947 / 959, were they taken), unless the plan decomposes one of the three or a sync edge begins
+// or ends inside the triple (the work of all three then has to stay where the plan put it).
+static bool attention_triple(const Tenant &T, int i)
+{
+    if (T.dtype != GACER_BF16 || i + 2 >= (int)T.ops.size()) return false;
+    const gacer_op &qk = T.ops[i], &sm = T.ops[i + 1], &pv = T.ops[i + 2];
+    if (qk.kind != GACER_BGEMM_QK || sm.kind != GACER_SOFTMAX || pv.kind != GACER_BGEMM_PV) return false;
+    if (sm.in0 != qk.out || pv.in0 != sm.out || pv.in1 != qk.in0 || sm.res >= 0 || pv.groups != qk.groups || pv.cout != qk.cin || qk.cin != 64) return false;
+    const gacer_tensor &qkv = T.tensors[qk.in0], &sc = T.tensors[qk.out], &pr = T.tensors[sm.out], &ctx = T.tensors[pv.out];
+    if (qkv.h > ATTENTION_KEYS_MAX || qkv.pitch || sc.pitch || pr.pitch || ctx.pitch) return false;
+    for (const gacer_tensor *t : {&qkv, &sc, &pr, &ctx})
+        if (!aligned16p(t->dptr)) return false;
+    return true;
+}
+
+template <typename Whole>
+static void fuse_attention(Ctx *c, std::vector<std::vector<OpExec>> &ex, Whole whole)
+{
+    if (!c->fuse_affine) return;
+    for (size_t t = 0; t < c->tenants.size(); ++t) {
+        const Tenant &T = c->tenants[t];
+        for (int i = 0; i + 2 < (int)T.ops.size(); ++i) {
+            if (!attention_triple(T, i) || !whole((int)t, i)) continue;
+            GemmArgs &g = ex[t][i].chunks[0].g;
+            g.attn_scores = g.y;
+            g.attn_probs = T.tensors[T.ops[i + 1].out].dptr;
+            g.y = T.tensors[T.ops[i + 2].out].dptr;
+            ex[t][i + 1].chunks[0].kind = ex[t][i + 2].chunks[0].kind = LK_ABSORBED;
+        }
+    }
+}
+
 static void expand_plain(Ctx *c)
 {
     c->plain_exec.assign(c->tenants.size(), {});
@@ -602,6 +639,7 @@ static void expand_plain(Ctx *c)
         longest = std::max(longest, T.ops.size());
     }
     fuse_affine_pairs(c, c->plain_exec, [](int, int) { return false; }, [](int, int) { return false; });
+    fuse_attention(c, c->plain_exec, [](int, int) { return true; });
     for (size_t i = 0; i < longest; ++i)
         for (size_t t = 0; t < c->tenants.size(); ++t)
             if (i < c->tenants[t].ops.size()) c->par_order.push_back({(int)t, (int)i});
@@ -726,6 +764,13 @@ static gacer_status install_plan(Ctx *c, const std::vector<gacer_split> &splits,
     fuse_affine_pairs(c, ex,
                       [&](int t, int i) { auto it = smap.find({t, i}); return it != smap.end() && it->second.factor > 1; },
                       [&](int t, int i) { return ex[t][i].record >= 0; });
+    fuse_attention(c, ex, [&](int t, int i) {
+        for (int k = 0; k < 3; ++k) {
+            const OpExec &e = ex[t][i + k];
+            if (e.chunks.size() != 1 || (k < 2 && e.record >= 0) || (k > 0 && (e.pre_record >= 0 || !e.waits.empty()))) return false;
+        }
+        return true;
+    });
     for (Tenant &t : c->tenants) (void)hipStreamSynchronize(t.stream);
     drop_graphs(c);                      // captured rounds belong to the plan they were captured under
     c->splits = splits;
@@ -1420,7 +1465,14 @@ gacer_status gacer_run_static(gacer_ctx *c, int mode, int rounds)
 // Algorithmic work of one launch (sub-range only).
 static void launch_work(const Launch &l, double *flops, double *bytes)
 {
-    *flops = 0;
+    *flops = *bytes = 0;
+    if (l.kind == LK_ABSORBED) return;
+    if (l.kind == LK_IGEMM && l.g.attn_scores) {            // both products; qkv read once, scores, probabilities and context written once
+        const double rows = (double)l.g.zb * l.g.zh * l.g.H;
+        *flops = 4.0 * rows * l.g.H * l.g.K;
+        *bytes = 2.0 * rows * (4.0 * l.g.K + 2.0 * l.g.H);
+        return;
+    }
     if (l.kind == LK_IGEMM) {
         const GemmArgs &g = l.g;
         const double esz = g.dtype == DT_BF16 ? 2.0 : 4.0;

@@ -10,6 +10,8 @@ namespace gacer {
 
 // most channels of a fused affine operator whose parameters slices_kernel keeps in LDS (with eight waves they fill it)
 enum { SLICES_PRE_MAX = 4096 };
+// most keys of an attention that runs as one launch
+enum { ATTENTION_KEYS_MAX = 128 };
 enum { DT_F32 = 0, DT_BF16 = 1 };
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3, ACT_HSWISH = 4, ACT_HSIGMOID = 5 };
 
@@ -69,6 +71,9 @@ struct GemmArgs {
     const float *pre_scale, *pre_shift;
     void *pre_y;
     int pre_act;
+    // A whole attention as one launch (attn_scores != null; bf16, K = 64 features per head, at most ATTENTION_KEYS_MAX keys): x is qkv, y the context, H the
+    // keys, zh the heads, zb the images; scores and probabilities are written as their own operators would.
+    void *attn_scores, *attn_probs;
 };
 
 // Channels-last streaming operators.  Sub-range: images [n_lo,n_hi), channels [c_lo,c_hi).
@@ -106,6 +111,7 @@ struct LaunchInfo { int workgroups; int threads; int lds_bytes; int wg_per_cu; c
 LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase = 0);
 LaunchInfo launch_stem(const GemmArgs &a, hipStream_t s, bool dry);        // launch_igemm hands over operators marked `stem`
 LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry);       // and operators marked `halo`
+LaunchInfo launch_attention(const GemmArgs &a, hipStream_t s, bool dry);    // and whole attentions (attn_scores)
 LaunchInfo launch_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase);   // and operators with `kwaves`
 bool rows_takes(const GemmArgs &a);                                         // short K: launch_rows instead of the tiled kernels
 LaunchInfo launch_rows(const GemmArgs &a, hipStream_t s, bool dry);

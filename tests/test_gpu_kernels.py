@@ -318,6 +318,48 @@ def test_tiles_finished_in_registers(dtype):
     check(tenants, [f"igemm_dma_{dtype}", f"igemm_{dtype}_64x64", f"igemm_taps_{dtype}", f"igemm_bt_{dtype}"], [("batch", 2), ("cout", 2), ("cout", 8)])
 
 
+@pytest.mark.parametrize("batch,keys,hidden", [(2, 72, 128), (3, 8, 64), (2, 24, 192), (1, 128, 128), (2, 120, 64), (1, 32, 64), (2, 104, 128)])
+def test_attention_as_one_launch(batch, keys, hidden):
+    """Scores, softmax and context of an attention in one launch: key counts that are no multiple of a query tile, of a k group or of
+    the lanes of a row, both ends of its range; every operator against the oracle, every tensor with the bits of the three launches.
+    Decomposing one of the three, or a sync edge inside the triple, brings the three launches back; batch and channel chunks elsewhere
+    and edges at its ends do not."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    t = G._bert("attention", "bf16", batch, keys, 2, hidden, hidden // 64, 96)
+    other = G._bert("longer", "bf16", 2, 136, 1, 64, 1, 96)     # stays three launches, and so do 16 features per head
+    check([t, other, G.small_bert("bf16", 2)], ["attention_bf16", "softmax", "igemm_bt_bf16"], [("batch", 2)] if batch > 1 else [])
+    sess = harness.Session([t, other], [G.materialise(x, 411, i << 20) for i, x in enumerate([t, other])])
+
+    def snapshot():
+        sess.poison_outputs()
+        sess.run(B.GACER_MODE_PLAN, 2)
+        return [sess.tensor_bytes(0, op.out) for op in t.ops]
+
+    def fused():
+        return [r["op"] for r in sess.trace(B.GACER_MODE_PLAN, 1) if r["kernel"] == "attention_bf16"]
+    qk = [i for i, op in enumerate(t.ops) if op.kind == "bgemm_qk"]
+    want, launches = snapshot(), sess.launch_count()
+    assert fused() == qk
+    sess.set_fuse_affine(False)
+    assert snapshot() == want and fused() == [] and sess.launch_count() == launches == len(t.ops) + len(other.ops)
+    sess.set_fuse_affine(True)
+    for syncs, left in [([(0, qk[0], 1, 3)], qk[1:]), ([(0, qk[0] + 1, 1, 3)], qk[1:]), ([(1, 2, 0, qk[1] + 1)], qk[:1]), ([(1, 2, 0, qk[1] + 2)], qk[:1]),
+                        ([(1, 2, 0, qk[1]), (0, qk[0] + 2, 1, 3)], qk), ([(0, qk[0] + 2, 1, 3, 1)], qk[1:])]:
+        sess.set_plan([(0, 0, "batch", 1)], syncs)
+        assert fused() == left, syncs
+        assert snapshot() == want, syncs
+    if batch > 1:
+        for k in range(3):
+            sess.set_plan([(0, qk[1] + k, "batch", 2), (0, qk[0] - 1, "cout", 2)], [])
+            assert fused() == qk[:1] and snapshot() == want, k
+    sess.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_output_tiles(dtype):
     """Every output tile of the depthwise kernel (from one output per thread to 2 x 4, chosen by the number of outputs), 3x3 and 5x5,
