@@ -95,6 +95,7 @@ template <> struct Vec<float, 4> {
     float4 raw;
     __device__ __forceinline__ float get(int i) const { return i == 0 ? raw.x : i == 1 ? raw.y : i == 2 ? raw.z : raw.w; }
     __device__ __forceinline__ void set(int i, float v) { if (i == 0) raw.x = v; else if (i == 1) raw.y = v; else if (i == 2) raw.z = v; else raw.w = v; }
+    __device__ __forceinline__ void pack(const float *f) { raw = make_float4(f[0], f[1], f[2], f[3]); }
 };
 template <> struct Vec<unsigned short, 8> {
     uint4 raw;
@@ -109,16 +110,22 @@ template <> struct Vec<unsigned short, 8> {
         unsigned &wd = (i >> 1) == 0 ? raw.x : (i >> 1) == 1 ? raw.y : (i >> 1) == 2 ? raw.z : raw.w;
         wd = (i & 1) ? ((wd & 0x0000FFFFu) | (b << 16)) : ((wd & 0xFFFF0000u) | b);
     }
+    __device__ __forceinline__ void pack(const float *f)
+    {
+        raw = make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
+    }
 };
 template <> struct Vec<float, 1> {
     float raw;
     __device__ __forceinline__ float get(int) const { return raw; }
     __device__ __forceinline__ void set(int, float v) { raw = v; }
+    __device__ __forceinline__ void pack(const float *f) { raw = *f; }
 };
 template <> struct Vec<unsigned short, 1> {
     unsigned short raw;
     __device__ __forceinline__ float get(int) const { return __uint_as_float(((unsigned)raw) << 16); }
     __device__ __forceinline__ void set(int, float v) { raw = to_bf16(v); }
+    __device__ __forceinline__ void pack(const float *f) { raw = to_bf16(*f); }
 };
 
 template <typename T, int V> __device__ __forceinline__ Vec<T, V> ld_vec(const T *p, int64_t i)

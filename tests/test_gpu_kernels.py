@@ -383,6 +383,33 @@ def test_depthwise_output_tiles(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pools_and_norms_read_up_front(dtype):
+    """Pooling windows of 2 and 3 (maximum with and without padding, mean, images smaller than the window) and the
+    ones left to the tap by tap kernel (5, ragged channels); global means around the 16 and 64 positions a wavefront has in flight,
+    with a remainder of channels; layer normalisation of one to four vectors per lane with and without a remainder and a residual;
+    softmax rows of every lane group."""
+    from synth import graphs as G
+    tenants = []
+
+    def one(name, batch, shape, op):
+        b = G._B(name, dtype, batch)
+        x = b.tensor(batch, *shape)
+        tenants.append(b.done(x, op(b, x)))
+    for i, (batch, c, h, w, k, stride, pad) in enumerate([(2, 24, 13, 11, 3, 2, 1), (3, 40, 9, 7, 3, 1, 1), (1, 8, 1, 2, 3, 1, 1), (2, 16, 8, 9, 2, 2, 0),
+                                                          (2, 16, 6, 5, 2, 1, 1), (2, 16, 9, 9, 5, 2, 2), (2, 11, 9, 8, 3, 2, 0)]):
+        one(f"max{i}", batch, (c, h, w), lambda b, x: b.maxpool(x, k, stride, pad))
+    for i, (c, h, k, stride) in enumerate([(24, 9, 2, 2), (16, 10, 3, 1), (9, 7, 3, 2)]):
+        one(f"mean{i}", 2, (c, h, h + 1), lambda b, x: b.avgpool(x, k, stride))
+    for i, (c, h, w) in enumerate([(65, 1, 1), (130, 8, 8), (72, 5, 13), (64, 16, 16), (20, 15, 17), (33, 25, 31)]):
+        one(f"gap{i}", 3, (c, h, w), lambda b, x: b.gavgpool(x))
+    for i, (c, rows) in enumerate([(8, 5), (256, 3), (512, 6), (520, 7), (768, 9), (1024, 2), (1032, 5), (2048, 3), (2056, 2), (13, 4)]):
+        one(f"ln{i}", 2, (c, rows, 1), lambda b, x: b.layernorm(x, x if i % 2 else -1))
+    for i, c in enumerate([8, 16, 24, 64, 120, 256, 512, 7]):
+        one(f"sm{i}", 2, (c, 9, 1), lambda b, x: b.softmax(x))
+    check(tenants, ["maxpool", "gavgpool", "layernorm", "softmax"], [("batch", 2)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_5x5(dtype):
     """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; few outputs
     (bf16), ragged channel ranges and stride 3 on the one-vector kernel.  Chunks of what is tiled as a whole run on either."""
