@@ -422,7 +422,8 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
     const int bk = bf16 ? 32 : 16;
     const int nkb = (K + bk - 1) / bk;
     // K slices inside a workgroup (slices_kernel, one 32x32 tile per workgroup) while there are at most about two such tiles per
-    // compute unit.  Measured in isolation, microseconds, this kernel against the tiled kernels with their finishing pass:
+    // compute unit.  Measured in isolation, microseconds, this kernel against the tiled kernels with their finishing pass (both have
+    // become faster since, this one by about 1.1 in a short launch, the tiled ones by 0.3 to 1.5; the lines are where they were):
     // bf16 49x160x960 4.5 / 8.8, 392x512x4608 9.6 / 13.8, 1568x256x2304 (392 tiles) 10.2 / 14.2, 144x3072x768 (480) 6.1 / 6.8,
     // 6272x128x512 (784) 9.0 / 6.5; fp32 125x32x1152 9.9 / 31.3, 392x160x960 8.5 / 11.5, 392x512x2048 13.8 / 18.4, 392x1280x320
     // (520) 10.9 / 10.3.  One column of tiles (N <= 32) wastes half of a 64-wide tile's work, so it goes on longer: fp32

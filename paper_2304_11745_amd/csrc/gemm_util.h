@@ -96,20 +96,6 @@ __device__ __forceinline__ void finish_vec(const GemmArgs &a, float *v, const fl
         *(float4 *)(yg + o) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// bias of EV consecutive channels (zeros without a bias pointer); n is a multiple of 4 and the pointer 16-byte aligned
-template <int EV> __device__ __forceinline__ void load_bias_vec(const float *bias, int n, bool ok, float *bv)
-{
-#pragma unroll
-    for (int q = 0; q < EV; ++q) bv[q] = 0.f;
-    if (bias && ok) {
-#pragma unroll
-        for (int q = 0; q < EV; q += 4) {
-            const float4 b4 = *(const float4 *)(bias + n + q);
-            bv[q] = b4.x; bv[q + 1] = b4.y; bv[q + 2] = b4.z; bv[q + 3] = b4.w;
-        }
-    }
-}
-
 // four consecutive elements as floats, and back (8-byte vectors for bf16, 16-byte for fp32)
 __device__ __forceinline__ void load_vec4(const float *p, float *v)
 {

@@ -664,50 +664,60 @@ void igemm_dma_kernel(GemmArgs a)
 // ------------------------------------------------------------------------------------------------
 // Second pass of a split-K operator: out = act(alpha * (s0 + s1 + ... ) + bias + res), slices added in
 // ascending order.  One thread per FV consecutive output channels of the launched sub-range (FV = 4 when
-// the range and the pointers allow 16-byte accesses), coalesced along n.
-template <typename T, int FV>
-__global__ __launch_bounds__(THREADS) void splitk_finish(GemmArgs a)
+// the range and the pointers allow 16-byte accesses), coalesced along n.  Bound by the chain of one thread: arguments in one struct
+// of its own, and slices, bias and residual requested at once, KS slices without a branch (those past the last read it again).
+// Us per operator with its pass, before (sixteen conditional loads, the operator's whole argument block) / here, fp32: 8x1000x2048
+// in eight slices 7.99 / 7.39, 32x1000x1280 in five 7.77 / 7.31, 147x512x4608 in three 14.24 / 13.74, 49x512x4608 10.40 / 9.99.
+struct FinishArgs {
+    const float *ws, *bias;
+    const void *res;
+    void *y;
+    int64_t slice;             // elements of a slice
+    int groups, Nl, m_lo, n_lo, y_row, last, act;      // threads that have outputs; last: the last slice
+    float alpha;
+    unsigned div_nl[2];
+};
+
+template <typename T, int FV, int KS>
+__global__ __launch_bounds__(THREADS) void splitk_finish(FinishArgs a)
 {
-    const int Nl = a.n_hi - a.n_lo;
-    const int64_t total = (int64_t)(a.m_hi - a.m_lo) * Nl;
-    const int64_t idx = ((int64_t)blockIdx.x * THREADS + threadIdx.x) * FV;
-    if (idx >= total) return;
+    const int i = (int)blockIdx.x * THREADS + (int)threadIdx.x;
+    if (i >= a.groups) return;
+    const int64_t idx = (int64_t)i * FV;
     const int mr = div_by((int)idx, a.div_nl);          // idx < 2^31: the launched sub-range holds fewer elements
-    const int m = a.m_lo + mr, n = a.n_lo + ((int)idx - mr * Nl);
-    const int64_t o = (int64_t)m * a.y_row + n;
-    // bias and residual are requested together with the slices: one global round trip for the whole kernel
+    const int n = a.n_lo + ((int)idx - mr * a.Nl);
+    const int64_t o = (int64_t)(a.m_lo + mr) * a.y_row + n;
+    typedef typename std::conditional<FV == 4, float4, float>::type F;
+    F p[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) p[q] = *(const F *)(a.ws + (int64_t)min(q, a.last) * a.slice + idx);
     float bv[FV], rv[FV];
 #pragma unroll
-    for (int e = 0; e < FV; ++e) bv[e] = a.bias ? a.bias[n + e] : 0.f;
+    for (int e = 0; e < FV; ++e) bv[e] = rv[e] = 0.f;
+    if (a.bias) {
 #pragma unroll
-    for (int e = 0; e < FV; ++e) rv[e] = a.res ? load_in((const T *)a.res, o + e) : 0.f;
+        for (int e = 0; e < FV; ++e) bv[e] = a.bias[n + e];
+    }
+    if (a.res) {
+#pragma unroll
+        for (int e = 0; e < FV; ++e) rv[e] = load_in((const T *)a.res, o + e);
+    }
     float v[FV];
-    if constexpr (FV == 4) {
-        float4 p[16];                          // all slice loads are issued before the first add (ksplit <= 16)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) p[q] = q < a.ksplit ? *(const float4 *)(a.ws + q * total + idx) : make_float4(0.f, 0.f, 0.f, 0.f);
-        v[0] = p[0].x; v[1] = p[0].y; v[2] = p[0].z; v[3] = p[0].w;
+    for (int e = 0; e < FV; ++e) v[e] = ((const float *)&p[0])[e];
 #pragma unroll
-        for (int q = 1; q < 16; ++q)
-            if (q < a.ksplit) {
-                v[0] = __fadd_rn(v[0], p[q].x); v[1] = __fadd_rn(v[1], p[q].y);
-                v[2] = __fadd_rn(v[2], p[q].z); v[3] = __fadd_rn(v[3], p[q].w);
-            }
-    } else {
-        float p[16];
+    for (int q = 1; q < KS; ++q)
+        if (q <= a.last) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) p[q] = q < a.ksplit ? a.ws[q * total + idx] : 0.f;
-        v[0] = p[0];
+            for (int e = 0; e < FV; ++e) v[e] = __fadd_rn(v[e], ((const float *)&p[q])[e]);
+        }
 #pragma unroll
-        for (int q = 1; q < 16; ++q)
-            if (q < a.ksplit) v[0] = __fadd_rn(v[0], p[q]);
+    for (int e = 0; e < FV; ++e) v[e] = __fmaf_rn(v[e], a.alpha, bv[e]);
+    if (a.res) {
+#pragma unroll
+        for (int e = 0; e < FV; ++e) v[e] = __fadd_rn(v[e], rv[e]);
     }
-#pragma unroll
-    for (int e = 0; e < FV; ++e) {
-        float t = __fmaf_rn(v[e], a.alpha, bv[e]);
-        if (a.res) t = __fadd_rn(t, rv[e]);
-        v[e] = act_apply(t, a.act);
-    }
+    activate_n<FV>(v, a.act);
     if constexpr (FV == 4 && sizeof(T) == 4) {
         *(float4 *)((float *)a.y + o) = make_float4(v[0], v[1], v[2], v[3]);
     } else if constexpr (FV == 4) {
@@ -717,18 +727,31 @@ __global__ __launch_bounds__(THREADS) void splitk_finish(GemmArgs a)
     }
 }
 
+template <typename T, int FV>
+static void go_finish(const GemmArgs &a, hipStream_t s)
+{
+    const int64_t total = (int64_t)(a.m_hi - a.m_lo) * (a.n_hi - a.n_lo);
+    FinishArgs b;
+    b.ws = a.ws; b.bias = a.bias; b.res = a.res; b.y = a.y;
+    b.slice = total;
+    b.groups = (int)(total / FV);
+    b.Nl = a.n_hi - a.n_lo; b.m_lo = a.m_lo; b.n_lo = a.n_lo; b.y_row = (int)a.y_row; b.last = a.ksplit - 1; b.act = a.act;
+    b.alpha = a.alpha;
+    divisor(b.Nl, b.div_nl);
+    const dim3 grid((unsigned)((b.groups + THREADS - 1) / THREADS)), block(THREADS);
+    if (a.ksplit <= 2) GACER_LAUNCH((splitk_finish<T, FV, 2>), grid, block, 0, s, b);
+    else if (a.ksplit <= 4) GACER_LAUNCH((splitk_finish<T, FV, 4>), grid, block, 0, s, b);
+    else if (a.ksplit <= 8) GACER_LAUNCH((splitk_finish<T, FV, 8>), grid, block, 0, s, b);
+    else GACER_LAUNCH((splitk_finish<T, FV, 16>), grid, block, 0, s, b);
+}
+
 template <typename T>
 static void finish(const GemmArgs &a, hipStream_t s)
 {
     const int Nl = a.n_hi - a.n_lo;
-    const int64_t total = (int64_t)(a.m_hi - a.m_lo) * Nl;
     const bool v4 = Nl % 4 == 0 && a.n_lo % 4 == 0 && a.y_row % 4 == 0 && (((uintptr_t)a.ws) & 15) == 0 && (((uintptr_t)a.y) & 15) == 0;
-    GemmArgs b = a;
-    divisor(Nl, b.div_nl);
-    if (v4)
-        GACER_LAUNCH((splitk_finish<T, 4>), dim3((unsigned)((total / 4 + THREADS - 1) / THREADS)), dim3(THREADS), 0, s, b);
-    else
-        GACER_LAUNCH((splitk_finish<T, 1>), dim3((unsigned)((total + THREADS - 1) / THREADS)), dim3(THREADS), 0, s, b);
+    if (v4) go_finish<T, 4>(a, s);
+    else go_finish<T, 1>(a, s);
 }
 
 void launch_finish(const GemmArgs &a, hipStream_t s) { a.dtype == DT_BF16 ? finish<unsigned short>(a, s) : finish<float>(a, s); }

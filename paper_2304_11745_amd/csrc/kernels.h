@@ -62,7 +62,6 @@ struct GemmArgs {
     // set by the launcher of the tiled kernels: tiles along m and n of this launch, divisors for them and for zh
     int tiles_m, tiles_n;
     unsigned div_tiles_m[2], div_tiles_n[2], div_zh[2];
-    unsigned div_nl[2];        // set by the launcher of the finishing pass: divisor for n_hi - n_lo
     // Per-channel affine + activation fused in front of a 1x1 product (pre_scale != null): x is the affine operator's INPUT
     // (same shape as its output, K = Cin channels) and A[m][k] = pre_act(x[m][k] * pre_scale[k] + pre_shift[k]), rounded to
     // the element type, is formed while the A tile is stored to LDS; the tiles that cover output channel 0 also write it to

@@ -119,6 +119,19 @@ def test_long_k_with_few_tiles_in_fp32():
     assert any(n.startswith("igemm_dma_taps_f32_64x64") for n in ran[416]) and any(n.startswith("igemm_dma_f32_64x64") for n in ran[405]), ran
 
 
+def test_finishing_pass_of_every_number_of_slices():
+    """splitk_finish for two, three, five and eight slices in fp32, whole vectors and channel counts or chunks that are none, with
+    and without a residual and an activation."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, hw, cin, cout, k, act) in enumerate([(8, 1, 4096, 512, 1, "relu"), (3, 7, 512, 512, 3, "none"), (1, 13, 256, 256, 3, "relu6"),
+                                                        (8, 1, 2048, 1001, 1, "gelu"), (8, 1, 2048, 1000, 1, "none"), (2, 7, 512, 510, 3, "hswish")]):
+        b = G._B(f"finish{i}", "f32", batch)
+        x = b.tensor(batch, cin, hw, hw)
+        tenants.append(b.done(x, b.conv(x, cout, k, 1, k // 2, act, res=x if cin == cout else -1)))
+    check(tenants, ["splitk_finish"], [("batch", 2), ("cout", 8)])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_affine_with_many_channels_in_front_of_k_slices(dtype):
     """The fused affine form of slices_kernel with several batches of K per wave (its stores counted by the waits), K that ends
