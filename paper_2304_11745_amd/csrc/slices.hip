@@ -17,15 +17,16 @@
 // as the rest.  Hence: arguments in one compact block whose loads the compiler issues at once; byte offsets in 32 bits; rows
 // beyond the launched range not masked (what they compute is not stored, and beyond the tensor the descriptor returns zeros);
 // the K position in the scalar offset of the loads, so that rows of one pitch (SL_ROWS) need no vector arithmetic per batch; the
-// K tail masked by one instruction per load; no requests beyond the slice; bias and residual requested before the K loop; in fp32
-// two batches in flight, not one (see the fragments' type).  Us per launch in a chain of eight dependent ones, before these / with
-// them: bf16 49x160x960 4.73 / 3.51, 144x768x768 4.71 / 3.52, 784x512x1024 7.45 / 5.55, 49x512x4608 9.09 / 7.77; fp32 49x160x960
+// K tail masked by one instruction per load; no requests beyond the slice, but for waves with fewer than two batches; bias and
+// residual requested before the K loop; in fp32 two batches in flight, not one (see the fragments' type).  Us per launch in a chain of
+// eight dependent ones, before these / with them: bf16 49x160x960 4.73 / 3.51, 144x768x768 4.71 / 3.52, 784x512x1024 7.45 / 5.55, 49x512x4608 9.09 / 7.77; fp32 49x160x960
 // 8.66 / 7.30, 784x128x512 6.58 / 5.15, 784x512x2048 25.0 / 21.5, affine + 98x128x128 5.26 / 4.15.
 #include <hip/hip_runtime.h>
 #include <string>
 #include "device_util.h"
 #include "gemm_util.h"
 #include "kernels.h"
+#include "slices_geom.h"
 
 namespace gacer {
 
@@ -107,7 +108,8 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
     // K range of this wave, in elements; loads at or beyond k_end return zeros.  Only the range that holds the end of K can end
     // inside a batch.
     const int slice = (int)blockIdx.y * S + wave;
-    const int k_lo = min(a.K, slice * a.per), k_end = min(a.K, k_lo + a.per);
+    const SlicesRange range = slices_range(a.K, a.per, slice);
+    const int k_lo = range.k_lo, k_end = range.k_end;
     const int batches = (k_end - k_lo + BE - 1) / BE;
     unsigned tail[2];                           // OOB where the lane's elements of the last batch lie beyond k_end
 #pragma unroll
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
         // What is masked gets the top bit (out of range) by arithmetic: of selects the compiler makes branches with loads in both
         // arms, cannot count across them and waits for loads of the newest batch too.
         unsigned bad[2];
-        const int soff = kb * ESZ;
+        const int soff = slices_offset(kb, k_end, ESZ);
         if constexpr (PRE) {                    // requests run past the end of the slice, see below
 #pragma unroll
             for (int h = 0; h < 2; ++h) bad[h] = ~(unsigned)((kb + kl[h] - k_end) >> 31) & OOB;

@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 #include "../../include/gacer.h"
+#include "../../paper_2304_11745_amd/csrc/slices_geom.h"
 #include "../../paper_2304_11745_amd/csrc/stem_geom.h"
 
 #define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #cond); std::exit(1); } } while (0)
@@ -59,10 +60,35 @@ static void check_stem_edge(std::mt19937 &rng)
     }
 }
 
+// slices_kernel requests two batches of 128 bytes per wave at least, its fused affine form two past the last: the scalar offset of each
+// lies in the shortest descriptor, that of a single row of K, and is the batch's K position wherever the batch is read
+static void check_slices_offset()
+{
+    for (int esz = 2; esz <= 4; esz += 2)
+        for (int waves = 4; waves <= 8; waves *= 2)
+            for (int K = 16 / esz; K <= 8192; K += 16 / esz) {
+                const int BE = 128 / esz, nb = (K + BE - 1) / BE;
+                for (int rows = 1; rows <= 8; rows += rows < 3 ? 1 : 5) {
+                    const int per = (nb + waves * rows - 1) / (waves * rows) * BE;
+                    for (int slice = 0; slice < waves * rows; ++slice) {
+                        const gacer::SlicesRange r = gacer::slices_range(K, per, slice);
+                        const int batches = (r.k_end - r.k_lo + BE - 1) / BE;
+                        CHECK(r.k_lo == std::min(K, slice * per) && r.k_end == std::min(K, (slice + 1) * per));
+                        for (int b = 0; b < batches + 2; ++b) {
+                            const int kb = r.k_lo + b * BE, off = gacer::slices_offset(kb, r.k_end, esz);
+                            CHECK(off >= 0 && off < K * esz);
+                            CHECK(b >= batches || off == kb * esz);
+                        }
+                    }
+                }
+            }
+}
+
 int main()
 {
     std::mt19937 rng(7);
     check_stem_edge(rng);
+    check_slices_offset();
     for (int trial = 0; trial < 30; ++trial) {
         gacer_ctx *ctx = nullptr;
         CHECK(gacer_create(&ctx) == GACER_OK);

@@ -104,6 +104,26 @@ def test_k_slices_addressing(dtype):
     assert all(n.startswith("igemm_slices") or n == "splitk_finish" for n in ran), ran
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_k_slices_of_one_row(dtype):
+    """slices_kernel where a descriptor holds a single row of K, of input or of weights, and waves have one batch of it or none: the
+    squeeze layers of a channel gate for one image, one channel, a 3x3 window on one pixel, a fused affine."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, hw, cin, cout, k, affine) in enumerate([(1, 1, 72, 24, 1, False), (1, 1, 120, 32, 1, False), (1, 1, 168, 42, 1, False), (1, 1, 240, 64, 1, False),
+                                                           (1, 1, 672, 168, 1, False), (1, 1, 120, 1, 1, False), (3, 5, 120, 1, 1, False), (1, 1, 24, 1, 3, False),
+                                                           (1, 1, 136, 33, 1, True), (2, 3, 264, 1, 1, True)]):
+        if dtype == "bf16" and cin == 72:
+            cin = 104                                # shorter rows are rowgemm_kernel's
+        b = G._B(f"row{i}", dtype, batch)
+        x = y = b.tensor(batch, cin, hw, hw)
+        if affine:
+            y = b.affine(x, "relu")
+        tenants.append(b.done(x, b.conv(y, cout, k, 1, k // 2, "relu")))
+    ran = check(tenants, [f"igemm_slices_{dtype}_x4", f"igemm_affine_slices_{dtype}_x4"], [("cout", 2)])
+    assert all("slices" in n for n in ran), ran
+
+
 def test_long_k_with_few_tiles_in_fp32():
     """K cut over the grid beside the slices of a workgroup (one, three, five and eight workgroup rows along K, the last row with
     fewer batches than the others), and the shapes with 65 to 128 tiles that the tiled kernels with their own cut of K take."""
