@@ -124,7 +124,8 @@ struct DwArgs {
 };
 
 // The loads of a thread need no arithmetic of their own: a window position is the scalar offset of the load, a row or column outside
-// the image puts the vector offset out of range (the hardware then returns zero).
+// the image puts the vector offset out of range (the hardware then returns zero).  That needs every scalar offset to lie in the
+// descriptor's range, which a tensor smaller than the window would not give: see dw_window_fits.
 template <typename T, int V, int S, int K, int TH, int TW>
 __global__ __launch_bounds__(TPB, K == 3 ? 4 : 2) void dwconv_tile_kernel(DwArgs a)
 {
@@ -753,6 +754,13 @@ static LaunchInfo info(int64_t wgs, const char *kernel)
         return info(g, NAME);                                                                                   \
     }
 
+// Whether the scalar offsets of a window of rows x cols input pixels stay inside the descriptor's range (the tensor and the pixels in
+// front of it).  They do not where the tensor is smaller than the window: its masked positions would pass the range.
+static bool dw_window_fits(const StreamArgs &a, int rows, int cols)
+{
+    return (int64_t)(rows - 1) * a.W + cols - 1 < (int64_t)a.N * a.H * a.W + (int64_t)a.pad * (a.W + 1);
+}
+
 template <typename T, int V, int S, int K, int TH, int TW>
 static LaunchInfo go_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
 {
@@ -797,11 +805,11 @@ static LaunchInfo pick_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
     constexpr bool BF16 = sizeof(T) == 2;
     const int64_t wgs = ((int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * ((a.c_hi - a.c_lo) / 4) + TPB - 1) / TPB;
     constexpr int one = BF16 ? (K == 3 && S == 2 ? 512 : 320) : K == 3 ? 256 : 128, two = S == 1 || K == 5 ? 512 : 1500, four = K == 3 ? 2500 : 1024;
-    if (wgs <= one) return go_dwconv_tile<T, BF16 ? 2 : 4, S, K, 1, 1>(a, s, dry);
-    if (wgs <= two || (!BF16 && S == 2)) return go_dwconv_tile<T, 4, S, K, 2, 1>(a, s, dry);
+    if (wgs <= one || !dw_window_fits(a, S + K, K)) return go_dwconv_tile<T, BF16 ? 2 : 4, S, K, 1, 1>(a, s, dry);
+    if (wgs <= two || (!BF16 && S == 2) || !dw_window_fits(a, S + K, S + K)) return go_dwconv_tile<T, 4, S, K, 2, 1>(a, s, dry);
     if constexpr (BF16 || S == 1) {
         if constexpr (BF16 && (S == 1 || K == 5))
-            if (wgs > four) return go_dwconv_tile<T, 4, S, K, 2, 4>(a, s, dry);
+            if (wgs > four && dw_window_fits(a, S + K, 3 * S + K)) return go_dwconv_tile<T, 4, S, K, 2, 4>(a, s, dry);
         return go_dwconv_tile<T, 4, S, K, 2, 2>(a, s, dry);
     }
 }
@@ -809,9 +817,11 @@ static LaunchInfo pick_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
 LaunchInfo launch_dwconv(const StreamArgs &a, hipStream_t s, bool dry)
 {
     const int64_t outs = (int64_t)(a.n_hi - a.n_lo) * a.Ho * a.Wo * (a.c_hi - a.c_lo);
-    // vectors of four channels; the pixels before the tensor that the kernel's offsets start from must not take them beyond 32 bits
+    // vectors of four channels; the pixels before the tensor that the kernel's offsets start from must not take them beyond 32 bits; no
+    // tensor smaller than the window of one output
     const bool vec = a.C % 4 == 0 && a.c_lo % 4 == 0 && (a.c_hi - a.c_lo) % 4 == 0 && aligned16(a.x) && aligned16(a.y) && aligned16(a.res) && aligned16(a.w) &&
-                     aligned16(a.bias) && (int64_t)a.pad * (a.W + 1) * a.C < (1 << 28);
+                     aligned16(a.bias) && (int64_t)a.pad * (a.W + 1) * a.C < (1 << 28) &&
+                     dw_window_fits(a, a.k, a.k);
     if (vec && (a.k == 3 || a.k == 5) && (a.stride == 1 || a.stride == 2)) {
         const bool one = a.stride == 1;
         if (a.dtype == DT_BF16) {

@@ -1,0 +1,66 @@
+// Which kernel, and how many workgroups, the launchers of the built library choose (dry runs: nothing is launched, no GPU is needed).
+// Exit code 0 = every check held.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include "../paper_2304_11745_amd/csrc/kernels.h"
+
+using namespace gacer;
+
+#define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #cond); std::exit(1); } } while (0)
+
+static LaunchInfo depthwise(int dtype, int n, int h, int w, int c, int k, int stride, int pad)
+{
+    StreamArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.x = a.w = a.y = (void *)0x10000;           // aligned, never dereferenced
+    a.dtype = dtype;
+    a.N = n; a.H = h; a.W = w; a.C = c; a.k = k; a.stride = stride; a.pad = pad;
+    a.Ho = (h + 2 * pad - k) / stride + 1; a.Wo = (w + 2 * pad - k) / stride + 1;
+    a.n_hi = n; a.c_hi = c; a.x_pitch = a.y_pitch = c;
+    return launch_dwconv(a, nullptr, true);
+}
+
+// A window position is a scalar offset of the tiled kernels' loads: none may pass the tensor and the pixels in front of it.
+static void check_depthwise_windows()
+{
+    int left = 0, tiled = 0;
+    for (int dtype : {DT_F32, DT_BF16})
+        for (int k : {3, 5})
+            for (int stride : {1, 2})
+                for (int pad = 0; pad <= k; ++pad)
+                    for (int n = 1; n <= 2; ++n)
+                        for (int h = 1; h <= 9; ++h)
+                            for (int w = 1; w <= 9; ++w)
+                                for (int c : {8, 64, 40000, 400000}) {
+                                    if (h + 2 * pad < k || w + 2 * pad < k) continue;
+                                    const LaunchInfo li = depthwise(dtype, n, h, w, c, k, stride, pad);
+                                    const int Ho = (h + 2 * pad - k) / stride + 1, Wo = (w + 2 * pad - k) / stride + 1;
+                                    const long range = (long)n * h * w + pad * (w + 1);
+                                    auto reach = [&](int th, int tw) { return (long)((th - 1) * stride + k - 1) * w + (tw - 1) * stride + k - 1; };
+                                    auto wgs = [&](int th, int tw, int v) { return ((long)n * ((Ho + th - 1) / th) * ((Wo + tw - 1) / tw) * (c / v) + 255) / 256; };
+                                    if (reach(1, 1) >= range) {
+                                        CHECK(li.kernel == std::string(k == 5 ? "dwconv5x5" : "dwconv"));
+                                        ++left;
+                                        continue;
+                                    }
+                                    CHECK(li.kernel == std::string(k == 5 ? "dwconv5x5_tiled" : "dwconv3x3"));
+                                    ++tiled;
+                                    // some tile whose window fits makes this many workgroups
+                                    bool ok = li.workgroups == wgs(1, 1, dtype == DT_BF16 ? 2 : 4);
+                                    for (int tw = 1; tw <= 4; tw *= 2) ok = ok || (reach(2, tw) < range && li.workgroups == wgs(2, tw, 4));
+                                    CHECK(ok);
+                                }
+    CHECK(left > 100 && tiled > 1000);
+    CHECK(depthwise(DT_F32, 1, 1, 1, 64, 3, 1, 1).kernel == std::string("dwconv"));
+    CHECK(depthwise(DT_BF16, 1, 2, 2, 64, 5, 1, 2).kernel == std::string("dwconv5x5"));
+    CHECK(depthwise(DT_BF16, 2, 2, 2, 64, 3, 1, 1).kernel == std::string("dwconv3x3"));
+}
+
+int main()
+{
+    check_depthwise_windows();
+    std::printf("dispatch driver: all checks held\n");
+    return 0;
+}

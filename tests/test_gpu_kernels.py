@@ -416,6 +416,21 @@ def test_depthwise_output_tiles(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_depthwise_windows_larger_than_the_tensor(dtype):
+    """One image smaller than its window runs on the generic kernels; two of them, or one that just holds the window of one output, on
+    the tiled ones."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, h, w, c, k, stride, pad) in enumerate([(1, 1, 1, 40, 3, 1, 1), (1, 2, 2, 40, 5, 1, 2), (1, 1, 1, 24, 5, 2, 2), (1, 1, 3, 12, 3, 1, 1),
+                                                          (1, 3, 1, 12, 5, 1, 2), (1, 2, 2, 40, 3, 1, 1), (2, 1, 1, 40, 3, 1, 1), (1, 3, 3, 40, 5, 2, 2)]):
+        b = G._B(f"tiny{i}", dtype, batch)
+        x = b.tensor(batch, c, h, w)
+        tenants.append(b.done(x, b.conv(x, c, k, stride, pad, "relu6", groups=c)))
+    ran = check(tenants, [], [("cout", 2)])
+    assert ran == {"dwconv", "dwconv5x5", "dwconv3x3", "dwconv5x5_tiled"}, sorted(ran)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_pools_and_norms_read_up_front(dtype):
     """Pooling windows of 2 and 3 (maximum with and without padding, mean, images smaller than the window) and the
     ones left to the tap by tap kernel (5, ragged channels); global means around the 16 and 64 positions a wavefront has in flight,
