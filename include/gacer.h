@@ -345,8 +345,9 @@ gacer_status gacer_set_sync_every_launch(gacer_ctx *ctx, int enable);
  *
  * The same switch lets the three operators of an attention (BGEMM_QK, SOFTMAX, BGEMM_PV on the same qkv; bf16, 64 features per head,
  * at most 128 positions) run as ONE kernel, named "attention_bf16", in the place of the first; all three tensors are written, with the
- * bits of the three kernels.  Not when the plan decomposes one of the three or a sync edge begins or ends inside the triple.  Launch counts
- * keep an entry for each of the three operators; traces show the one kernel.
+ * bits of the three kernels.  Not when the plan decomposes one of the three, a sync edge begins or ends inside the triple, or two of the four
+ * tensors share memory (a softmax in place excepted).  Launch counts keep an entry for each of the three operators; traces show the one
+ * kernel.
  */
 gacer_status gacer_set_fuse_affine(gacer_ctx *ctx, int enable);
 

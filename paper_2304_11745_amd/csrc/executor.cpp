@@ -549,6 +549,18 @@ static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
 // not 16-byte aligned or whose channel count or position pitch is not a multiple of a 16-byte vector.
 static bool aligned16p(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
+// Whether two tensors of a tenant share memory: windows of one tensor by their channels, others by their address ranges
+static bool share_memory(const Tenant &T, int i, int j)
+{
+    const gacer_tensor &a = T.tensors[i], &b = T.tensors[j];
+    const int64_t a_lo = a.pitch ? a.c_off : 0, b_lo = b.pitch ? b.c_off : 0;
+    if ((a.pitch ? a.base : i) == (b.pitch ? b.base : j)) return a_lo < b_lo + b.c && b_lo < a_lo + a.c;
+    const int64_t esz = T.dtype == GACER_BF16 ? 2 : 4;
+    auto bytes = [&](const gacer_tensor &t) { return (uintptr_t)(((t.n * t.h * t.w - 1) * (t.pitch ? t.pitch : t.c) + t.c) * esz); };
+    const uintptr_t pa = (uintptr_t)a.dptr, pb = (uintptr_t)b.dptr;
+    return pa < pb + bytes(b) && pb < pa + bytes(a);
+}
+
 static bool fusable_pair(const Tenant &T, int i)
 {
     if (i + 1 >= (int)T.ops.size()) return false;
@@ -607,7 +619,10 @@ static bool attention_triple(const Tenant &T, int i)
     if (qkv.h > ATTENTION_KEYS_MAX || qkv.pitch || sc.pitch || pr.pitch || ctx.pitch) return false;
     for (const gacer_tensor *t : {&qkv, &sc, &pr, &ctx})
         if (!aligned16p(t->dptr)) return false;
-    return true;
+    // The one launch writes what the three write one after the other: a buffer that a caller uses again (the context where the scores were)
+    // would be written by workgroups in any order.  A softmax in place is not: one lane writes both.
+    return !share_memory(T, qk.in0, qk.out) && !share_memory(T, qk.in0, sm.out) && !share_memory(T, qk.in0, pv.out) &&
+           !share_memory(T, qk.out, pv.out) && !share_memory(T, sm.out, pv.out) && (sc.dptr == pr.dptr || !share_memory(T, qk.out, sm.out));
 }
 
 template <typename Whole>

@@ -393,6 +393,36 @@ def test_attention_as_one_launch(batch, keys, hidden):
     sess.close()
 
 
+def test_attention_whose_context_lies_where_the_scores_were():
+    """A caller that uses buffers again: in the first layer the context over the scores, which nothing reads any more, in the second a
+    softmax in place.  Outputs are those of tensors with memory of their own; the first layer goes back to three launches, the second does
+    not."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    t = G._bert("attention", "bf16", 4, 120, 2, 128, 2, 96)
+    sess = harness.Session([t], [G.materialise(t, 411, 0)])
+    qk = [i for i, op in enumerate(t.ops) if op.kind == "bgemm_qk"]
+
+    def run():
+        sess.run(B.GACER_MODE_SEQUENTIAL, 2)
+        return sess.tensor_bytes(0, t.output), [r["op"] for r in sess.trace(B.GACER_MODE_SEQUENTIAL, 1) if r["kernel"] == "attention_bf16"]
+    want, fused = run()
+    assert fused == qk
+    tensors = sess._descs[0].tensors
+    for q, (tensor, over, left) in ((qk[0], (t.ops[qk[0] + 2].out, t.ops[qk[0]].out, qk[1:])), (qk[1], (t.ops[qk[1] + 1].out, t.ops[qk[1]].out, qk[1:]))):
+        assert sess.acts[0][tensor].numel() <= sess.acts[0][over].numel()
+        tensors[tensor].dptr = tensors[over].dptr
+        sess.poison_outputs()
+        B.check(sess.ctx, B.gacer_load_tenants(sess.ctx, sess._descs, 1))
+        got, fused = run()
+        assert got == want and fused == left, q
+    sess.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_output_tiles(dtype):
     """Every output tile of the depthwise kernel (from one output per thread to 2 x 4, chosen by the number of outputs), 3x3 and 5x5,

@@ -226,6 +226,44 @@ def test_affine_that_reads_unaligned_rows_keeps_its_own_launch(ctx, dtype):
         assert n.value == launches, pitch_in
 
 
+def _own_memory(descs, overlay=()):
+    """Gives every gap-free tensor of every tenant an address range of its own; (tenant, tensor, other) puts a tensor where another is."""
+    at = FAKE
+    for d in descs:
+        for i in range(d.n_tensors):
+            t = d.tensors[i]
+            if not t.pitch:
+                t.dptr = at
+                at += (t.n * t.c * t.h * t.w * 4 + 255) // 256 * 256
+    for ti, i, j in overlay:
+        descs[ti].tensors[i].dptr = descs[ti].tensors[j].dptr
+    for d in descs:
+        for i in range(d.n_tensors):
+            t = d.tensors[i]
+            if t.pitch:
+                t.dptr = d.tensors[t.base].dptr + t.c_off * (2 if d.dtype else 4)
+
+
+def _kernels(ctx):
+    n = C.c_size_t()
+    assert B.gacer_trace_run(ctx, B.GACER_MODE_SEQUENTIAL, 1, None, 0, C.byref(n)) == B.GACER_OK, B.gacer_last_error(ctx)
+    return n.value
+
+
+def test_attention_over_buffers_that_are_used_again_keeps_three_launches(ctx):
+    """One launch writes scores, probabilities and context in any order: with a tensor where another of the four is, only the softmax in
+    place may be fused over."""
+    from synth import graphs as G
+    t = G._bert("attention", "bf16", 2, 72, 1, 64, 1, 96)
+    qk = next(i for i, op in enumerate(t.ops) if op.kind == "bgemm_qk")
+    qkv, scores, probs, context = t.ops[qk].in0, t.ops[qk].out, t.ops[qk + 1].out, t.ops[qk + 2].out
+    for overlay, kernels in (((), len(t.ops) - 2), (((0, probs, scores),), len(t.ops) - 2), (((0, context, scores),), len(t.ops)),
+                             (((0, context, probs),), len(t.ops)), (((0, probs, qkv),), len(t.ops)), (((0, context, qkv),), len(t.ops))):
+        st, _ = load(ctx, [t], lambda d: _own_memory(d, overlay))
+        assert st == B.GACER_OK, B.gacer_last_error(ctx)
+        assert _kernels(ctx) == kernels, overlay
+
+
 def _plan(splits=(), syncs=()):
     sp = (B.gacer_split * max(1, len(splits)))(*[B.gacer_split(*s) for s in splits])
     sy = (B.gacer_sync * max(1, len(syncs)))(*[B.gacer_sync(*s) for s in syncs])
