@@ -337,8 +337,9 @@ gacer_status gacer_set_sync_every_launch(gacer_ctx *ctx, int enable);
  * consumes it are issued as ONE kernel: the product applies the affine operator's arithmetic while it loads its A tile and
  * also writes the affine operator's output tensor, which then exists as if its own kernel had run.  Outputs and every
  * intermediate tensor keep the bits of the unfused kernels.  A pair is left alone when the plan decomposes either operator,
- * when the affine operator's completion is the source of a sync edge, and when its tensors or parameter vectors are not
- * 16-byte aligned or its channel count is not a multiple of a 16-byte vector.  In traces and launch counts the affine
+ * when the affine operator's completion is the source of a sync edge, when its tensors or parameter vectors are not
+ * 16-byte aligned or its channel count is not a multiple of a 16-byte vector, and when the affine operator's input shares memory
+ * with its output or with the product's output.  In traces and launch counts the affine
  * operator of a fused pair has no launch of its own; the fused kernel's name starts with "igemm_affine_".  enable = 0 issues
  * every operator on its own (the lookup table of gacer_profile always describes the unfused operators).  Re-installs the
  * current plan.

@@ -545,8 +545,8 @@ static void plan_workspaces(Ctx *c, std::vector<Tenant> &ts)
 // convolution, stride 1, reading i's output) as one launch of the product, whose A loader applies the affine operator's
 // arithmetic on the way in and also writes operator i's output tensor; operator i then has no launch of its own.  Both give
 // the bits of the two stand-alone kernels.  Not fused: pairs of which either operator is decomposed by the plan, pairs whose
-// first operator's completion is a sync pointer's source, pairs whose tensor in between is a channel window, operands that are
-// not 16-byte aligned or whose channel count or position pitch is not a multiple of a 16-byte vector.
+// first operator's completion is a sync pointer's source, pairs whose tensor in between is a channel window, pairs over memory that
+// is used again, operands that are not 16-byte aligned or whose channel count or position pitch is not a multiple of a 16-byte vector.
 static bool aligned16p(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // Whether two tensors of a tenant share memory: windows of one tensor by their channels, others by their address ranges
@@ -572,6 +572,10 @@ static bool fusable_pair(const Tenant &T, int i)
     const int vec = T.dtype == GACER_BF16 ? 8 : 4;
     if (mid.pitch) return false;                 // the fused launch stores the tensor between the two gap-free
     if (in.c % vec || (in.pitch && in.pitch % vec) || (T.ksplit[i + 1].kwaves && in.c > SLICES_PRE_MAX)) return false;
+    // One launch reads the affine's input while it writes both outputs: not over memory that a caller uses again (an affine in place, the
+    // product's output where the input was, a residual where the tensor in between is).  A product in place has no result to keep.
+    if (!share_memory(T, af.out, pw.out) && (share_memory(T, af.in0, af.out) || share_memory(T, af.in0, pw.out) ||
+                                             (pw.res >= 0 && share_memory(T, pw.res, af.out)))) return false;
     return aligned16p(in.dptr) && aligned16p(mid.dptr) && aligned16p(af.scale) && aligned16p(af.shift) && aligned16p(pw.w);
 }
 

@@ -526,3 +526,41 @@ def test_affine_in_front_of_a_product_around_channel_windows(dtype):
         b.t.ops.append(G.Op("affine", y, mid, scale=b.param((16,), "uniform"), shift=b.param((16,), "uniform"), cin=16, cout=16, act="relu"))
         tenants.append(b.done(x, b.conv(mid, cout, 1, 1, 0, "relu")))
     check(tenants, ["eltwise"], [("batch", 2), ("cout", 2)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_affine_pair_over_buffers_that_are_used_again(dtype):
+    """Two buffers in turn: an affine in place, and a product that writes where the affine's input was.  Outputs are those of tensors with
+    memory of their own, the pairs are issued one by one."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, hw, c) in enumerate([(2, 9, 136), (3, 40, 64)]):
+        b = G._B(f"turn{i}", dtype, batch)
+        x = b.tensor(batch, 24, hw, hw)
+        y = b.conv(x, c, 3, 1, 1, "none")
+        tenants.append(b.done(x, b.conv(b.affine(y, "relu"), c, 1, 1, 0, "relu")))
+    sess = harness.Session(tenants, [G.materialise(t, 411, i << 20) for i, t in enumerate(tenants)])
+
+    def run():
+        sess.run(B.GACER_MODE_SEQUENTIAL, 2)
+        return [sess.tensor_bytes(i, t.output) for i, t in enumerate(tenants)], sess.launch_count(B.GACER_MODE_SEQUENTIAL)
+    want, launches = run()
+    assert launches == 4
+    assert tenants[0].output == tenants[1].output
+    for tensor, over in ((tenants[0].output, tenants[0].ops[0].out), (tenants[0].ops[1].out, tenants[0].ops[0].out)):
+        at = [sess._descs[i].tensors[tensor].dptr for i in range(2)]
+        for i in range(2):
+            sess._descs[i].tensors[tensor].dptr = sess._descs[i].tensors[over].dptr
+        sess.poison_outputs()
+        B.check(sess.ctx, B.gacer_load_tenants(sess.ctx, sess._descs, 2))
+        sess.run(B.GACER_MODE_SEQUENTIAL, 2)
+        assert sess.launch_count(B.GACER_MODE_SEQUENTIAL) == 6
+        assert [sess.tensor_bytes(i, over if tensor == t.output else t.output) for i, t in enumerate(tenants)] == want, (tensor, over)
+        for i in range(2):
+            sess._descs[i].tensors[tensor].dptr = at[i]
+    sess.close()

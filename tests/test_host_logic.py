@@ -250,6 +250,42 @@ def _kernels(ctx):
     return n.value
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_affine_pair_over_buffers_that_are_used_again_keeps_two_launches(ctx, dtype):
+    """The fused launch reads the affine's input while it writes both outputs: an affine in place, a product that writes where the input was,
+    a residual that lies where the tensor in between does.  Windows of one tensor share memory only where their channels meet."""
+    from synth import graphs as G
+    b = G._B("pair", dtype, 2)
+    x = b.tensor(2, 24, 5, 5)
+    y = b.conv(x, 16, 3, 1, 1, "relu")
+    r = b.conv(x, 16, 3, 1, 1, "relu")
+    mid = b.affine(y, "relu")
+    t = b.done(x, b.conv(mid, 16, 1, 1, 0, "relu", res=r))
+    for overlay, launches in (((), 3), (((0, mid, y),), 4), (((0, t.output, y),), 4), (((0, r, mid),), 4), (((0, t.output, r),), 3)):
+        st, _ = load(ctx, [t], lambda d: _own_memory(d, overlay))
+        assert st == B.GACER_OK, B.gacer_last_error(ctx)
+        n = C.c_int()
+        assert B.gacer_launch_count(ctx, B.GACER_MODE_SEQUENTIAL, C.byref(n)) == B.GACER_OK
+        assert n.value == launches, overlay
+    for first, launches in ((16, 3), (24, 3), (8, 4)):           # the input is channels 0..15 of a wider tensor, the output 16 from `first` on
+        b = G._B("windows", dtype, 2)
+        x, wide = b.tensor(2, 24, 5, 5), b.tensor(2, 40, 5, 5)
+        y = b.conv(x, 16, 3, 1, 1, "relu", out=b.view(wide, 0, 16))
+        mid = b.affine(y, "relu")
+        out = b.conv(mid, 16, 1, 1, 0, "relu", out=b.view(wide, max(first, 16), 16))
+        t = b.done(x, out)
+
+        def overlap(d):
+            _own_memory(d)
+            if first < 16:                                       # a tensor of its own, placed over the window's memory
+                d[0].tensors[out].pitch = 0
+                d[0].tensors[out].dptr = d[0].tensors[wide].dptr + 256
+        st, _ = load(ctx, [t], overlap)
+        assert st == B.GACER_OK, B.gacer_last_error(ctx)
+        assert B.gacer_launch_count(ctx, B.GACER_MODE_SEQUENTIAL, C.byref(n)) == B.GACER_OK
+        assert n.value == launches - 1, first
+
+
 def test_attention_over_buffers_that_are_used_again_keeps_three_launches(ctx):
     """One launch writes scores, probabilities and context in any order: with a tensor where another of the four is, only the softmax in
     place may be fused over."""
