@@ -96,7 +96,8 @@ def test_k_slices_addressing(dtype):
     for i, (batch, hw, cin, cout, k, stride, pad, res) in enumerate([
             (3, 9, 2 * e, 40, 1, 2, 0, False), (2, 7, 4 * e - 8, 33, 1, 3, 0, False), (2, 6, 3 * e, 36, 1, 1, 1, False), (2, 5, e, 40, 3, 1, 4, False),
             (3, 7, 72, 32, 3, 2, 3, False), (2, 1, 4 * e, 33, 3, 1, 1, False), (3, 5, 3 * e + 8, 3 * e + 8, 1, 1, 0, True),
-            (3, 5, 7 * e + 8, 70, 1, 1, 0, False), (3, 5, 11 * e + 8, 33, 1, 1, 0, False), (1, 9, 16 * e, 36, 1, 1, 0, False), (1, 9, 20 * e - 8, 36, 1, 1, 0, False)]):
+            (3, 5, 7 * e + 8, 70, 1, 1, 0, False), (3, 5, 11 * e + 8, 33, 1, 1, 0, False), (1, 9, 16 * e, 36, 1, 1, 0, False), (1, 9, 20 * e - 8, 36, 1, 1, 0, False),
+            (1, 9, 36 * e - 8, 36, 1, 1, 0, False)]):             # eight waves, five batches each, in either type
         b = G._B(f"rows{i}", dtype, batch)
         x = b.tensor(batch, cin, hw, hw)
         tenants.append(b.done(x, b.conv(x, cout, k, stride, pad, "relu", res=x if res else -1)))
@@ -140,12 +141,13 @@ def test_long_k_with_few_tiles_in_fp32():
 
 
 def test_finishing_pass_of_every_number_of_slices():
-    """splitk_finish for two, three, five and eight slices in fp32, whole vectors and channel counts or chunks that are none, with
+    """splitk_finish for two, three, four, five and eight slices in fp32, whole vectors and channel counts or chunks that are none, with
     and without a residual and an activation."""
     from synth import graphs as G
     tenants = []
     for i, (batch, hw, cin, cout, k, act) in enumerate([(8, 1, 4096, 512, 1, "relu"), (3, 7, 512, 512, 3, "none"), (1, 13, 256, 256, 3, "relu6"),
-                                                        (8, 1, 2048, 1001, 1, "gelu"), (8, 1, 2048, 1000, 1, "none"), (2, 7, 512, 510, 3, "hswish")]):
+                                                        (8, 1, 2048, 1001, 1, "gelu"), (8, 1, 2048, 1000, 1, "none"), (2, 7, 512, 510, 3, "hswish"),
+                                                        (2, 7, 1536, 1000, 1, "relu")]):
         b = G._B(f"finish{i}", "f32", batch)
         x = b.tensor(batch, cin, hw, hw)
         tenants.append(b.done(x, b.conv(x, cout, k, 1, k // 2, act, res=x if cin == cout else -1)))
@@ -313,7 +315,7 @@ def test_rows_with_short_k(dtype):
         (2, 181, 183, 5 * v, 42, 1, "none", False), (1, 9, 7, 5 * v, 20, 1, "relu", False), (1, 1, 1, 2 * v, 7, 1, "none", False),
     ]
     if dtype == "bf16":
-        specs += [(1, 241, 203, 16, 97, 1, "relu6", False), (2, 157, 131, 64, 160, 1, "none", False), (1, 227, 225, 88, 100, 1, "relu", False), (1, 143, 199, 256, 264, 1, "none", False)]
+        specs += [(1, 241, 203, 16, 97, 1, "relu6", False), (1, 227, 223, 24, 128, 1, "none", False), (1, 241, 211, 40, 100, 1, "relu", False), (2, 157, 131, 64, 160, 1, "none", False), (1, 227, 225, 88, 100, 1, "relu", False), (1, 143, 199, 256, 264, 1, "none", False)]
     tenants = []
     for i, (batch, h, w, cin, cout, stride, act, res) in enumerate(specs):
         b = G._B(f"rows{i}", dtype, batch)
@@ -435,6 +437,7 @@ def test_depthwise_output_tiles(dtype):
         (6, 47, 45, 64, 3, 2, 1, "relu", False), (15, 47, 47, 64, 3, 2, 1, "none", False), (45, 47, 45, 64, 3, 2, 1, "relu6", False),
         (3, 47, 47, 64, 5, 1, 2, "relu", True), (7, 45, 47, 64, 5, 1, 2, "none", True), (11, 45, 47, 64, 5, 1, 2, "relu6", True),
         (9, 47, 45, 64, 5, 2, 2, "none", False), (15, 47, 47, 64, 5, 2, 2, "relu", False), (31, 47, 45, 64, 5, 2, 2, "hswish", False),
+        (1, 12, 13, 20, 5, 1, 2, "relu6", True), (12, 47, 45, 64, 5, 2, 2, "none", False),
     ]
     tenants = []
     for i, (batch, h, w, c, k, stride, pad, act, res) in enumerate(specs):
@@ -489,8 +492,8 @@ def test_pools_and_norms_read_up_front(dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_5x5(dtype):
-    """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; few outputs
-    (bf16), ragged channel ranges and stride 3 on the one-vector kernel.  Chunks of what is tiled as a whole run on either."""
+    """The tiled 5x5 kernel: output rows shorter than a tile, one past it, strides 1 and 2, padding 0 to 2, a residual; ragged channel
+    ranges and stride 3 on the one-vector kernel.  Chunks of what is tiled as a whole run on either."""
     from synth import graphs as G
     specs = [  # batch, hw, c, stride, pad, act, residual
         (3, 7, 24, 1, 2, "hswish", True), (2, 14, 40, 2, 2, "relu", False), (1, 5, 8, 1, 0, "none", False), (2, 9, 12, 2, 1, "relu6", False),
