@@ -19,7 +19,7 @@ __device__ __forceinline__ unsigned short f32_to_bf16(float f)     // round to n
 }
 
 // exact (erf) GELU; kept out of line so that the unrolled epilogues stay small
-static __device__ __attribute__((noinline)) float gelu_erf(float v)
+static inline __device__ __attribute__((noinline)) float gelu_erf(float v)
 {
     return __fmul_rn(__fmul_rn(0.5f, v), __fadd_rn(1.f, erff(__fmul_rn(v, 0.70710678118654752440f))));
 }
@@ -27,15 +27,6 @@ static __device__ __attribute__((noinline)) float gelu_erf(float v)
 __device__ __forceinline__ float gelu_erf_inl(float v)
 {
     return __fmul_rn(__fmul_rn(0.5f, v), __fadd_rn(1.f, erff(__fmul_rn(v, 0.70710678118654752440f))));
-}
-
-__device__ __forceinline__ float act_apply(float v, int act)
-{
-    if (act == ACT_RELU) return __builtin_fmaxf(v, 0.f);
-    if (act == ACT_RELU6) return __builtin_amdgcn_fmed3f(v, 0.f, 6.f);
-    if (act == ACT_GELU) return gelu_erf(v);
-    if (act == ACT_HSWISH || act == ACT_HSIGMOID) return hard_act(v, act);
-    return v;
 }
 
 template <int DT> struct El;

@@ -710,12 +710,12 @@ static bool vec_ok(const StreamArgs &a)
            aligned16(a.x2) && aligned16(a.res) && aligned16(a.w) && aligned16(a.gate);
 }
 
-// the launch's copy of the arguments with the divisors of its index decomposition: V channels per vector, TW positions per tile
-static StreamArgs with_divisors(const StreamArgs &a, int V, int TW)
+// the launch's copy of the arguments with the divisors of its index decomposition, V channels per vector
+static StreamArgs with_divisors(const StreamArgs &a, int V)
 {
     StreamArgs b = a;
     divisor((a.c_hi - a.c_lo) / V, b.div_cv);
-    divisor((a.Wo + TW - 1) / TW, b.div_w);
+    divisor(a.Wo, b.div_w);
     divisor(a.Ho, b.div_h);
     return b;
 }
@@ -736,21 +736,21 @@ static LaunchInfo info(int64_t wgs, const char *kernel)
     if (a.dtype == DT_BF16) {                                                                              \
         if (vec_ok<unsigned short, 8>(a)) {                                                                \
             const int64_t g = (outs / 8 + TPB - 1) / TPB;                                                  \
-            if (!dry && g) GACER_LAUNCH((KERNEL<unsigned short, 8>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 8, 1)); \
+            if (!dry && g) GACER_LAUNCH((KERNEL<unsigned short, 8>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 8)); \
             return info(g, NAME);                                                                               \
         }                                                                                                  \
         const int64_t g = (outs + TPB - 1) / TPB;                                                          \
-        if (!dry && g) GACER_LAUNCH((KERNEL<unsigned short, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1, 1));     \
+        if (!dry && g) GACER_LAUNCH((KERNEL<unsigned short, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1));     \
         return info(g, NAME);                                                                                   \
     }                                                                                                      \
     if (vec_ok<float, 4>(a)) {                                                                             \
         const int64_t g = (outs / 4 + TPB - 1) / TPB;                                                      \
-        if (!dry && g) GACER_LAUNCH((KERNEL<float, 4>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 4, 1));      \
+        if (!dry && g) GACER_LAUNCH((KERNEL<float, 4>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 4));      \
         return info(g, NAME);                                                                                   \
     }                                                                                                      \
     {                                                                                                      \
         const int64_t g = (outs + TPB - 1) / TPB;                                                          \
-        if (!dry && g) GACER_LAUNCH((KERNEL<float, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1, 1));      \
+        if (!dry && g) GACER_LAUNCH((KERNEL<float, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1));      \
         return info(g, NAME);                                                                                   \
     }
 
@@ -793,8 +793,8 @@ static LaunchInfo go_dwconv_tile(const StreamArgs &a, hipStream_t s, bool dry)
 
 // Outputs per thread, by the workgroups that single vectors of four channels would make (`wgs`).  Few: one output per thread (bf16:
 // of two channels), because one thread's chain of instructions is what the launch takes; many: a tile, which shares window loads
-// and conversions.  fp32 tiles stop where they no longer fit the registers.  One launch, us, of 1x1 / 2x1 / 2x2 / 2x4 outputs (bf16
-// 1x1: two channels): bf16 3x3 14x14x384 1 image (74) 2.62 / 3.05 / 3.36 / 3.95, 56x56x144 1 image (441) 3.40 / 3.16 / 3.48 / 4.06,
+// and conversions.  fp32 tiles stop where they no longer fit the registers (5x5 at stride 1 with 2x2 outputs keeps 7 values in scratch
+// beside its 256 registers and is still the fastest).  One launch, us, of 1x1 / 2x1 / 2x2 / 2x4 outputs (bf16 1x1: two channels): bf16 3x3 14x14x384 1 image (74) 2.62 / 3.05 / 3.36 / 3.95, 56x56x144 1 image (441) 3.40 / 3.16 / 3.48 / 4.06,
 // 8 images (3528) 10.6 / 7.86 / 6.67 / 5.86; stride 2 56x56x144 8 images (882) 4.20 / 4.02 / 3.94 / 6.49, 28x28x192 32 images
 // (1176) 5.00 / 4.77 / 4.92 / 6.71; 5x5 28x28x120 1 image (92) 3.21 / 4.31 / 5.01 / 6.23, 8 images (735) 6.76 / 6.10 / 5.26 /
 // 6.41, 7x7x960 32 images (1470) 11.2 / 9.61 / 7.34 / 6.73; fp32 3x3 56x56x144 8 images 11.4 / 8.34 / 7.36 / 10.1, stride 2 4.80 /
@@ -888,8 +888,8 @@ LaunchInfo launch_concat(const StreamArgs &a, hipStream_t s, bool dry)
     if (a.c_split % full) {                      // the seam is not on a vector boundary: element by element
         const int64_t g = (outs + TPB - 1) / TPB;
         if (!dry && g) {
-            if (a.dtype == DT_BF16) GACER_LAUNCH((concat_kernel<unsigned short, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1, 1));
-            else GACER_LAUNCH((concat_kernel<float, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1, 1));
+            if (a.dtype == DT_BF16) GACER_LAUNCH((concat_kernel<unsigned short, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1));
+            else GACER_LAUNCH((concat_kernel<float, 1>), dim3((unsigned)g), dim3(TPB), 0, s, with_divisors(a, 1));
         }
         return info(g, "concat");
     }
