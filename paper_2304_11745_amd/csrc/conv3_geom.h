@@ -48,11 +48,14 @@ inline int64_t conv3_wgs(const GemmArgs &a, int bm, int bn)
 }
 
 // Whether the operator (its UNSPLIT shape, so that every chunk of it adds in the same order) runs on conv3_kernel: from about
-// three tiles of 256 positions on four compute units; below, smaller tiles fill the chip better.  At 196, microseconds on the
-// tiled kernels / here: 16 images 28x28 512->512 77.6 / 57.0, 8 images 56x56 128->256 28.1 / 21.1, 4 images 112x112 64->128
-// 20.2 / 15.6, 16 images 56x56 64->64 12.5 / 12.2.  Its chunks: half of the images or of the channels 42.2 / 36.2 (8 images 28x28
-// 512->512), a quarter 28.1 / 27.0 (4 images) and 28.4 / 32.4 (128 channels), an eighth 20.4 / 22.8 (2 images); 2 images 56x56
-// 256->256 16.4 / 15.1.
+// three tiles of 256 positions on four compute units.  One launch in a chain, microseconds on the tiled kernels / here, by the number of
+// such tiles: 196 (16 images 28x28 512->512) 75.6 / 57.4, (8 images 56x56 128->256) 25.7 / 20.6, (4 images 112x112 64->128) 18.5 / 14.5,
+// (16 images 56x56 64->64) 12.6 / 10.5.  The limit is where it was before the epilogue of both became shorter; today the crossing lies at
+// about 100: 147 (12 images 56x56 64->64) 10.8 / 9.9, 100 (8 images 28x28 512->512) 38.3 / 37.7, 98 (4 images 56x56 256->256)
+// 23.0 / 22.3, (8 images 56x56 64->64) 8.7 / 7.6, 68 (3 images 75x75 128->128) 12.9 / 13.6, 52 (4 images 28x28 512->512) 27.2 / 28.6,
+// 50 (2 images 56x56 256->256) 16.0 / 17.0.  Chunks of the operators taken (measured with longer epilogues): half of the images or of the
+// channels 42.2 / 36.2 (8 images 28x28 512->512), a quarter 28.1 / 27.0 (4 images) and 28.4 / 32.4 (128 channels), an eighth
+// 20.4 / 22.8 (2 images); 2 images 56x56 256->256 16.4 / 15.1.
 inline bool conv3_takes(const GemmArgs &a)
 {
     if (a.dtype != DT_BF16 || a.kh != 3 || a.kw != 3 || a.stride != 1 || a.pad != 1 || a.Cin % 64 || a.b_trans || a.pre_scale) return false;

@@ -422,32 +422,38 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
     const int bk = bf16 ? 32 : 16;
     const int nkb = (K + bk - 1) / bk;
     // K slices inside a workgroup (slices_kernel, one 32x32 tile per workgroup) while there are at most about two such tiles per
-    // compute unit.  Measured in isolation, microseconds, this kernel against the tiled kernels with their finishing pass (both have
-    // become faster since, this one by about 1.1 in a short launch, the tiled ones by 0.3 to 1.5; the lines are where they were):
-    // bf16 49x160x960 4.5 / 8.8, 392x512x4608 9.6 / 13.8, 1568x256x2304 (392 tiles) 10.2 / 14.2, 144x3072x768 (480) 6.1 / 6.8,
-    // 6272x128x512 (784) 9.0 / 6.5; fp32 125x32x1152 9.9 / 31.3, 392x160x960 8.5 / 11.5, 392x512x2048 13.8 / 18.4, 392x1280x320
-    // (520) 10.9 / 10.3.  One column of tiles (N <= 32) wastes half of a 64-wide tile's work, so it goes on longer: fp32
-    // 19200x32x1152 (600) 26.4 / 33.4, 25088x32x1152 (784) 31.8 / 34.0; bf16 11.8 / 11.8 and 13.7 / 12.1.  At a short K a launch
-    // beyond 512 tiles is slower alone (fp32 25088x24x144 10.9 / 8.3, 25088x24x96 8.8 / 6.9), but whole rounds are not: ResNet-18 and
-    // MobileNetV2 of 8 images 737 us here, 749 there, MobileNetV2 alone 417 / 414, two of them 607 / 602, three mobile networks 910 / 893.
+    // compute unit.  Microseconds per operator in a chain of eight, this kernel / the tiled kernels with their finishing pass: bf16
+    // 49x160x960 3.5 / 7.9, 392x512x4608 (3x3) 8.5 / 13.6, 1568x256x2304 (3x3, 392 tiles) 8.2 / 13.8, 144x3072x768 (480) 4.9 / 6.8,
+    // 6272x128x512 (784) 6.0 / 6.0, 3136x256x2304 (3x3, 784) 14.2 / 11.8; fp32 125x32x1152 8.3 / 27.3, 392x512x2048 12.5 / 17.1,
+    // 2048x256x1024 (512) 13.2 / 20.7, 6272x128x512 14.1 / 13.1.  The limit is where it was before both kernels became shorter; with
+    // today's the crossing lies between 640 and 750 tiles: 392x1280x320 (520) fp32 8.6 / 10.3, bf16 4.8 / 4.8, 2304x256x1024 (576)
+    // 18.0 / 20.9 and 7.1 / 7.7, 784x768x512 (600) 11.5 / 13.0 and 5.8 / 6.7, 784x960x160 (750) 7.6 / 7.3 and 5.1 / 4.5.  One column
+    // of tiles (N <= 32) wastes half of a 64-wide tile's work, so it goes on longer: 19200x32x1152 (600) fp32 21.1 / 28.7, bf16
+    // 9.9 / 11.8, 25088x32x1152 (784) 26.6 / 29.4 and 12.2 / 13.3.  At a short K a launch beyond 512 tiles is slower alone (25088x24x144
+    // fp32 8.7 / 7.8, 19200x32x192 bf16 5.0 / 4.6), but whole rounds were not when that was tried, with longer launches on both sides:
+    // ResNet-18 and MobileNetV2 of 8 images 737 us here, 749 there, MobileNetV2 alone 417 / 414, two of them 607 / 602, three mobile networks
+    // 910 / 893.
     const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t32_max = N > 32 ? 512 : bf16 ? 600 : 800;
     const int nb = (nkb + 1) / 2;                // 128-byte batches of K per row
-    // short bf16 rows belong to rowgemm_kernel.  In fp32 a batch is 1024 clocks of MFMA, and a long K is as fast or faster with each
-    // operand shared by four waves once tiles fill most units (512x768x3072: 34.2 here, 30.8 there), or where the slices would
-    // be cut over the grid at most three ways and 64x64 tiles compute little that is not needed (416x256x2304 14.4 / 13.6,
-    // 245x512x4608 20.6 / 19.3, 320x256x4608 16.8 / 15.6; 147x512x4608, with a row of tiles three quarters empty, 15.6 / 17.0)
+    // Short bf16 rows belong to rowgemm_kernel.  fp32 shapes with a long K that fill most units, or whose slices would be cut over the grid
+    // at most three ways and of which 64x64 tiles compute little that is not needed, are left to the tiled kernels, where four waves
+    // share each operand.  That gained 3 to 10 % when the rule was made; since the chain of this kernel became shorter it gains
+    // nothing: here / there 512x768x3072 29.5 / 29.8, 416x256x2304 11.8 / 13.1, 245x512x4608 16.9 / 17.6, 320x256x4608 14.2 / 14.7,
+    // 392x512x4608 (3x3) 23.2 / 28.3, beside 147x512x4608 (taken here) 13.2 / 16.2.  Moving the line changes the order of additions of
+    // these operators.
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
     const bool shared = !bf16 && (t32 > 128 ? nb > 80 : t32 > 64 && nb > 64 && 32 * tiles <= 9 * t32);
     if (slices_ok && nb >= 2 && (!bf16 || K > 96) && t32 <= t32_max && !shared) {
         // more workgroups along K, and a finishing pass, only where units would stay empty and a wave's chain is long.  bf16: doubled
         // while a wave has more than twelve batches: 8x4096x25088; at 9 batches the pass costs more than it gives (49x512x4608: 9.0 ->
-        // 11.1).  fp32: as many as the chip holds at once: 8x1000x2048 in one workgroup row 14.0, two 12.0, eight 8.8 (tiled kernel
-        // 9.9), 49x512x4608 26.3, 18.3 and 11.5 (13.0), 169x256x2304 15.1, 13.3 and five 9.9 (11.6), 147x512x4608 26.2, 18.9 and
-        // three 15.6 (17.0), 8x4096x4096 28.2 and two 22.5 (26.9), 32x1000x1280 10.7 and five 8.6 (10.1); below 40 batches the pass
-        // costs more than it gives (392x256x1024: 9.4 and two 10.1).
+        // 11.1).  fp32: as many as the chip holds at once: 8x1000x2048 in one workgroup row 14.0, two 12.0, eight 8.8, 49x512x4608
+        // 26.3, 18.3 and six 11.5, 169x256x2304 15.1, 13.3 and five 9.9; below 40 batches the pass costs more than it gives
+        // (392x256x1024: 9.4 and two 10.1).  Those were measured before launches and pass became shorter; today, and on the tiled
+        // kernels: 8x1000x2048 7.4 / 9.1, 49x512x4608 9.8 / 12.3, 169x256x2304 8.7 / 10.7, 147x512x4608 in three 13.6 / 17.0, 8x4096x4096
+        // in two 18.2 / 26.1, 32x1000x1280 in five 7.3 / 9.4.
         // The cut follows the unsplit shape: chunks of a long product can be slower than on the tiled kernels, which cut the unsplit
-        // shape finer (quarters of 784x512x2048, of 400 tiles, 18.1 / 13.7 each, halves of 392x512x2048 14.3 / 12.9; unsplit 24.9 /
-        // 26.8 and 14.8 / 18.5).
+        // shape finer (quarters of 784x512x2048, of 400 tiles, 18.1 / 13.7 each, halves of 392x512x2048 14.3 / 12.9; unsplit, today,
+        // 21.1 / 25.1 and 12.5 / 17.1).
         int64_t so = 1;
         if (bf16) while (so < 8 && t32 * so * 2 <= 256 && nb > 96 * so) so *= 2;
         else if (nb >= 40) so = std::max<int64_t>(1, std::min<int64_t>(8, 256 / t32));

@@ -911,7 +911,11 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     // fused per-channel affine: the A tile passes through registers (the executor fuses only 16-byte aligned, vector-multiple operands)
     if (a.pre_scale) return staged(blocks128, true);
     // Long K rows: the direct-to-LDS pipeline (igemm_dma_kernel) keeps several K blocks in flight and wins once the K
-    // loop is long enough to amortise filling its stages (measured layer by layer: from about 1.5 KB of K per row).
+    // loop is long enough to amortise filling its stages.  The line, 1.5 KB of K per row, dates from longer prologues and epilogues.
+    // Microseconds here / on the register-staged kernel today: bf16 12544x128x768 8.2 / 10.0, 3136x1024x768 11.2 / 13.9, 12544x512x768
+    // 19.8 / 21.2, and below the line 12544x128x512 6.8 / 8.1, x256 5.5 / 6.2, x128 4.9 / 5.1, 100352x128x256 19.3 / 22.5, 6272x1024x192
+    // 10.5 / 10.2; fp32 12544x512x384 48.6 / 50.9, 6272x256x384 18.0 / 18.3, below 12544x512x192 29.4 / 28.9, 3136x1024x96 13.5 / 12.5:
+    // bf16 is ahead here from 256 bytes on, fp32 from about 1 KB.
     const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
     if (vec_ok && !a.b_trans && shape != T128x32 && (!taps || a.kh * a.kw <= 31) && (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 1536) {
         if constexpr (DT == DT_BF16) {
