@@ -34,7 +34,7 @@ HBM_PEAK = 8.0e12
 TRAFFIC = {
     2: {"kernel": "igemm_dma_taps_f32_64x64x32s3", "fetch_bytes": 12.36e6, "write_bytes": 5.47e6, "plan": "unsplit",
         "launches_per_round": 11, "algorithmic_bytes": 12.45e6,
-        "sources_sha256": "6afe8023b9cba182409dcd3060a1bec35f3ad291b224848d87ef54ba29843847"},
+        "sources_sha256": "6d889e41634e56d3a739381fd7431c6b0a747bf34f5193943a210380e394b0bd"},
 }
 TRAFFIC_SOURCES = ["igemm.hip", "slices.hip", "rows.hip", "stream_ops.hip", "gemm_util.h", "slices_geom.h", "device_util.h", "kernels.h"]
 

@@ -46,7 +46,7 @@ struct SlicesArgs {
     unsigned div_inner[2];         // tile number -> (outer, inner) tile index
     int inner, n_major;
     int m_lo, m_hi, n_lo, n_hi;
-    int K, per;                    // K elements, of which a wave has `per`
+    int K, per, k_last;            // K elements, of which a wave has `per`; see slices_offset
     int y_row, act;
     float alpha;
     int split, vec_out;
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
         // What is masked gets the top bit (out of range) by arithmetic: of selects the compiler makes branches with loads in both
         // arms, cannot count across them and waits for loads of the newest batch too.
         unsigned bad[2];
-        const int soff = slices_offset(kb, k_end, ESZ);
+        const int soff = slices_offset(kb, a.k_last, ESZ);
         if constexpr (PRE) {                    // requests run past the end of the slice, see below
 #pragma unroll
             for (int h = 0; h < 2; ++h) bad[h] = ~(unsigned)((kb + kl[h] - k_end) >> 31) & OOB;
@@ -394,6 +394,7 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
         b.m_lo = a.m_lo; b.m_hi = a.m_hi; b.n_lo = a.n_lo; b.n_hi = a.n_hi;
         b.K = a.K;
         b.per = a.kb_per_wave * (64 / ESZ);
+        b.k_last = slices_last(a.K, ESZ);
         b.y_row = (int)a.y_row;
         b.act = a.act;
         b.alpha = a.alpha;

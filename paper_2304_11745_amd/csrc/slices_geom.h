@@ -14,7 +14,9 @@ __host__ __device__ inline SlicesRange slices_range(int K, int per, int slice)
 
 // Scalar offset of the loads of the batch at element kb: its K position in bytes.  A batch beyond the slice (a wave requests two batches
 // whatever it has; the fused affine form two past the last) is masked by its vector offsets, which stand for "out of range" only as
-// long as the scalar offset lies in the descriptor's range; with a single row that range ends with K, so such a batch gets 0.
-__host__ __device__ inline int slices_offset(int kb, int k_end, int esz) { return kb < k_end ? kb * esz : 0; }
+// long as the scalar offset lies in the descriptor's range.  With a single row that range ends with K, so no offset passes `last`, K's
+// last vector.
+__host__ __device__ inline int slices_offset(int kb, int last, int esz) { return kb * esz < last ? kb * esz : last; }
+inline int slices_last(int K, int esz) { return K * esz - 16; }
 
 }  // namespace gacer

@@ -75,7 +75,7 @@ static void check_slices_offset()
                         const int batches = (r.k_end - r.k_lo + BE - 1) / BE;
                         CHECK(r.k_lo == std::min(K, slice * per) && r.k_end == std::min(K, (slice + 1) * per));
                         for (int b = 0; b < batches + 2; ++b) {
-                            const int kb = r.k_lo + b * BE, off = gacer::slices_offset(kb, r.k_end, esz);
+                            const int kb = r.k_lo + b * BE, off = gacer::slices_offset(kb, gacer::slices_last(K, esz), esz);
                             CHECK(off >= 0 && off < K * esz);
                             CHECK(b >= batches || off == kb * esz);
                         }
