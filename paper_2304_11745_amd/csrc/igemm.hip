@@ -827,7 +827,7 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_GATHER>), grid, block, 0, s, b);
     else if (taps)
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_TAPS>), grid, block, 0, s, b);
-    else
+    else if constexpr (DT == DT_F32 || KV == 4)        // one tap and more than 256 bytes of K: igemm_dma_kernel in bf16
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_VEC>), grid, block, 0, s, b);
     if (ks > 1 && phase == 0) finish<T>(a, s);
     return li;
@@ -872,6 +872,40 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
     return li;
 }
 
+// Tile of igemm_dma_kernel in bf16.  Two things bound these launches: the bytes that a unit draws from its L2, which the stages receive
+// at 105 to 115 bytes per ns (a 64x64 tile alone on its unit takes 0.2 us per 128 bytes of K, of which 0.15 are the 16 KB and 0.05 the
+// matrix cores), and what a tile costs beside its K loop (1 us for 64x64, 4 for 128x128 with one workgroup per unit).  So: the
+// largest tile of which about one per unit is left, counted in workgroups, and smaller ones the shorter K is.
+// Us a launch in a chain, 64x64 / 128x64 / 128x128 / 256x128, by the workgroups of 128x64: 3136x256x1024 (100) 6.9 / 9.1 / 11.5 / 18.4, 12544x128x512
+// (196) 6.4 / 6.3 / 8.6 / 12.3, 1568x1280x320 (260) 6.4 / 7.3 / 8.5 / 11.4, 50176x64x256 (392) 8.9 / 7.1 / 9.2 / 10.8, 12544x256x512 (392) 11.0 / 9.0 / 9.6 / 13.2,
+// 3136x1024x256 with a residual (400) 9.3 / 7.8 / 8.7 / 12.0, 12544x512x128 with a residual (784) 11.8 / 9.3 / 10.3 / 11.4, 12544x512x256 (784) 12.6 / 11.5 / 10.7 / 11.6, 3136x2048x512 with a
+// residual (800) 19.5 / 18.6 / 16.2 / 17.2, 12544x1024x256 with a residual (1568) 23.8 / 21.1 / 21.4 / 19.2; long K: 2048x768x768 (192) 7.9 / 8.4 / 10.4 / 15.8,
+// 2048x768x3072 (192) 19.9 / 18.8 / 23.0 / 45.9, 4096x768x768 (384) 11.2 / 12.0 / 11.2 / 16.0, 4096x768x3072 (384) 31.5 / 30.3 / 25.0 / 45.7, 1024x3072x768 with a GELU
+// (384) 13.0 / 14.7 / 17.8 / 29.0, 8192x768x3072 (768) 60.5 / 48.7 / 49.9 / 48.7, 8192x2304x768 (2304) 55.6 / 50.6 / 49.1 / 46.1; and 128x32 / 64x64 for N <= 32:
+// 25088x32x1152 (3x3) 7.9 / 9.1, 50176x32x192 5.7 / 7.9.  Before (64x64 and 128x128 tiles staged through registers below 1.5 KB of K, fewer
+// tiles to choose from above) 98 such shapes took 9 % longer, 12544x96x576 8.5, 25088x32x1152 11.1, 12544x256x512 11.5, 4096x768x3072 31.7.
+static LaunchInfo pick_dma_bf16(const GemmArgs &a, hipStream_t s, bool dry, int phase)
+{
+    const int64_t M = a.m_hi - a.m_lo, N = a.n_hi - a.n_lo, z = (int64_t)a.zb * a.zh * a.ksplit, k_bytes = (int64_t)a.K * 2;
+    const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
+    auto wgs = [&](int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn) * z; };
+    if (N <= 32) return go_dma<DT_BF16, 128, 32, 4, 1, 8, 3>(a, s, dry, true, phase);
+    const bool wide = (N + 127) / 128 * 128 <= (N + 63) / 64 * 64;             // 128 columns waste no more than 64
+    if (wide && k_bytes >= 512) {
+        if (wgs(256, 128) >= 384) return go_dma<DT_BF16, 256, 128, 2, 2, 4, 3>(a, s, dry, true, phase);
+        const int64_t w = wgs(128, 128);
+        if (k_bytes <= 1024 ? w >= 384 : taps && w > 256) return go_dma<DT_BF16, 128, 128, 2, 2, 4, 4>(a, s, dry, true, phase);
+        // one workgroup per unit: nothing covers the epilogue, so not where that is long (erf)
+        if (k_bytes >= 1536 && w >= 160 && w <= 256 && a.act != ACT_GELU) return go_dma<DT_BF16, 128, 128, 2, 2, 8, 3>(a, s, dry, true, phase);
+    }
+    const int64_t w = wgs(128, 64);
+    if (k_bytes <= 512 && w >= 300) return go_dma<DT_BF16, 128, 64, 2, 2, 4, 3>(a, s, dry, true, phase);       // four per unit
+    if (k_bytes <= 1024 ? w >= 300 : w > 400 || (k_bytes >= 4096 && w >= 192)) return go_dma<DT_BF16, 128, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
+    // alone on its unit with a long K a fourth stage pays (1024x768x768 7.0 -> 6.5); with more workgroups it costs one of them its place
+    if (wgs(64, 64) <= 256 && k_bytes >= (taps ? 4096 : 1024)) return go_dma<DT_BF16, 64, 64, 2, 2, 8, 4>(a, s, dry, true, phase);
+    return go_dma<DT_BF16, 64, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
+}
+
 template <int DT>
 static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
@@ -910,26 +944,17 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     const std::integral_constant<int, 4> blocks64;
     // fused per-channel affine: the A tile passes through registers (the executor fuses only 16-byte aligned, vector-multiple operands)
     if (a.pre_scale) return staged(blocks128, true);
-    // Long K rows: the direct-to-LDS pipeline (igemm_dma_kernel) keeps several K blocks in flight and wins once the K
-    // loop is long enough to amortise filling its stages.  The line, 1.5 KB of K per row, dates from longer prologues and epilogues.
-    // Microseconds here / on the register-staged kernel today: bf16 12544x128x768 8.2 / 10.0, 3136x1024x768 11.2 / 13.9, 12544x512x768
-    // 19.8 / 21.2, and below the line 12544x128x512 6.8 / 8.1, x256 5.5 / 6.2, x128 4.9 / 5.1, 100352x128x256 19.3 / 22.5, 6272x1024x192
-    // 10.5 / 10.2; fp32 12544x512x384 48.6 / 50.9, 6272x256x384 18.0 / 18.3, below 12544x512x192 29.4 / 28.9, 3136x1024x96 13.5 / 12.5:
-    // bf16 is ahead here from 256 bytes on, fp32 from about 1 KB.
+    // The direct-to-LDS pipeline (igemm_dma_kernel) wins once the K loop is long enough to fill its stages: in bf16 from 256 bytes of K on
+    // (windows, with their longer address code: 512), fp32 from 1.5 KB (here / on the register-staged kernel: 12544x512x384 48.6 / 50.9, 6272x256x384 18.0 / 18.3, below
+    // 12544x512x192 29.4 / 28.9, 3136x1024x96 13.5 / 12.5).
     const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
-    if (vec_ok && !a.b_trans && shape != T128x32 && (!taps || a.kh * a.kw <= 31) && (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 1536) {
+    const int64_t k_bytes = (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T);
+    if (vec_ok && !a.b_trans && (!taps || a.kh * a.kw <= 31)) {
         if constexpr (DT == DT_BF16) {
-            const bool long_k = (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T) >= 4096;
-            if (shape == T128x128) {
-                // 256x128 halves the L2 traffic of the A operand per flop again; it needs enough rows to still fill the chip
-                if (wgs(256, 128) >= 384) return go_dma<DT, 256, 128, 2, 2, 4, 3>(a, s, dry, vec_ok, phase);
-                // one workgroup per compute unit anyway: whole 128-byte row segments (fewer, larger L2 requests)
-                if (wgs(128, 128) <= 256) return go_dma<DT, 128, 128, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
-                return go_dma<DT, 128, 128, 2, 2, 4, 4>(a, s, dry, vec_ok, phase);
-            }
-            if (long_k) return go_dma<DT, 64, 64, 2, 2, 8, 4>(a, s, dry, vec_ok, phase);   // measured: a fourth stage pays for bf16 only
+            if (k_bytes >= (taps ? 512 : 256)) return pick_dma_bf16(a, s, dry, phase);
+        } else {
+            if (shape != T128x32 && k_bytes >= 1536) return go_dma<DT, 64, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
         }
-        return go_dma<DT, 64, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
     }
     // short K, or the latency-bound gather loader (more waves per unit): 64-byte blocks
     if (a.b_trans || a.K <= 16 * VEC || !vec_ok) return staged(blocks64, vec_ok);

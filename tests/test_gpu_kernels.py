@@ -231,6 +231,22 @@ def test_direct_to_lds_pipeline(dtype):
     assert ran == {"igemm_dma_" + n for n in names[dtype]}, sorted(ran)
 
 
+@pytest.mark.parametrize("name,spec", [
+    ("128x32x64s3", (3, 81, 83, 144, 27, 1, 1, "none", True)), ("taps_128x32x64s3", (3, 81, 83, 72, 30, 3, 1, "relu6", False)),
+    ("128x64x32s3", (1, 131, 127, 136, 200, 1, 1, "relu", True)), ("taps_128x64x32s3", (4, 113, 111, 64, 58, 2, 1, "none", True)),
+    ("128x64x64s3", (1, 131, 127, 328, 136, 1, 1, "hswish", True)), ("taps_128x64x64s3", (2, 113, 111, 40, 130, 3, 1, "relu", False)),
+    ("128x128x32s4", (2, 161, 155, 256, 122, 1, 1, "none", False)), ("64x64x64s4", (1, 130, 8, 1032, 520, 1, 1, "gelu", False))])
+def test_direct_to_lds_tiles_of_short_k(name, spec):
+    """The bf16 tiles of igemm_dma_kernel that short rows and narrow outputs take: ragged rows, channels (no multiple of a vector or of four) and K."""
+    from synth import graphs as G
+    batch, h, w, cin, cout, k, stride, act, res = spec
+    b = G._B("tile", "bf16", batch)
+    x = b.tensor(batch, cin, h, w)
+    y = b.conv(x, cout, k, stride, k // 2, "none") if res else -1
+    ran = check([b.done(x, b.conv(x, cout, k, stride, k // 2, act, res=y))], [], [("batch", 2), ("cout", 2), ("cout", 8)])
+    assert ran == {"igemm_dma_" + ("taps_bf16_" + name[5:] if name.startswith("taps_") else "bf16_" + name)}, sorted(ran)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_non_finite_inputs_reach_their_windows_only(dtype):
     """Infinities and NaN in the input make exactly the outputs non-finite whose window holds one (padding, tails of K and of tiles
