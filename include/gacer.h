@@ -349,6 +349,11 @@ gacer_status gacer_set_sync_every_launch(gacer_ctx *ctx, int enable);
  * bits of the three kernels.  Not when the plan decomposes one of the three, a sync edge begins or ends inside the triple, or two of the four
  * tensors share memory (a softmax in place excepted).  Launch counts keep an entry for each of the three operators; traces show the one
  * kernel.
+ *
+ * And it lets a 1x1 convolution (stride 1, no residual) and the depthwise convolution that reads it (3x3 or 5x5, stride 1 or 2, "same"
+ * padding; bf16) run as ONE kernel, named "expand_dw_bf16_...", in the place of the first, at the sizes where that is faster; both tensors are written, with
+ * the bits of the two kernels.  Not when the plan decomposes one of the two, a sync edge begins or ends between them, or two of the three tensors
+ * share memory.  Launch counts keep an entry for each of the two operators; traces show the one kernel.
  */
 gacer_status gacer_set_fuse_affine(gacer_ctx *ctx, int enable);
 

@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgacer.so")
-SOURCES = ["igemm.hip", "slices.hip", "rows.hip", "conv3.hip", "attention.hip", "stem.hip", "stream_ops.hip", "executor.cpp", "search.cpp"]
+SOURCES = ["igemm.hip", "slices.hip", "rows.hip", "conv3.hip", "attention.hip", "expand.hip", "stem.hip", "stream_ops.hip", "executor.cpp", "search.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -8,8 +8,9 @@
 
 namespace gacer {
 
-// LK_ABSORBED: the operator's work is done by the launch of an operator before it
-enum LaunchKind { LK_IGEMM, LK_DWCONV, LK_MAXPOOL, LK_GAVGPOOL, LK_ELTWISE, LK_LAYERNORM, LK_SOFTMAX, LK_CONCAT, LK_ABSORBED };
+// LK_EXPAND_DW: a pointwise convolution (`g`) and the depthwise convolution behind it (`s`); LK_ABSORBED: the operator's work is done by
+// the launch of an operator before it
+enum LaunchKind { LK_IGEMM, LK_DWCONV, LK_MAXPOOL, LK_GAVGPOOL, LK_ELTWISE, LK_LAYERNORM, LK_SOFTMAX, LK_CONCAT, LK_EXPAND_DW, LK_ABSORBED };
 
 struct Launch {
     LaunchKind kind;
@@ -74,7 +75,7 @@ struct Ctx {
     std::vector<hipEvent_t> t_start, t_end;         // per round, timing enabled
     hipGraphExec_t graph_exec[3] = {nullptr, nullptr, nullptr};   // captured round per mode (optional)
     bool issue_threads = false;                     // one host thread per tenant enqueues that tenant's stream
-    bool fuse_affine = true;                        // launch fusion: an affine operator + the 1x1 convolution that reads it, the operators of an attention
+    bool fuse_affine = true;                        // launch fusion: an affine operator + the 1x1 convolution that reads it, the operators of an attention, a 1x1 convolution + the depthwise one that reads it
     bool sync_every_launch = false;                 // checking mode: wait for, and check, every kernel before the next is issued
     bool capturing = false;                         // a stream capture is open: nothing may synchronise
     std::string launch_detail;                      // checking mode: which launch failed

@@ -21,6 +21,7 @@
 #include <tuple>
 #include "ctx.h"
 #include "conv3_geom.h"
+#include "expand_geom.h"
 #include "stem_geom.h"
 
 using namespace gacer;
@@ -239,6 +240,11 @@ LaunchInfo enqueue(const Launch &l, hipStream_t s, bool dry, int phase, float *w
     case LK_GAVGPOOL: return launch_gavgpool(l.s, s, dry);
     case LK_LAYERNORM: return launch_layernorm(l.s, s, dry);
     case LK_SOFTMAX: return launch_softmax(l.s, s, dry);
+    case LK_EXPAND_DW: {
+        GemmArgs g = l.g;
+        g.dw = &l.s;
+        return launch_igemm(g, s, dry, phase);
+    }
     case LK_ABSORBED: return {0, 0, 0, 1, "absorbed", 0};
     default: return launch_eltwise(l.s, s, dry);
     }
@@ -652,6 +658,46 @@ static void fuse_attention(Ctx *c, std::vector<std::vector<OpExec>> &ex, Whole w
     }
 }
 
+// ---- a pointwise convolution and the depthwise convolution behind it, as one launch -------------------------------------------------
+// Operators i (1x1, stride 1) and i + 1 (depthwise 3x3 or 5x5, stride 1 or 2, "same" padding, reading i's output) are issued as one launch
+// in i's place, which writes both tensors with the bits of the two kernels; i + 1 keeps an entry in its launch list that issues nothing.
+// Not taken where the plan decomposes one of the two or a sync edge begins or ends between them, over memory that is used again, with a
+// residual, or with operands that are not whole vectors.
+static bool expand_pair(const Tenant &T, int i)
+{
+    if (i + 1 >= (int)T.ops.size()) return false;
+    const gacer_op &pw = T.ops[i], &dw = T.ops[i + 1];
+    if ((pw.kind != GACER_CONV2D && pw.kind != GACER_GEMM) || dw.kind != GACER_DWCONV2D || dw.in0 != pw.out || pw.res >= 0 || dw.res >= 0) return false;
+    const gacer_tensor &in = T.tensors[pw.in0], &mid = T.tensors[pw.out], &out = T.tensors[dw.out];
+    if (pw.kind == GACER_CONV2D ? pw.kh != 1 || pw.kw != 1 || pw.stride != 1 || pw.pad != 0 : pw.cin != in.c) return false;
+    if ((dw.kh != 3 && dw.kh != 5) || dw.stride > 2 || dw.pad != dw.kh / 2 || mid.pitch || out.pitch) return false;
+    const KSplit &k = T.ksplit[i];
+    if (k.ksplit != 1 || k.stem || k.halo) return false;
+    const int vec = T.dtype == GACER_BF16 ? 8 : 4;
+    if (in.c % vec || (in.pitch && in.pitch % vec) || mid.c % vec || mid.n != in.n) return false;
+    for (const void *p : {(const void *)in.dptr, (const void *)mid.dptr, (const void *)out.dptr, (const void *)pw.w, (const void *)dw.w, (const void *)pw.bias, (const void *)dw.bias})
+        if (!aligned16p(p)) return false;
+    if (share_memory(T, pw.in0, pw.out) || share_memory(T, pw.in0, dw.out) || share_memory(T, pw.out, dw.out)) return false;
+    return expand_dw_takes(make_launch(T, i, 0, T.batch, 0, (int)mid.c).g, make_launch(T, i + 1, 0, T.batch, 0, (int)out.c).s);
+}
+
+template <typename Whole>
+static void fuse_expand(Ctx *c, std::vector<std::vector<OpExec>> &ex, Whole whole)
+{
+    if (!c->fuse_affine) return;
+    for (size_t t = 0; t < c->tenants.size(); ++t) {
+        const Tenant &T = c->tenants[t];
+        for (int i = 0; i + 1 < (int)T.ops.size(); ++i) {
+            if (!expand_pair(T, i) || !whole((int)t, i)) continue;
+            Launch &pw = ex[t][i].chunks[0], &dw = ex[t][i + 1].chunks[0];
+            if (pw.kind != LK_IGEMM || pw.g.pre_scale) continue;
+            pw.s = dw.s;
+            pw.kind = LK_EXPAND_DW;
+            dw.kind = LK_ABSORBED;
+        }
+    }
+}
+
 static void expand_plain(Ctx *c)
 {
     c->plain_exec.assign(c->tenants.size(), {});
@@ -666,6 +712,7 @@ static void expand_plain(Ctx *c)
     }
     fuse_affine_pairs(c, c->plain_exec, [](int, int) { return false; }, [](int, int) { return false; });
     fuse_attention(c, c->plain_exec, [](int, int) { return true; });
+    fuse_expand(c, c->plain_exec, [](int, int) { return true; });
     for (size_t i = 0; i < longest; ++i)
         for (size_t t = 0; t < c->tenants.size(); ++t)
             if (i < c->tenants[t].ops.size()) c->par_order.push_back({(int)t, (int)i});
@@ -790,13 +837,16 @@ static gacer_status install_plan(Ctx *c, const std::vector<gacer_split> &splits,
     fuse_affine_pairs(c, ex,
                       [&](int t, int i) { auto it = smap.find({t, i}); return it != smap.end() && it->second.factor > 1; },
                       [&](int t, int i) { return ex[t][i].record >= 0; });
-    fuse_attention(c, ex, [&](int t, int i) {
-        for (int k = 0; k < 3; ++k) {
+    // whether n operators from i on are undecomposed and no sync edge begins or ends between them
+    auto whole = [&](int t, int i, int n) {
+        for (int k = 0; k < n; ++k) {
             const OpExec &e = ex[t][i + k];
-            if (e.chunks.size() != 1 || (k < 2 && e.record >= 0) || (k > 0 && (e.pre_record >= 0 || !e.waits.empty()))) return false;
+            if (e.chunks.size() != 1 || (k + 1 < n && e.record >= 0) || (k > 0 && (e.pre_record >= 0 || !e.waits.empty()))) return false;
         }
         return true;
-    });
+    };
+    fuse_attention(c, ex, [&](int t, int i) { return whole(t, i, 3); });
+    fuse_expand(c, ex, [&](int t, int i) { return whole(t, i, 2); });
     for (Tenant &t : c->tenants) (void)hipStreamSynchronize(t.stream);
     drop_graphs(c);                      // captured rounds belong to the plan they were captured under
     c->splits = splits;
@@ -1497,6 +1547,14 @@ static void launch_work(const Launch &l, double *flops, double *bytes)
         const double rows = (double)l.g.zb * l.g.zh * l.g.H;
         *flops = 4.0 * rows * l.g.H * l.g.K;
         *bytes = 2.0 * rows * (4.0 * l.g.K + 2.0 * l.g.H);
+        return;
+    }
+    if (l.kind == LK_EXPAND_DW) {                           // both operators; the tensor between them written once, not read
+        const GemmArgs &g = l.g;
+        const StreamArgs &d = l.s;
+        const double esz = g.dtype == DT_BF16 ? 2.0 : 4.0, images = d.n_hi - d.n_lo, in = images * d.H * d.W, out = images * d.Ho * d.Wo;
+        *flops = 2.0 * in * d.C * g.K + 2.0 * out * d.C * d.k * d.k;
+        *bytes = (in * (g.K + d.C) + out * d.C + (double)d.C * (g.K + d.k * d.k)) * esz + d.C * 4.0 * ((g.bias ? 1 : 0) + (d.bias ? 1 : 0));
         return;
     }
     if (l.kind == LK_IGEMM) {

@@ -964,6 +964,7 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     if (a.attn_scores) return launch_attention(a, s, dry);
+    if (a.dw) return launch_expand_dw(a, *a.dw, s, dry);
     if (a.stem) return launch_stem(a, s, dry);
     if (a.halo) return launch_conv3(a, s, dry);
     if (a.kwaves) return launch_slices(a, s, dry, phase);

@@ -15,6 +15,8 @@ enum { ATTENTION_KEYS_MAX = 128 };
 enum { DT_F32 = 0, DT_BF16 = 1 };
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3, ACT_HSWISH = 4, ACT_HSIGMOID = 5 };
 
+struct StreamArgs;
+
 // Implicit-GEMM view of conv / GEMM / attention products:  Y[m][n] = sum_k A[m][k] * B[n][k].
 //   rows m  = output positions (image, oh, ow), cols n = output channels, k = (tap r, tap s, ci).
 //   A is gathered from a channels-last tensor, B rows are contiguous in k (b_trans == 0) or
@@ -73,6 +75,7 @@ struct GemmArgs {
     // A whole attention as one launch (attn_scores != null; bf16, K = 64 features per head, at most ATTENTION_KEYS_MAX keys): x is qkv, y the context, H the
     // keys, zh the heads, zb the images; scores and probabilities are written as their own operators would.
     void *attn_scores, *attn_probs;
+    const StreamArgs *dw;      // the depthwise convolution that the same launch forms from this product (null: none); valid during the call only
 };
 
 // Channels-last streaming operators.  Sub-range: images [n_lo,n_hi), channels [c_lo,c_hi).
@@ -111,6 +114,7 @@ LaunchInfo launch_igemm(const GemmArgs &a, hipStream_t s, bool dry, int phase = 
 LaunchInfo launch_stem(const GemmArgs &a, hipStream_t s, bool dry);        // launch_igemm hands over operators marked `stem`
 LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry);       // and operators marked `halo`
 LaunchInfo launch_attention(const GemmArgs &a, hipStream_t s, bool dry);    // and whole attentions (attn_scores)
+LaunchInfo launch_expand_dw(const GemmArgs &g, const StreamArgs &d, hipStream_t s, bool dry);   // and a pointwise with a depthwise convolution (dw)
 LaunchInfo launch_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase);   // and operators with `kwaves`
 bool rows_takes(const GemmArgs &a);                                         // short K: launch_rows instead of the tiled kernels
 LaunchInfo launch_rows(const GemmArgs &a, hipStream_t s, bool dry);

@@ -441,6 +441,84 @@ def test_attention_whose_context_lies_where_the_scores_were():
     sess.close()
 
 
+# batch, h, w, cin, c, window, stride, activations: bands that end inside the image, one band, images of one row or column, channels that end
+# inside a block of 32, K of half a 32-byte group, of one block and of several, cut into slices (few tiles) or not (many)
+EXPAND = [(1, 28, 28, 32, 192, 3, 1, "relu6", "relu6"), (2, 27, 23, 24, 40, 3, 2, "relu", "none"), (3, 14, 13, 64, 72, 3, 1, "none", "relu"), (1, 14, 14, 96, 576, 3, 2, "relu6", "relu6"),
+          (2, 7, 7, 160, 960, 3, 1, "hswish", "hswish"), (9, 14, 14, 112, 136, 5, 2, "gelu", "relu"), (5, 9, 11, 48, 56, 5, 1, "relu", "gelu"), (2, 1, 28, 40, 32, 3, 1, "relu", "relu"),
+          (2, 28, 1, 40, 32, 3, 2, "relu", "relu"), (1, 56, 55, 8, 96, 3, 1, "relu6", "relu6"), (1, 97, 113, 16, 24, 3, 2, "relu", "relu6"), (1, 2, 2, 16, 8, 5, 1, "relu", "none"),
+          (40, 7, 7, 160, 200, 3, 1, "relu", "relu"), (1, 1, 1, 264, 64, 3, 2, "relu", "relu"), (33, 13, 15, 104, 96, 3, 2, "relu6", "none")]
+
+
+@pytest.mark.parametrize("spec", EXPAND, ids=lambda s: "x".join(map(str, s[:7])))
+def test_pointwise_and_depthwise_as_one_launch(spec):
+    """expand_dw_kernel against the oracle and, every tensor, against the two launches; decomposing either operator or a sync edge between
+    them brings the two launches back, other edges do not."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    batch, h, w, cin, c, k, stride, act1, act2 = spec
+    tenants = []
+    for i in range(2):
+        b = G._B(f"expand{i}", "bf16", batch)
+        x, wide = b.tensor(batch, 8, h, w), b.tensor(batch, cin + 16, h, w)
+        y = b.conv(x, cin, 1, 1, 0, "none", out=b.view(wide, 8, cin)) if i else b.conv(x, cin, 1, 1, 0, "none")       # a window as input
+        y = b.conv(b.conv(y, c, 1, 1, 0, act1), c, k, stride, k // 2, act2, groups=c)
+        tenants.append(b.done(x, b.conv(y, 16, 1, 1, 0, "relu")))
+    check(tenants, ["expand_dw_bf16"], [("batch", 2), ("cout", 2)] if batch > 1 else [("cout", 2)])
+    sess = harness.Session(tenants, [G.materialise(t, 411, i << 20) for i, t in enumerate(tenants)])
+
+    def snapshot():
+        sess.poison_outputs()
+        sess.run(B.GACER_MODE_PLAN, 2)
+        return [sess.tensor_bytes(i, op.out) for i, t in enumerate(tenants) for op in t.ops]
+
+    def fused():
+        return sorted((r["tenant"], r["op"]) for r in sess.trace(B.GACER_MODE_PLAN, 1) if r["kernel"].startswith("expand_dw_bf16"))
+    want = snapshot()
+    assert fused() == [(0, 1), (1, 1)] and sess.launch_count() == 8
+    sess.set_fuse_affine(False)
+    assert snapshot() == want and fused() == [] and sess.launch_count() == 8
+    sess.set_fuse_affine(True)
+    for syncs, left in [([(0, 1, 1, 3)], [(1, 1)]), ([(0, 0, 1, 2)], [(0, 1)]), ([(0, 2, 1, 3, 1)], [(1, 1)]), ([(0, 2, 1, 1), (0, 0, 1, 3)], [(0, 1), (1, 1)])]:
+        sess.set_plan([], syncs)
+        assert fused() == left and snapshot() == want, syncs
+    for op in (1, 2):
+        sess.set_plan([(0, op, "cout", 2), (1, 0, "cout", 2)], [])
+        assert fused() == [(1, 1)] and snapshot() == want, op
+    sess.close()
+
+
+def test_pointwise_and_depthwise_over_a_buffer_that_is_used_again():
+    """The depthwise result where the pointwise operator's input was: two launches, and the outputs of tensors with memory of their own."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
+    from synth import graphs as G
+    b = G._B("turn", "bf16", 2)
+    x = b.tensor(2, 8, 14, 14)
+    first = b.conv(x, 64, 1, 1, 0, "none")
+    y = b.conv(b.conv(first, 64, 1, 1, 0, "relu"), 64, 3, 1, 1, "relu", groups=64)
+    t = b.done(x, b.conv(y, 16, 1, 1, 0, "relu"))
+    sess = harness.Session([t], [G.materialise(t, 411, 0)])
+
+    def run():
+        sess.run(B.GACER_MODE_SEQUENTIAL, 2)
+        return sess.tensor_bytes(0, t.output), any(r["kernel"].startswith("expand_dw") for r in sess.trace(B.GACER_MODE_SEQUENTIAL, 1))
+    want, fused = run()
+    assert fused
+    sess._descs[0].tensors[y].dptr = sess._descs[0].tensors[first].dptr
+    sess.poison_outputs()
+    B.check(sess.ctx, B.gacer_load_tenants(sess.ctx, sess._descs, 1))
+    got, fused = run()
+    assert got == want and not fused
+    sess.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_depthwise_output_tiles(dtype):
     """Every output tile of the depthwise kernel (from one output per thread to 2 x 4, chosen by the number of outputs), 3x3 and 5x5,
