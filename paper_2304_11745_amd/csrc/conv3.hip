@@ -5,7 +5,8 @@
 // x BN channels.  Per block of 32 channels the positions and their one-pixel halo (for 256 positions at most 384 pixels of 64
 // bytes) go into LDS by direct loads (zeros left and right of the image); all nine taps read their A fragments from there, a tap being a fixed
 // displacement of the LDS row.  Taps above or below an image read a row of zeros instead.  The weights stream past in stages of
-// one tap (BN = 128, three stages) or three taps (BN = 64, two stages).  Two input blocks alternate, the next one being
+// one tap (BN = 128, three stages) or three taps (BN = 64, three stages, or two where that leaves room for a second workgroup of 256
+// positions).  Two input blocks alternate, the next one being
 // requested while this one is used.  The step structure is that of igemm_dma_kernel: counted waits, one bare barrier per
 // step, fragments one k group ahead, requests spread between the MFMA groups.
 //
@@ -15,6 +16,10 @@
 // 224x224 64->64 284.6 / 179.0, 112x112 64->128 110.7 / 80.2, 112x112 128->128 156.4 / 122.2, 56x56 256->256 153.8 / 119.3,
 // 28x28 512->512 144.2 / 112.4 (1053 TFLOP/s), 56x56 64->64 22.0 / 16.8.  Outputs finished in registers (store_tiles) took, before / after:
 // 16 images 112x112 64->128 49.0 / 44.5, 56x56 64->64 11.1 / 10.4, 224x224 64->64 85.3 / 81.3, 8 images 112x112 128->128 39.2 / 36.9.
+//
+// A third weight stage where BN = 64, us: 8 images 28x28 512->512 37.7 / 32.3, 16 images 28x28 128->128 10.0 / 8.6 (on the tiled kernels before),
+// 14x14 512->512 25.5 / 20.7 (likewise), 32 images 28x28 128->128 14.6 / 12.2.  A workgroup alone on its unit keeps the matrix cores 52 %
+// busy; reading fragments two or three k groups ahead, more stages and work put between the MFMAs of a group change that by 1 to 3 %.
 //
 // An output element is one MFMA chain over channel blocks of 32, in a block over the taps in ascending order, whatever the tile;
 // which kernel an operator takes depends on its unsplit shape only, so every chunk of it adds alike.
@@ -41,22 +46,28 @@ template <int N> __device__ __forceinline__ void wait_loads()       // at most N
     asm volatile("" ::: "memory");
 }
 
-template <int BM, int BN>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+// the wait for N to 0 outstanding loads, `pending` being a constant once the steps are unrolled
+template <int N> __device__ __forceinline__ void wait_pending(int pending)
+{
+    if (pending == N) wait_loads<N>();
+    else if constexpr (N > 0) wait_pending<N - 1>(pending);
+}
+
+// TPS: taps per step; NSB: weight stages
+template <int BM, int BN, int TPS, int NSB>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2 * (2 * conv3_input_bytes(BM) + NSB * TPS * BN * ROWB) <= 160 * 1024 ? 2 : 1)))
 void conv3_kernel(GemmArgs a, Conv3Geom geo)
 {
     constexpr int WM = BM == 256 && BN == 64 ? 4 : 2, WN = 4 / WM;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int ROWS = conv3_rows(BM);       // input pixels (LDS rows) per tile and channel block
-    constexpr int TPS = BN == 128 ? 1 : 3;     // taps per step
-    constexpr int NSB = BN == 128 ? 3 : 2;     // weight stages
     constexpr int SPB = 9 / TPS;               // steps per channel block (a multiple of NSB over two blocks)
     constexpr int NB = BN * TPS / 64;          // weight loads per thread and step
     constexpr int NA = ROWS / 64;              // input loads per thread and channel block
     constexpr int A_STEPS = TPS == 1 ? NA : 2, PA = NA / A_STEPS;               // the steps of a block that request inputs, and how many each
     constexpr int G = 2 * TPS;                 // k groups (32 bytes of k) per step
     constexpr int ABYTES = conv3_input_bytes(BM), BBYTES = BN * TPS * ROWB;
-    static_assert(NA % A_STEPS == 0 && A_STEPS <= SPB * 2 / 3, "inputs are requested in the first two thirds of a block");
+    static_assert(NSB <= 3 && 2 * SPB % NSB == 0 && NA % A_STEPS == 0 && A_STEPS <= SPB * 2 / 3, "inputs are requested in the first two thirds of a block");
 
     // separate arrays named by compile-time indices: the compiler can tell what is being filled from what is being read
     __shared__ __align__(1024) unsigned char a0[ABYTES];
@@ -197,17 +208,15 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
                 mfmas(set ^ 1);
                 __builtin_amdgcn_sched_barrier(SCHED_ALU_MAY_CROSS);
             }
-            // The weights of the next step have landed.  Younger than them: with three stages the inputs of the step before
-            // and this step's requests, with two stages this step's inputs.  Before a new block no input is outstanding.
-            constexpr int NA_MAX = 2 * PA + NB;
-            const int before = t > 0 && t - 1 < A_STEPS ? PA : 0;
-            const int pending = NSB == 3 ? before + NB + na : na;
-            static_assert(NA_MAX < 16, "the wait count is encoded in four bits");
-            if (pending == 0) wait_loads<0>();
-            else if (pending == PA) wait_loads<PA>();
-            else if (pending == NB) wait_loads<NB>();
-            else if (pending == NB + PA) wait_loads<NB + PA>();
-            else wait_loads<NB + 2 * PA>();
+            // The weights of the next step, requested NSB - 2 steps ago, have landed.  Younger than them: the inputs of that step and all
+            // requests since (a step requests weights first; ahead of the first block nothing but weights, and counting fewer is safe).  Before a
+            // new block its inputs have landed too; younger than those: the weights requested since.
+            auto inputs = [&](int step) { return step >= 0 && step % SPB < A_STEPS ? PA : 0; };
+            int pending = inputs(u - NSB + 2);
+#pragma unroll
+            for (int w = u - NSB + 3; w <= u; ++w) pending += NB + inputs(w);
+            if (t == SPB - 1 && pending > (SPB - A_STEPS) * NB) pending = (SPB - A_STEPS) * NB;
+            wait_pending<(NSB - 2) * (NB + PA) + PA>(pending);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
@@ -225,7 +234,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     });
 }
 
-template <int BM, int BN>
+template <int BM, int BN, int TPS, int NSB>
 static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
 {
     Conv3Geom g;
@@ -239,8 +248,8 @@ static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
     LaunchInfo li;
     li.workgroups = g.tiles_m * g.tiles_n;
     li.threads = THREADS;
-    li.lds_bytes = 2 * conv3_input_bytes(BM) + (BN == 128 ? 3 : 6) * BN * ROWB;
-    li.wg_per_cu = 2;
+    li.lds_bytes = 2 * conv3_input_bytes(BM) + NSB * TPS * BN * ROWB;
+    li.wg_per_cu = 160 * 1024 / li.lds_bytes;
     static const std::string name = "conv3_bf16_" + std::to_string(BM) + "x" + std::to_string(BN);
     li.kernel = name.c_str();
     li.phases = 1;
@@ -254,15 +263,18 @@ static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
     divisor(g.tiles_strip, g.div_strip);
     divisor(g.tiles_m, g.div_tiles_m);
     divisor(g.tiles_n, g.div_tiles_n);
-    GACER_LAUNCH((conv3_kernel<BM, BN>), dim3(li.workgroups), dim3(THREADS), 0, s, a, g);
+    GACER_LAUNCH((conv3_kernel<BM, BN, TPS, NSB>), dim3(li.workgroups), dim3(THREADS), 0, s, a, g);
     return li;
 }
 
 LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry)
 {
     const Conv3Tile t = conv3_tile(a);
-    if (t.bn == 128) return go_conv3<256, 128>(a, s, dry);
-    return t.bm == 256 ? go_conv3<256, 64>(a, s, dry) : go_conv3<128, 64>(a, s, dry);
+    if (t.bn == 128) return go_conv3<256, 128, 1, 3>(a, s, dry);
+    if (t.bm == 128) return go_conv3<128, 64, 3, 3>(a, s, dry);
+    // a third weight stage costs the second workgroup its place on the unit: where there is at most one anyway
+    if (conv3_wgs(a, 256, 64) <= 256) return go_conv3<256, 64, 3, 3>(a, s, dry);
+    return go_conv3<256, 64, 3, 2>(a, s, dry);
 }
 
 }  // namespace gacer

@@ -47,15 +47,12 @@ inline int64_t conv3_wgs(const GemmArgs &a, int bm, int bn)
     return strips * ((positions + bm - 1) / bm) * ((a.n_hi - a.n_lo + bn - 1) / bn);
 }
 
-// Whether the operator (its UNSPLIT shape, so that every chunk of it adds in the same order) runs on conv3_kernel: from about
-// three tiles of 256 positions on four compute units.  One launch in a chain, microseconds on the tiled kernels / here, by the number of
-// such tiles: 196 (16 images 28x28 512->512) 75.6 / 57.4, (8 images 56x56 128->256) 25.7 / 20.6, (4 images 112x112 64->128) 18.5 / 14.5,
-// (16 images 56x56 64->64) 12.6 / 10.5.  The limit is where it was before the epilogue of both became shorter; today the crossing lies at
-// about 100: 147 (12 images 56x56 64->64) 10.8 / 9.9, 100 (8 images 28x28 512->512) 38.3 / 37.7, 98 (4 images 56x56 256->256)
-// 23.0 / 22.3, (8 images 56x56 64->64) 8.7 / 7.6, 68 (3 images 75x75 128->128) 12.9 / 13.6, 52 (4 images 28x28 512->512) 27.2 / 28.6,
-// 50 (2 images 56x56 256->256) 16.0 / 17.0.  Chunks of the operators taken (measured with longer epilogues): half of the images or of the
-// channels 42.2 / 36.2 (8 images 28x28 512->512), a quarter 28.1 / 27.0 (4 images) and 28.4 / 32.4 (128 channels), an eighth
-// 20.4 / 22.8 (2 images); 2 images 56x56 256->256 16.4 / 15.1.
+// Whether the operator (its UNSPLIT shape, so that every chunk of it adds in the same order) runs on conv3_kernel: from about three tiles
+// of 128 positions x 64 channels on four compute units.  One launch in a chain, microseconds on the tiled kernels / here, by the
+// number of such tiles: 392 (16 images 28x28 128->256) 20.4 / 16.3, (32 images 28x28 128->128) 14.6 / 12.2, 392 (4 images 56x56 256->256) 22.3 / 19.0, 200
+// (16 images 14x14 512->512) 25.5 / 20.7, 196 (32 images 14x14 256->256) 15.5 / 12.8, (16 images 28x28 128->128) 10.0 / 8.6, (8 images 56x56 64->64) 7.2 / 6.8, 111
+// (3 images 37x41 192->192) 9.9 / 10.1, 104 (8 images 14x14 512->512) 18.5 / 19.5, 100 (16 images 14x14 256->256) 11.4 / 12.1, 98 (8 images 28x28
+// 128->128) 7.5 / 8.2.  Chunks of the operators taken: halves of 196 tiles are up to 10 % slower than on the tiled kernels.
 inline bool conv3_takes(const GemmArgs &a)
 {
     if (a.dtype != DT_BF16 || a.kh != 3 || a.kw != 3 || a.stride != 1 || a.pad != 1 || a.Cin % 64 || a.b_trans || a.pre_scale) return false;
@@ -63,25 +60,23 @@ inline bool conv3_takes(const GemmArgs &a)
     if (((uintptr_t)a.x | (uintptr_t)a.w) & 15) return false;
     if (conv3_strip(a.W) < CONV3_STRIP_MIN) return false;
     const int N = a.n_hi - a.n_lo;
-    return N > 32 && conv3_wgs(a, 256, conv3_bn(N)) >= 180;
+    return N > 32 && conv3_wgs(a, 128, 64) >= 180;
 }
 
 // Tile of one launch, chunks of a decomposed operator included (the tile never changes an element's order of additions).
-// 256 x 128 moves the fewest bytes per MFMA once there are well over one such tile per compute unit; 256 x 64 while those reach
-// half of the units; 128 x 64 below.  One launch alone, microseconds of 256x128 / 256x64 / 128x64, by the number of 256x128 tiles:
-// 50 (2 images 56x56 256->256) 33.4 / 19.1 / 15.1, 100 (8 images 28x28 512->512) 59.7 / 36.2 / 37.1, 196 (16 of those) 66.3 / 57.0 /
-// 71.6, 358 (16 images 75x75 128->128) 35.9 / 32.5 / 38.3, 392 (16 images 56x56 256->256) 59.7 / 62.7 / 74.4, 784 (32 of those)
-// 114.6 / 109.8 / 134.4, 1568 (32 images 112x112 64->128) 77.2 / 78.3 / 93.7.  By the number of 256x64 tiles at 64 channels: 98 (8
-// images 56x56) 10.4 / 7.9, 196 (16) 12.2 / 9.8, 264 (3 images 150x150) 14.1 / 15.3, 392 (32 images 56x56) 16.0 / 18.1.
-// Alone, 128 x 64 gains up to 256 tiles, but other tenants use the units that a launch leaves: the round of VGG-16, 8 images, halved
-// along the batch, ResNet-50, 16 images, halved along the channels, and MobileNetV3, 32 images, takes 1760 us with 128 x 64 below 256
-// tiles, 1730 below 128 and 1717 with 256 x 128 throughout (which alone costs that VGG 864 instead of 775, in quarters 1436
-// instead of 1183).
+// 256 x 128 moves the fewest bytes per MFMA once there are well over one such tile per compute unit; 256 x 64 down to three of those on
+// four units if K is long; 128 x 64 below.  One launch alone, microseconds of 256x128 / 256x64 / 128x64, by the number of 256x64 tiles: 98 (16
+// images 28x28 128->128) 19.8 / 12.1 / 8.6, 104 (16 images 14x14 512->512) 55.7 / 29.0 / 20.7, 196 (32 images 28x28 128->128) 20.4 / 12.9 / 12.2, (64 images
+// 14x14 256->256) 32.5 / 19.0 / 19.9, 200 (8 images 28x28 512->512) 57 / 32.3 / 35.7, 392 (8 images 56x56 256->256) 33.9 / 31.3 / 38.4, 784 (16 images 28x28
+// 512->512) 59.3 / 57.5 / 73.2; at 64 channels 196 (16 images 56x56) 14.5 / 9.8 / 9.1, 392 (32 images 56x56) - / 16.0 / 18.1.
+// In rounds other tenants use the units that a launch leaves, so alone is not all: VGG-16, 8 images, halved along the batch, ResNet-50, 16
+// images, halved along the channels, and MobileNetV3, 32 images, took 1760 us with 128 x 64 below 256 tiles, 1730 below 128 (both with two
+// weight stages).
 struct Conv3Tile { int bm, bn; };
 inline Conv3Tile conv3_tile(const GemmArgs &a)
 {
     if (conv3_bn(a.n_hi - a.n_lo) == 128 && conv3_wgs(a, 256, 128) > 360) return {256, 128};
-    return {conv3_wgs(a, 256, 64) >= 128 ? 256 : 128, 64};
+    return {conv3_wgs(a, 256, 64) >= (a.Cin >= 256 ? 180 : 257) ? 256 : 128, 64};
 }
 
 }  // namespace gacer

@@ -318,6 +318,18 @@ def test_input_staged_once_for_nine_taps():
     check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128"], [("batch", 2), ("cout", 2), ("cout", 8)], ["conv3_bf16_128x64", "conv3_bf16_256x64"])
 
 
+@pytest.mark.parametrize("tile,spec", [("128x64", (4, 61, 59, 64, 120, "relu", True)), ("128x64", (16, 27, 29, 64, 130, "hswish", False)), ("256x64", (4, 57, 53, 256, 250, "none", False))])
+def test_staged_3x3_with_three_weight_stages(tile, spec):
+    """conv3_kernel with few tiles: 128 positions, and 256 where K is long, both with three stages of weights; ragged images and channels."""
+    from synth import graphs as G
+    batch, h, w, cin, cout, act, res = spec
+    b = G._B("staged", "bf16", batch)
+    x = b.tensor(batch, cin, h, w)
+    y = b.conv(x, cout, 1, 1, 0, "none") if res else -1
+    ran = check([b.done(x, b.conv(x, cout, 3, 1, 1, act, res=y))], ["conv3_bf16_" + tile], [("batch", 2), ("cout", 2)])
+    assert sum(n.startswith("conv3") for n in ran) == 1
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_rows_with_short_k(dtype):
     """rowgemm_kernel: every number of 32-byte k groups, K that fills half a group, one column of tiles, two and more, four side by
