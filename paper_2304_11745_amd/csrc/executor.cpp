@@ -457,6 +457,8 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
         // (392x256x1024: 9.4 and two 10.1).  Those were measured before launches and pass became shorter; today, and on the tiled
         // kernels: 8x1000x2048 7.4 / 9.1, 49x512x4608 9.8 / 12.3, 169x256x2304 8.7 / 10.7, 147x512x4608 in three 13.6 / 17.0, 8x4096x4096
         // in two 18.2 / 26.1, 32x1000x1280 in five 7.3 / 9.4.
+        // With 16x16 tiles (see launch_slices) one workgroup row would do for some of these (8x1000x1280 in five 6.8, in one 5.5; 8x4096x4096 in two
+        // 18.3, in one 14.2), but the longer chains err more against 64-bit sums (1.3e-7 -> 2.3e-7, 2.9e-7 -> 4.1e-7).
         // The cut follows the unsplit shape: chunks of a long product can be slower than on the tiled kernels, which cut the unsplit
         // shape finer (quarters of 784x512x2048, of 400 tiles, 18.1 / 13.7 each, halves of 392x512x2048 14.3 / 12.9; unsplit, today,
         // 21.1 / 25.1 and 12.5 / 17.1).

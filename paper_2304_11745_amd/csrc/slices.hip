@@ -1,6 +1,6 @@
 // K slices side by side in one workgroup: for products with few output tiles and a long K (late convolution layers, short
-// token batches, classifiers).  Wave w of the workgroup owns slice w of the K range and a whole 32x32 output tile; the slice
-// accumulators meet in LDS, are added in ascending order and go through the epilogue, so one launch does what a slice kernel
+// token batches, classifiers).  Wave w of the workgroup owns slice w of the K range and a whole 32x32 output tile (fp32: 16x16 where
+// there are few); the slice accumulators meet in LDS, are added in ascending order and go through the epilogue, so one launch does what a slice kernel
 // plus a finishing pass over fp32 partial tiles in memory did.  Very long K (the first classifier layer of a VGG) is cut once
 // more over the grid: workgroup row y owns slices y * S .. y * S + S - 1 and writes its sum to the workspace, splitk_finish
 // adds those.  An output element is the sum of its slice chains in that fixed order, whatever part of the operator is launched.
@@ -61,14 +61,17 @@ struct SlicesArgs {
     int pre_act;
 };
 
-template <int DT, int LOAD, int S, int PRE_MAX = 0>
+template <int DT, int LOAD, int S, int PRE_MAX = 0, int TILE = 32>
 __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
 {
     typedef typename El<DT>::T T;
     constexpr int VEC = El<DT>::VEC;
     constexpr int ESZ = (int)sizeof(T);
     constexpr int BE = 128 / ESZ;               // elements per batch and row
-    constexpr int STAGE = 64 * 128;             // bytes of one wave's stage: 32 A rows, then 32 B rows
+    constexpr int PL = TILE / 8;                // loads of A rows, and of B rows, per batch
+    constexpr int HALF = TILE * 128, STAGE = 2 * HALF;                          // bytes of one wave's stage: A rows, then B rows
+    constexpr bool T32 = TILE == 32;
+    static_assert(T32 || (TILE == 16 && DT == DT_F32), "tile");
     constexpr bool PRE = LOAD == SL_AFFINE, TAPS = LOAD == SL_TAPS || LOAD == SL_TAPS_ANY, PITCH = LOAD == SL_ROWS || PRE;
     __shared__ __align__(1024) unsigned char st0[S * STAGE];
     __shared__ __align__(1024) unsigned char st1[S * STAGE];
@@ -79,16 +82,16 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
     const int xcd = (int)blockIdx.x & 7;        // see xcd_contiguous
     const int tile = xcd * a.run + min(xcd, a.extra) + ((int)blockIdx.x >> 3);
     const int outer = div_by(tile, a.div_inner), inner = tile - outer * a.inner;
-    const int m0 = a.m_lo + (a.n_major ? inner : outer) * 32, n0 = a.n_lo + (a.n_major ? outer : inner) * 32;
+    const int m0 = a.m_lo + (a.n_major ? inner : outer) * TILE, n0 = a.n_lo + (a.n_major ? outer : inner) * TILE;
     const __amdgpu_buffer_rsrc_t xr = rsrc_of(a.x, a.x_bytes), wr = rsrc_of(a.w, a.w_bytes);
 
     // Load p of a stage fills rows 8 p .. 8 p + 7: lane l row 8 p + l / 8, slot l % 8, which holds logical chunk
     // (l % 8) ^ ((row / 2) % 8) -- two values per lane, by the parity of p
     const int c0 = (lane & 7) ^ (lane >> 4), row0 = lane >> 3;
     const int kl[2] = {c0 * VEC, (c0 ^ 4) * VEC};
-    unsigned a_off[4], a_bad[4], b_off[4];      // a_bad: one bit per tap, set where the tap reads nothing
+    unsigned a_off[PL], a_bad[PL], b_off[PL];      // a_bad: one bit per tap, set where the tap reads nothing
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
+    for (int p = 0; p < PL; ++p) {
         const unsigned kb = (unsigned)(kl[p & 1] * ESZ);
         b_off[p] = (unsigned)(n0 + row0) * a.w_pitch + (unsigned)p * 8u * a.w_pitch + kb;
         a_bad[p] = 0u;
@@ -138,10 +141,10 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
 #pragma unroll
             for (int h = 0; h < 2; ++h) bad[h] = (tail[h] & last) | beyond;
         }
-        unsigned off[4];
+        unsigned off[PL];
         if constexpr (LOAD == SL_TAPS) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) off[p] = (a_off[p] + da) | (a_bad[p] << (31 - tap) & OOB) | bad[p & 1];
+            for (int p = 0; p < PL; ++p) off[p] = (a_off[p] + da) | (a_bad[p] << (31 - tap) & OOB) | bad[p & 1];
         } else if constexpr (LOAD == SL_TAPS_ANY) {
             unsigned dl[2], tl[2];
 #pragma unroll
@@ -152,17 +155,17 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
                 tl[h] = 31u - ((unsigned)t & 31u);
             }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) off[p] = (a_off[p] + dl[p & 1]) | (a_bad[p] << tl[p & 1] & OOB) | bad[p & 1];
+            for (int p = 0; p < PL; ++p) off[p] = (a_off[p] + dl[p & 1]) | (a_bad[p] << tl[p & 1] & OOB) | bad[p & 1];
         } else {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) off[p] = a_off[p] | bad[p & 1];
+            for (int p = 0; p < PL; ++p) off[p] = a_off[p] | bad[p & 1];
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
+        for (int p = 0; p < PL; ++p)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GACER_LDS(stage + p * 1024), 16, (int)off[p], TAPS ? 0 : soff, 0, 0);
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + 4096 + p * 1024), 16, (int)(b_off[p] | bad[p & 1]), soff, 0, 0);
+        for (int p = 0; p < PL; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, GACER_LDS(stage + HALF + p * 1024), 16, (int)(b_off[p] | bad[p & 1]), soff, 0, 0);
         kb += BE;
         if constexpr (LOAD == SL_TAPS) {
             kci += BE;
@@ -177,11 +180,12 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
         }
     };
 
-    // the four consecutive channels of one row that thread t of the first 256 finishes: accumulator element e of lane l is row
-    // (e/4)*8 + (l/32)*4 + e%4, column l%32; thread t owns element t / 16 of lanes 4 (t % 16) .. + 3 and reads LDS contiguously
+    // the four consecutive channels of one row that thread t of the first 256 (64) finishes: accumulator element e of lane l is row
+    // (e/4)*8 + (l/32)*4 + e%4, column l%32 (16x16 tiles: row l/16*4 + e, column l%16); thread t owns element t / 16 of lanes 4 (t % 16)
+    // .. + 3 and reads LDS contiguously
     const int e0 = tid >> 4, l0 = (tid & 15) * 4;
-    const int m = m0 + (e0 >> 2) * 8 + (l0 >> 5) * 4 + (e0 & 3), n = n0 + (l0 & 31);
-    const bool inside = tid < 256 && m < a.m_hi && n < a.n_hi, n_vec = inside && a.vec_out && n + 4 <= a.n_hi;
+    const int m = m0 + (T32 ? (e0 >> 2) * 8 + (l0 >> 5) * 4 + (e0 & 3) : (l0 >> 4) * 4 + e0), n = n0 + (l0 & (TILE - 1));
+    const bool inside = tid < TILE * TILE / 4 && m < a.m_hi && n < a.n_hi, n_vec = inside && a.vec_out && n + 4 <= a.n_hi;
     const unsigned o = (unsigned)m * (unsigned)a.y_row + (unsigned)n;
     typedef typename std::conditional<DT == DT_BF16, uint2, uint4>::type R;
     uint4 braw;
@@ -196,12 +200,16 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
     // knowing any more which stage they read, and waits for every outstanding request before them
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef typename std::conditional<DT == DT_BF16, bf16x8, f32x4>::type F;
-    f32x16 acc;
+    typename std::conditional<T32, f32x16, f32x4>::type acc;
+    constexpr int NE = T32 ? 16 : 4;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    const int lrow = lane & 31, lhalf = lane >> 5;
+    for (int e = 0; e < NE; ++e) acc[e] = 0.f;
+    // 16x16 tiles: a quarter of the wave has one k of an MFMA's four.  So that they follow each other as in the 32x32 MFMAs (0, 4, 1, 5, 2, 6, 3,
+    // 7 of a 32-byte group), quarters 0 and 2 read the group's first chunk, 1 and 3 its second, the upper two its odd elements.
+    const int lrow = lane & (TILE - 1), lhalf = T32 ? lane >> 5 : (lane >> 4) & 1;
+    const bool odd = !T32 && lane >= 32;
     const int frag = lrow * 128, frag_lo = (lhalf ^ ((lrow >> 1) & 7)) * 16;
-    constexpr int WAIT_BATCH = (8 & 15) | (7 << 4) | (15 << 8);                 // vmcnt(8): the older of the two batches in flight has landed
+    constexpr int WAIT_BATCH = (2 * PL & 15) | (7 << 4) | (15 << 8);            // vmcnt: the older of the two batches in flight has landed
     constexpr int WAIT_LAST = (7 << 4) | (15 << 8);                             // vmcnt(0)
     constexpr int WAIT_LDS = 15 | (7 << 4) | (3 << 14);                         // lgkmcnt(0)
     // SL_AFFINE: the waves of channel 0 also store the transformed A, four stores per batch behind the batch's requests (the
@@ -209,7 +217,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
     // at every second batch, where a wait for eight would cost one memory latency (at the loop's entry there are no stores yet).
     // With that and the parameters requested together with the operands, DenseNet's 40 such products of 8 images take 299 us in
     // bf16, 378 before.  So that the counts hold, every step requests a batch, beyond the slice one of zeros.
-    constexpr int WAIT_STORED = 12 | (7 << 4) | (15 << 8);
+    constexpr int WAIT_STORED = (2 * PL + 4) | (7 << 4) | (15 << 8);
     const __amdgpu_buffer_rsrc_t yr = rsrc_of(PRE ? a.pre_y : nullptr, PRE && n0 == 0 ? (unsigned)(a.m_hi * a.K) * ESZ : 0u);
     auto step = [&](unsigned char *stage, int k0, int wait, bool more) {
         if (wait == WAIT_STORED) __builtin_amdgcn_s_waitcnt(WAIT_STORED);
@@ -220,7 +228,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             fa[g] = *(const F *)(stage + frag + (frag_lo ^ (g * 32)));
-            fb[g] = *(const F *)(stage + 4096 + frag + (frag_lo ^ (g * 32)));
+            fb[g] = *(const F *)(stage + HALF + frag + (frag_lo ^ (g * 32)));
         }
         // left alone, the scheduler reads fragments group by group between the MFMAs and issues the requests behind most of them
         __builtin_amdgcn_sched_barrier(0);
@@ -243,11 +251,14 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
                 }
                 fa[g] = __builtin_bit_cast(F, affine_vec<DT>(__builtin_bit_cast(uint4, fa[g]), sc, sh, a.pre_act));
                 const i32x4 v = __builtin_bit_cast(i32x4, fa[g]);
-                const unsigned bad = ~(unsigned)(((m0 + lrow - a.m_hi) & (kv - k_end)) >> 31) & OOB;
+                const unsigned bad = (~(unsigned)(((m0 + lrow - a.m_hi) & (kv - k_end)) >> 31) & OOB) | (odd ? OOB : 0u);
                 __builtin_amdgcn_raw_buffer_store_b128(v, yr, (int)((unsigned)((m0 + lrow) * a.K + kv) * ESZ | bad), 0, 0);
             }
             if constexpr (DT == DT_BF16) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[g], fb[g], acc, 0, 0, 0);
+            } else if constexpr (!T32) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? fa[g][1] : fa[g][0], odd ? fb[g][1] : fb[g][0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? fa[g][3] : fa[g][2], odd ? fb[g][3] : fb[g][2], acc, 0, 0, 0);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[g][e], fb[g][e], acc, 0, 0, 0);
@@ -311,8 +322,9 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
     }
 
     // ---- sum over the slices and epilogue; each wave's accumulator goes into its own first stage ----
+    if constexpr (!T32) asm volatile("s_nop 15" : "+v"(acc));                  // see expand_dw_kernel
 #pragma unroll
-    for (int e = 0; e < 16; ++e) *(float *)(w0 + (e * 64 + lane) * 4) = acc[e];
+    for (int e = 0; e < NE; ++e) *(float *)(w0 + (e * 64 + lane) * 4) = acc[e];
     __syncthreads();
     if (!inside) return;
     const unsigned char *part = st0 + (e0 * 64 + l0) * 4;
@@ -351,12 +363,12 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
 }
 
 // S waves per workgroup (one K slice each), ksplit workgroups along K
-template <int DT, int S>
+template <int DT, int S, int TILE = 32>
 static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     typedef typename El<DT>::T T;
     constexpr int ESZ = (int)sizeof(T);
-    const int tiles_m = (a.m_hi - a.m_lo + 31) / 32, tiles_n = (a.n_hi - a.n_lo + 31) / 32;
+    const int tiles_m = (a.m_hi - a.m_lo + TILE - 1) / TILE, tiles_n = (a.n_hi - a.n_lo + TILE - 1) / TILE;
     LaunchInfo li;
     li.workgroups = tiles_m * tiles_n * a.ksplit;
     li.threads = 64 * S;
@@ -368,7 +380,7 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
     // knows that the loads into the stages do not fill it, and waits for them.)
     constexpr int PRE_SMALL = S == 4 ? SLICES_PRE_MAX / 2 : SLICES_PRE_MAX;
     const bool small = a.K <= PRE_SMALL && tiles_m * tiles_n * a.ksplit > 256;
-    li.lds_bytes = S * 16384 + (a.pre_scale ? 8 * (small ? PRE_SMALL : SLICES_PRE_MAX) : 0);
+    li.lds_bytes = S * 512 * TILE + (a.pre_scale ? 8 * (small ? PRE_SMALL : SLICES_PRE_MAX) : 0);
     li.wg_per_cu = (160 * 1024) / li.lds_bytes;
     static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S);
     static const std::string n_one = "igemm_slices_" + shape, n_pre = "igemm_affine_slices_" + shape;
@@ -414,12 +426,12 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
         const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
         // rows of one pitch: unit stride and no gap between images (a single image has none)
         const bool pitch = !taps && a.stride == 1 && a.x_img == (int64_t)a.Ho * a.Wo * a.x_pix;
-        if (a.pre_scale && small) GACER_LAUNCH((slices_kernel<DT, SL_AFFINE, S, PRE_SMALL>), grid, block, 0, s, b);
-        else if (a.pre_scale) GACER_LAUNCH((slices_kernel<DT, SL_AFFINE, S, SLICES_PRE_MAX>), grid, block, 0, s, b);
-        else if (pitch) GACER_LAUNCH((slices_kernel<DT, SL_ROWS, S>), grid, block, 0, s, b);
-        else if (!taps) GACER_LAUNCH((slices_kernel<DT, SL_STRIDED, S>), grid, block, 0, s, b);
-        else if (a.Cin * ESZ % 128 == 0) GACER_LAUNCH((slices_kernel<DT, SL_TAPS, S>), grid, block, 0, s, b);
-        else GACER_LAUNCH((slices_kernel<DT, SL_TAPS_ANY, S>), grid, block, 0, s, b);
+        if (a.pre_scale && small) GACER_LAUNCH((slices_kernel<DT, SL_AFFINE, S, PRE_SMALL, TILE>), grid, block, 0, s, b);
+        else if (a.pre_scale) GACER_LAUNCH((slices_kernel<DT, SL_AFFINE, S, SLICES_PRE_MAX, TILE>), grid, block, 0, s, b);
+        else if (pitch) GACER_LAUNCH((slices_kernel<DT, SL_ROWS, S, 0, TILE>), grid, block, 0, s, b);
+        else if (!taps) GACER_LAUNCH((slices_kernel<DT, SL_STRIDED, S, 0, TILE>), grid, block, 0, s, b);
+        else if (a.Cin * ESZ % 128 == 0) GACER_LAUNCH((slices_kernel<DT, SL_TAPS, S, 0, TILE>), grid, block, 0, s, b);
+        else GACER_LAUNCH((slices_kernel<DT, SL_TAPS_ANY, S, 0, TILE>), grid, block, 0, s, b);
     }
     if (a.ksplit > 1 && phase != 1) launch_finish(a, s);
     return li;
@@ -428,6 +440,12 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
 LaunchInfo launch_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
     if (a.dtype == DT_BF16) return a.kwaves == 8 ? go_slices<DT_BF16, 8>(a, s, dry, phase) : go_slices<DT_BF16, 4>(a, s, dry, phase);
+    // 16x16 tiles give the bits of 32x32 ones with a quarter of the matrix work per workgroup and half of its bytes, for twice the bytes per
+    // output: up to two such workgroups per unit.  Us with 32x32 / 16x16, by the number of these: 125x32x1152 (16) 8.67 / 5.50, 1568x32x1152 (196)
+    // 8.91 / 5.88, affine + 125x128x992 (64) 10.8 / 7.0, affine + 500x128x352 (256) 6.66 / 4.90, 392x160x960 (250) 7.60 / 5.15, 128x768x768 (384) 6.48 / 5.74,
+    // 507x256x1152 (512) 9.01 / 8.49, 1568x96x576 (588) 5.70 / 6.53, 1875x128x1152 (944) 9.02 / 13.3.
+    const int64_t t16 = (int64_t)((a.m_hi - a.m_lo + 15) / 16) * ((a.n_hi - a.n_lo + 15) / 16) * a.ksplit;
+    if (t16 <= 512) return a.kwaves == 8 ? go_slices<DT_F32, 8, 16>(a, s, dry, phase) : go_slices<DT_F32, 4, 16>(a, s, dry, phase);
     return a.kwaves == 8 ? go_slices<DT_F32, 8>(a, s, dry, phase) : go_slices<DT_F32, 4>(a, s, dry, phase);
 }
 

@@ -140,6 +140,23 @@ def test_long_k_with_few_tiles_in_fp32():
     assert any(n.startswith("igemm_dma_taps_f32_64x64") for n in ran[416]) and any(n.startswith("igemm_dma_f32_64x64") for n in ran[405]), ran
 
 
+def test_k_slices_on_small_tiles_in_fp32():
+    """16x16 tiles (up to 512 of them) and 32x32 ones give the same bits: whole operators on either side of the line, whose halves and eighths lie
+    below it; rows, strided rows, windows, a fused affine with a remainder of rows and channels, K cut over the grid."""
+    from synth import graphs as G
+    tenants = []
+    for i, (batch, h, w, cin, cout, k, stride, affine, res) in enumerate([
+            (1, 17, 15, 132, 33, 1, 1, False, True), (2, 9, 9, 260, 70, 1, 2, False, False), (3, 5, 5, 128, 32, 3, 1, False, False), (2, 13, 11, 40, 47, 3, 1, False, True),
+            (3, 5, 7, 612, 120, 1, 1, True, False), (1, 7, 7, 100, 31, 1, 1, True, False), (1, 33, 31, 128, 144, 1, 1, False, False), (4, 16, 16, 96, 140, 3, 1, False, False),
+            (4, 23, 11, 200, 132, 1, 1, True, False), (1, 1, 1, 2048, 1000, 1, 1, False, False), (2, 7, 7, 2052, 250, 1, 1, False, True), (8, 1, 1, 4096, 2050, 1, 1, False, False)]):
+        b = G._B(f"small{i}", "f32", batch)
+        x = b.tensor(batch, cin, h, w)
+        r = b.conv(x, cout, 1, stride, 0, "none") if res else -1
+        tenants.append(b.done(x, b.conv(b.affine(x, "relu") if affine else x, cout, k, stride, k // 2, "relu", res=r)))
+    ran = check(tenants, ["igemm_slices_f32_x4", "igemm_slices_f32_x8", "igemm_affine_slices_f32", "splitk_finish"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    assert all("slices" in n or n == "splitk_finish" for n in ran), ran
+
+
 def test_finishing_pass_of_every_number_of_slices():
     """splitk_finish for two, three, four, five and eight slices in fp32, whole vectors and channel counts or chunks that are none, with
     and without a residual and an activation."""
