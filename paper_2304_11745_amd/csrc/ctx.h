@@ -1,6 +1,7 @@
 // Library-internal state behind the opaque gacer_ctx.
 #pragma once
 #include <hip/hip_runtime_api.h>
+#include <memory>
 #include <string>
 #include <vector>
 #include "../../include/gacer.h"
@@ -75,6 +76,7 @@ struct Ctx {
     std::vector<hipEvent_t> t_start, t_end;         // per round, timing enabled
     hipGraphExec_t graph_exec[3] = {nullptr, nullptr, nullptr};   // captured round per mode (optional)
     bool issue_threads = false;                     // one host thread per tenant enqueues that tenant's stream
+    std::shared_ptr<void> issue_pool;               // those threads, from the first run that uses them on (IssuePool in executor.cpp)
     bool fuse_affine = true;                        // launch fusion: an affine operator + the 1x1 convolution that reads it, the operators of an attention, a 1x1 convolution + the depthwise one that reads it
     bool sync_every_launch = false;                 // checking mode: wait for, and check, every kernel before the next is issued
     bool capturing = false;                         // a stream capture is open: nothing may synchronise

@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <condition_variable>
 #include <memory>
 #include <mutex>
 #include <thread>
@@ -892,6 +893,7 @@ gacer_status gacer_create(gacer_ctx **out)
 void gacer_destroy(gacer_ctx *c)
 {
     if (!c) return;
+    c->issue_pool.reset();
     for (Tenant &t : c->tenants) (void)hipStreamSynchronize(t.stream);
     drop_graphs(c);
     release_workspaces(c->tenants);
@@ -1225,8 +1227,9 @@ gacer_status ensure_events(Ctx *c, int rounds)
     return ensure_plan_events(c);
 }
 
-// Enqueues one round from the calling thread: fork from tenant 0's stream, every operator in issue order, join back.
-gacer_status issue_round(Ctx *c, int mode, int round)
+// Enqueues one round from the calling thread: fork from tenant 0's stream, every operator in issue order, join back.  `fork`: an event
+// that has just been recorded on tenant 0's stream (the round's start), or null.
+gacer_status issue_round(Ctx *c, int mode, int round, hipEvent_t fork = nullptr)
 {
     const int NT = (int)c->tenants.size();
     hipStream_t s0 = c->tenants[0].stream;
@@ -1236,8 +1239,10 @@ gacer_status issue_round(Ctx *c, int mode, int round)
                 ISSUE(c, issue_op(c, t, i, c->plain_exec[t][i], s0, false, round, nullptr));
         return GACER_OK;
     }
-    hipEvent_t fork = c->join_events[NT];
-    HIPCHK(c, hipEventRecord(fork, s0));
+    if (!fork) {
+        fork = c->join_events[NT];
+        HIPCHK(c, hipEventRecord(fork, s0));
+    }
     for (int t = 1; t < NT; ++t)
         if (c->tenants[t].stream != s0) HIPCHK(c, hipStreamWaitEvent(c->tenants[t].stream, fork, 0));
     const bool plan = (mode == GACER_MODE_PLAN);
@@ -1280,10 +1285,9 @@ struct ThreadedIssue {
     void worker(int t)
     {
         if (hipSetDevice(c->device) != hipSuccess) { fail_with("hipSetDevice", hipGetLastError()); return; }
-        const int NT = (int)c->tenants.size();
         for (int r = 0; r < rounds; ++r) {
             if (!gate.wait_gen(gate.fork_gen, r + 1)) return;
-            hipError_t e = hipStreamWaitEvent(c->tenants[t].stream, c->join_events[NT], 0);
+            hipError_t e = hipStreamWaitEvent(c->tenants[t].stream, c->t_start[r], 0);
             if (e != hipSuccess) { fail_with("hipStreamWaitEvent(fork)", e); return; }
             if (!issue_tenant(t, r)) return;
             e = hipEventRecord(c->join_events[t], c->tenants[t].stream);
@@ -1297,8 +1301,7 @@ struct ThreadedIssue {
         const int NT = (int)c->tenants.size();
         hipStream_t s0 = c->tenants[0].stream;
         for (int r = 0; r < rounds; ++r) {
-            TI_CHK(hipEventRecord(c->t_start[r], s0));
-            TI_CHK(hipEventRecord(c->join_events[NT], s0));
+            TI_CHK(hipEventRecord(c->t_start[r], s0));      // also the event that the other tenants' streams wait for
             gate.fork_gen.store(r + 1, std::memory_order_release);
             if (!issue_tenant(0, r)) return false;
             for (int t = 1; t < NT; ++t) {
@@ -1312,7 +1315,73 @@ struct ThreadedIssue {
 #undef TI_CHK
 };
 
-gacer_status run_threaded(Ctx *c, int mode, int rounds)
+// The issuing threads of a context, one per tenant but the first, kept from its first threaded run until it stops issuing by threads or is
+// destroyed.  (Started and joined in every run, seven of them took 100 us before the first kernel of a round of eight batch-1 tenants.)
+struct IssuePool {
+    std::mutex mu;
+    std::condition_variable work, done;
+    std::vector<std::thread> threads;
+    ThreadedIssue *job = nullptr;
+    long gen = 0;                            // jobs handed out
+    int wanted = 0, busy = 0;                // threads that the job needs, those still at it
+    bool stop = false;
+
+    ~IssuePool()
+    {
+        { std::lock_guard<std::mutex> g(mu); stop = true; }
+        work.notify_all();
+        for (std::thread &t : threads) t.join();
+    }
+    bool grow(int n)
+    {
+        try {
+            while ((int)threads.size() < n) {
+                const int t = (int)threads.size() + 1;
+                const long seen = gen;       // no job runs while the pool grows
+                threads.emplace_back([this, t, seen] { loop(t, seen); });
+            }
+        } catch (const std::exception &) {
+            return false;
+        }
+        return true;
+    }
+    void start(ThreadedIssue *j, int n)
+    {
+        { std::lock_guard<std::mutex> g(mu); job = j; wanted = busy = n; ++gen; }
+        work.notify_all();
+    }
+    void finish()
+    {
+        std::unique_lock<std::mutex> g(mu);
+        done.wait(g, [this] { return busy == 0; });
+        job = nullptr;
+    }
+    void loop(int t, long seen)
+    {
+        std::unique_lock<std::mutex> g(mu);
+        for (;;) {
+            work.wait(g, [&] { return stop || gen != seen; });
+            if (stop) return;
+            seen = gen;
+            if (t > wanted) continue;
+            ThreadedIssue *j = job;
+            g.unlock();
+            j->worker(t);
+            g.lock();
+            if (--busy == 0) done.notify_one();
+        }
+    }
+};
+
+// The pool with a thread for every tenant but the first, or null when the system gives no more threads
+IssuePool *issue_pool(Ctx *c)
+{
+    if (!c->issue_pool) c->issue_pool = std::make_shared<IssuePool>();
+    IssuePool *pool = static_cast<IssuePool *>(c->issue_pool.get());
+    return pool->grow((int)c->tenants.size() - 1) ? pool : nullptr;
+}
+
+gacer_status run_threaded(Ctx *c, IssuePool *pool, int mode, int rounds)
 {
     const int NT = (int)c->tenants.size();
     ThreadedIssue ti;
@@ -1322,11 +1391,10 @@ gacer_status run_threaded(Ctx *c, int mode, int rounds)
     ti.gate.join_gen.reset(new std::atomic<long>[NT]);
     for (size_t i = 0; i < ne; ++i) ti.gate.ev_gen[i].store(0);
     for (int t = 0; t < NT; ++t) ti.gate.join_gen[t].store(0);
-    std::vector<std::thread> workers;
-    for (int t = 1; t < NT; ++t) workers.emplace_back([&ti, t] { ti.worker(t); });
+    pool->start(&ti, NT - 1);
     const bool ok = ti.lead();
     if (!ok) ti.gate.failed.store(1);
-    for (std::thread &w : workers) w.join();
+    pool->finish();
     if (ti.gate.failed.load()) return fail(c, GACER_EHIP, "%s", ti.err.empty() ? "threaded issue failed" : ti.err.c_str());
     return GACER_OK;
 }
@@ -1347,13 +1415,14 @@ gacer_status run_rounds(Ctx *c, int mode, int rounds, bool allow_graph)
     const bool graph = allow_graph && c->graph_exec[mode] && !c->sync_every_launch;   // the checking mode issues every launch itself
     const bool threaded = c->issue_threads && mode != GACER_MODE_SEQUENTIAL && !graph && c->tenants.size() > 1 && distinct_streams(c);
     gacer_status st = GACER_OK;
-    if (threaded) {
-        st = run_threaded(c, mode, rounds);
+    IssuePool *pool = threaded ? issue_pool(c) : nullptr;          // without threads the calling thread issues everything
+    if (pool) {
+        st = run_threaded(c, pool, mode, rounds);
     } else {
         for (int r = 0; r < rounds && st == GACER_OK; ++r) {
             HIPCHK(c, hipEventRecord(c->t_start[r], s0));
             if (graph) HIPCHK(c, hipGraphLaunch(c->graph_exec[mode], s0));
-            else st = issue_round(c, mode, r);
+            else st = issue_round(c, mode, r, c->t_start[r]);
             if (st == GACER_OK) HIPCHK(c, hipEventRecord(c->t_end[r], s0));
         }
     }
@@ -1466,6 +1535,7 @@ gacer_status gacer_set_issue_threads(gacer_ctx *c, int enable)
 {
     if (!c) return GACER_EINVAL;
     c->issue_threads = enable != 0;
+    if (!enable) c->issue_pool.reset();
     return GACER_OK;
 }
 
