@@ -389,6 +389,30 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
     igemm_epilogue<DT, TM, TN>(a, acc, smem + wave * 4608, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, slice, y_off);
 }
 
+constexpr int DMA_PATCH = 32 * 36 * 4;          // igemm_dma_kernel: bytes of one wave's epilogue patch
+constexpr bool dma_own_patch(int stage, int ns) { return stage < DMA_PATCH * ((4 + ns - 1) / ns); }      // whether it needs LDS beside the stages
+
+// Epilogue of a 16x16 tile (fp32): the lane has channels n .. n + 3 of row m.
+__device__ __forceinline__ void finish_16x16(const GemmArgs &a, const float __attribute__((ext_vector_type(4))) &acc, int m, int n)
+{
+    if (m >= a.m_hi || n >= a.n_hi) return;
+    const int64_t o = (int64_t)m * a.y_row + n;
+    float *y = (float *)a.y + o;
+    const float *res = a.res ? (const float *)a.res + o : nullptr;
+    if (n + 4 <= a.n_hi && a.y_row % 4 == 0 && a.n_lo % 4 == 0 && (((uintptr_t)a.y | (uintptr_t)a.res | (uintptr_t)a.bias) & 15) == 0) {
+        const float4 b = a.bias ? *(const float4 *)(a.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+        float v[4] = {__fmaf_rn(acc[0], a.alpha, b.x), __fmaf_rn(acc[1], a.alpha, b.y), __fmaf_rn(acc[2], a.alpha, b.z), __fmaf_rn(acc[3], a.alpha, b.w)};
+        if (res) {
+            const float4 r = *(const float4 *)res;
+            v[0] = __fadd_rn(v[0], r.x); v[1] = __fadd_rn(v[1], r.y); v[2] = __fadd_rn(v[2], r.z); v[3] = __fadd_rn(v[3], r.w);
+        }
+        act_vec<4>(v, a.act);
+        store_vec4(y, v);
+    } else {
+        for (int c = 0; c < 4; ++c) finish_one<DT_F32>(acc[c], a.alpha, a.bias, a.act, (const float *)a.res, (float *)a.y, o + c, n + c, a.n_hi);
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // The same product with the global -> LDS leg done by the memory pipeline itself ("buffer_load ... lds", 16 bytes per
 // lane on gfx950): tiles go straight from L2 / HBM into LDS without passing through registers, so many K blocks can be
@@ -409,10 +433,12 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
 // NS - 2 youngest blocks are outstanding (block kb + 1 has landed), and for its own fragment reads, then meets the
 // others at a bare s_barrier.  The stages are separate __shared__ arrays so that the compiler can see that a load
 // into one stage does not alias the reads of another (with one array it waits for vmcnt(0) before every read).
-template <int DT, int BM, int BN, int WM, int WN, int KV, int NS, bool TAPS>
-__global__ __launch_bounds__(THREADS)
-__attribute__((amdgpu_waves_per_eu(2 * NS * (BM + BN) * KV * 16 <= 160 * 1024 ? 2 : 1)))      // two workgroups per unit where LDS allows
-void igemm_dma_kernel(GemmArgs a)
+//
+// MF is the edge of an MFMA tile.  16 (fp32 only: v_mfma_f32_16x16x4_f32) is for a launch's surplus tiles, see igemm_dma_kernel: lanes 0-15, 16-31,
+// 32-47 and 48-63 then hold one k each of an MFMA's four, and take them from the 32-byte group such that they follow each other as in the
+// 32x32 MFMAs (0, 4, 1, 5, 2, 6, 3, 7).
+template <int DT, int BM, int BN, int WM, int WN, int KV, int NS, bool TAPS, int MF, typename Stage>
+__device__ __forceinline__ void igemm_dma_tile(const GemmArgs &a, Stage stage_at, unsigned char *own_patch, int m0, int n0, int slice, int z)
 {
     typedef typename El<DT>::T T;
     constexpr int VEC = El<DT>::VEC;
@@ -420,40 +446,18 @@ void igemm_dma_kernel(GemmArgs a)
     constexpr int BK = KV * VEC;
     constexpr int ROWB = KV * 16;               // unpadded tile row
     constexpr int RPP = THREADS / KV;           // tile rows covered by one pass of all threads
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int TM = BM / WM / MF, TN = BN / WN / MF;
     constexpr int AV = BM / RPP, BV = BN / RPP; // loads per thread and block
-    constexpr int STAGE = (BM + BN) * ROWB;
+    constexpr int STAGE = (BM + BN) * ROWB;     // of which a stage holds at least as many bytes
     constexpr int R256 = 256 / ROWB;            // tile rows per 256 bytes of LDS (one sweep over the 64 banks)
-    constexpr int PATCH = 32 * 36 * 4;          // bytes of one wave's epilogue patch
-    constexpr bool OWN_PATCH = STAGE < PATCH * ((4 + NS - 1) / NS);
-    static_assert(WM * WN == 4 && TM >= 1 && TN >= 1 && BM % RPP == 0 && BN % RPP == 0 && NS >= 3 && NS <= 8 && (KV == 4 || KV == 8), "tile shape");
+    constexpr int PATCH = DMA_PATCH;
+    constexpr bool OWN_PATCH = dma_own_patch(STAGE, NS);
+    static_assert((MF == 32 || (MF == 16 && DT == DT_F32 && TM == 1 && TN == 1)) && WM * WN == 4 && TM >= 1 && TN >= 1 && BM % RPP == 0 && BN % RPP == 0 && NS >= 3 && NS <= 8 && (KV == 4 || KV == 8), "tile shape");
     static_assert((NS - 2) * (AV + BV) < 64, "outstanding loads exceed the counter");
-
-    __shared__ __align__(1024) unsigned char st0[STAGE];
-    __shared__ __align__(1024) unsigned char st1[STAGE];
-    __shared__ __align__(1024) unsigned char st2[STAGE];
-    __shared__ __align__(1024) unsigned char st3[NS > 3 ? STAGE : 16];
-    __shared__ __align__(1024) unsigned char st4[NS > 4 ? STAGE : 16];
-    __shared__ __align__(1024) unsigned char st5[NS > 5 ? STAGE : 16];
-    __shared__ __align__(1024) unsigned char st6[NS > 6 ? STAGE : 16];
-    __shared__ __align__(1024) unsigned char st7[NS > 7 ? STAGE : 16];
-    // the stages are separate arrays and always named by a compile-time index, so that the compiler can tell a stage
-    // being filled from the one being read (it would otherwise wait for every outstanding load before each LDS read)
-    auto stage_at = [&](int i) -> unsigned char * {
-        return i == 0 ? st0 : i == 1 ? st1 : i == 2 ? st2 : i == 3 ? st3 : i == 4 ? st4 : i == 5 ? st5 : i == 6 ? st6 : st7;
-    };
-    __shared__ __align__(16) unsigned char own_patch[OWN_PATCH ? 4 * PATCH : 16];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int tile = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
-    const int by_m = div_by(tile, a.div_tiles_m), by_n = div_by(tile, a.div_tiles_n);
-    const int tile_m = __builtin_amdgcn_readfirstlane(a.n_major ? tile - by_m * a.tiles_m : by_n);
-    const int tile_n = __builtin_amdgcn_readfirstlane(a.n_major ? by_m : tile - by_n * a.tiles_n);
-    const int m0 = a.m_lo + tile_m * BM, n0 = a.n_lo + tile_n * BN;
-
-    const int z = blockIdx.z;
     const int zq = __builtin_amdgcn_readfirstlane(div_by(z, a.div_zh));
     const int zb = a.z_lo + zq, zh = z - zq * a.zh;
     const int64_t x_zoff = zb * a.x_zb + zh * a.x_zh, w_zoff = zb * a.w_zb + zh * a.w_zh;
@@ -490,7 +494,6 @@ void igemm_dma_kernel(GemmArgs a)
     // K range of this slice, in blocks of BK (kb_per_slice counts 64-byte blocks)
     const int nkb_all = (a.K + BK - 1) / BK;
     const int per = a.kb_per_slice / (KV / 4);
-    const int slice = blockIdx.y;
     const int kb_lo = slice * per;
     const int nkb = min(nkb_all, kb_lo + per);
     const int k_end = min(a.K, nkb * BK);       // loads at or beyond k_end return zeros
@@ -560,16 +563,18 @@ void igemm_dma_kernel(GemmArgs a)
         request_end();
     };
 
-    f32x16 acc[TM][TN];
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typename std::conditional<MF == 32, f32x16, f32x4>::type acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < MF * MF / 64; ++e) acc[i][j][e] = 0.f;
 
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    // fragment reads: tile row lrow (+ a multiple of 32, which leaves the swizzle unchanged), logical chunk 2 g + lhalf
+    const int lrow = lane & (MF - 1), lhalf = MF == 32 ? lane >> 5 : (lane >> 4) & 1;
+    const bool odd = MF == 16 && lane >= 32;
+    // fragment reads: tile row lrow (+ a multiple of MF, which leaves the swizzle unchanged), logical chunk 2 g + lhalf
     const int frag_lo = (lhalf ^ ((lrow / R256) % KV)) * 16;
     const int a_row0 = (wm * (BM / WM) + lrow) * ROWB, b_row0 = (BM + wn * (BN / WN) + lrow) * ROWB;
     constexpr int G = KV / 2;                   // k groups (32 bytes of k) per block; group g lives in register set g & 1
@@ -593,6 +598,10 @@ void igemm_dma_kernel(GemmArgs a)
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[set][j]),
                                                                         __builtin_bit_cast(bf16x8, fa[set][i]), acc[i][j], 0, 0, 0);
+        } else if constexpr (MF == 16) {
+            const uint4 &va = fa[set][0], &vb = fb[set][0];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(odd ? vb.y : vb.x), __uint_as_float(odd ? va.y : va.x), acc[0][0], 0, 0, 0);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(odd ? vb.w : vb.z), __uint_as_float(odd ? va.w : va.z), acc[0][0], 0, 0, 0);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -657,8 +666,58 @@ void igemm_dma_kernel(GemmArgs a)
     mfmas(1);                                   // last group of the last block
     meet(1);                                    // trailing requests (all beyond K: zeros) have landed; the epilogue reuses the stages
 
-    unsigned char *patch = OWN_PATCH ? own_patch + wave * PATCH : stage_at(wave % NS) + (wave / NS) * PATCH;
-    igemm_epilogue<DT, TM, TN>(a, acc, patch, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, slice, y_off);
+    if constexpr (MF == 16) {
+        asm volatile("s_nop 15" : "+v"(acc[0][0]));                            // see expand_dw_kernel
+        finish_16x16(a, acc[0][0], m0 + wm * 16 + lrow, n0 + wn * 16 + (lane >> 4) * 4);
+    } else {
+        unsigned char *patch = OWN_PATCH ? own_patch + wave * PATCH : stage_at(wave % NS) + (wave / NS) * PATCH;
+        igemm_epilogue<DT, TM, TN>(a, acc, patch, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, slice, y_off);
+    }
+}
+
+// The launch.  `surplus` (fp32, 64x64 tiles, one slice): the last tiles, a.surplus of them, are computed as four 32x32 tiles each, by
+// workgroups of their own at the end of the grid.  fp32 is bound by the matrix cores, so that a launch takes as long as the unit with
+// the most tiles; 784 tiles on 256 units took as long as 1024 (150 us for 6272x512x2304), and take the time of 832 with the last 16 cut up.
+template <int DT, int BM, int BN, int WM, int WN, int KV, int NS, bool TAPS>
+__global__ __launch_bounds__(THREADS)
+__attribute__((amdgpu_waves_per_eu(2 * NS * (BM + BN) * KV * 16 <= 160 * 1024 ? 2 : 1)))      // two workgroups per unit where LDS allows
+void igemm_dma_kernel(GemmArgs a)
+{
+    constexpr int STAGE = (BM + BN) * KV * 16;
+    constexpr bool OWN_PATCH = dma_own_patch(STAGE, NS);
+    __shared__ __align__(1024) unsigned char st0[STAGE];
+    __shared__ __align__(1024) unsigned char st1[STAGE];
+    __shared__ __align__(1024) unsigned char st2[STAGE];
+    __shared__ __align__(1024) unsigned char st3[NS > 3 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char st4[NS > 4 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char st5[NS > 5 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char st6[NS > 6 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char st7[NS > 7 ? STAGE : 16];
+    // the stages are separate arrays and always named by a compile-time index, so that the compiler can tell a stage
+    // being filled from the one being read (it would otherwise wait for every outstanding load before each LDS read)
+    auto stage_at = [&](int i) -> unsigned char * {
+        return i == 0 ? st0 : i == 1 ? st1 : i == 2 ? st2 : i == 3 ? st3 : i == 4 ? st4 : i == 5 ? st5 : i == 6 ? st6 : st7;
+    };
+    __shared__ __align__(16) unsigned char own_patch[OWN_PATCH ? 4 * DMA_PATCH : 16];
+
+
+    constexpr bool SURPLUS = DT == DT_F32 && BM == 64 && BN == 64;
+    const int whole = SURPLUS ? (int)gridDim.x - 4 * a.surplus : (int)gridDim.x;
+    const bool cut = SURPLUS && (int)blockIdx.x >= whole;
+    const int part = cut ? xcd_contiguous((int)blockIdx.x - whole, 4 * a.surplus) : 0;
+    const int tile = cut ? whole + (part >> 2) : xcd_contiguous((int)blockIdx.x, whole);
+    const int by_m = div_by(tile, a.div_tiles_m), by_n = div_by(tile, a.div_tiles_n);
+    const int tile_m = __builtin_amdgcn_readfirstlane(a.n_major ? tile - by_m * a.tiles_m : by_n);
+    const int tile_n = __builtin_amdgcn_readfirstlane(a.n_major ? by_m : tile - by_n * a.tiles_n);
+    const int m0 = a.m_lo + tile_m * BM, n0 = a.n_lo + tile_n * BN;
+    if constexpr (SURPLUS) {
+        if (cut) {
+            const int m1 = m0 + (part >> 1 & 1) * 32, n1 = n0 + (part & 1) * 32;
+            if (m1 < a.m_hi && n1 < a.n_hi) igemm_dma_tile<DT, 32, 32, 2, 2, KV, NS, TAPS, 16>(a, stage_at, own_patch, m1, n1, 0, 0);
+            return;
+        }
+    }
+    igemm_dma_tile<DT, BM, BN, WM, WN, KV, NS, TAPS, 32>(a, stage_at, own_patch, m0, n0, blockIdx.y, blockIdx.z);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -833,20 +892,30 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
     return li;
 }
 
+// How many of `tiles` 64x64 tiles (fp32, one slice) to cut into quarters: those beyond a multiple of the compute units, up to half of these.
+// Us whole / cut, by the tiles: 276 (5832x192x1600) 55.7 / 42.9, 288 (512x2304x768) 28.2 / 21.5, 296 (4704x256x2304) 77.8 / 59.9, 384 (512x3072x768, GELU)
+// 30.6 / 26.6, 588 (9408x256x2304) 114 / 109, 784 (6272x512x2304) 151 / 133, 1568 (25088x256x2304) 260 / 243, 3136 (100352x128x1152) 248 / 239; more than half
+// of them: 132 (1352x384x1728) 34.2 / 38.1, 392 (25088x64x576) 24.5 / 26.5, 400 (1568x1024x512) 21.3 / 22.3.
+static int surplus_tiles(int tiles)
+{
+    const int r = tiles % 256;
+    return r <= 128 ? r : 0;
+}
+
 // launcher of igemm_dma_kernel (operands 16-byte aligned in every stride, B rows contiguous in k, at most 31 taps)
 template <int DT, int BM, int BN, int WM, int WN, int KV, int NS>
 static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, int phase)
 {
     typedef typename El<DT>::T T;
-    constexpr int STAGE = (BM + BN) * KV * 16, PATCH = 32 * 36 * 4;
-    constexpr bool OWN_PATCH = STAGE < PATCH * ((4 + NS - 1) / NS);
+    constexpr int STAGE = (BM + BN) * KV * 16;
     const int tiles_m = (a.m_hi - a.m_lo + BM - 1) / BM, tiles_n = (a.n_hi - a.n_lo + BN - 1) / BN;
     const int z = a.zb * a.zh;
     const int ks = a.ksplit;
+    const int surplus = DT == DT_F32 && z * ks == 1 ? surplus_tiles(tiles_m * tiles_n) : 0;
     LaunchInfo li;
-    li.workgroups = tiles_m * tiles_n * z * ks;
+    li.workgroups = tiles_m * tiles_n * z * ks + 3 * surplus;
     li.threads = THREADS;
-    li.lds_bytes = NS * STAGE + (OWN_PATCH ? 4 * PATCH : 0);
+    li.lds_bytes = NS * STAGE + (dma_own_patch(STAGE, NS) ? 4 * DMA_PATCH : 0);
     const int by_lds = (160 * 1024) / li.lds_bytes;
     li.wg_per_cu = by_lds < 8 ? by_lds : 8;
     static const std::string shape = std::string(DT == DT_BF16 ? "bf16_" : "f32_") + std::to_string(BM) + "x" + std::to_string(BN) +
@@ -857,7 +926,7 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
     li.phases = ks > 1 ? 2 : 1;
     if (phase == 2) li.kernel = "splitk_finish";
     if (dry || li.workgroups == 0) return li;
-    dim3 grid(tiles_m * tiles_n, ks, z), block(THREADS);
+    dim3 grid(tiles_m * tiles_n + 3 * surplus, ks, z), block(THREADS);
     if (phase == 2) {
         if (ks > 1) finish<T>(a, s);
         return li;
@@ -866,6 +935,7 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
     b.n_major = tile_order(a, tiles_m, tiles_n, (int)sizeof(T));
     set_divisors(b);
     set_tiling(b, tiles_m, tiles_n);
+    b.surplus = surplus;
     if (taps) GACER_LAUNCH((igemm_dma_kernel<DT, BM, BN, WM, WN, KV, NS, true>), grid, block, 0, s, b);
     else GACER_LAUNCH((igemm_dma_kernel<DT, BM, BN, WM, WN, KV, NS, false>), grid, block, 0, s, b);
     if (ks > 1 && phase == 0) finish<T>(a, s);
@@ -945,15 +1015,16 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     // fused per-channel affine: the A tile passes through registers (the executor fuses only 16-byte aligned, vector-multiple operands)
     if (a.pre_scale) return staged(blocks128, true);
     // The direct-to-LDS pipeline (igemm_dma_kernel) wins once the K loop is long enough to fill its stages: in bf16 from 256 bytes of K on
-    // (windows, with their longer address code: 512), fp32 from 1.5 KB (here / on the register-staged kernel: 12544x512x384 48.6 / 50.9, 6272x256x384 18.0 / 18.3, below
-    // 12544x512x192 29.4 / 28.9, 3136x1024x96 13.5 / 12.5).
+    // (windows, with their longer address code: 512), fp32 from 512 bytes (windows 1.5 KB): us on the register-staged kernel / here,
+    // 25088x128x256 23.4 / 20.6, 392x1280x320 10.5 / 9.1, 1568x1024x256 14.3 / 14.0, 12544x512x128 24.7 / 24.8, 4704x256x256 13.4 / 10.3, below
+    // 6272x576x96 13.5 / 13.7, 25088x256x64 16.9 / 17.1.
     const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
     const int64_t k_bytes = (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T);
     if (vec_ok && !a.b_trans && (!taps || a.kh * a.kw <= 31)) {
         if constexpr (DT == DT_BF16) {
             if (k_bytes >= (taps ? 512 : 256)) return pick_dma_bf16(a, s, dry, phase);
         } else {
-            if (shape != T128x32 && k_bytes >= 1536) return go_dma<DT, 64, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
+            if (shape != T128x32 && k_bytes >= (taps ? 1536 : 512)) return go_dma<DT, 64, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
         }
     }
     // short K, or the latency-bound gather loader (more waves per unit): 64-byte blocks

@@ -63,6 +63,7 @@ struct GemmArgs {
     unsigned tap_bits;         // set by the launcher: see tap_rows()
     // set by the launcher of the tiled kernels: tiles along m and n of this launch, divisors for them and for zh
     int tiles_m, tiles_n;
+    int surplus;               // igemm_dma_kernel in fp32: the last tiles of the launch that are computed in quarters
     unsigned div_tiles_m[2], div_tiles_n[2], div_zh[2];
     // Per-channel affine + activation fused in front of a 1x1 product (pre_scale != null): x is the affine operator's INPUT
     // (same shape as its output, K = Cin channels) and A[m][k] = pre_act(x[m][k] * pre_scale[k] + pre_shift[k]), rounded to

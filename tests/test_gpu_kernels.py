@@ -264,6 +264,23 @@ def test_direct_to_lds_tiles_of_short_k(name, spec):
     assert ran == {"igemm_dma_" + ("taps_bf16_" + name[5:] if name.startswith("taps_") else "bf16_" + name)}, sorted(ran)
 
 
+@pytest.mark.parametrize("spec", [(1, 139, 30, 132, 250, 1, 1, "relu6", True), (3, 39, 37, 44, 250, 3, 1, "relu", False), (1, 139, 30, 132, 251, 1, 1, "none", True),
+                                  (4, 113, 59, 392, 190, 1, 2, "hswish", False), (5, 40, 27, 60, 247, 3, 1, "gelu", True)])
+def test_surplus_tiles_in_quarters(spec):
+    """fp32 launches with some tiles more than a multiple of the units: the last ones in quarters, ragged rows and channels (quarters that lie
+    outside, vectors that reach over the end), chunks that are cut up altogether."""
+    from synth import graphs as G
+    batch, h, w, cin, cout, k, stride, act, res = spec
+    b = G._B("surplus", "f32", batch)
+    x = b.tensor(batch, cin, h, w)
+    y = b.conv(x, cout, 1, stride, 0, "none") if res else -1
+    t = b.done(x, b.conv(x, cout, k, stride, k // 2, act, res=y))
+    n, c, ho, wo = t.tensors[t.output]
+    tiles = ((n * ho * wo + 63) // 64) * ((c + 63) // 64)
+    assert tiles > 256 and 0 < tiles % 256 <= 128
+    check([t], ["igemm_dma"], [("batch", 2), ("cout", 2), ("cout", 8)])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_non_finite_inputs_reach_their_windows_only(dtype):
     """Infinities and NaN in the input make exactly the outputs non-finite whose window holds one (padding, tails of K and of tiles
