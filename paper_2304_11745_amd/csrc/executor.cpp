@@ -433,23 +433,31 @@ static KSplit decide_split(int64_t M, int64_t N, int K, gacer_dtype dtype, bool 
     // 49x160x960 3.5 / 7.9, 392x512x4608 (3x3) 8.5 / 13.6, 1568x256x2304 (3x3, 392 tiles) 8.2 / 13.8, 144x3072x768 (480) 4.9 / 6.8,
     // 6272x128x512 (784) 6.0 / 6.0, 3136x256x2304 (3x3, 784) 14.2 / 11.8; fp32 125x32x1152 8.3 / 27.3, 392x512x2048 12.5 / 17.1,
     // 2048x256x1024 (512) 13.2 / 20.7, 6272x128x512 14.1 / 13.1.  The limit is where it was before both kernels became shorter; with
-    // today's the crossing lies between 640 and 750 tiles: 392x1280x320 (520) fp32 8.6 / 10.3, bf16 4.8 / 4.8, 2304x256x1024 (576)
+    // today's the crossing in bf16 lies between 640 and 750 tiles: 392x1280x320 (520) fp32 8.6 / 10.3, bf16 4.8 / 4.8, 2304x256x1024 (576)
     // 18.0 / 20.9 and 7.1 / 7.7, 784x768x512 (600) 11.5 / 13.0 and 5.8 / 6.7, 784x960x160 (750) 7.6 / 7.3 and 5.1 / 4.5.  One column
     // of tiles (N <= 32) wastes half of a 64-wide tile's work, so it goes on longer: 19200x32x1152 (600) fp32 21.1 / 28.7, bf16
     // 9.9 / 11.8, 25088x32x1152 (784) 26.6 / 29.4 and 12.2 / 13.3.  At a short K a launch beyond 512 tiles is slower alone (25088x24x144
     // fp32 8.7 / 7.8, 19200x32x192 bf16 5.0 / 4.6), but whole rounds were not when that was tried, with longer launches on both sides:
     // ResNet-18 and MobileNetV2 of 8 images 737 us here, 749 there, MobileNetV2 alone 417 / 414, two of them 607 / 602, three mobile networks
     // 910 / 893.
-    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t32_max = N > 32 ? 512 : bf16 ? 600 : 800;
     const int nb = (nkb + 1) / 2;                // 128-byte batches of K per row
+    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
+    // fp32 goes on to four tiles per unit where K has 72 batches: the tiled kernels' 129 to 256 tiles are alone on their units and cut no K.  Here / there:
+    // 592 tiles 1176x512x4608 (3x3) 60.7 / 83.9, 640 160x4096x4096 56.2 / 70.8, 768 1024x768x3072 44.9 / 51.9, 784 1568x512x4608 (3x3) 77.9 / 84.0, 3136x256x2304
+    // (3x3) 41.9 / 44.1, 896 224x4096x4096 71.2 / 71.1, 992 1960x512x4608 (3x3) 79.1 / 84.3; fewer batches: 588 6272x96x576 12.2 / 16.6, 768 6144x128x576 12.9 /
+    // 13.8, 784 3136x256x1024 22.1 / 20.8, 6272x128x512 13.6 / 12.8, 936 400x2304x768 18.9 / 17.3 (up to 768 tiles they would gain too, and would add in
+    // another order; they stay).
+    const int64_t t32_max = N <= 32 ? (bf16 ? 600 : 800) : bf16 || nb < 72 ? 512 : 1024;
     // Short bf16 rows belong to rowgemm_kernel.  fp32 shapes with a long K that fill most units, or whose slices would be cut over the grid
     // at most three ways and of which 64x64 tiles compute little that is not needed, are left to the tiled kernels, where four waves
     // share each operand.  That gained 3 to 10 % when the rule was made; since the chain of this kernel became shorter it gains
     // nothing: here / there 512x768x3072 29.5 / 29.8, 416x256x2304 11.8 / 13.1, 245x512x4608 16.9 / 17.6, 320x256x4608 14.2 / 14.7,
     // 392x512x4608 (3x3) 23.2 / 28.3, beside 147x512x4608 (taken here) 13.2 / 16.2.  Moving the line changes the order of additions of
     // these operators.
+    // But where the 64x64 tiles fill half of the units (128) K is not cut there: one chain over all of it, alone on its unit, takes twice as long and errs
+    // twice as much (here / there 980x512x4608 40.7 / 82.7, 128x4096x4096 41.8 / 70.8, 500x1024x3072 30.7 / 54.4; 5.8e-7 / 1.13e-6).
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    const bool shared = !bf16 && (t32 > 128 ? nb > 80 : t32 > 64 && nb > 64 && 32 * tiles <= 9 * t32);
+    const bool shared = !bf16 && (t32 > 128 ? nb > 80 && tiles < 128 : t32 > 64 && nb > 64 && 32 * tiles <= 9 * t32);
     if (slices_ok && nb >= 2 && (!bf16 || K > 96) && t32 <= t32_max && !shared) {
         // more workgroups along K, and a finishing pass, only where units would stay empty and a wave's chain is long.  bf16: doubled
         // while a wave has more than twelve batches: 8x4096x25088; at 9 batches the pass costs more than it gives (49x512x4608: 9.0 ->

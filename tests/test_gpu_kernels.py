@@ -157,6 +157,18 @@ def test_k_slices_on_small_tiles_in_fp32():
     assert all("slices" in n or n == "splitk_finish" for n in ran), ran
 
 
+def test_number_of_tiles_for_k_slices_in_fp32():
+    """Either side of each limit on the 32x32 tiles (512, 1024) and on the batches of K they ask for (72), and of the 64x64 tiles (128) from which on a long K
+    stays on slices; halves and eighths of the channels give the bits of the whole operator."""
+    from synth import graphs as G
+    for rows, cout, cin, sliced in [(3270, 130, 2276, True), (3270, 130, 2272, False), (1010, 1000, 2308, True), (1030, 1000, 2308, False),
+                                    (1000, 500, 2564, True), (960, 500, 2564, False)]:
+        b = G._B(f"limit{rows}", "f32", 1)
+        x = b.tensor(1, cin, rows, 1)
+        names = check([b.done(x, b.conv(x, cout, 1, 1, 0, "relu"))], [], [("cout", 2), ("cout", 8)])
+        assert any(n.startswith("igemm_slices_f32_x4") for n in names) == sliced, (rows, cout, cin, names)
+
+
 def test_finishing_pass_of_every_number_of_slices():
     """splitk_finish for two, three, four, five and eight slices in fp32, whole vectors and channel counts or chunks that are none, with
     and without a residual and an activation."""
