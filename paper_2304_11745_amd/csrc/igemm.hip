@@ -392,14 +392,15 @@ __global__ __launch_bounds__(THREADS) void igemm_kernel(GemmArgs a)
 constexpr int DMA_PATCH = 32 * 36 * 4;          // igemm_dma_kernel: bytes of one wave's epilogue patch
 constexpr bool dma_own_patch(int stage, int ns) { return stage < DMA_PATCH * ((4 + ns - 1) / ns); }      // whether it needs LDS beside the stages
 
-// Epilogue of a 16x16 tile (fp32): the lane has channels n .. n + 3 of row m.
-__device__ __forceinline__ void finish_16x16(const GemmArgs &a, const float __attribute__((ext_vector_type(4))) &acc, int m, int n)
+// Epilogue of a 16x16 tile (fp32): the lane has channels n .. n + 3 of row m of the problem at y_off (a launch of one problem need not be
+// the first: a chunk of one image of a batched product).
+__device__ __forceinline__ void finish_16x16(const GemmArgs &a, const float __attribute__((ext_vector_type(4))) &acc, int m, int n, int64_t y_off)
 {
     if (m >= a.m_hi || n >= a.n_hi) return;
-    const int64_t o = (int64_t)m * a.y_row + n;
+    const int64_t o = (int64_t)m * a.y_row + n + y_off;
     float *y = (float *)a.y + o;
     const float *res = a.res ? (const float *)a.res + o : nullptr;
-    if (n + 4 <= a.n_hi && a.y_row % 4 == 0 && a.n_lo % 4 == 0 && (((uintptr_t)a.y | (uintptr_t)a.res | (uintptr_t)a.bias) & 15) == 0) {
+    if (n + 4 <= a.n_hi && a.y_row % 4 == 0 && a.n_lo % 4 == 0 && y_off % 4 == 0 && (((uintptr_t)a.y | (uintptr_t)a.res | (uintptr_t)a.bias) & 15) == 0) {
         const float4 b = a.bias ? *(const float4 *)(a.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
         float v[4] = {__fmaf_rn(acc[0], a.alpha, b.x), __fmaf_rn(acc[1], a.alpha, b.y), __fmaf_rn(acc[2], a.alpha, b.z), __fmaf_rn(acc[3], a.alpha, b.w)};
         if (res) {
@@ -668,7 +669,7 @@ __device__ __forceinline__ void igemm_dma_tile(const GemmArgs &a, Stage stage_at
 
     if constexpr (MF == 16) {
         asm volatile("s_nop 15" : "+v"(acc[0][0]));                            // see expand_dw_kernel
-        finish_16x16(a, acc[0][0], m0 + wm * 16 + lrow, n0 + wn * 16 + (lane >> 4) * 4);
+        finish_16x16(a, acc[0][0], m0 + wm * 16 + lrow, n0 + wn * 16 + (lane >> 4) * 4, y_off);
     } else {
         unsigned char *patch = OWN_PATCH ? own_patch + wave * PATCH : stage_at(wave % NS) + (wave / NS) * PATCH;
         igemm_epilogue<DT, TM, TN>(a, acc, patch, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, slice, y_off);

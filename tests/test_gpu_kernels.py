@@ -294,6 +294,18 @@ def test_surplus_tiles_in_quarters(spec):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("keys", [64, 72, 120, 256])
+@pytest.mark.parametrize("head", [128, 192])
+def test_attention_of_one_head(dtype, keys, head):
+    """Products of one head, in chunks of three, two and one image: a launch of a single problem that is not the first one.  Key counts
+    that fill the last 64x64 tile, half of it, and less."""
+    from synth import graphs as G
+    b = G._B("one_head", dtype, 5)
+    x = b.tensor(5, 3 * head, keys, 1)
+    check([b.done(x, b.attention(x, 1))], [], [("batch", 2), ("batch", 4)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_non_finite_inputs_reach_their_windows_only(dtype):
     """Infinities and NaN in the input make exactly the outputs non-finite whose window holds one (padding, tails of K and of tiles
     and the neighbours in memory are zeros times something finite); all other outputs are as without them."""
