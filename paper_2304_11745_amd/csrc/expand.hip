@@ -126,9 +126,7 @@ __global__ __launch_bounds__(256, 2) void expand_dw_kernel(ExpandArgs a)
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(fb0 + c), *(const bf16x8 *)(fa0 + c), acc, 0, 0, 0);
                 }
             }
-            // The compiler counts the wait states between the last MFMA and the first read of its result over this loop's exits and
-            // misses some (elements 14 and 15 were read without the last group): wait for all of them here.
-            asm volatile("s_nop 15" : "+v"(acc));
+            mfma_settle<DT_BF16>();
             if (first == 0) {
                 sum = acc;
             } else {

@@ -33,6 +33,17 @@ template <int DT> struct El;
 template <> struct El<DT_F32> { typedef float T; static constexpr int VEC = 4; };
 template <> struct El<DT_BF16> { typedef unsigned short T; static constexpr int VEC = 8; };
 
+// The wait states that the result of a 32x32 MFMA takes (its passes and two more, bf16 another two).  hipcc puts them in front of whatever
+// reads or overwrites the result first, but where several ways lead on from a loop of MFMAs it has counted one to three too few on one of
+// them; so they stand behind such loops.
+template <int DT> __device__ __forceinline__ void mfma_settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (DT == DT_BF16) asm volatile("s_nop 11");
+    else asm volatile("s_nop 15\n\ts_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 template <typename T> __device__ __forceinline__ void store_out(T *y, int64_t o, float v);
 template <> __device__ __forceinline__ void store_out<float>(float *y, int64_t o, float v) { y[o] = v; }
 template <> __device__ __forceinline__ void store_out<unsigned short>(unsigned short *y, int64_t o, float v) { y[o] = f32_to_bf16(v); }

@@ -668,7 +668,6 @@ __device__ __forceinline__ void igemm_dma_tile(const GemmArgs &a, Stage stage_at
     meet(1);                                    // trailing requests (all beyond K: zeros) have landed; the epilogue reuses the stages
 
     if constexpr (MF == 16) {
-        asm volatile("s_nop 15" : "+v"(acc[0][0]));                            // see expand_dw_kernel
         finish_16x16(a, acc[0][0], m0 + wm * 16 + lrow, n0 + wn * 16 + (lane >> 4) * 4, y_off);
     } else {
         unsigned char *patch = OWN_PATCH ? own_patch + wave * PATCH : stage_at(wave % NS) + (wave / NS) * PATCH;

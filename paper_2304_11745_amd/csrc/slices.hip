@@ -306,6 +306,7 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
             step(w0, 0, WAIT_BATCH, true);
             step(w1, 0, WAIT_BATCH, true);
         }
+        if constexpr (DT == DT_F32 && T32) mfma_settle<DT>();
         const int rest = batches - b;           // 0 to 3; every batch but the last two requests the one after next
         if (rest == 3) {
             step(w0, 0, WAIT_BATCH, true);
@@ -322,7 +323,6 @@ __global__ __launch_bounds__(64 * S) void slices_kernel(SlicesArgs a)
     }
 
     // ---- sum over the slices and epilogue; each wave's accumulator goes into its own first stage ----
-    if constexpr (!T32) asm volatile("s_nop 15" : "+v"(acc));                  // see expand_dw_kernel
 #pragma unroll
     for (int e = 0; e < NE; ++e) *(float *)(w0 + (e * 64 + lane) * 4) = acc[e];
     __syncthreads();
