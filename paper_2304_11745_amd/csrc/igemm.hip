@@ -886,8 +886,8 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_GATHER>), grid, block, 0, s, b);
     else if (taps)
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_TAPS>), grid, block, 0, s, b);
-    else if constexpr (DT == DT_F32 || KV == 4)        // one tap and more than 256 bytes of K: igemm_dma_kernel in bf16
-        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_VEC>), grid, block, 0, s, b);
+    else            // bf16 rows of more than 256 bytes are igemm_dma_kernel's: no loader of their own here, the one for windows takes them too
+        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, DT == DT_F32 || KV == 4 ? LOAD_VEC : LOAD_TAPS>), grid, block, 0, s, b);
     if (ks > 1 && phase == 0) finish<T>(a, s);
     return li;
 }

@@ -58,9 +58,40 @@ static void check_depthwise_windows()
     CHECK(depthwise(DT_BF16, 2, 2, 2, 64, 3, 1, 1).kernel == std::string("dwconv3x3"));
 }
 
+// A product of M rows, N channels and K elements per row (or K input channels under a k x k window on an image of M positions).
+static GemmArgs product(int dtype, int M, int N, int K, int k = 1)
+{
+    GemmArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.x = a.w = a.y = (void *)0x10000;
+    a.dtype = dtype;
+    a.H = M; a.W = 1; a.Cin = K; a.Ho = M; a.Wo = 1;
+    a.kh = a.kw = k; a.stride = 1; a.pad = k / 2; a.K = K * k * k;
+    a.x_pix = K; a.x_img = (int64_t)M * K; a.w_row = a.K; a.y_row = N;
+    a.m_hi = M; a.n_hi = N; a.alpha = 1.f;
+    a.zb = a.zh = 1; a.ksplit = 1; a.kb_per_slice = 1 << 20;
+    return a;
+}
+
+// The kernels that stage bf16 rows through registers have no loader for aligned single-tap rows of more than 256 bytes: none may come there.
+static void check_bf16_rows()
+{
+    int dma = 0;
+    for (int K = 8; K <= 4096; K += K < 256 ? 8 : 248)
+        for (int M : {1, 31, 300, 5000, 70000})
+            for (int N : {1, 32, 33, 64, 128, 200, 1000}) {
+                const std::string name = launch_igemm(product(DT_BF16, M, N, K), nullptr, true).kernel;
+                CHECK(name.find("igemm_bf16_") != 0 || name.rfind("x32") == name.size() - 3);
+                dma += name.find("igemm_dma_bf16_") == 0;
+                CHECK((K * 2 >= 256) == (name.find("igemm_dma_bf16_") == 0));
+            }
+    CHECK(dma > 500);
+}
+
 int main()
 {
     check_depthwise_windows();
+    check_bf16_rows();
     std::printf("dispatch driver: all checks held\n");
     return 0;
 }
