@@ -677,7 +677,7 @@ __device__ __forceinline__ void igemm_dma_tile(const GemmArgs &a, Stage stage_at
 
 // The launch.  `surplus` (fp32, 64x64 tiles, one slice): the last tiles, a.surplus of them, are computed as four 32x32 tiles each, by
 // workgroups of their own at the end of the grid.  fp32 is bound by the matrix cores, so that a launch takes as long as the unit with
-// the most tiles; 784 tiles on 256 units took as long as 1024 (150 us for 6272x512x2304), and take the time of 832 with the last 16 cut up.
+// the most tiles; 784 tiles on 256 units took as long as 1024 (151 us for 6272x512x2304), and take 132 us with the last 16 cut up.
 template <int DT, int BM, int BN, int WM, int WN, int KV, int NS, bool TAPS>
 __global__ __launch_bounds__(THREADS)
 __attribute__((amdgpu_waves_per_eu(2 * NS * (BM + BN) * KV * 16 <= 160 * 1024 ? 2 : 1)))      // two workgroups per unit where LDS allows
@@ -892,10 +892,13 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
     return li;
 }
 
-// How many of `tiles` 64x64 tiles (fp32, one slice) to cut into quarters: those beyond a multiple of the compute units, up to half of these.
-// Us whole / cut, by the tiles: 276 (5832x192x1600) 55.7 / 42.9, 288 (512x2304x768) 28.2 / 21.5, 296 (4704x256x2304) 77.8 / 59.9, 384 (512x3072x768, GELU)
-// 30.6 / 26.6, 588 (9408x256x2304) 114 / 109, 784 (6272x512x2304) 151 / 133, 1568 (25088x256x2304) 260 / 243, 3136 (100352x128x1152) 248 / 239; more than half
-// of them: 132 (1352x384x1728) 34.2 / 38.1, 392 (25088x64x576) 24.5 / 26.5, 400 (1568x1024x512) 21.3 / 22.3.
+// How many of `tiles` 64x64 tiles (fp32, one slice) to cut into quarters: those beyond a multiple of the compute units, up to half of these (a quarter per
+// unit and tile then still fits beside the others).  Up to 128 tiles, mostly chunks of decomposed operators, are cut altogether.
+// Us whole / cut, by the tiles: chunks of 256 channels, K = 2048: 32 (512 rows) 35.7 / 20.4, 64 35.8 / 20.4, 100 35.9 / 28.2, 128 36.1 / 28.5, K = 144: 32 6.1 / 4.3,
+// 64 6.2 / 4.5, 100 and 128 6.3 / 5.3; 272 (4352x256x512) 20.2 / 16.5, 288 (512x2304x768) 28.2 / 21.5, 320 (5120x256x144) 9.8 / 8.3,
+// (5120x256x1152, 3x3) 41.4 / 32.4, 356 (5696x256x512) 20.4 / 19.5, 384 (512x3072x768, GELU) 30.6 / 26.6, 588 (9408x256x2304) 114 / 109, 784 (6272x512x2304)
+// 151 / 132, 800 (12800x256x2048) 126 / 111, 1568 (25088x256x1152) 134 / 125, 3136 (100352x128x1152) 248 / 239; more than half of
+// them: 132 (1352x384x1728) 34.2 / 38.1, 392 (25088x64x576) 24.5 / 26.5, 400 (1568x1024x512) 21.3 / 22.3.
 static int surplus_tiles(int tiles)
 {
     const int r = tiles % 256;

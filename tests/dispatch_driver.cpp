@@ -88,10 +88,40 @@ static void check_bf16_rows()
     CHECK(dma > 500);
 }
 
+// fp32 launches of 64x64 tiles: as many tiles as lie beyond a multiple of 256, if at most 128, make four workgroups each, in launches of one
+// problem (wherever in the batch it lies) and one slice of K.
+static void check_surplus_tiles()
+{
+    for (int k : {1, 3})
+        for (int rows : {1, 15, 16, 17, 31, 32, 33, 64, 65, 72, 96, 97, 128, 129, 200, 300})
+            for (int N : {64, 120, 256})
+                for (int z : {1, 2}) {
+                    GemmArgs a = product(DT_F32, rows * 64 - 3, N, 260, k);
+                    a.zb = z;
+                    a.z_lo = rows % 2;
+                    LaunchInfo li = launch_igemm(a, nullptr, true);
+                    const int tiles = rows * ((N + 63) / 64), r = tiles % 256;
+                    CHECK(std::string(li.kernel) == (k == 1 ? "igemm_dma_f32_64x64x32s3" : "igemm_dma_taps_f32_64x64x32s3"));
+                    CHECK(li.workgroups == (z == 1 ? tiles + (r <= 128 ? 3 * r : 0) : 2 * tiles));
+                    a.zb = 1;
+                    a.ksplit = 2;
+                    CHECK(launch_igemm(a, nullptr, true).workgroups == 2 * tiles);
+                }
+    // scores of one head, a chunk of one image of three
+    for (int S : {64, 128, 256}) {
+        GemmArgs a = product(DT_F32, S, S, 128);
+        a.x_pix = a.w_row = 384; a.x_img = 0;
+        a.x_zb = a.w_zb = (int64_t)S * 384; a.y_zb = (int64_t)S * S;
+        a.z_lo = 1;
+        CHECK(launch_igemm(a, nullptr, true).workgroups == 4 * (S / 64) * (S / 64));
+    }
+}
+
 int main()
 {
     check_depthwise_windows();
     check_bf16_rows();
+    check_surplus_tiles();
     std::printf("dispatch driver: all checks held\n");
     return 0;
 }

@@ -280,7 +280,12 @@ def test_direct_to_lds_tiles_of_short_k(name, spec):
                                   (4, 113, 59, 392, 190, 1, 2, "hswish", False), (5, 40, 27, 60, 247, 3, 1, "gelu", True)])
 def test_surplus_tiles_in_quarters(spec):
     """fp32 launches with some tiles more than a multiple of the units: the last ones in quarters, ragged rows and channels (quarters that lie
-    outside, vectors that reach over the end), chunks that are cut up altogether."""
+    outside, vectors that reach over the end), chunks that are cut up altogether.  Each of those tiles makes four workgroups."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_11745_amd import binding as B
+    from paper_2304_11745_amd import harness
     from synth import graphs as G
     batch, h, w, cin, cout, k, stride, act, res = spec
     b = G._B("surplus", "f32", batch)
@@ -291,6 +296,10 @@ def test_surplus_tiles_in_quarters(spec):
     tiles = ((n * ho * wo + 63) // 64) * ((c + 63) // 64)
     assert tiles > 256 and 0 < tiles % 256 <= 128
     check([t], ["igemm_dma"], [("batch", 2), ("cout", 2), ("cout", 8)])
+    sess = harness.Session([t], [G.materialise(t, 411, 0)])
+    last = sess.trace(B.GACER_MODE_SEQUENTIAL, 1)[-1]
+    sess.close()
+    assert last["kernel"].endswith("f32_64x64x32s3") and last["workgroups"] == tiles + 3 * (tiles % 256), (last, tiles)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
