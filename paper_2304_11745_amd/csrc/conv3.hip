@@ -64,7 +64,7 @@ void conv3_kernel(GemmArgs a, Conv3Geom geo)
     constexpr int SPB = 9 / TPS;               // steps per channel block (a multiple of NSB over two blocks)
     constexpr int NB = BN * TPS / 64;          // weight loads per thread and step
     constexpr int NA = ROWS / 64;              // input loads per thread and channel block
-    constexpr int A_STEPS = TPS == 1 ? NA : 2, PA = NA / A_STEPS;               // the steps of a block that request inputs, and how many each
+    constexpr int A_STEPS = TPS == 1 ? NA : 2 - NA % 2, PA = NA / A_STEPS;      // the steps of a block that request inputs, and how many each
     constexpr int G = 2 * TPS;                 // k groups (32 bytes of k) per step
     constexpr int ABYTES = conv3_input_bytes(BM), BBYTES = BN * TPS * ROWB;
     static_assert(NSB <= 3 && 2 * SPB % NSB == 0 && NA % A_STEPS == 0 && A_STEPS <= SPB * 2 / 3, "inputs are requested in the first two thirds of a block");
@@ -271,6 +271,7 @@ LaunchInfo launch_conv3(const GemmArgs &a, hipStream_t s, bool dry)
 {
     const Conv3Tile t = conv3_tile(a);
     if (t.bn == 128) return go_conv3<256, 128, 1, 3>(a, s, dry);
+    if (t.bm == 64) return go_conv3<64, 64, 3, 3>(a, s, dry);
     if (t.bm == 128) return go_conv3<128, 64, 3, 3>(a, s, dry);
     // a third weight stage costs the second workgroup its place on the unit: where there is at most one anyway
     if (conv3_wgs(a, 256, 64) <= 256) return go_conv3<256, 64, 3, 3>(a, s, dry);

@@ -5,8 +5,8 @@
 
 namespace gacer {
 
-// Output positions per tile: 256 or 128.  Input pixels (LDS rows) staged for them per channel block:
-constexpr int conv3_rows(int bm) { return bm == 256 ? 384 : 256; }
+// Output positions per tile: 256, 128 or 64.  Input pixels (LDS rows) staged for them per channel block:
+constexpr int conv3_rows(int bm) { return bm == 256 ? 384 : bm == 128 ? 256 : 192; }
 static constexpr int CONV3_STRIP = 56;         // most columns of a strip
 
 // Whether bm consecutive positions of a strip and their one-pixel halo fit: the last of them lies at most `down` image rows
@@ -23,7 +23,8 @@ constexpr bool conv3_fits_all(int tw_lo, int tw_hi, int bm)
     return true;
 }
 static constexpr int CONV3_STRIP_MIN = 5;      // images under 5 pixels wide have too many rows in a tile of 256
-static_assert(conv3_fits_all(CONV3_STRIP_MIN, CONV3_STRIP, 256) && conv3_fits_all(CONV3_STRIP_MIN, CONV3_STRIP, 128), "LDS rows");
+static_assert(conv3_fits_all(CONV3_STRIP_MIN, CONV3_STRIP, 256) && conv3_fits_all(CONV3_STRIP_MIN, CONV3_STRIP, 128) &&
+              conv3_fits_all(CONV3_STRIP_MIN, CONV3_STRIP, 64), "LDS rows");
 
 struct Conv3Geom {
     int tw, strips;            // the image is cut into `strips` column strips of `tw` (the last one may be narrower)
@@ -49,10 +50,10 @@ inline int64_t conv3_wgs(const GemmArgs &a, int bm, int bn)
 
 // Whether the operator (its UNSPLIT shape, so that every chunk of it adds in the same order) runs on conv3_kernel: from about three tiles
 // of 128 positions x 64 channels on four compute units.  One launch in a chain, microseconds on the tiled kernels / here, by the
-// number of such tiles: 392 (16 images 28x28 128->256) 20.4 / 16.3, (32 images 28x28 128->128) 14.6 / 12.2, 392 (4 images 56x56 256->256) 22.3 / 19.0, 200
-// (16 images 14x14 512->512) 25.5 / 20.7, 196 (32 images 14x14 256->256) 15.5 / 12.8, (16 images 28x28 128->128) 10.0 / 8.6, (8 images 56x56 64->64) 7.2 / 6.8, 111
-// (3 images 37x41 192->192) 9.9 / 10.1, 104 (8 images 14x14 512->512) 18.5 / 19.5, 100 (16 images 14x14 256->256) 11.4 / 12.1, 98 (8 images 28x28
-// 128->128) 7.5 / 8.2.  Chunks of the operators taken: halves of 196 tiles are up to 10 % slower than on the tiled kernels.
+// number of such tiles: 392 (16 images 28x28 128->256) 20.4 / 16.3, (32 images 28x28 128->128) 14.6 / 12.2, 392 (4 images 56x56 256->256) 22.3 / 19.0, 344
+// (7 images 28x28 512->512) 36.2 / 35.3, 296 (6 images) 37.2 / 33.4, 248 (5 images) 28.0 / 24.8, 200 (16 images 14x14 512->512) 25.5 / 20.7, 196 (32 images 14x14
+// 256->256) 15.5 / 12.8, (16 images 28x28 128->128) 10.0 / 8.6, (8 images 56x56 64->64) 7.2 / 6.8, 108 (3 images 37x41 192->192) 9.9 / 10.1, 104 (8 images 14x14
+// 512->512) 18.5 / 19.5, 100 (16 images 14x14 256->256) 11.4 / 12.1, 98 (8 images 28x28 128->128) 7.5 / 8.2.
 inline bool conv3_takes(const GemmArgs &a)
 {
     if (a.dtype != DT_BF16 || a.kh != 3 || a.kw != 3 || a.stride != 1 || a.pad != 1 || a.Cin % 64 || a.b_trans || a.pre_scale) return false;
@@ -65,10 +66,16 @@ inline bool conv3_takes(const GemmArgs &a)
 
 // Tile of one launch, chunks of a decomposed operator included (the tile never changes an element's order of additions).
 // 256 x 128 moves the fewest bytes per MFMA once there are well over one such tile per compute unit; 256 x 64 down to three of those on
-// four units if K is long; 128 x 64 below.  One launch alone, microseconds of 256x128 / 256x64 / 128x64, by the number of 256x64 tiles: 98 (16
+// four units if K is long; 128 x 64 below, and 64 x 64 where those leave half of the units empty (only chunks come there).  One launch alone,
+// microseconds of 256x128 / 256x64 / 128x64, by the number of 256x64 tiles: 98 (16
 // images 28x28 128->128) 19.8 / 12.1 / 8.6, 104 (16 images 14x14 512->512) 55.7 / 29.0 / 20.7, 196 (32 images 28x28 128->128) 20.4 / 12.9 / 12.2, (64 images
 // 14x14 256->256) 32.5 / 19.0 / 19.9, 200 (8 images 28x28 512->512) 57 / 32.3 / 35.7, 392 (8 images 56x56 256->256) 33.9 / 31.3 / 38.4, 784 (16 images 28x28
 // 512->512) 59.3 / 57.5 / 73.2; at 64 channels 196 (16 images 56x56) 14.5 / 9.8 / 9.1, 392 (32 images 56x56) - / 16.0 / 18.1.
+// Operators in two or four chunks, microseconds on the tiled kernels (they would add in another
+// order) / on 128x64 / on 64x64, by the 128x64 tiles of a chunk: 52 (four of 32 images 14x14 256->256) 40.0 / 46.3 / 32.8, 50 (four of 512 channels, 16 images 14x14)
+// 66.6 / 77.1 / 58.3, 98 (halves of 16 images 28x28 128->128) 14.6 / 16.1 / 12.8, (8 images 56x56 64->64) 11.1 / 12.5 / 10.3, 104 (16 images 14x14 512->512)
+// 33.6 / 39.0 / 31.4, 124 (20 images) 34.7 / 39.1 / 36.1, 124 (40 images 14x14 256->256) 21.3 / 24.1 / 20.9, 136 (44 images) - / 24.0 / 27.4, 148 (24 images
+// 14x14 512->512) 47.6 / 39.8 / 47.9, 172 (28 images 28x28 128->128) 18.1 / 16.6 / 18.2.
 // In rounds other tenants use the units that a launch leaves, so alone is not all: VGG-16, 8 images, halved along the batch, ResNet-50, 16
 // images, halved along the channels, and MobileNetV3, 32 images, took 1760 us with 128 x 64 below 256 tiles, 1730 below 128 (both with two
 // weight stages).
@@ -76,6 +83,7 @@ struct Conv3Tile { int bm, bn; };
 inline Conv3Tile conv3_tile(const GemmArgs &a)
 {
     if (conv3_bn(a.n_hi - a.n_lo) == 128 && conv3_wgs(a, 256, 128) > 360) return {256, 128};
+    if (conv3_wgs(a, 128, 64) <= 128) return {64, 64};
     return {conv3_wgs(a, 256, 64) >= (a.Cin >= 256 ? 180 : 257) ? 256 : 128, 64};
 }
 

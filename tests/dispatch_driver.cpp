@@ -117,8 +117,37 @@ static void check_surplus_tiles()
     }
 }
 
+// A 3x3 convolution marked for conv3_kernel: images [b_lo, b_hi) and channels [n_lo, n_hi) of it.
+static LaunchInfo staged(int images, int hw, int cin, int n_lo, int n_hi)
+{
+    GemmArgs a = product(DT_BF16, images * hw * hw, n_hi, cin, 3);
+    a.H = a.W = a.Ho = a.Wo = hw;
+    a.x_img = (int64_t)hw * hw * cin;
+    a.x_bytes = images * a.x_img * 2;
+    a.w_bytes = (int64_t)n_hi * a.K * 2;
+    a.n_lo = n_lo;
+    a.halo = 1;
+    return launch_igemm(a, nullptr, true);
+}
+
+// Tiles of conv3_kernel on either side of its lines.
+static void check_staged_tiles()
+{
+    struct { int images, hw, cin, n; const char *kernel; int wgs; } cases[] = {
+        {8, 28, 128, 128, "conv3_bf16_64x64", 196}, {16, 28, 128, 128, "conv3_bf16_128x64", 196}, {20, 14, 512, 256, "conv3_bf16_64x64", 248},
+        {21, 14, 512, 256, "conv3_bf16_128x64", 132}, {10, 56, 64, 32, "conv3_bf16_128x64", 245}, {5, 56, 64, 32, "conv3_bf16_64x64", 245},
+        {40, 56, 64, 64, "conv3_bf16_256x64", 490}, {32, 56, 256, 256, "conv3_bf16_256x128", 784}};
+    for (auto &c : cases) {
+        const LaunchInfo li = staged(c.images, c.hw, c.cin, 0, c.n);
+        CHECK(li.kernel == std::string(c.kernel));
+        CHECK(li.workgroups == c.wgs);
+        CHECK(li.lds_bytes <= 160 * 1024 && li.wg_per_cu == 160 * 1024 / li.lds_bytes);
+    }
+}
+
 int main()
 {
+    check_staged_tiles();
     check_depthwise_windows();
     check_bf16_rows();
     check_surplus_tiles();

@@ -397,6 +397,20 @@ def test_staged_3x3_with_three_weight_stages(tile, spec):
     assert sum(n.startswith("conv3") for n in ran) == 1
 
 
+@pytest.mark.parametrize("spec", [(3, 61, 59, 64, 250, "relu", True), (16, 29, 27, 64, 130, "none", False), (5, 57, 113, 128, 64, "hswish", True), (30, 5, 100, 192, 70, "relu6", False)])
+def test_staged_3x3_in_chunks_of_few_tiles(spec):
+    """conv3_kernel on 64x64 tiles, for chunks of an operator that leave half of the units empty on larger ones: two strips of columns, images that
+    end inside a tile, ragged channels; every chunk has the bits of the whole."""
+    from synth import graphs as G
+    batch, h, w, cin, cout, act, res = spec
+    b = G._B("chunks", "bf16", batch)
+    x = b.tensor(batch, cin, h, w)
+    y = b.conv(x, cout, 1, 1, 0, "none") if res else -1
+    t = b.done(x, b.conv(x, cout, 3, 1, 1, act, res=y))
+    ran = check([t], ["conv3_bf16_128x64"], [("batch", 2), ("cout", 2), ("cout", 8)], ["conv3_bf16_64x64"])
+    assert "conv3_bf16_64x64" not in ran
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_rows_with_short_k(dtype):
     """rowgemm_kernel: every number of 32-byte k groups, K that fills half a group, one column of tiles, two and more, four side by
