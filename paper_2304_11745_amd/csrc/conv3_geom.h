@@ -65,12 +65,18 @@ inline bool conv3_takes(const GemmArgs &a)
 }
 
 // Tile of one launch, chunks of a decomposed operator included (the tile never changes an element's order of additions).
-// 256 x 128 moves the fewest bytes per MFMA once there are well over one such tile per compute unit; 256 x 64 down to three of those on
-// four units if K is long; 128 x 64 below, and 64 x 64 where those leave half of the units empty (only chunks come there).  One launch alone,
+// 256 x 128 moves the fewest bytes per MFMA once there are well over one such tile per compute unit; 256 x 64 if 128 x 64 would leave some units
+// a second tile and K is long, or if there is more than one per unit; 128 x 64 below, and 64 x 64 where those leave half of the units empty (only chunks come
+// there).  One launch alone,
 // microseconds of 256x128 / 256x64 / 128x64, by the number of 256x64 tiles: 98 (16
 // images 28x28 128->128) 19.8 / 12.1 / 8.6, 104 (16 images 14x14 512->512) 55.7 / 29.0 / 20.7, 196 (32 images 28x28 128->128) 20.4 / 12.9 / 12.2, (64 images
 // 14x14 256->256) 32.5 / 19.0 / 19.9, 200 (8 images 28x28 512->512) 57 / 32.3 / 35.7, 392 (8 images 56x56 256->256) 33.9 / 31.3 / 38.4, 784 (16 images 28x28
-// 512->512) 59.3 / 57.5 / 73.2; at 64 channels 196 (16 images 56x56) 14.5 / 9.8 / 9.1, 392 (32 images 56x56) - / 16.0 / 18.1.
+// 512->512) 59.3 / 57.5 / 73.2;
+// at 64 channels 196 (16 images 56x56) 14.5 / 9.8 / 9.1, 392 (32 images 56x56) - / 16.0 / 18.1.  Between those, 256x64 / 128x64: K of 256 or 512 channels
+// 128 (20 images 14x14 512->512, 248 tiles of 128x64) 29.5 / 24.3, 132 (42 images 14x14 256->256, 260) 18.8 / 18.7, 136 (21 images 14x14 512->512, 264) 29.8 / 32.0, 152 (24
+// images) 30.2 / 33.0, 148 (48 images 14x14 256->256) 19.3 / 19.5, 176 (7 images 28x28 512->512) 31.7 / 34.6; 64 or 128 channels 148 (24 images 28x28 128->128)
+// 12.7 / 12.2, 172 (14 images 56x56 64->64) 10.0 / 9.2, 222 (36 images 28x28 128->128) 13.9 / 13.9, 245 (20 images 56x56 64->64) 10.7 / 10.1, 258 (21 images) 12.5 /
+// 13.6, 258 (42 images 28x28 128->128) 18.0 / 19.9.
 // Operators in two or four chunks, microseconds on the tiled kernels (they would add in another
 // order) / on 128x64 / on 64x64, by the 128x64 tiles of a chunk: 52 (four of 32 images 14x14 256->256) 40.0 / 46.3 / 32.8, 50 (four of 512 channels, 16 images 14x14)
 // 66.6 / 77.1 / 58.3, 98 (halves of 16 images 28x28 128->128) 14.6 / 16.1 / 12.8, (8 images 56x56 64->64) 11.1 / 12.5 / 10.3, 104 (16 images 14x14 512->512)
@@ -84,7 +90,7 @@ inline Conv3Tile conv3_tile(const GemmArgs &a)
 {
     if (conv3_bn(a.n_hi - a.n_lo) == 128 && conv3_wgs(a, 256, 128) > 360) return {256, 128};
     if (conv3_wgs(a, 128, 64) <= 128) return {64, 64};
-    return {conv3_wgs(a, 256, 64) >= (a.Cin >= 256 ? 180 : 257) ? 256 : 128, 64};
+    return {(a.Cin >= 256 ? conv3_wgs(a, 128, 64) : conv3_wgs(a, 256, 64)) > 256 ? 256 : 128, 64};
 }
 
 }  // namespace gacer
