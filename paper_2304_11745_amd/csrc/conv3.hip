@@ -250,7 +250,8 @@ static LaunchInfo go_conv3(const GemmArgs &a, hipStream_t s, bool dry)
     li.threads = THREADS;
     li.lds_bytes = 2 * conv3_input_bytes(BM) + NSB * TPS * BN * ROWB;
     li.wg_per_cu = 160 * 1024 / li.lds_bytes;
-    static const std::string name = "conv3_bf16_" + std::to_string(BM) + "x" + std::to_string(BN);
+    // 256x64 tiles have two forms: with three weight stages, and with two
+    static const std::string name = "conv3_bf16_" + std::to_string(BM) + "x" + std::to_string(BN) + (BM == 256 && BN == 64 && NSB == 3 ? "s3" : "");
     li.kernel = name.c_str();
     li.phases = 1;
     if (dry || li.workgroups == 0) return li;

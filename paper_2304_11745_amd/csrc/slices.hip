@@ -382,7 +382,7 @@ static LaunchInfo go_slices(const GemmArgs &a, hipStream_t s, bool dry, int phas
     const bool small = a.K <= PRE_SMALL && tiles_m * tiles_n * a.ksplit > 256;
     li.lds_bytes = S * 512 * TILE + (a.pre_scale ? 8 * (small ? PRE_SMALL : SLICES_PRE_MAX) : 0);
     li.wg_per_cu = (160 * 1024) / li.lds_bytes;
-    static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S);
+    static const std::string shape = std::string(DT == DT_BF16 ? "bf16_x" : "f32_x") + std::to_string(S) + (TILE == 16 ? "_16x16" : "");
     static const std::string n_one = "igemm_slices_" + shape, n_pre = "igemm_affine_slices_" + shape;
     li.kernel = phase == 2 ? "splitk_finish" : a.pre_scale ? n_pre.c_str() : n_one.c_str();
     li.phases = a.ksplit > 1 ? 2 : 1;

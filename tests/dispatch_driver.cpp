@@ -137,7 +137,7 @@ static void check_staged_tiles()
         {8, 28, 128, 128, "conv3_bf16_64x64", 196}, {16, 28, 128, 128, "conv3_bf16_128x64", 196}, {20, 14, 512, 256, "conv3_bf16_64x64", 248},
         {21, 14, 512, 256, "conv3_bf16_128x64", 132}, {10, 56, 64, 32, "conv3_bf16_128x64", 245}, {5, 56, 64, 32, "conv3_bf16_64x64", 245},
         {20, 56, 64, 64, "conv3_bf16_128x64", 490}, {21, 56, 64, 64, "conv3_bf16_256x64", 258}, {20, 14, 512, 512, "conv3_bf16_128x64", 248},
-        {21, 14, 512, 512, "conv3_bf16_256x64", 136}, {40, 56, 64, 64, "conv3_bf16_256x64", 490}, {32, 56, 256, 256, "conv3_bf16_256x128", 784}};
+        {21, 14, 512, 512, "conv3_bf16_256x64s3", 136}, {42, 14, 512, 512, "conv3_bf16_256x64", 264}, {40, 56, 64, 64, "conv3_bf16_256x64", 490}, {32, 56, 256, 256, "conv3_bf16_256x128", 784}};
     for (auto &c : cases) {
         const LaunchInfo li = staged(c.images, c.hw, c.cin, 0, c.n);
         CHECK(li.kernel == std::string(c.kernel));

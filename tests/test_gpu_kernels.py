@@ -153,8 +153,9 @@ def test_k_slices_on_small_tiles_in_fp32():
         x = b.tensor(batch, cin, h, w)
         r = b.conv(x, cout, 1, stride, 0, "none") if res else -1
         tenants.append(b.done(x, b.conv(b.affine(x, "relu") if affine else x, cout, k, stride, k // 2, "relu", res=r)))
-    ran = check(tenants, ["igemm_slices_f32_x4", "igemm_slices_f32_x8", "igemm_affine_slices_f32", "splitk_finish"], [("batch", 2), ("cout", 2), ("cout", 8)])
-    assert all("slices" in n or n == "splitk_finish" for n in ran), ran
+    small = {"igemm_slices_f32_x4_16x16", "igemm_slices_f32_x8_16x16", "igemm_affine_slices_f32_x4_16x16", "igemm_affine_slices_f32_x8_16x16"}
+    ran = check(tenants, [], [("batch", 2), ("cout", 2), ("cout", 8)], ["igemm_slices_f32_x4_16x16", "igemm_slices_f32_x8_16x16"])
+    assert ran == small | {"igemm_slices_f32_x4", "igemm_slices_f32_x8", "igemm_affine_slices_f32_x4", "splitk_finish"}, sorted(ran)
 
 
 def test_number_of_tiles_for_k_slices_in_fp32():
@@ -385,16 +386,18 @@ def test_input_staged_once_for_nine_taps():
     check(tenants, ["conv3_bf16_256x64", "conv3_bf16_256x128"], [("batch", 2), ("cout", 2), ("cout", 8)], ["conv3_bf16_128x64", "conv3_bf16_256x64"])
 
 
-@pytest.mark.parametrize("tile,spec", [("128x64", (4, 61, 59, 64, 120, "relu", True)), ("128x64", (16, 27, 29, 64, 130, "hswish", False)), ("256x64", (4, 57, 53, 256, 250, "none", False))])
+@pytest.mark.parametrize("tile,spec", [("128x64", (4, 61, 59, 64, 120, "relu", True)), ("128x64", (16, 27, 29, 64, 130, "hswish", False)), ("256x64s3", (4, 57, 53, 256, 250, "none", False)),
+                                       ("256x64", (12, 57, 53, 256, 120, "relu", True))])
 def test_staged_3x3_with_three_weight_stages(tile, spec):
-    """conv3_kernel with few tiles: 128 positions, and 256 where K is long, both with three stages of weights; ragged images and channels."""
+    """conv3_kernel with few tiles: 128 positions, and 256 where K is long, both with three stages of weights, and 256 with two where there are more
+    than one per unit; ragged images and channels."""
     from synth import graphs as G
     batch, h, w, cin, cout, act, res = spec
     b = G._B("staged", "bf16", batch)
     x = b.tensor(batch, cin, h, w)
     y = b.conv(x, cout, 1, 1, 0, "none") if res else -1
-    ran = check([b.done(x, b.conv(x, cout, 3, 1, 1, act, res=y))], ["conv3_bf16_" + tile], [("batch", 2), ("cout", 2)])
-    assert sum(n.startswith("conv3") for n in ran) == 1
+    ran = check([b.done(x, b.conv(x, cout, 3, 1, 1, act, res=y))], [], [("batch", 2), ("cout", 2)])
+    assert [n for n in ran if n.startswith("conv3")] == ["conv3_bf16_" + tile]
 
 
 @pytest.mark.parametrize("spec", [(3, 61, 59, 64, 250, "relu", True), (16, 29, 27, 64, 130, "none", False), (5, 57, 113, 128, 64, "hswish", True), (30, 5, 100, 192, 70, "relu6", False)])
