@@ -886,8 +886,8 @@ static LaunchInfo go(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok, in
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_GATHER>), grid, block, 0, s, b);
     else if (taps)
         GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, LOAD_TAPS>), grid, block, 0, s, b);
-    else            // bf16 rows of more than 256 bytes are igemm_dma_kernel's: no loader of their own here, the one for windows takes them too
-        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, DT == DT_F32 || KV == 4 ? LOAD_VEC : LOAD_TAPS>), grid, block, 0, s, b);
+    else            // wide bf16 rows of more than 256 bytes are igemm_dma_kernel's: no loader of their own here, the one for windows takes them too
+        GACER_LAUNCH((igemm_kernel<DT, BM, BN, WM, WN, KV, DT == DT_F32 || KV == 4 || BN == 32 ? LOAD_VEC : LOAD_TAPS>), grid, block, 0, s, b);
     if (ks > 1 && phase == 0) finish<T>(a, s);
     return li;
 }
@@ -1025,7 +1025,14 @@ static LaunchInfo pick(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     const int64_t k_bytes = (int64_t)a.K * (int64_t)sizeof(typename El<DT>::T);
     if (vec_ok && !a.b_trans && (!taps || a.kh * a.kw <= 31)) {
         if constexpr (DT == DT_BF16) {
-            if (k_bytes >= (taps ? 512 : 256)) return pick_dma_bf16(a, s, dry, phase);
+            // N <= 32: two of these workgroups fit a unit, three of the register-staged ones (six with 64-byte blocks).  Rows go where fewer waves of
+            // workgroups are needed, here if both need as many; windows of up to 64 channels stay there where there are many.  Us there / here, by the
+            // workgroups: rows of K = 128 784 (two halves) 19.0 / 20.5, 1568 15.1 / 17.8, 2809 23.5 / 27.3, K = 136 512 6.8 / 6.2, 600 7.7 / 8.2, 800 9.9 / 9.6, 1300
+            // 15.7 / 16.8, K = 256 700 11.9 / 12.1, 1000 15.9 / 15.7, 2500 32.1 / 34.4; 3x3 of 32 channels 784 11.9 / 10.9, 1960 19.3 / 19.3, 2940 26.0 / 27.7, of
+            // 64 1960 27.7 / 27.7, 2940 36.8 / 37.8, of 96 2940 53.2 / 50.1.
+            const int64_t w = wgs(128, 32), there = k_bytes <= 256 ? 1536 : 768;
+            const bool narrow = N <= 32 && (taps ? w > 2048 && k_bytes <= 1152 : (w + 511) / 512 > (w + there - 1) / there);
+            if (k_bytes >= (taps ? 512 : 256) && !narrow) return pick_dma_bf16(a, s, dry, phase);
         } else {
             if (shape != T128x32 && k_bytes >= (taps ? 1536 : 512)) return go_dma<DT, 64, 64, 2, 2, 8, 3>(a, s, dry, vec_ok, phase);
         }

@@ -73,7 +73,8 @@ static GemmArgs product(int dtype, int M, int N, int K, int k = 1)
     return a;
 }
 
-// The kernels that stage bf16 rows through registers have no loader for aligned single-tap rows of more than 256 bytes: none may come there.
+// The kernels that stage bf16 rows through registers have no loader for aligned single-tap rows of more than 256 bytes and more than 32 channels: none
+// may come there.  Up to 32 channels the tiles' number decides.
 static void check_bf16_rows()
 {
     int dma = 0;
@@ -81,11 +82,22 @@ static void check_bf16_rows()
         for (int M : {1, 31, 300, 5000, 70000})
             for (int N : {1, 32, 33, 64, 128, 200, 1000}) {
                 const std::string name = launch_igemm(product(DT_BF16, M, N, K), nullptr, true).kernel;
-                CHECK(name.find("igemm_bf16_") != 0 || name.rfind("x32") == name.size() - 3);
-                dma += name.find("igemm_dma_bf16_") == 0;
-                CHECK((K * 2 >= 256) == (name.find("igemm_dma_bf16_") == 0));
+                const bool is_dma = name.find("igemm_dma_bf16_") == 0, many = N <= 32 && M > 65536 && (K == 128 || M < 98304);
+                CHECK(name.find("igemm_bf16_") != 0 || N <= 32 || name.rfind("x32") == name.size() - 3);
+                CHECK((K * 2 >= 256 && !many) == is_dma);
+                dma += is_dma;
             }
-    CHECK(dma > 500);
+    CHECK(dma > 450);
+    auto rows = [](int tiles, int K) { return std::string(launch_igemm(product(DT_BF16, tiles * 128, 32, K), nullptr, true).kernel); };
+    for (int K : {136, 512}) {
+        for (int tiles : {100, 512, 769, 1024}) CHECK(rows(tiles, K) == "igemm_dma_bf16_128x32x64s3");
+        for (int tiles : {513, 768, 1025, 1600, 2500}) CHECK(rows(tiles, K) == "igemm_bf16_128x32x64");
+    }
+    CHECK(rows(512, 128) == "igemm_dma_bf16_128x32x64s3" && rows(513, 128) == "igemm_bf16_128x32x32" && rows(1024, 128) == "igemm_bf16_128x32x32");
+    // windows of few channels
+    auto kernel = [](int M, int N, int K, int k) { return std::string(launch_igemm(product(DT_BF16, M, N, K, k), nullptr, true).kernel); };
+    CHECK(kernel(2048 * 128, 32, 64, 3) == "igemm_dma_taps_bf16_128x32x64s3" && kernel(2049 * 128, 32, 64, 3) == "igemm_taps_bf16_128x32x64");
+    CHECK(kernel(2049 * 128, 32, 72, 3) == "igemm_dma_taps_bf16_128x32x64s3");
 }
 
 // fp32 launches of 64x64 tiles: as many tiles as lie beyond a multiple of 256, if at most 128, make four workgroups each, in launches of one
