@@ -955,7 +955,12 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
 // residual (800) 19.5 / 18.6 / 16.2 / 17.2, 12544x1024x256 with a residual (1568) 23.8 / 21.1 / 21.4 / 19.2; long K: 2048x768x768 (192) 7.9 / 8.4 / 10.4 / 15.8,
 // 2048x768x3072 (192) 19.9 / 18.8 / 23.0 / 45.9, 4096x768x768 (384) 11.2 / 12.0 / 11.2 / 16.0, 4096x768x3072 (384) 31.5 / 30.3 / 25.0 / 45.7, 1024x3072x768 with a GELU
 // (384) 13.0 / 14.7 / 17.8 / 29.0, 8192x768x3072 (768) 60.5 / 48.7 / 49.9 / 48.7, 8192x2304x768 (2304) 55.6 / 50.6 / 49.1 / 46.1; and 128x32 / 64x64 for N <= 32:
-// 25088x32x1152 (3x3) 7.9 / 9.1, 50176x32x192 5.7 / 7.9.  Before (64x64 and 128x128 tiles staged through registers below 1.5 KB of K, fewer
+// 25088x32x1152 (3x3) 7.9 / 9.1, 50176x32x192 5.7 / 7.9.
+// Where a launch has a few workgroups more than the units hold, us 64x64 / 128x64 (64-byte blocks of K) / 128x64 / 128x128, by the workgroups of 128x64:
+// 66560x64x1024 (520) 24.7 / - / 28.5 / 32.4, 102400x64x1024 (800) 35.8 / - / 38.3 / 43.8, 66560x64x2048 (520) 48.5 / - / 53.9 / 60.4, 33856x128x1024 (530)
+// 20.3 / - / 21.3 / 23.4, 16640x256x768 (520) 16.0 / - / 17.2 / 16.8, 6272x1024x1024 (784) 26.1 / - / 23.9 / 21.9, 2560x3072x3072 (960) 109 / - / 79.7 / 70.3;
+// 66560x64x384 (520) 13.6 / 14.8 / 15.9 / -, 89600x64x384 (700) 17.3 / 16.1 / 17.9 / -, 140800x64x512 (1100) - / 28.7 / 30.5 / -; 33920x256x512 (1060) - / - / 21.3 / 21.9;
+// 100352x64x2160 (784, 3x3) 59.7 / - / 54.0 / -.  Before (64x64 and 128x128 tiles staged through registers below 1.5 KB of K, fewer
 // tiles to choose from above) 98 such shapes took 9 % longer, 12544x96x576 8.5, 25088x32x1152 11.1, 12544x256x512 11.5, 4096x768x3072 31.7.
 static LaunchInfo pick_dma_bf16(const GemmArgs &a, hipStream_t s, bool dry, int phase)
 {
@@ -967,13 +972,17 @@ static LaunchInfo pick_dma_bf16(const GemmArgs &a, hipStream_t s, bool dry, int 
     if (wide && k_bytes >= 512) {
         if (wgs(256, 128) >= 384) return go_dma<DT_BF16, 256, 128, 2, 2, 4, 3>(a, s, dry, true, phase);
         const int64_t w = wgs(128, 128);
-        if (k_bytes <= 1024 ? w >= 384 : taps && w > 256) return go_dma<DT_BF16, 128, 128, 2, 2, 4, 4>(a, s, dry, true, phase);
+        // two per unit; some more than these wait for a whole second wave of them
+        if (k_bytes <= 1024 ? w >= 384 && (w <= 512 || w > 560 || k_bytes <= 576) : w > 256 && (taps || (w > 384 && w <= 512)))
+            return go_dma<DT_BF16, 128, 128, 2, 2, 4, 4>(a, s, dry, true, phase);
         // one workgroup per unit: nothing covers the epilogue, so not where that is long (erf)
         if (k_bytes >= 1536 && w >= 160 && w <= 256 && a.act != ACT_GELU) return go_dma<DT_BF16, 128, 128, 2, 2, 8, 3>(a, s, dry, true, phase);
     }
     const int64_t w = wgs(128, 64);
-    if (k_bytes <= 512 && w >= 300) return go_dma<DT_BF16, 128, 64, 2, 2, 4, 3>(a, s, dry, true, phase);       // four per unit
-    if (k_bytes <= 1024 ? w >= 300 : w > 400 || (k_bytes >= 4096 && w >= 192)) return go_dma<DT_BF16, 128, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
+    if (k_bytes <= 512 ? w >= 300 : k_bytes <= 1024 && N <= 64 && w > 512) return go_dma<DT_BF16, 128, 64, 2, 2, 4, 3>(a, s, dry, true, phase);       // four per unit
+    // two per unit, with the same wait; 64x64 tiles, of which there are three per unit, wait for less
+    const bool spill = !taps && w > 512 && k_bytes > 1024 && w <= (k_bytes <= 2048 ? (N <= 64 ? 832 : 600) : N <= 64 ? 640 : 512);
+    if (!spill && (k_bytes <= 1024 ? w >= 300 : w > 400 || (k_bytes >= 4096 && w >= 192))) return go_dma<DT_BF16, 128, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
     // alone on its unit with a long K a fourth stage pays (1024x768x768 7.0 -> 6.5); with more workgroups it costs one of them its place
     if (wgs(64, 64) <= 256 && k_bytes >= (taps ? 4096 : 1024)) return go_dma<DT_BF16, 64, 64, 2, 2, 8, 4>(a, s, dry, true, phase);
     return go_dma<DT_BF16, 64, 64, 2, 2, 8, 3>(a, s, dry, true, phase);

@@ -94,10 +94,14 @@ static void check_bf16_rows()
         for (int tiles : {513, 768, 1025, 1600, 2500}) CHECK(rows(tiles, K) == "igemm_bf16_128x32x64");
     }
     CHECK(rows(512, 128) == "igemm_dma_bf16_128x32x64s3" && rows(513, 128) == "igemm_bf16_128x32x32" && rows(1024, 128) == "igemm_bf16_128x32x32");
-    // windows of few channels
+    // windows of few channels, and 128x64 tiles that would begin a second wave on the units
     auto kernel = [](int M, int N, int K, int k) { return std::string(launch_igemm(product(DT_BF16, M, N, K, k), nullptr, true).kernel); };
     CHECK(kernel(2048 * 128, 32, 64, 3) == "igemm_dma_taps_bf16_128x32x64s3" && kernel(2049 * 128, 32, 64, 3) == "igemm_taps_bf16_128x32x64");
     CHECK(kernel(2049 * 128, 32, 72, 3) == "igemm_dma_taps_bf16_128x32x64s3");
+    CHECK(kernel(512 * 128, 64, 1024, 1) == "igemm_dma_bf16_128x64x64s3" && kernel(513 * 128, 64, 1024, 1) == "igemm_dma_bf16_64x64x64s3");
+    CHECK(kernel(832 * 128, 64, 1024, 1) == "igemm_dma_bf16_64x64x64s3" && kernel(833 * 128, 64, 1024, 1) == "igemm_dma_bf16_128x64x64s3");
+    CHECK(kernel(384 * 64, 256, 2048, 1) == "igemm_dma_bf16_128x64x64s3" && kernel(386 * 64, 256, 2048, 1) == "igemm_dma_bf16_128x128x32s4");
+    CHECK(kernel(300 * 64, 256, 1024, 1) == "igemm_dma_bf16_64x64x64s3" && kernel(302 * 64, 256, 1024, 1) == "igemm_dma_bf16_128x64x64s3");
 }
 
 // fp32 launches of 64x64 tiles: as many tiles as lie beyond a multiple of 256, if at most 128, make four workgroups each, in launches of one
