@@ -445,7 +445,8 @@ LaunchInfo launch_slices(const GemmArgs &a, hipStream_t s, bool dry, int phase)
     // 8.91 / 5.88, affine + 125x128x992 (64) 10.8 / 7.0, affine + 500x128x352 (256) 6.66 / 4.90, 392x160x960 (250) 7.60 / 5.15, 128x768x768 (384) 6.48 / 5.74,
     // 507x256x1152 (512) 9.01 / 8.49, 1568x96x576 (588) 5.70 / 6.53, 1875x128x1152 (944) 9.02 / 13.3.
     const int64_t t16 = (int64_t)((a.m_hi - a.m_lo + 15) / 16) * ((a.n_hi - a.n_lo + 15) / 16) * a.ksplit;
-    if (t16 <= 512) return a.kwaves == 8 ? go_slices<DT_F32, 8, 16>(a, s, dry, phase) : go_slices<DT_F32, 4, 16>(a, s, dry, phase);
+    // Beside a fused affine's parameters, eight waves leave room for one workgroup per unit: affine + 784x128x896 (392) 10.6 / 12.6.
+    if (t16 <= (a.kwaves == 8 && a.pre_scale ? 256 : 512)) return a.kwaves == 8 ? go_slices<DT_F32, 8, 16>(a, s, dry, phase) : go_slices<DT_F32, 4, 16>(a, s, dry, phase);
     return a.kwaves == 8 ? go_slices<DT_F32, 8>(a, s, dry, phase) : go_slices<DT_F32, 4>(a, s, dry, phase);
 }
 

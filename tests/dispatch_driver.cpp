@@ -162,8 +162,23 @@ static void check_staged_tiles()
     }
 }
 
+// 16x16 tiles of K slices in fp32: as many as the units hold at once.
+static void check_small_tiles()
+{
+    for (int affine = 0; affine < 2; ++affine)
+        for (int waves : {4, 8})
+            for (int tiles : {1, 256, 257, 512, 513}) {
+                GemmArgs a = product(DT_F32, tiles * 16, 16, 1024);
+                a.kwaves = waves; a.kb_per_wave = 64 / waves;
+                if (affine) a.pre_scale = a.pre_shift = (const float *)0x10000;
+                const std::string name = launch_igemm(a, nullptr, true).kernel;
+                CHECK((name.find("_16x16") != std::string::npos) == (tiles <= (affine && waves == 8 ? 256 : 512)));
+            }
+}
+
 int main()
 {
+    check_small_tiles();
     check_staged_tiles();
     check_depthwise_windows();
     check_bf16_rows();
