@@ -1,5 +1,6 @@
 // Geometry of expand_dw_kernel's launches (host code): how an image is cut into bands, what a workgroup keeps in LDS.
 #pragma once
+#include <algorithm>
 #include "kernels.h"
 
 namespace gacer {
@@ -41,19 +42,26 @@ inline ExpandGeom expand_geometry(const GemmArgs &g, const StreamArgs &d)
     return e;
 }
 
-// Whether the pair (whole operators; the executor has checked their kinds, strides and alignment) runs as one launch.  Measured as above
-// the kernel, two launches / one: images up to 28 pixels wide gain while the wide tensor times the bytes of K stays under about 5e8 (32
-// images 7x7 160->960 9.48 / 8.04, 14x14 80->480 11.0 / 11.1, 96->576 11.6 / 12.3), 5x5 windows under 2.5e8 (8 images 14x14 112->672
-// 9.67 / 7.24, 32 images 16.7 / 17.8); wider ones only where a launch leaves units idle (one image 112x112 16->96 6.50 / 5.92, 8 images
-// 13.9 / 14.4, 32 images 34.7 / 39.3), with 5x5 windows not at all (one image 56x56 24->72 5.86 / 6.28).
+// Whether the pair (whole operators; the executor has checked their kinds, strides and alignment) runs as one launch: while what it forms,
+// counted as products (the halo and the rest of the last tiles included) times how often a position is formed, stays below a bound, since that
+// grows faster than what two launches take.  Us two launches / one, by that count in 1e9: 3x3 one image 28x28 40->240 (0.13) 5.6 / 4.3, 8 images 28x28
+// 40->240 (1.1) 7.9 / 6.6, 14x14 96->576 (0.3) 6.7 / 5.9, 32 images 7x7 160->960 (0.8) 9.5 / 8.1; 16 images 28x28 40->240 (1.2, more
+// workgroups than fit at once) 10.0 / 11.0, 32 images (2.4) 16.5 / 18.4, 4 images 28x28 160->480 (2.6) 9.3 / 12.7, 8 images 14x14 192->768 (2.8) 9.2 / 10.5.
+// 5x5 one image 14x14 112->672 (0.4) 5.9 / 5.0, 8 images (1.8, bands of four rows) 9.7 / 7.1, 8 images 28x28 40->120 (1.2) 7.8 / 7.0; 16 images
+// (2.4) 9.6 / 10.3, 8 images 28x28 80->160 (4.2, bands of one row) 8.9 / 12.9, 32 images 7x7 256->256 (17, likewise) 8.0 / 16.4.  Of 4290 pairs of 1 to 64
+// images the rule takes 3949, 56 of which are more than 3 % slower as one launch (by 17 % at most); a bound on the operators' own products had taken 250
+// of those, up to twice as slow.  Images wider than 28 pixels only where a launch leaves units idle (one image 112x112 16->96 6.50 / 5.92, 8 images 13.9 / 14.4,
+// 32 images 34.7 / 39.3), with 5x5 windows not at all (one image 56x56 24->72 5.86 / 6.28).
 inline bool expand_dw_takes(const GemmArgs &g, const StreamArgs &d)
 {
     if (g.dtype != DT_BF16) return false;
     const ExpandGeom e = expand_geometry(g, d);
     if (e.lds > ExpandGeom::LDS_MAX || (int64_t)(d.n_hi - d.n_lo) * e.bands * e.blocks > 1 << 24) return false;
-    const int64_t work = (int64_t)(d.n_hi - d.n_lo) * d.H * d.W * d.C * g.K * 2;
-    if (d.W > 28) return d.k == 3 && e.workgroups <= 256;
-    return work <= (d.k == 3 ? 500000000 : 250000000);
+    const double formed = (double)e.workgroups * e.tiles * 32 * 32 * (e.k_blocks * e.rowb), again = (double)e.bands * e.tiles * 32 / ((double)d.H * d.W);
+    const double count = formed * again;
+    if (d.k == 3) return count <= 1.5e9 && e.workgroups <= 256 * (d.W > 28 ? 1 : std::min(8, 160 * 1024 / e.lds));
+    if (d.W > 28 || count <= 1e8) return d.W <= 28;
+    return e.rows >= 2 && d.W > 4 && count <= (d.W <= 16 && e.rows >= 4 ? 2e9 : d.stride == 1 ? 1.3e9 : d.W <= 16 ? 5e8 : 3e8);
 }
 
 }  // namespace gacer

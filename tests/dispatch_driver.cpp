@@ -4,7 +4,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
-#include "../paper_2304_11745_amd/csrc/kernels.h"
+#include "../paper_2304_11745_amd/csrc/expand_geom.h"
 
 using namespace gacer;
 
@@ -162,6 +162,25 @@ static void check_staged_tiles()
     }
 }
 
+// A pointwise product and the depthwise convolution behind it as one launch: pairs on either side of what expand_dw_takes allows.
+static void check_pointwise_depthwise_pairs()
+{
+    struct { int n, hw, c, co, k, stride; bool one; } cases[] = {
+        {8, 28, 40, 240, 3, 1, true}, {16, 28, 40, 240, 3, 1, false}, {4, 28, 160, 480, 3, 1, false}, {8, 14, 192, 768, 3, 1, false}, {32, 7, 160, 960, 3, 1, true},
+        {1, 112, 16, 96, 3, 2, true}, {8, 112, 16, 96, 3, 2, false}, {8, 14, 112, 672, 5, 1, true}, {9, 14, 112, 136, 5, 2, true}, {8, 28, 40, 120, 5, 1, true},
+        {16, 28, 40, 120, 5, 1, false}, {8, 28, 80, 160, 5, 1, false}, {32, 7, 256, 256, 5, 1, false}, {64, 3, 160, 960, 5, 1, false}, {1, 56, 24, 72, 5, 1, false}};
+    for (auto &c : cases) {
+        const GemmArgs g = product(DT_BF16, c.n * c.hw * c.hw, c.co, c.c);
+        StreamArgs d;
+        std::memset(&d, 0, sizeof d);
+        d.dtype = DT_BF16;
+        d.N = d.n_hi = c.n; d.H = d.W = c.hw; d.C = d.c_hi = c.co; d.k = c.k; d.stride = c.stride; d.pad = c.k / 2;
+        d.Ho = d.Wo = (c.hw + 2 * d.pad - c.k) / c.stride + 1;
+        if (expand_dw_takes(g, d) != c.one) std::fprintf(stderr, "%d images %dx%d %d->%d %dx%d\n", c.n, c.hw, c.hw, c.c, c.co, c.k, c.k);
+        CHECK(expand_dw_takes(g, d) == c.one);
+    }
+}
+
 // 16x16 tiles of K slices in fp32: as many as the units hold at once.
 static void check_small_tiles()
 {
@@ -178,6 +197,7 @@ static void check_small_tiles()
 
 int main()
 {
+    check_pointwise_depthwise_pairs();
     check_small_tiles();
     check_staged_tiles();
     check_depthwise_windows();
