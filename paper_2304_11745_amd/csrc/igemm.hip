@@ -975,8 +975,9 @@ static LaunchInfo pick_dma_bf16(const GemmArgs &a, hipStream_t s, bool dry, int 
         // two per unit; some more than these wait for a whole second wave of them
         if (k_bytes <= 1024 ? w >= 384 && (w <= 512 || w > 560 || k_bytes <= 576) : w > 256 && (taps || (w > 384 && w <= 512)))
             return go_dma<DT_BF16, 128, 128, 2, 2, 4, 4>(a, s, dry, true, phase);
-        // one workgroup per unit: nothing covers the epilogue, so not where that is long (erf)
-        if (k_bytes >= 1536 && w >= 160 && w <= 256 && a.act != ACT_GELU) return go_dma<DT_BF16, 128, 128, 2, 2, 8, 3>(a, s, dry, true, phase);
+        // one workgroup per unit: nothing covers the epilogue, so where that is long (erf) only with a long K (us 128x64 / here: 2688x1024x1024 14.7 / 20.3, x2048
+        // 24.7 / 27.7, x3072 34.2 / 33.5, x4096 40.4 / 38.3)
+        if (k_bytes >= (a.act == ACT_GELU ? 6144 : 1536) && w >= 160 && w <= 256) return go_dma<DT_BF16, 128, 128, 2, 2, 8, 3>(a, s, dry, true, phase);
     }
     const int64_t w = wgs(128, 64);
     if (k_bytes <= 512 ? w >= 300 : k_bytes <= 1024 && N <= 64 && w > 512) return go_dma<DT_BF16, 128, 64, 2, 2, 4, 3>(a, s, dry, true, phase);       // four per unit

@@ -101,6 +101,13 @@ static void check_bf16_rows()
     CHECK(kernel(512 * 128, 64, 1024, 1) == "igemm_dma_bf16_128x64x64s3" && kernel(513 * 128, 64, 1024, 1) == "igemm_dma_bf16_64x64x64s3");
     CHECK(kernel(832 * 128, 64, 1024, 1) == "igemm_dma_bf16_64x64x64s3" && kernel(833 * 128, 64, 1024, 1) == "igemm_dma_bf16_128x64x64s3");
     CHECK(kernel(384 * 64, 256, 2048, 1) == "igemm_dma_bf16_128x64x64s3" && kernel(386 * 64, 256, 2048, 1) == "igemm_dma_bf16_128x128x32s4");
+    GemmArgs gelu = product(DT_BF16, 2688, 1024, 3072);
+    gelu.act = ACT_GELU;
+    CHECK(launch_igemm(gelu, nullptr, true).kernel == std::string("igemm_dma_bf16_128x128x64s3"));
+    gelu = product(DT_BF16, 2688, 1024, 3064);
+    CHECK(launch_igemm(gelu, nullptr, true).kernel == std::string("igemm_dma_bf16_128x128x64s3"));
+    gelu.act = ACT_GELU;
+    CHECK(launch_igemm(gelu, nullptr, true).kernel == std::string("igemm_dma_bf16_128x64x64s3"));
     CHECK(kernel(300 * 64, 256, 1024, 1) == "igemm_dma_bf16_64x64x64s3" && kernel(302 * 64, 256, 1024, 1) == "igemm_dma_bf16_128x64x64s3");
 }
 
