@@ -317,6 +317,9 @@ gacer_status gacer_release_graphs(gacer_ctx *ctx);
  * modes enqueues every tenant's stream from its own host thread (the caller's thread takes tenant 0), which
  * multiplies the launch rate when many small-kernel tenants make the issue loop the bottleneck.  Results and
  * ordering guarantees are unchanged.  Needs a distinct stream per tenant (otherwise the call runs single-threaded).
+ * The threads are made by the first gacer_run that uses them and wait, without using the CPU, between calls; they end when the setting is
+ * turned off or the context is destroyed.  A process that forks does not take them along: a context whose rounds were issued by
+ * threads is destroyed by the process that ran them.
  */
 gacer_status gacer_set_issue_threads(gacer_ctx *ctx, int enable);
 

@@ -2,8 +2,8 @@
 // of once per tap.
 //
 // A workgroup owns BM output positions (consecutive in a column strip of at most 56 columns, row by row through all images)
-// x BN channels.  Per block of 32 channels the positions and their one-pixel halo (for 256 positions at most 384 pixels of 64
-// bytes) go into LDS by direct loads (zeros left and right of the image); all nine taps read their A fragments from there, a tap being a fixed
+// x BN channels (256x128, 256x64, 128x64, 64x64).  Per block of 32 channels the positions and their one-pixel halo (for 256 positions at most 384 pixels
+// of 64 bytes) go into LDS by direct loads (zeros left and right of the image); all nine taps read their A fragments from there, a tap being a fixed
 // displacement of the LDS row.  Taps above or below an image read a row of zeros instead.  The weights stream past in stages of
 // one tap (BN = 128, three stages) or three taps (BN = 64, three stages, or two where that leaves room for a second workgroup of 256
 // positions).  Two input blocks alternate, the next one being

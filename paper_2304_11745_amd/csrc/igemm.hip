@@ -946,8 +946,8 @@ static LaunchInfo go_dma(const GemmArgs &a, hipStream_t s, bool dry, bool vec_ok
 }
 
 // Tile of igemm_dma_kernel in bf16.  Two things bound these launches: the bytes that a unit draws from its L2, which the stages receive
-// at 105 to 115 bytes per ns (a 64x64 tile alone on its unit takes 0.2 us per 128 bytes of K, of which 0.15 are the 16 KB and 0.05 the
-// matrix cores), and what a tile costs beside its K loop (1 us for 64x64, 4 for 128x128 with one workgroup per unit).  So: the
+// at 105 to 115 bytes per ns (a 64x64 tile alone on its unit takes 0.2 us per 128 bytes of K; its 16 KB alone take 0.15 us, the matrix cores alone
+// 0.05), and what a tile costs beside its K loop (1 us for 64x64, 4 for 128x128 with one workgroup per unit).  So: the
 // largest tile of which about one per unit is left, counted in workgroups, and smaller ones the shorter K is.
 // Us a launch in a chain, 64x64 / 128x64 / 128x128 / 256x128, by the workgroups of 128x64: 3136x256x1024 (100) 6.9 / 9.1 / 11.5 / 18.4, 12544x128x512
 // (196) 6.4 / 6.3 / 8.6 / 12.3, 1568x1280x320 (260) 6.4 / 7.3 / 8.5 / 11.4, 50176x64x256 (392) 8.9 / 7.1 / 9.2 / 10.8, 12544x256x512 (392) 11.0 / 9.0 / 9.6 / 13.2,
