@@ -968,22 +968,35 @@ static LaunchInfo pick_dma_bf16(const GemmArgs &a, hipStream_t s, bool dry, int 
     const bool taps = !(a.kh == 1 && a.kw == 1 && a.pad == 0);
     auto wgs = [&](int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn) * z; };
     if (N <= 32) return go_dma<DT_BF16, 128, 32, 4, 1, 8, 3>(a, s, dry, true, phase);
+    const int64_t w = wgs(128, 64);
+    // A GELU's epilogue (erf) takes as long as a kilobyte of K, and only other workgroups of the unit cover it: smaller tiles, or those of which more fit.
+    // Us 64x64 / 128x64 (64-byte blocks) / 128x64 / 128x128, by the workgroups of 128x64: K = 256 384 (900x3072) 8.4 / 10.1 / 10.1 / 14.1, 480 12.1 / 10.7 / 10.6 / 14.5, 768
+    // 14.2 / 13.1 / 17.1 / 16.4, 1152 18.7 / 20.6 / 23.9 / 26.7, 3072 43.6 / 37.5 / 46.5 / 44.9; K = 512 384 10.4 / 12.2 / 11.9 / 16.1, 512 15.2 / 13.8 / 12.9 / 17.0, 576 15.4 / 16.1 /
+    // 19.3 / 18.3, 1008 22.5 / 21.9 / 22.0 / 21.8, 1152 24.6 / 26.2 / 28.9 / 31.7, 3072 57.8 / 53.6 / 64.1 / 57.4; K = 768 672 21.0 / 21.6 / 22.9 / 23.5, 816 26.0 / 27.3 / 25.7 /
+    // 25.0, 1136 30.6 / 33.5 / 33.9 / 39.9, 1344 42.5 / 38.3 / 40.8 / 42.5; K = 2048 192 16.9 / 22.6 / 18.4 / 27.6, 576 36.8 / 45.4 / 40.8 / 40.5, 672 44.7 / 46.7 / 42.2 / 43.3.
+    const bool gelu = !taps && a.act == ACT_GELU;
+    if (gelu && k_bytes <= 1024) {
+        if (w < 450 || (w > 1024 && w <= 1200)) return go_dma<DT_BF16, 64, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
+        if (w > 512 || k_bytes <= 512) return go_dma<DT_BF16, 128, 64, 2, 2, 4, 3>(a, s, dry, true, phase);
+        return go_dma<DT_BF16, 128, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
+    }
+    if (gelu && ((w > 512 && w <= (k_bytes <= 2048 ? 800 : k_bytes <= 3072 ? 700 : k_bytes <= 4096 ? 600 : 512)) || (w > 1024 && w <= 1200 && k_bytes <= 3072)))
+        return go_dma<DT_BF16, 64, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
     const bool wide = (N + 127) / 128 * 128 <= (N + 63) / 64 * 64;             // 128 columns waste no more than 64
     if (wide && k_bytes >= 512) {
         if (wgs(256, 128) >= 384) return go_dma<DT_BF16, 256, 128, 2, 2, 4, 3>(a, s, dry, true, phase);
-        const int64_t w = wgs(128, 128);
+        const int64_t w2 = wgs(128, 128);
         // two per unit; some more than these wait for a whole second wave of them
-        if (k_bytes <= 1024 ? w >= 384 && (w <= 512 || w > 560 || k_bytes <= 576) : w > 256 && (taps || (w > 384 && w <= 512)))
+        if (k_bytes <= 1024 ? w2 >= 384 && (w2 <= 512 || w2 > 560 || k_bytes <= 576) : w2 > 256 && (taps || (w2 > 384 && w2 <= 512)))
             return go_dma<DT_BF16, 128, 128, 2, 2, 4, 4>(a, s, dry, true, phase);
         // one workgroup per unit: nothing covers the epilogue, so where that is long (erf) only with a long K (us 128x64 / here: 2688x1024x1024 14.7 / 20.3, x2048
         // 24.7 / 27.7, x3072 34.2 / 33.5, x4096 40.4 / 38.3)
-        if (k_bytes >= (a.act == ACT_GELU ? 6144 : 1536) && w >= 160 && w <= 256) return go_dma<DT_BF16, 128, 128, 2, 2, 8, 3>(a, s, dry, true, phase);
+        if (k_bytes >= (a.act == ACT_GELU ? 6144 : 1536) && w2 >= 160 && w2 <= 256) return go_dma<DT_BF16, 128, 128, 2, 2, 8, 3>(a, s, dry, true, phase);
     }
-    const int64_t w = wgs(128, 64);
     if (k_bytes <= 512 ? w >= 300 : k_bytes <= 1024 && N <= 64 && w > 512) return go_dma<DT_BF16, 128, 64, 2, 2, 4, 3>(a, s, dry, true, phase);       // four per unit
     // two per unit, with the same wait; 64x64 tiles, of which there are three per unit, wait for less
     const bool spill = !taps && w > 512 && k_bytes > 1024 && w <= (k_bytes <= 2048 ? (N <= 64 ? 832 : 600) : N <= 64 ? 640 : 512);
-    if (!spill && (k_bytes <= 1024 ? w >= 300 : w > 400 || (k_bytes >= 4096 && w >= 192))) return go_dma<DT_BF16, 128, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
+    if (!spill && (k_bytes <= 1024 ? w >= 300 : w > 400 || (k_bytes >= 4096 && w >= (gelu ? 300 : 192)))) return go_dma<DT_BF16, 128, 64, 2, 2, 8, 3>(a, s, dry, true, phase);
     // alone on its unit with a long K a fourth stage pays (1024x768x768 7.0 -> 6.5); with more workgroups it costs one of them its place
     if (wgs(64, 64) <= 256 && k_bytes >= (taps ? 4096 : 1024)) return go_dma<DT_BF16, 64, 64, 2, 2, 8, 4>(a, s, dry, true, phase);
     return go_dma<DT_BF16, 64, 64, 2, 2, 8, 3>(a, s, dry, true, phase);

@@ -108,6 +108,12 @@ static void check_bf16_rows()
     CHECK(launch_igemm(gelu, nullptr, true).kernel == std::string("igemm_dma_bf16_128x128x64s3"));
     gelu.act = ACT_GELU;
     CHECK(launch_igemm(gelu, nullptr, true).kernel == std::string("igemm_dma_bf16_128x64x64s3"));
+    auto with_gelu = [](int M, int N, int K) { GemmArgs a = product(DT_BF16, M, N, K); a.act = ACT_GELU; return std::string(launch_igemm(a, nullptr, true).kernel).substr(15); };
+    CHECK(with_gelu(896, 3072, 256) == "64x64x64s3" && with_gelu(1280, 3072, 256) == "128x64x32s3" && with_gelu(3072, 3072, 256) == "64x64x64s3");
+    CHECK(with_gelu(896, 3072, 512) == "64x64x64s3" && with_gelu(1280, 3072, 512) == "128x64x64s3" && with_gelu(1408, 3072, 512) == "128x64x32s3");
+    CHECK(with_gelu(1280, 3072, 768) == "128x64x64s3" && with_gelu(1408, 3072, 768) == "64x64x64s3" && with_gelu(2048, 3072, 768) == "64x64x64s3" &&
+          with_gelu(2176, 3072, 768) == "128x128x32s4" && with_gelu(3072, 3072, 768) == "64x64x64s3" && with_gelu(3328, 3072, 768) == "128x64x64s3");
+    CHECK(with_gelu(512, 3072, 2048) == "64x64x64s3" && with_gelu(1536, 3072, 2048) == "64x64x64s3" && with_gelu(1664, 3072, 2048) == "128x64x64s3");
     CHECK(kernel(300 * 64, 256, 1024, 1) == "igemm_dma_bf16_64x64x64s3" && kernel(302 * 64, 256, 1024, 1) == "igemm_dma_bf16_128x64x64s3");
 }
 
