@@ -34,7 +34,7 @@ HBM_PEAK = 8.0e12
 TRAFFIC = {
     2: {"kernel": "igemm_dma_taps_f32_64x64x32s3", "fetch_bytes": 12.39e6, "write_bytes": 5.47e6, "plan": "unsplit",
         "launches_per_round": 11, "algorithmic_bytes": 12.45e6,
-        "sources_sha256": "b2c972238e476c5a70fe087a269f20c406efcdb94688be5ddde3aec886701557"},
+        "sources_sha256": "80f07e3788111b24679abb2a698cf770ec2ee00bf57e95854c05bbc3bfd62952"},
 }
 TRAFFIC_SOURCES = ["igemm.hip", "slices.hip", "rows.hip", "stream_ops.hip", "gemm_util.h", "slices_geom.h", "device_util.h", "kernels.h"]
 
